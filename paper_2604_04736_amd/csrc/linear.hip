@@ -27,6 +27,8 @@
 //                                              two output groups per wave), tiles dealt out by XCD
 //             hot_linear_wgrad_tile_kernel     the same for large layers: 128 inputs x 128 outputs per workgroup, rows of
 //                                              x and dy loaded straight into LDS
+//             hot_linear_wgrad_row_parts_kernel  the same for smaller layers and many rows, with a workspace: the rows cut into
+//                                              parts, bf16 pieces straight from memory, no LDS before the last sum
 //             hot_linear_xgrad_kernel          input gradients up to a few hundred rows
 //             hot_linear_xgrad_rows_kernel     input gradients from 256 rows: shared draws, as in the forward kernel
 #include <hip/hip_runtime.h>
@@ -1779,6 +1781,330 @@ void wgrad_tile_go(hipStream_t s, const LinearGradArgs &a, long tiles)
     hot_linear_wgrad_tile_kernel<<<dim3((unsigned)(kXcds * per_xcd)), dim3(256), 0, s>>>(a);
 }
 
+// ---------------------------------------------------------------------------------
+// Weight gradients of layers with few tiles and many rows, given a workspace: the rows are cut into parts for different
+// workgroups, as in the PARTS runs of the first kernel above, but the products are formed from bf16 pieces (see
+// split2_bf16), and what a part leaves in the workspace is the raw product P_s of each sample: eps is drawn once per
+// weight and sample by the finish kernel instead of once per part and wave.
+//
+// A wave owns a tile of 128 x 64 (BIG x SMALL blocks of 32; XBIG: 128 inputs x 64 outputs, else 64 inputs x 128 outputs) and
+// takes 16 rows at a time, the four waves of a workgroup round-robin over the rows of its part.  Lane (l32, half) reads rows
+// 8 half .. 8 half + 7 of the step at the four (two) consecutive columns 4 l32 .. (2 l32 ..) of the larger (smaller) operand: whole rows of
+// 512 (256) contiguous bytes per load, and element i of what it read is the lane's operand of block i, so that nothing
+// passes through LDS and no wave waits for another before the end.  Two waves share a SIMD (128 accumulators and 60
+// registers of pieces each) and one's cutting into pieces (about 1060 vector cycles a step) runs beside the other's
+// matrix instructions (1540).  The larger operand is cut first and its next rows are sent for at once, the smaller
+// one block by block.  At the end the waves' tiles are added through LDS in a fixed order.
+// ---------------------------------------------------------------------------------
+constexpr int kRowPartWaves = 4;
+constexpr int kRowPartRows = 16;                          // rows per wave and step
+constexpr int kRowPartBig = 4, kRowPartSmall = 2;         // blocks of 32 per side of a wave's tile
+
+template <int N>
+struct Floats;
+template <>
+struct Floats<2> {
+    typedef f2 V;
+    static __device__ __forceinline__ V load(window_t w, unsigned off) { return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(w, (int)off, 0, 0)); }
+};
+template <>
+struct Floats<4> {
+    typedef f4 V;
+    static __device__ __forceinline__ V load(window_t w, unsigned off) { return window_load4<false>(w, off); }
+};
+
+// floats of one part's share of the workspace: per sample the weights, then the biases (a multiple of four, so that quads stay aligned)
+inline __host__ __device__ long row_part_floats(long K, long O, int s_loc) { return (O * K + ((O + 3) & ~3L)) * s_loc; }
+
+template <bool XBIG>
+__global__ void __launch_bounds__(64 * kRowPartWaves, 2)
+hot_linear_wgrad_row_parts_kernel(LinearGradArgs a, int parts)
+{
+    constexpr int NB = kRowPartBig, NS = kRowPartSmall, KB = XBIG ? NB : NS, OB = XBIG ? NS : NB;
+    constexpr int TK = 32 * KB, TO = 32 * OB, PITCH = TK + 4;
+    typedef Floats<NB> LB;
+    typedef Floats<NS> LS;
+    __shared__ __attribute__((aligned(16))) float turn[kRowPartWaves][32 * PITCH];
+    const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const long K = a.in_features, O = a.out_features, R = a.rows;
+    const long k_tiles = (K + TK - 1) / TK, o_tiles = (O + TO - 1) / TO, tiles = k_tiles * o_tiles;
+    // the list of (part, sample, tile), tiles changing fastest, is cut into one contiguous range per XCD: workgroups that read the
+    // same rows share an L2
+    const long all = tiles * a.s_loc * parts, per_xcd = (all + kXcds - 1) / kXcds;
+    const long xcd = blockIdx.x % kXcds, nth = blockIdx.x / kXcds, item = xcd * per_xcd + nth;
+    if (nth >= per_xcd || item >= all) return;          // the whole workgroup
+    const long tile = item % tiles, ps = item / tiles;
+    const int s = (int)(ps % a.s_loc);
+    const long part = ps / a.s_loc;
+    const long o0 = (O >= K ? tile / k_tiles : tile % o_tiles) * TO, k0 = (O >= K ? tile % k_tiles : tile / o_tiles) * TK;
+    const long r_lo = part * a.rows_per_part, r_hi = r_lo + a.rows_per_part < R ? r_lo + a.rows_per_part : R;
+    const bool bias_tile = a.mu_b != nullptr && k0 == 0;
+
+    // Windows end behind the part's last row, so that rows beyond it arrive as zeros.  (Columns beyond the layer read some other
+    // element of the operand, which only reaches accumulators that are never stored.)
+    const window_t x_win = window(a.x + (size_t)s * (size_t)a.x_sample_stride, (unsigned)(((r_hi - 1) * a.ldx + K) * 4));
+    const window_t d_win = window(a.dy + (size_t)s * (size_t)R * (size_t)O, (unsigned)(r_hi * O * 4));
+    const window_t b_win = XBIG ? x_win : d_win, s_win = XBIG ? d_win : x_win;
+    const unsigned x_pitch = (unsigned)(a.ldx * 4), d_pitch = (unsigned)(O * 4);
+    const unsigned b_pitch = XBIG ? x_pitch : d_pitch, s_pitch = XBIG ? d_pitch : x_pitch;
+    const unsigned row0 = (unsigned)(r_lo + kRowPartRows * wave + 8 * half);
+    unsigned b_off = row0 * b_pitch + (unsigned)((XBIG ? k0 : o0) * 4 + 4 * NB * l32);
+    unsigned s_off = row0 * s_pitch + (unsigned)((XBIG ? o0 : k0) * 4 + 4 * NS * l32);
+
+    Acc32x32 mm[NB][NS];
+    float col_sum[OB];
+#pragma unroll
+    for (int j = 0; j < OB; ++j) col_sum[j] = 0.0f;
+    typename LB::V br[8];
+    typename LS::V sr[8];
+    auto ask_big = [&] {
+#pragma unroll
+        for (int t = 0; t < 8; ++t) br[t] = LB::load(b_win, b_off + (unsigned)t * b_pitch);
+        b_off += (unsigned)(kRowPartRows * kRowPartWaves) * b_pitch;
+    };
+    auto ask_small = [&] {
+#pragma unroll
+        for (int t = 0; t < 8; ++t) sr[t] = LS::load(s_win, s_off + (unsigned)t * s_pitch);
+        s_off += (unsigned)(kRowPartRows * kRowPartWaves) * s_pitch;
+    };
+    ask_big();
+    ask_small();
+    for (long r = r_lo + kRowPartRows * wave; r < r_hi; r += kRowPartRows * kRowPartWaves) {       // uniform over the wave
+        if (bias_tile) {
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+#pragma unroll
+                for (int j = 0; j < OB; ++j) col_sum[j] += XBIG ? sr[t][j % NS] : br[t][j];
+        }
+        bf8 b1[NB], b2[NB], b3[NB];
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+            split8_bf16(f4{br[0][i], br[1][i], br[2][i], br[3][i]}, f4{br[4][i], br[5][i], br[6][i], br[7][i]}, b1[i], b2[i], b3[i]);
+        ask_big();
+#pragma unroll
+        for (int j = 0; j < NS; ++j) {
+            bf8 c1, c2, c3;
+            split8_bf16(f4{sr[0][j], sr[1][j], sr[2][j], sr[3][j]}, f4{sr[4][j], sr[5][j], sr[6][j], sr[7][j]}, c1, c2, c3);
+            if (j == NS - 1) ask_small();
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                // (x is the A operand: its index runs over the registers of a result)
+                auto mac = [&](const bf8 &b, const bf8 &c) {
+                    if constexpr (XBIG) mm[i][j].mac(b, c);
+                    else mm[i][j].mac(c, b);
+                };
+                mac(b3[i], c1);
+                mac(b2[i], c2);
+                mac(b1[i], c3);
+                mac(b2[i], c1);
+                mac(b1[i], c2);
+                mac(b1[i], c1);
+            }
+        }
+    }
+    const MfmaSettled settled;
+
+    // result register 4 q + c of a block: input index 8 q + 4 half + c, output index l32; input k0 + KB index + i, output o0 + OB index + j
+    float *const P = a.ws + (size_t)part * (size_t)row_part_floats(K, O, a.s_loc) + (size_t)s * (size_t)(O * K);
+#pragma unroll
+    for (int j = 0; j < OB; ++j) {
+        float *mine = turn[wave];
+#pragma unroll
+        for (int g = 0; g < 16; ++g) {
+            const int m = 8 * (g >> 2) + 4 * half + (g & 3);
+            typename Floats<KB>::V v;
+#pragma unroll
+            for (int i = 0; i < KB; ++i) v[i] = XBIG ? mm[i][j % NS].read(settled)[g] : mm[j][i % NS].read(settled)[g];
+            *reinterpret_cast<typename Floats<KB>::V *>(mine + l32 * PITCH + KB * m) = v;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < KB; ++it) {
+            const int idx = it * 64 * kRowPartWaves + (int)threadIdx.x, row = idx / (TK / 4), quad = idx % (TK / 4);
+            f4 of_wave[kRowPartWaves], sum;
+#pragma unroll
+            for (int v = 0; v < kRowPartWaves; ++v) of_wave[v] = *reinterpret_cast<const f4 *>(turn[v] + row * PITCH + 4 * quad);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) sum[c] = (of_wave[0][c] + of_wave[1][c]) + (of_wave[2][c] + of_wave[3][c]);
+            const long o = o0 + OB * row + j, k = k0 + 4 * quad;
+            if (o < O && k < K) store4<true, false>(P + o * K + k, sum);
+        }
+        __syncthreads();
+    }
+    if (bias_tile) {            // uniform over the workgroup
+#pragma unroll
+        for (int j = 0; j < OB; ++j) {
+            const float both = col_sum[j] + __shfl_xor(col_sum[j], 32);
+            if (half == 0) turn[wave][OB * l32 + j] = both;
+        }
+        __syncthreads();
+        if (threadIdx.x < TO && o0 + (long)threadIdx.x < O) {
+            float sum = turn[0][threadIdx.x];
+#pragma unroll
+            for (int v = 1; v < kRowPartWaves; ++v) sum += turn[v][threadIdx.x];
+            a.ws[(size_t)part * (size_t)row_part_floats(K, O, a.s_loc) + (size_t)a.s_loc * (size_t)(O * K) +
+                 (size_t)s * (size_t)((O + 3) & ~3L) + (size_t)o0 + threadIdx.x] = sum;
+        }
+    }
+}
+
+// Adds the parts in a fixed order, draws eps and finishes the gradients: thread q owns quad q of the O*K weights, the threads
+// behind them one quad of biases each.
+__global__ void __launch_bounds__(64)
+hot_linear_wgrad_row_parts_finish_kernel(LinearGradArgs a, int parts)
+{
+    const long K = a.in_features, O = a.out_features, quads = O * K / 4, O4 = (O + 3) & ~3L;
+    const long q = (long)blockIdx.x * 64 + threadIdx.x;
+    const bool weights = q < quads;
+    const long b = q - quads;                   // bias quad
+    if (!weights && (a.mu_b == nullptr || 4 * b >= O)) return;
+    const size_t per_part = (size_t)row_part_floats(K, O, a.s_loc), per_sample = (size_t)(weights ? O * K : O4);
+    const float *first = a.ws + (weights ? (size_t)q * 4 : (size_t)a.s_loc * (size_t)(O * K) + (size_t)b * 4);
+    f4 gm = {0.0f, 0.0f, 0.0f, 0.0f}, gs = gm;
+    for (int s = 0; s < a.s_loc; ++s) {
+        const float *theirs = first + (size_t)s * per_sample;
+        // (four running sums, so that neither the additions nor their roundings form one long chain)
+        f4 of[4], P;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) of[v] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int p0 = 0; p0 < parts; p0 += 4)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                if (p0 + v < parts) {           // uniform over the grid
+                    const f4 u = load4<true, false>(theirs + (size_t)(p0 + v) * per_part);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) of[v][c] += u[c];
+                }
+            }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) P[c] = (of[0][c] + of[1][c]) + (of[2][c] + of[3][c]);
+        const f4 e = eps_quad(weights ? a.weight_quad0 + q : a.bias_quad0 + b, s, a.rng);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            gm[c] += P[c];
+            gs[c] = __builtin_fmaf(P[c], e[c], gs[c]);
+        }
+    }
+    if (weights) {
+        const f4 m4 = load4<true, false>(a.mu_w + 4 * q), sd4 = load4<true, false>(a.sigma_w + 4 * q);
+        f4 om, os;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            float u, v;
+            finish_pair(gm[c], gs[c], m4[c], sd4[c], (float)a.g, (float)a.k, u, v);
+            om[c] = u;
+            os[c] = v;
+        }
+        store4<true, false>(a.gmu_w + 4 * q, om);
+        store4<true, false>(a.gsig_w + 4 * q, os);
+        return;
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const long o = 4 * b + c;
+        if (o < O) {
+            float u, v;
+            finish_pair(gm[c], gs[c], a.mu_b[o], a.sigma_b[o], (float)a.g, (float)a.k, u, v);
+            a.gmu_b[o] = u;
+            a.gsig_b[o] = v;
+        }
+    }
+}
+
+// How the two kernels above run a layer; parts == 0: they do not.
+struct RowPartsPlan {
+    int parts;
+    long rows_per_part;
+    bool xbig;
+};
+
+template <bool XBIG>
+inline long row_part_tiles(const hot_linear_desc *d)
+{
+    constexpr int tk = 32 * (XBIG ? kRowPartBig : kRowPartSmall), to = 32 * (XBIG ? kRowPartSmall : kRowPartBig);
+    return ((d->in_features + tk - 1) / tk) * ((d->out_features + to - 1) / to);
+}
+
+// Where they run, measured against the first kernel above with a workspace, 40 shapes: 16640 x 192 x 768 173 -> 75 us,
+// 7260 x 2160 x 540 435 -> 202, 1024 x 540 x 2160 96 -> 52, 300 x 540 x 2160 41 -> 28, 513 x 2160 x 2160 x 8 samples 478 -> 293;
+// below 300 rows they win once rows x samples reach 600 (256 x 192 x 768 x 4: 20 -> 17 us) and lose below that (256 x 1024^2 x 2:
+// 24 -> 28, 129 x 8192 x 1024 x 1: 43 -> 52), and at a hundred rows and less (64 x 128^2 x 4: 15 -> 18).  Layers of 512 tiles of
+// 128 x 128 and more stay with the kernel above this one: level with it (0.96-1.08x), it needs no workspace.
+constexpr long kRowPartMinRows = 129, kRowPartAlwaysRows = 300, kRowPartMinRowSamples = 600;
+constexpr long kRowPartMinWeights = 8192, kRowPartAnyWeightsRows = 512;     // (one or two tiles need that many rows to be worth two launches)
+constexpr long kRowPartMaxTileCount = 512;
+constexpr int kRowPartMaxParts = 64;
+constexpr int64_t kRowPartMaxBytes = (int64_t)256 << 20;
+// The bf16 matrix instruction rounds every accumulation towards zero, so errors grow with the rows a wave adds up: 16640 x 192 x
+// 768, 2-norm against 64 bits: 3.2e-7 at 297 rows, 3.0e-7 at 245, 2.7e-7 at 198 (the fp32 instruction with 260: 3.0e-7).  From 8192
+// rows on, where the first kernel also cuts many parts, a wave takes at most 208.
+constexpr long kRowPartLongRows = 8192, kRowPartLongMost = 208 * kRowPartWaves;
+
+inline bool row_parts_suit(const hot_linear_desc *d)
+{
+    if (d->rows < kRowPartMinRows || (d->rows < kRowPartAlwaysRows && d->rows * d->s_local < kRowPartMinRowSamples)) return false;
+    if (d->rows < kRowPartAnyWeightsRows && d->in_features * d->out_features < kRowPartMinWeights) return false;
+    if ((d->out_features & 3) || wgrad_tile_count(d) >= kRowPartMaxTileCount) return false;       // (rows of dy are read in 16-byte quads)
+    const unsigned long long lim = 0xFFFFFFF0ull;           // 32-bit byte offsets
+    const unsigned long long reach = (unsigned long long)d->rows + 2 * kRowPartRows * kRowPartWaves;
+    return (reach * d->ldx + d->in_features) * 4 < lim && reach * d->out_features * 4 < lim;
+}
+
+// the best plan whose parts fit into `budget` bytes
+inline RowPartsPlan row_parts_within(const hot_linear_desc *d, int64_t budget)
+{
+    RowPartsPlan p = {0, 0, false};
+    const long tall = row_part_tiles<true>(d), wide = row_part_tiles<false>(d);
+    p.xbig = tall <= wide;
+    const long tiles = p.xbig ? tall : wide;
+    const int64_t part_bytes = row_part_floats(d->in_features, d->out_features, d->s_local) * (int64_t)sizeof(float);
+    // The number of parts whose rounds of workgroups (two per compute unit; a last round of one per compute unit runs its
+    // workgroups faster) times steps per workgroup is least; a workgroup's start, its sums through LDS and its share
+    // of the finish kernel take about as long as four steps.  At least 128 rows to a part.
+    const long step_rows = kRowPartRows * kRowPartWaves;
+    double best = 0.0;
+    bool best_long = true;
+    for (int parts = 1; parts <= kRowPartMaxParts && parts * part_bytes <= budget && (parts == 1 || d->rows >= 128L * parts); ++parts) {
+        const long rows = ((d->rows + parts - 1) / parts + kRowPartRows - 1) / kRowPartRows * kRowPartRows;
+        if (rows * (parts - 1) >= d->rows) continue;       // (the parts must all exist)
+        const long wgs = tiles * d->s_local * parts, last = wgs % 512;
+        const double rounds = (double)(wgs / 512) + (last == 0 ? 0.0 : (last <= 256 ? 0.65 : 1.0));
+        const double cost = rounds * ((double)((rows + step_rows - 1) / step_rows) + 4.0);
+        const bool too_long = d->rows >= kRowPartLongRows && rows > kRowPartLongMost;
+        if (p.parts == 0 || (best_long && !too_long) || (best_long == too_long && cost < best)) {
+            best = cost;
+            best_long = too_long;
+            p.parts = parts;
+            p.rows_per_part = rows;
+        }
+    }
+    return p;
+}
+
+// ws_bytes: what the caller's workspace holds (negative: as much as wanted, for the size query).  With less than half of the
+// parts it wants the chip would stand too empty: then the first kernel runs, which needs no workspace to split the rows.
+inline RowPartsPlan row_parts_plan(const hot_linear_desc *d, int64_t ws_bytes)
+{
+    const RowPartsPlan none = {0, 0, false};
+    if (ws_bytes == 0 || !row_parts_suit(d)) return none;
+    const RowPartsPlan wanted = row_parts_within(d, kRowPartMaxBytes);
+    const int64_t part_bytes = row_part_floats(d->in_features, d->out_features, d->s_local) * (int64_t)sizeof(float);
+    if (ws_bytes < 0 || wanted.parts * part_bytes <= ws_bytes) return wanted;
+    const RowPartsPlan p = row_parts_within(d, ws_bytes);
+    return 2 * p.parts >= wanted.parts ? p : none;
+}
+
+void row_parts_go(const RowPartsPlan &p, hipStream_t s, const LinearGradArgs &a, long tiles)
+{
+    const long per_xcd = (tiles * a.s_loc * p.parts + kXcds - 1) / kXcds;
+    const dim3 grid((unsigned)(kXcds * per_xcd)), block(64 * kRowPartWaves);
+    if (p.xbig) hot_linear_wgrad_row_parts_kernel<true><<<grid, block, 0, s>>>(a, p.parts);
+    else hot_linear_wgrad_row_parts_kernel<false><<<grid, block, 0, s>>>(a, p.parts);
+    const long threads = a.out_features * a.in_features / 4 + (a.mu_b ? (a.out_features + 3) / 4 : 0);
+    hot_linear_wgrad_row_parts_finish_kernel<<<dim3((unsigned)((threads + 63) / 64)), dim3(64), 0, s>>>(a, p.parts);
+}
+
 // A wave's finished 64-input x 16*RB-row tile of one sample's dx goes to memory.  Register rr of accumulator
 // i is input k0 + 16 j + 4 rr + i of row r0 + 16 rb + n; the lanes of a row exchange quads so that each store
 // covers 64 contiguous bytes of the row.  Every lane of the wave must call it.
@@ -2686,6 +3012,10 @@ int64_t hot_linear_backward_workspace_bytes(const hot_linear_desc *d)
     const int x_parts = xgrad_parts(d, -1);
     const int64_t for_inputs = x_parts > 1 ? (int64_t)x_parts * d->s_local * d->rows * d->in_features * (int64_t)sizeof(float) : 0;
     int64_t most = for_weights > for_inputs ? for_weights : for_inputs;     // the two kernels use it one after the other
+    if (const RowPartsPlan plan = row_parts_plan(d, -1); plan.parts) {
+        const int64_t for_parts = plan.parts * row_part_floats(d->in_features, d->out_features, d->s_local) * (int64_t)sizeof(float);
+        if (for_parts > most) most = for_parts;
+    }
     // (whether input gradients will be asked for the query does not know: enough for either way)
     if (const OnePassPlan plan = one_pass_plan(d, true, -1); plan.rb && plan.parts > 1) {
         const int64_t for_one_pass = plan.parts * (int64_t)d->s_local * d->rows * d->in_features * (int64_t)sizeof(float);
@@ -2894,7 +3224,11 @@ int hot_linear_backward_rng_ws(const hot_linear_desc *d, int32_t s_total, double
         return hot_detail::note_hip(hipGetLastError());
     }
     const WgradShape shape = wgrad_shape(d, workspace ? workspace_bytes : 0);
-    if (shape.tile) {
+    if (const RowPartsPlan plan = row_parts_plan(d, workspace ? workspace_bytes : 0); plan.parts) {
+        a.ws = static_cast<float *>(workspace);
+        a.rows_per_part = plan.rows_per_part;
+        row_parts_go(plan, s, a, plan.xbig ? row_part_tiles<true>(d) : row_part_tiles<false>(d));
+    } else if (shape.tile) {
         wgrad_tile_go(s, a, wgrad_tile_count(d));
     } else {
         const long tiles = shape.tiles;

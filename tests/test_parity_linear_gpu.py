@@ -396,6 +396,39 @@ def test_backward_in_one_pass_matches_oracle(oracle, hot, rows, k, o, s, xs, bia
     _backward_with_a_workspace(oracle, hot, rows, k, o, s, xs, bias, True, fraction, used, wants_none=((rows, k) == (3, 12800)))
 
 
+# Weight gradients from row parts on the bf16 matrix instruction: the fewest rows (129, samples making up for them) and
+# ragged tiles; one exact tile of 128 inputs x 64 outputs and of 64 x 128; a layer narrower than any tile; rows that leave
+# the last wave of the last part one row or none; enough rows for the bound on a wave's rows; half of the workspace
+ROW_PARTS = [(129, 132, 260, 5, True, True, 1.0), (300, 128, 64, 2, False, True, 1.0), (300, 64, 128, 2, True, False, 1.0),
+             (512, 8, 12, 1, False, True, 1.0), (577, 260, 68, 3, True, True, 1.0), (1041, 128, 516, 2, False, True, 0.5),
+             (8195, 36, 44, 2, True, True, 1.0), (1025, 200, 4, 1, False, False, 1.0)]
+
+
+@pytest.mark.parametrize("rows,k,o,s,xs,bias,fraction", ROW_PARTS)
+def test_weight_gradients_from_row_parts_match_oracle(oracle, hot, rows, k, o, s, xs, bias, fraction):
+    _backward_with_a_workspace(oracle, hot, rows, k, o, s, xs, bias, False, fraction, True)
+
+
+def test_weight_gradients_from_row_parts_with_pitched_x_and_unaligned_dy(hot):
+    """Rows of x with padding (holding NaN) behind them and a dy that starts on a 4-byte boundary give the bits of the packed call."""
+    rows, k, o, s = 600, 140, 72, 2
+    g = torch.Generator(device=DEV).manual_seed(3)
+    wide = torch.full((s, rows, k + 12), float("nan"), device=DEV)
+    wide[:, :, :k] = torch.randn(s, rows, k, device=DEV, generator=g)
+    flat = torch.randn(s * rows * o + 1, device=DEV, generator=g)
+    mu, sg = torch.randn(o, k, device=DEV, generator=g), torch.rand(o, k, device=DEV, generator=g) + 0.1
+    mb, sb = torch.randn(o, device=DEV, generator=g), torch.rand(o, device=DEV, generator=g) + 0.1
+    ws = torch.empty(hot.hot_linear_backward_workspace_bytes(rows, k, o, s) // 4, device=DEV)
+    outs = []
+    for x, dy in ((wide[:, :, :k], flat[1:].view(s, rows, o)), (wide[:, :, :k].contiguous(), flat[1:].clone().view(s, rows, o))):
+        out = [torch.full_like(t, float("nan")) for t in (mu, mu, mb, mb)]
+        hot.hot_linear_backward_rng(hot.hot_rng(seed=9, step=1, first_sample=0), x, dy, mu, sg, mb, sb, *out, None, s, 100.0, workspace=ws)
+        torch.cuda.synchronize()
+        outs.append(out)
+    for a, b in zip(*outs):
+        assert bool(torch.isfinite(a).all()) and torch.equal(a, b)
+
+
 def _backward_with_a_workspace(oracle, hot, rows, k, o, s, xs, bias, want_dx, fraction, used, wants_none=None):
     print("case linear backward with workspace", rows, k, o, s, xs, bias, want_dx, fraction, flush=True)
     c = _layer(rows + k + o, rows, k, o)
