@@ -3013,8 +3013,10 @@ int64_t hot_linear_backward_workspace_bytes(const hot_linear_desc *d)
     const int64_t for_inputs = x_parts > 1 ? (int64_t)x_parts * d->s_local * d->rows * d->in_features * (int64_t)sizeof(float) : 0;
     int64_t most = for_weights > for_inputs ? for_weights : for_inputs;     // the two kernels use it one after the other
     if (const RowPartsPlan plan = row_parts_plan(d, -1); plan.parts) {
+        // (never less than two parts of the first kernel: what this returns has always held at least that)
         const int64_t for_parts = plan.parts * row_part_floats(d->in_features, d->out_features, d->s_local) * (int64_t)sizeof(float);
-        if (for_parts > most) most = for_parts;
+        const int64_t at_least = for_parts > 2 * wgrad_part_bytes(d) ? for_parts : 2 * wgrad_part_bytes(d);
+        if (at_least > most) most = at_least;
     }
     // (whether input gradients will be asked for the query does not know: enough for either way)
     if (const OnePassPlan plan = one_pass_plan(d, true, -1); plan.rb && plan.parts > 1) {
