@@ -1818,7 +1818,7 @@ inline __host__ __device__ long row_part_floats(long K, long O, int s_loc) { ret
 
 template <bool XBIG>
 __global__ void __launch_bounds__(64 * kRowPartWaves, 2)
-hot_linear_wgrad_row_parts_kernel(LinearGradArgs a, int parts)
+hot_linear_wgrad_row_parts_kernel(LinearGradArgs a, int parts, int chunk)
 {
     constexpr int NB = kRowPartBig, NS = kRowPartSmall, KB = XBIG ? NB : NS, OB = XBIG ? NS : NB;
     constexpr int TK = 32 * KB, TO = 32 * OB, PITCH = TK + 4;
@@ -1852,7 +1852,6 @@ hot_linear_wgrad_row_parts_kernel(LinearGradArgs a, int parts)
     unsigned b_off = row0 * b_pitch + (unsigned)((XBIG ? k0 : o0) * 4 + 4 * NB * l32);
     unsigned s_off = row0 * s_pitch + (unsigned)((XBIG ? o0 : k0) * 4 + 4 * NS * l32);
 
-    Acc32x32 mm[NB][NS];
     float col_sum[OB];
 #pragma unroll
     for (int j = 0; j < OB; ++j) col_sum[j] = 0.0f;
@@ -1870,7 +1869,13 @@ hot_linear_wgrad_row_parts_kernel(LinearGradArgs a, int parts)
     };
     ask_big();
     ask_small();
-    for (long r = r_lo + kRowPartRows * wave; r < r_hi; r += kRowPartRows * kRowPartWaves) {       // uniform over the wave
+    // A long part is added up in chunks of `chunk` rows (a multiple of 64), each into accumulators of its own and then to what the
+    // chunks before left in the workspace (the same thread holds the same sums every time).  What is sent for beyond the end
+    // of a chunk are the first rows of the next.
+    for (long c_lo = r_lo; c_lo < r_hi; c_lo += chunk) {
+    const long c_hi = c_lo + chunk < r_hi ? c_lo + chunk : r_hi;
+    Acc32x32 mm[NB][NS];
+    for (long r = c_lo + kRowPartRows * wave; r < c_hi; r += kRowPartRows * kRowPartWaves) {       // uniform over the wave
         if (bias_tile) {
 #pragma unroll
             for (int t = 0; t < 8; ++t)
@@ -1928,9 +1933,13 @@ hot_linear_wgrad_row_parts_kernel(LinearGradArgs a, int parts)
 #pragma unroll
             for (int c = 0; c < 4; ++c) sum[c] = (of_wave[0][c] + of_wave[1][c]) + (of_wave[2][c] + of_wave[3][c]);
             const long o = o0 + OB * row + j, k = k0 + 4 * quad;
-            if (o < O && k < K) store4<true, false>(P + o * K + k, sum);
+            if (o < O && k < K) {
+                if (c_lo != r_lo) sum += load4<true, false>(P + o * K + k);
+                store4<true, false>(P + o * K + k, sum);
+            }
         }
         __syncthreads();
+    }
     }
     if (bias_tile) {            // uniform over the workgroup
 #pragma unroll
@@ -2035,10 +2044,10 @@ constexpr long kRowPartMinRows = 129, kRowPartAlwaysRows = 300, kRowPartMinRowSa
 constexpr long kRowPartMinWeights = 8192, kRowPartAnyWeightsRows = 512;     // (one or two tiles need that many rows to be worth two launches)
 constexpr long kRowPartMaxTileCount = 512;
 constexpr int kRowPartMaxParts = 64;
-constexpr int64_t kRowPartMaxBytes = (int64_t)256 << 20;
+constexpr int64_t kRowPartMaxBytes = (int64_t)256 << 20, kRowPartSmallBytes = (int64_t)8 << 20;
 // The bf16 matrix instruction rounds every accumulation towards zero, so errors grow with the rows a wave adds up: 16640 x 192 x
 // 768, 2-norm against 64 bits: 3.2e-7 at 297 rows, 3.0e-7 at 245, 2.7e-7 at 198 (the fp32 instruction with 260: 3.0e-7).  From 8192
-// rows on, where the first kernel also cuts many parts, a wave takes at most 208.
+// rows on, where the first kernel also cuts many parts, a wave takes at most 208 before its sums leave the registers.
 constexpr long kRowPartLongRows = 8192, kRowPartLongMost = 208 * kRowPartWaves;
 
 inline bool row_parts_suit(const hot_linear_desc *d)
@@ -2064,22 +2073,31 @@ inline RowPartsPlan row_parts_within(const hot_linear_desc *d, int64_t budget)
     // of the finish kernel take about as long as four steps.  At least 128 rows to a part.
     const long step_rows = kRowPartRows * kRowPartWaves;
     double best = 0.0;
-    bool best_long = true;
     for (int parts = 1; parts <= kRowPartMaxParts && parts * part_bytes <= budget && (parts == 1 || d->rows >= 128L * parts); ++parts) {
         const long rows = ((d->rows + parts - 1) / parts + kRowPartRows - 1) / kRowPartRows * kRowPartRows;
         if (rows * (parts - 1) >= d->rows) continue;       // (the parts must all exist)
         const long wgs = tiles * d->s_local * parts, last = wgs % 512;
         const double rounds = (double)(wgs / 512) + (last == 0 ? 0.0 : (last <= 256 ? 0.65 : 1.0));
         const double cost = rounds * ((double)((rows + step_rows - 1) / step_rows) + 4.0);
-        const bool too_long = d->rows >= kRowPartLongRows && rows > kRowPartLongMost;
-        if (p.parts == 0 || (best_long && !too_long) || (best_long == too_long && cost < best)) {
+        if (p.parts == 0 || cost < best) {
             best = cost;
-            best_long = too_long;
             p.parts = parts;
             p.rows_per_part = rows;
         }
     }
     return p;
+}
+
+inline int64_t wgrad_part_bytes(const hot_linear_desc *d)
+{
+    return 2 * (d->out_features * d->in_features + ((d->out_features + 3) & ~(int64_t)3)) * (int64_t)sizeof(float);
+}
+
+// What the parts may take: as much as the first kernel's sixteen, for small layers up to 8 MiB.
+inline int64_t row_parts_budget(const hot_linear_desc *d)
+{
+    const int64_t sixteen = kWgradMaxParts * wgrad_part_bytes(d), most = sixteen > kRowPartSmallBytes ? sixteen : kRowPartSmallBytes;
+    return most < kRowPartMaxBytes ? most : kRowPartMaxBytes;
 }
 
 // ws_bytes: what the caller's workspace holds (negative: as much as wanted, for the size query).  With less than half of the
@@ -2088,7 +2106,7 @@ inline RowPartsPlan row_parts_plan(const hot_linear_desc *d, int64_t ws_bytes)
 {
     const RowPartsPlan none = {0, 0, false};
     if (ws_bytes == 0 || !row_parts_suit(d)) return none;
-    const RowPartsPlan wanted = row_parts_within(d, kRowPartMaxBytes);
+    const RowPartsPlan wanted = row_parts_within(d, row_parts_budget(d));
     const int64_t part_bytes = row_part_floats(d->in_features, d->out_features, d->s_local) * (int64_t)sizeof(float);
     if (ws_bytes < 0 || wanted.parts * part_bytes <= ws_bytes) return wanted;
     const RowPartsPlan p = row_parts_within(d, ws_bytes);
@@ -2099,8 +2117,10 @@ void row_parts_go(const RowPartsPlan &p, hipStream_t s, const LinearGradArgs &a,
 {
     const long per_xcd = (tiles * a.s_loc * p.parts + kXcds - 1) / kXcds;
     const dim3 grid((unsigned)(kXcds * per_xcd)), block(64 * kRowPartWaves);
-    if (p.xbig) hot_linear_wgrad_row_parts_kernel<true><<<grid, block, 0, s>>>(a, p.parts);
-    else hot_linear_wgrad_row_parts_kernel<false><<<grid, block, 0, s>>>(a, p.parts);
+    const long chunks = a.rows >= kRowPartLongRows ? (p.rows_per_part + kRowPartLongMost - 1) / kRowPartLongMost : 1;
+    const long step_rows = kRowPartRows * kRowPartWaves, chunk = ((p.rows_per_part + chunks - 1) / chunks + step_rows - 1) / step_rows * step_rows;
+    if (p.xbig) hot_linear_wgrad_row_parts_kernel<true><<<grid, block, 0, s>>>(a, p.parts, (int)chunk);
+    else hot_linear_wgrad_row_parts_kernel<false><<<grid, block, 0, s>>>(a, p.parts, (int)chunk);
     const long threads = a.out_features * a.in_features / 4 + (a.mu_b ? (a.out_features + 3) / 4 : 0);
     hot_linear_wgrad_row_parts_finish_kernel<<<dim3((unsigned)((threads + 63) / 64)), dim3(64), 0, s>>>(a, p.parts);
 }
@@ -2911,11 +2931,6 @@ struct WgradShape {
     bool tile;      // the kernel with tiles of 128 x 128 instead (no parts; the other fields do not apply)
 };
 
-inline int64_t wgrad_part_bytes(const hot_linear_desc *d)
-{
-    return 2 * (d->out_features * d->in_features + ((d->out_features + 3) & ~(int64_t)3)) * (int64_t)sizeof(float);
-}
-
 // ws_bytes: what the caller's workspace holds (0: none; a negative value: as much as wanted, for the size query)
 // wide_through_parts: count on eight row parts when deciding for two output groups per tile
 WgradShape wgrad_shape_with(const hot_linear_desc *d, int64_t ws_bytes, bool wide_through_parts)
@@ -3013,10 +3028,12 @@ int64_t hot_linear_backward_workspace_bytes(const hot_linear_desc *d)
     const int64_t for_inputs = x_parts > 1 ? (int64_t)x_parts * d->s_local * d->rows * d->in_features * (int64_t)sizeof(float) : 0;
     int64_t most = for_weights > for_inputs ? for_weights : for_inputs;     // the two kernels use it one after the other
     if (const RowPartsPlan plan = row_parts_plan(d, -1); plan.parts) {
-        // (never less than two parts of the first kernel: what this returns has always held at least that)
+        // (a power of two of the first kernel's parts where that is at most sixteen of them: so many the call has always asked for)
         const int64_t for_parts = plan.parts * row_part_floats(d->in_features, d->out_features, d->s_local) * (int64_t)sizeof(float);
-        const int64_t at_least = for_parts > 2 * wgrad_part_bytes(d) ? for_parts : 2 * wgrad_part_bytes(d);
-        if (at_least > most) most = at_least;
+        int64_t ask = 2 * wgrad_part_bytes(d);
+        while (ask < for_parts) ask *= 2;
+        if (ask > kWgradMaxParts * wgrad_part_bytes(d)) ask = for_parts;
+        if (ask > most) most = ask;
     }
     // (whether input gradients will be asked for the query does not know: enough for either way)
     if (const OnePassPlan plan = one_pass_plan(d, true, -1); plan.rb && plan.parts > 1) {
