@@ -30,6 +30,8 @@ struct Rng {
     unsigned step;
 };
 
+__device__ __forceinline__ unsigned xor3(unsigned a, unsigned b, unsigned c) { return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96); }
+
 __device__ __forceinline__ u4 philox4x32_10(unsigned c0, unsigned c1, unsigned c2, unsigned c3,
                                             unsigned k0, unsigned k1)
 {
@@ -38,8 +40,8 @@ __device__ __forceinline__ u4 philox4x32_10(unsigned c0, unsigned c1, unsigned c
     for (int r = 0; r < 10; ++r) {
         const unsigned long long p0 = (unsigned long long)kM0 * c0;
         const unsigned long long p1 = (unsigned long long)kM1 * c2;
-        const unsigned n0 = (unsigned)(p1 >> 32) ^ c1 ^ k0;
-        const unsigned n2 = (unsigned)(p0 >> 32) ^ c3 ^ k1;
+        const unsigned n0 = xor3((unsigned)(p1 >> 32), c1, k0);
+        const unsigned n2 = xor3((unsigned)(p0 >> 32), c3, k1);
         c1 = (unsigned)p1;
         c3 = (unsigned)p0;
         c0 = n0;
