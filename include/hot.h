@@ -226,16 +226,13 @@ int hot_last_hip_error(const hot_plan *plan);
  * addend magnitudes, against 3e-7 on the fp32 instruction; a factor below about 1e-33 in magnitude has pieces
  * below bf16's normal range, which the instruction may flush, and an infinite factor gives NaN, not infinity).
  * Runs on the current device, asynchronous on `stream`.
- * Up to a few hundred rows a wave draws the weights it multiplies (re-drawing eps per block of 64
- * rows is then cheaper than writing and re-reading w); from 256 rows on, given at least 128 workgroups
- * of 256 rows x 16 outputs, the four waves of a workgroup share every draw through LDS; where tiles of 256, 512
- * or 1024 rows x 32 to 128 outputs fill the chip (hot_linear_launch_shape tells; the 256-row tiles from 129 rows
- * on, tiles of 128 rows from 65 to 128), four, eight or sixteen waves share it and x goes from memory straight into LDS (150-190 TFLOP/s
- * of fp32 work on layers that fill the chip).  The draw and the matrix instructions do not overlap on this chip; against writing w once
- * with hot_forward_rng and calling a library GEMM the call is 1.8-2.9x faster up to tens of rows, level at
- * 64 rows, 1.8-2.0x at the 7260 and 16640 rows of a Swin and a ViT layer, and 1.4x on the largest squares;
- * between about 80 and 500 rows large layers stay behind that route (0.75-1.0x at 8192 x 8192, 0.7-0.95x at
- * 2160 x 8640): one draw serves too few rows there and the two do not overlap.
+ * Up to 32 rows a wave draws the weights it multiplies for those rows.  From 33 rows on (layers of at least 128 inputs) one wave
+ * holds all of a workgroup's 64 to 320 rows and draws every weight once for them (2160 x 8640, two samples: 84 us at 64 rows,
+ * 210 at 300; 172 TFLOP/s of fp32 work at 256 rows x 8192^2); from about 700 rows on, on layers that fill the chip,
+ * tiles of 256, 512 or 1024 rows x 32 to 128 outputs, whose four, eight or sixteen waves share every draw through LDS and take x
+ * from memory straight into it (hot_linear_launch_shape tells; tiles of 128 and 256 rows also serve fewer rows on layers
+ * of fewer inputs), at 120-190 TFLOP/s of fp32 work.  What the other kernels cannot take goes, from 256 rows on, to one whose
+ * four waves share the draws, else to the first.
  */
 typedef struct hot_linear_desc {
     int64_t rows;          /* R >= 1: rows of x (batch x tokens) */
@@ -270,10 +267,10 @@ int hot_linear_forward_rng(const hot_linear_desc *desc, const hot_rng *rng, cons
  * when x is shared (the caller adds them up), or NULL to skip it (a first layer); with dx, rows <=
  * 1 048 560 and s_local <= 65 535 (grid limits; HOT_EINVAL beyond, before anything runs).  Other arguments
  * and rules as for hot_linear_forward_rng.  Every weight is drawn once per sample (and per wave that
- * shares its tile) for the weight gradients, and for dx once per block of 64 rows, or, from 256 rows
- * on, once per workgroup of 64 to 256 rows (its waves share the draws through LDS), or, where tiles of 512
- * or 1024 rows fill the chip, once per such tile (the forward pass's kernel for many rows with dy as its
- * input; it needs out_features to be a multiple of 4 and dy 16-byte aligned).  Large layers
+ * shares its tile) for the weight gradients, and for dx once per block of 64 rows, or, from 65 rows
+ * on, once per workgroup of 64 to 320 rows, or, where tiles of 512 or 1024 rows fill the chip, once per such tile (the
+ * forward pass's kernels with dy as their input; they need out_features to be a multiple of 4 and dy 16-byte
+ * aligned; else from 256 rows on once per workgroup of 64 to 256 rows, whose waves share the draws through LDS).  Large layers
  * (from 129 rows on, at least 512 tiles of 128 inputs x 128 outputs, or from 256 rows on at least 140) take their
  * weight gradients from a kernel that stages x and dy through LDS and multiplies bf16 pieces of both, as the
  * forward call's large tiles do (up to 180 TFLOP/s of fp32 work); it needs out_features to
@@ -293,8 +290,8 @@ int hot_linear_backward_rng(const hot_linear_desc *desc, int32_t s_total, double
 /*
  * Which launch shape the calls above choose for a layer (host arithmetic only; for tests and for tuning, same
  * passages of the paper).  which = 0: hot_linear_forward_rng; which = 1: the input-gradient part of
- * hot_linear_backward_rng (dy taken to be 16-byte aligned).  Returns 0 where the layer goes to the kernels for up
- * to a few hundred rows per workgroup; else, for the kernel with 256, 512 or 1024 rows per workgroup (64 per wave),
+ * hot_linear_backward_rng (dy taken to be 16-byte aligned, no workspace).  Returns 0 where the layer goes to the kernels for up
+ * to a few hundred rows per workgroup (those for tens to hundreds of rows among them); else, for the kernel with 256, 512 or 1024 rows per workgroup (64 per wave),
  * 100 * waves + 10 * (outputs per workgroup / 32) + samples per pass of its (first) launch, e.g. 822: eight waves
  * (512 rows), 64 outputs, two samples per pass; 1621: sixteen waves (1024 rows), 64 outputs, one sample per pass;
  * 412: four waves (256 rows), 32 outputs, two samples per pass; 2xx: four waves of 32 rows each (128 rows), e.g. 212;

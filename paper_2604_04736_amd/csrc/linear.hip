@@ -22,6 +22,8 @@
 //             hot_linear_slab_kernel           from 256 rows on layers that fill the chip: 256 to 1024 rows x 32 to 128 outputs per
 //                                              workgroup, x loaded straight into LDS, the drawn weights shared through it,
 //                                              v_mfma_f32_32x32x2_f32; also the input gradients of such layers
+//             hot_linear_deep_kernel           tens to hundreds of rows (and more on small layers): a wave holds all rows of its
+//                                              workgroup, the waves split the contraction; also the input gradients
 //   backward  hot_linear_wgrad_kernel          weight and bias gradients (per-sample G never stored); variants for
 //                                              few tiles (waves split the rows), many rows (operands prefetched,
 //                                              two output groups per wave), tiles dealt out by XCD
@@ -433,6 +435,8 @@ hot_linear_forward_rows_kernel(LinearArgs a)
 // 32-63 inputs k + 4 .. k + 7; instruction i takes element i of both operands, so the contraction index is enumerated
 // in another order, identically on both sides.  All global accesses go through range-checked windows (see vec.h).
 // ---------------------------------------------------------------------------------
+constexpr int kComputeUnits = 256;
+constexpr int kXcds = 8;
 constexpr int kSlabRows = 512;               // rows per workgroup of eight waves (sixteen: twice as many, four: half)
 constexpr int kSlabK = 16;                   // contraction indices per step
 constexpr unsigned kOutside = 0xFFFFFFF0u;   // a byte offset beyond any window
@@ -764,6 +768,398 @@ hot_linear_slab_kernel(SlabArgs a)
     }
 }
 
+// ---------------------------------------------------------------------------------
+// Tens to hundreds of rows.  The kernel above shares a drawn weight among waves that hold 64 rows each and meet at a barrier
+// in every step; with few rows its workgroups are few or its waves idle, and what runs instead draws every weight once per 64 or
+// 256 rows, on the fp32 instruction.  Here ONE wave holds all rows of a workgroup (32 RB, 64 to 320) x 32 CB outputs, and the four
+// waves take turns on the contraction, 16 indices at a time: every weight is drawn and cut into pieces by one lane, every
+// element of x by one lane, nothing is shared, and no wave waits for another before their tiles are added up at the end.
+// Products, layouts and lane roles are those of the kernel above (bf16 pieces; x by buffer loads straight into LDS, 64 bytes per
+// row, the weights through three planes there), but all of it is the wave's own, so program order and counts of outstanding
+// loads replace the barriers.  Per block of 32 rows: the pieces of the next block are cut and a twelfth or so of the next step's
+// quads is drawn between the matrix instructions of this one; a block's place in LDS is sent for again, for the next step, as
+// soon as its values are in registers.  What bounds it: vector and matrix work, which on this chip overlap only in
+// part (256 x 8192^2: 172 TFLOP/s of fp32 work, the library's bf16 product at six products each would do 202), and the last round
+// of workgroups.  Two outputs' width (CB = 2) halves the cutting of x per product but leaves one wave per SIMD; RB = 10 with
+// CB = 2 does not fit the registers.  RB is even: a block's two operand registers alternate.
+// ---------------------------------------------------------------------------------
+constexpr int kDeepWaves = 4;
+constexpr long kDeepStep = kSlabK * kDeepWaves;     // contraction indices that the waves take together
+constexpr unsigned kFarOutside = 0x80000000u;      // a byte offset beyond any window of this kernel, also with a tile's rows added
+
+struct DeepArgs {
+    long rows, contract, outs;
+    long ld_in, in_sample_stride;
+    long contract_per_part;      // multiple of 16 * kDeepWaves
+    int parts, n_begin, samples;
+    int items, per_xcd;          // tiles of the launch, and per XCD
+    long part_stride;            // floats between the parts' outputs
+    long weight_quad0, bias_quad0;
+    const float *in, *mu_w, *sigma_w, *mu_b, *sigma_b;
+    float *out;
+    Rng rng;
+};
+
+template <int N>
+__device__ __forceinline__ void wait_for_all_but()
+{
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N < 63 ? N : 63) : "memory");
+}
+
+// Philox in pieces (rounds R0 .. R1 - 1 of philox4x32_10), so that a draw can be spread over a loop
+template <int R0, int R1>
+__device__ __forceinline__ void philox_rounds(u4 &c, unsigned k0, unsigned k1)
+{
+    constexpr unsigned kM0 = 0xD2511F53u, kM1 = 0xCD9E8D57u, kW0 = 0x9E3779B9u, kW1 = 0xBB67AE85u;
+#pragma unroll
+    for (int r = R0; r < R1; ++r) {
+        const unsigned long long p0 = (unsigned long long)kM0 * c[0], p1 = (unsigned long long)kM1 * c[2];
+        const unsigned n0 = xor3((unsigned)(p1 >> 32), c[1], k0 + (unsigned)r * kW0);
+        const unsigned n2 = xor3((unsigned)(p0 >> 32), c[3], k1 + (unsigned)r * kW1);
+        c[1] = (unsigned)p1;
+        c[3] = (unsigned)p0;
+        c[0] = n0;
+        c[2] = n2;
+    }
+}
+
+template <int RB, int CB, bool TR>
+__global__ void __launch_bounds__(64 * kDeepWaves, RB * CB <= 2 ? 4 : RB * CB <= 4 ? 3 : (RB * CB <= 8 ? 2 : 1))
+hot_linear_deep_kernel(DeepArgs a)
+{
+    static_assert(RB % 2 == 0, "the operand registers of a step's last block and of the next step's first differ");
+    constexpr int KS = kSlabK, ROWS = 32 * RB, OUTS = 32 * CB, QW = 2 * CB;     // QW: quads a lane draws per step
+    constexpr int XW = ROWS * KS, WW = OUTS * KS * 3 / 2;                        // floats of a wave's x and of its three planes of weights
+    constexpr int RP = OUTS + 1;                                                 // pitch of a row block on its way out
+    constexpr int LDS_LOOP = XW + WW, LDS_OUT = 32 * RP;
+    __shared__ __attribute__((aligned(16))) float lds[kDeepWaves * (LDS_LOOP > LDS_OUT ? LDS_LOOP : LDS_OUT)];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l32 = lane & 31, half = lane >> 5;
+    const int C = (int)a.contract, N = (int)a.outs, R = (int)a.rows;
+    // The list of tiles (row blocks fastest, then samples, then parts, then outputs) is cut into one contiguous range per XCD:
+    // the workgroups that need the same mu and sigma run at about the same time behind one L2.
+    const int row_tiles = (R + ROWS - 1) / ROWS;
+    const int item = ((int)blockIdx.x % kXcds) * a.per_xcd + (int)blockIdx.x / kXcds;
+    if ((int)blockIdx.x / kXcds >= a.per_xcd || item >= a.items) return;         // the whole workgroup
+    const int s = item / row_tiles % a.samples, part = item / (row_tiles * a.samples) % a.parts;
+    const int n0 = a.n_begin + item / (row_tiles * a.samples * a.parts) * OUTS, r0 = item % row_tiles * ROWS;
+    const int c_lo = part * (int)a.contract_per_part, c_hi = c_lo + (int)a.contract_per_part < C ? c_lo + (int)a.contract_per_part : C;
+    lds_float *const X = (lds_float *)lds + wave * LDS_LOOP, *const W = X + XW;
+
+    // operand reads of x: quads half and 2 + half of row l32 of a block
+    int op_off[2];
+#pragma unroll
+    for (int k8 = 0; k8 < 2; ++k8) op_off[k8] = (l32 >> 4) * 256 + (4 * (l32 & 15) + ((2 * k8 + half) ^ slab_swizzle(l32 & 15))) * 4;
+    const int wb_off = l32 * 32 + ((half ^ ((l32 >> 3) & 1)) << 4);              // bytes within a plane and block of 32 outputs
+    // loads of x: an instruction brings 16 rows x 16 indices
+    const int lq = (lane & 3) ^ slab_swizzle(lane >> 2);
+    const unsigned in_bytes = (unsigned)((((long)R - 1) * a.ld_in + C) * 4);
+    const window_t in_win = window(a.in + (size_t)s * (size_t)a.in_sample_stride, in_bytes);
+    const window_t mu_win = window(a.mu_w, (unsigned)((long)C * N * 4)), sg_win = window(a.sigma_w, (unsigned)((long)C * N * 4));
+    const int my_row = r0 + (lane >> 2);        // (of the first 16)
+    const unsigned x_pitch16 = (unsigned)(16 * a.ld_in * 4);
+    const unsigned x_lane = (unsigned)(((long)my_row * a.ld_in + 4 * lq) * 4);
+
+    // drawing.  Not TR: quad i of the lane is output n0 + 16 i + lane / 4, indices 4 (lane % 4) .. + 3 of the step.  TR: outputs
+    // n0 + 4 (lane % (8 CB)) .. + 3, index QW (lane / (8 CB)) + i.
+    const int d_n = TR ? 4 * (lane % (8 * CB)) : lane >> 2;
+    const int d_c = TR ? QW * (lane / (8 * CB)) : 4 * (lane & 3);
+    int d_put;
+    {
+        const int h = (d_c >> 2) & 1, prt = d_c >> 3;
+        d_put = d_n * 32 + ((h ^ ((d_n >> 3) & 1)) << 4) + prt * 8 + (TR ? (d_c & 3) * 2 : 0);
+    }
+    auto d_flat = [&](int i, int cb) -> long {
+        return TR ? (long)(cb + d_c + i) * N + n0 + d_n : (long)(n0 + 16 * i + d_n) * C + cb + d_c;
+    };
+    auto d_ok = [&](int i, int cb) -> bool { return TR ? (n0 + d_n < N && cb + d_c + i < c_hi) : (n0 + 16 * i + d_n < N && cb + d_c < c_hi); };
+
+    f4 m4[QW], sd4[QW];
+    auto ask_w = [&](int i, int cb) {
+        const int off = (int)(d_ok(i, cb) ? (unsigned)(d_flat(i, cb) * 4) : kOutside);
+        m4[i] = window_load4<false>(mu_win, off);
+        sd4[i] = window_load4<false>(sg_win, off);
+    };
+    u4 ph;
+    f4 wprev;
+    unsigned held[3][4];
+    // piece t of the step's drawing: rounds 0-4, rounds 5-9, the rest of quad t / 3; then sends for what the quad needs a step later
+    auto draw_piece = [&](int t, int cb) {
+        const int i = t / 3;
+        if (t % 3 == 0) {
+            const long quad = a.weight_quad0 + (d_flat(i, cb) >> 2);
+            ph = u4{(unsigned)((unsigned long long)quad & 0xFFFFFFFFull), (unsigned)((unsigned long long)quad >> 32),
+                    a.rng.first_sample + (unsigned)s, a.rng.step};
+            philox_rounds<0, 5>(ph, a.rng.k0, a.rng.k1);
+        } else if (t % 3 == 1) {
+            philox_rounds<5, 10>(ph, a.rng.k0, a.rng.k1);
+        } else {
+            const f4 e = eps_from_words(ph);
+            f4 w4;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) w4[c] = __builtin_fmaf(sd4[i][c], e[c], m4[i][c]);
+            if constexpr (!TR) {
+                unsigned pc[3][2];
+                split2_bf16(w4[0], w4[1], pc[0][0], pc[1][0], pc[2][0]);
+                split2_bf16(w4[2], w4[3], pc[0][1], pc[1][1], pc[2][1]);
+#pragma unroll
+                for (int pl = 0; pl < 3; ++pl) *(lds_u2 *)((lds_char *)W + pl * (OUTS * 32) + d_put + i * 16 * 32) = u2{pc[pl][0], pc[pl][1]};
+            } else {
+                if ((i & 1) == 0) wprev = w4;
+                else {
+#pragma unroll
+                    for (int e4 = 0; e4 < 4; ++e4) {
+                        unsigned p1, p2, p3;
+                        split2_bf16(wprev[e4], w4[e4], p1, p2, p3);
+                        if constexpr (CB == 2) {
+                            if (i == 1) {
+                                held[0][e4] = p1;
+                                held[1][e4] = p2;
+                                held[2][e4] = p3;
+                            } else {
+                                *(lds_u2 *)((lds_char *)W + 0 * (OUTS * 32) + d_put + e4 * 32) = u2{held[0][e4], p1};
+                                *(lds_u2 *)((lds_char *)W + 1 * (OUTS * 32) + d_put + e4 * 32) = u2{held[1][e4], p2};
+                                *(lds_u2 *)((lds_char *)W + 2 * (OUTS * 32) + d_put + e4 * 32) = u2{held[2][e4], p3};
+                            }
+                        } else {
+                            typedef __attribute__((address_space(3))) unsigned lds_unsigned;
+                            *(lds_unsigned *)((lds_char *)W + 0 * (OUTS * 32) + d_put + e4 * 32) = p1;
+                            *(lds_unsigned *)((lds_char *)W + 1 * (OUTS * 32) + d_put + e4 * 32) = p2;
+                            *(lds_unsigned *)((lds_char *)W + 2 * (OUTS * 32) + d_put + e4 * 32) = p3;
+                        }
+                    }
+                }
+            }
+        }
+    };
+    // sends for block rb of the step that starts at cb
+    auto ask_x = [&](int rb, int cb) {
+        // (rows beyond the last lie behind the window, which ends with it; indices beyond the part's end are moved there)
+        const unsigned base = cb + 4 * lq < c_hi ? x_lane + (unsigned)cb * 4u : kFarOutside;
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(in_win, (lds_void *)(X + (2 * rb + j) * 256), 16,
+                                                     (int)(base + (unsigned)(2 * rb + j) * x_pitch16), 0, 0, 0);
+    };
+    auto read_x = [&](int rb, f4 &lo, f4 &hi) {
+        lo = *(const volatile lds_f4 *)(X + op_off[0] + rb * 512);
+        hi = *(const volatile lds_f4 *)(X + op_off[1] + rb * 512);
+    };
+    bf8 b[CB][3];
+    auto read_w = [&] {
+#pragma unroll
+        for (int c = 0; c < CB; ++c)
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl) b[c][pl] = *(const volatile lds_bf8 *)((const lds_char *)W + pl * (OUTS * 32) + c * 1024 + wb_off);
+    };
+
+    Acc32x32 mm[RB][CB];
+    const int first = c_lo + KS * wave, stride = KS * kDeepWaves;
+    if (first < c_hi) {
+#pragma unroll
+        for (int i = 0; i < QW; ++i) ask_w(i, first);
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) ask_x(rb, first);
+#pragma unroll
+        for (int t = 0; t < 3 * QW; ++t) draw_piece(t, first);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < QW; ++i) ask_w(i, first + stride);
+        wait_for_all_but<0>();
+        f4 raw[2][2];
+        read_x(0, raw[0][0], raw[0][1]);
+        read_x(1 % RB, raw[1][0], raw[1][1]);
+        bf8 cur[3], nxt[3];
+        asm volatile("" : "+v"(raw[0][0]), "+v"(raw[0][1])::"memory");
+        ask_x(0, first + stride);
+        split8_bf16(raw[0][0], raw[0][1], cur[0], cur[1], cur[2]);
+        for (int cb = first; cb < c_hi; cb += stride) {
+            read_w();
+            // (the weights of this step are in registers before the next ones overwrite them: the LDS executes a wave's
+            // instructions in order)
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) {
+                // here: pieces of block rb in cur; block rb + 1 on its way into raw[(rb + 1) % 2].  Sent for since the two loads of
+                // block rb + 2: those of the RB - 1 blocks behind it (and mu, sigma), so that many may be outstanding.
+                f4 &lo = raw[(rb + 1) & 1][0], &hi = raw[(rb + 1) & 1][1];
+                asm volatile("" : "+v"(lo), "+v"(hi)::"memory");          // (has arrived: its place may be refilled)
+                const int ahead = rb + 1;
+                if (ahead < RB) ask_x(ahead, cb + stride);
+                else ask_x(0, cb + 2 * stride);
+                wait_for_all_but<2 * (RB - 1)>();
+                f4 nlo, nhi;
+                read_x((rb + 2) % RB, nlo, nhi);
+                __builtin_amdgcn_sched_barrier(0);
+                split8_bf16(lo, hi, nxt[0], nxt[1], nxt[2]);
+#pragma unroll
+                for (int t = 0; t < 3 * QW; ++t)
+                    if (t * RB / (3 * QW) == rb) draw_piece(t, cb + stride);
+                constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};
+#pragma unroll
+                for (int p = 0; p < 6; ++p)
+#pragma unroll
+                    for (int c = 0; c < CB; ++c) mm[rb][c].mac(cur[PA[p]], b[c][PB[p]]);
+                __builtin_amdgcn_sched_barrier(0);
+                // (the parameters of the quads drawn above are dead: send for those of the step after next)
+#pragma unroll
+                for (int t = 2; t < 3 * QW; t += 3)
+                    if (t * RB / (3 * QW) == rb) ask_w(t / 3, cb + 2 * stride);
+                cur[0] = nxt[0];
+                cur[1] = nxt[1];
+                cur[2] = nxt[2];
+                raw[rb & 1][0] = nlo;
+                raw[rb & 1][1] = nhi;
+            }
+        }
+    }
+    wait_for_all_but<0>();          // (what was sent for beyond the last step must not land in the sums below)
+    const MfmaSettled settled;
+
+    const int col = (int)threadIdx.x % OUTS, n = n0 + col;
+    float bias = 0.0f;
+    if (!TR && a.mu_b && n < N) bias = __builtin_fmaf(a.sigma_b[n], pick4_of(eps_quad(a.bias_quad0 + (n >> 2), s, a.rng), n & 3), a.mu_b[n]);
+    float *const dst = a.out + (size_t)part * (size_t)a.part_stride + (size_t)s * (size_t)R * (size_t)N;
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        __syncthreads();
+        lds_float *mine = (lds_float *)lds + wave * (32 * RP);
+#pragma unroll
+        for (int c = 0; c < CB; ++c) {
+            const f16v acc = mm[rb][c].read(settled);
+#pragma unroll
+            for (int g = 0; g < 16; ++g) mine[(8 * (g >> 2) + 4 * half + (g & 3)) * RP + 32 * c + l32] = acc[g];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < OUTS / 8; ++it) {
+            const int row = it * (256 / OUTS) + (int)threadIdx.x / OUTS;
+            float v[kDeepWaves];
+#pragma unroll
+            for (int w = 0; w < kDeepWaves; ++w) v[w] = ((const lds_float *)lds)[w * (32 * RP) + row * RP + col];
+            const int at = r0 + 32 * rb + row;
+            if (at < R && n < N) dst[(size_t)at * (size_t)N + (size_t)n] = (v[0] + v[1]) + (v[2] + v[3]) + bias;
+        }
+    }
+}
+
+template <int RB, int CB, bool TR>
+void deep_go(hipStream_t s, DeepArgs a, int samples, int n_begin, int n_end)
+{
+    const long items = (n_end - n_begin + 32 * CB - 1) / (32 * CB) * ((a.rows + 32 * RB - 1) / (32 * RB)) * a.parts * samples;
+    a.n_begin = n_begin;
+    a.samples = samples;
+    a.items = (int)items;
+    a.per_xcd = (int)((items + kXcds - 1) / kXcds);
+    hot_linear_deep_kernel<RB, CB, TR><<<dim3((unsigned)(kXcds * a.per_xcd)), dim3(64 * kDeepWaves), 0, s>>>(a);
+}
+
+// The shapes of the kernel above and what they cost: microseconds per step of a workgroup with 1 .. `resident` workgroups on its
+// compute unit (as many as registers and LDS admit).  Measured on layers of 16 to 128 steps; the model ranks shapes, and picks
+// the number of parts.
+struct DeepShape {
+    int rb, cb, resident;
+    double us[4];
+};
+constexpr DeepShape kDeepShapes[] = {{2, 1, 4, {1.05, 1.9, 2.3, 2.9}}, {4, 1, 3, {1.1, 2.05, 2.8}}, {6, 1, 2, {1.5, 2.7}}, {8, 1, 2, {1.75, 3.8}}, {10, 1, 1, {2.3}},
+                                     {6, 2, 1, {2.2}}, {8, 2, 1, {3.0}}, {4, 2, 2, {2.1, 3.9}}};
+constexpr int kDeepCodes = sizeof(kDeepShapes) / sizeof(kDeepShapes[0]);
+constexpr int kDeepCodesTr = kDeepCodes - 1;        // (the last one's transposed draw spills its registers)
+
+struct DeepPlan {
+    int code;               // index into kDeepShapes, -1: none
+    int rest_code;          // the shape of the outputs n_cut .. N - 1, which would start a round of their own (-1: one launch)
+    long n_cut;
+    int parts;
+    long contract_per_part;
+    double cost;
+};
+
+inline double deep_cost(const DeepShape &h, long wgs, long steps)
+{
+    const long round = (long)kComputeUnits * h.resident, full = wgs / round, left = wgs % round;
+    double t = (double)full * ((double)steps * h.us[h.resident - 1] + 5.0);
+    if (left) t += (double)steps * h.us[(left + kComputeUnits - 1) / kComputeUnits - 1] + 5.0;
+    return t + 4.0;
+}
+
+// Where it runs, measured against the other kernels on 60 layer shapes: forward from 33 rows on (64 x 2160 x 8640 x 2 samples 130 ->
+// 84 us, 300: 655 -> 210, 256 x 8192^2 590 -> 400, 64 x 1024^2 x 8 95 -> 21; at 16 rows 59 -> 79, so fewer stay), input gradients from
+// 65 (below, the other kernel draws as few weights and has more waves: 0.87-1.04x), both given two (four) steps of contraction per
+// wave and, without parts, 100 workgroups for the input gradients (below, the other kernel's up to sixteen waves per tile win:
+// 200 x 192 x 768 27 -> 32).  From 705 rows on the kernel above shares every draw among as many rows: there the cheaper one by
+// the two models runs (900 x 2160 x 8640 534 -> 476, 2048 x 1024^2 71 -> 60, 7260 x 540 x 2160 206 against 301 stays).
+constexpr long kDeepMinRows = 33, kDeepMinRowsTr = 65, kDeepAlwaysRows = 704;
+constexpr long kDeepMinContract = 128, kDeepMinContractTr = 256, kDeepMinWorkgroupsTr = 100;
+constexpr int kDeepMaxParts = 16;
+constexpr int64_t kDeepMaxBytes = (int64_t)256 << 20;
+
+// R rows, C contraction indices, N outputs; ws_bytes: as in wgrad_shape (0: no parts)
+inline DeepPlan deep_plan(long R, long C, long N, long ld_in, int S, bool tr, int64_t ws_bytes)
+{
+    DeepPlan best = {-1, -1, 0, 1, 0, 0.0};
+    if (R < (tr ? kDeepMinRowsTr : kDeepMinRows) || C < (tr ? kDeepMinContractTr : kDeepMinContract) || S > 65535) return best;
+    constexpr long kIndexMost = 1L << 29;                // (so that the products below stay within 64 bits)
+    if (R > kIndexMost || C > kIndexMost || N > kIndexMost || ld_in > kIndexMost) return best;
+    const unsigned long long lim = 0x7FFFFFF0ull;
+    if ((unsigned long long)(R + 640) * ld_in * 4 >= lim || (unsigned long long)(C + 256) * (N + 64) * 4 >= 2 * lim) return best;
+    if ((N + 31) / 32 * ((R + 127) / 128) > 0x3fffffffL / ((long)S * (tr ? kDeepMaxParts : 1))) return best;      // (tiles are counted in 32 bits)
+    const int64_t block_bytes = (int64_t)S * R * N * (int64_t)sizeof(float);
+    const int64_t budget = ws_bytes < 0 || ws_bytes > kDeepMaxBytes ? kDeepMaxBytes : ws_bytes;
+    for (int i = 0; i < (tr ? kDeepCodesTr : kDeepCodes); ++i) {
+        const DeepShape &h = kDeepShapes[i];
+        const long row_tiles = (R + 32 * h.rb - 1) / (32 * h.rb), col_tiles = (N + 32 * h.cb - 1) / (32 * h.cb);
+        const long per_col = row_tiles * S;             // workgroups of one column of tiles
+        for (int parts = 1; parts <= (tr ? kDeepMaxParts : 1); ++parts) {
+            if (parts > 1 && parts * block_bytes > budget) break;
+            const long per_part = ((C + parts - 1) / parts + kDeepStep - 1) / kDeepStep * kDeepStep;
+            if (parts > 1 && (per_part * (parts - 1) >= C || per_part < 2 * kDeepStep)) continue;
+            if (tr && parts == 1 && col_tiles * per_col < kDeepMinWorkgroupsTr) continue;
+            double cost = deep_cost(h, col_tiles * per_col * parts, per_part / kDeepStep);
+            if (parts > 1) cost += 4.0 + (double)(parts + 1) * (double)block_bytes / 4e6;
+            if (best.code < 0 || cost < best.cost) best = DeepPlan{i, -1, N, parts, per_part, cost};
+        }
+        // whole rounds of this shape, and what is left over in the shape that does it fastest
+        const long steps = (C + kDeepStep - 1) / kDeepStep, round = (long)kComputeUnits * h.resident;
+        const long main_tiles = col_tiles * per_col / round * round / per_col;
+        if (main_tiles < 1 || main_tiles >= col_tiles) continue;
+        const double main_cost = deep_cost(h, main_tiles * per_col, steps);
+        const long n_cut = main_tiles * 32 * h.cb;
+        for (int j = 0; j < (tr ? kDeepCodesTr : kDeepCodes); ++j) {
+            const DeepShape &r = kDeepShapes[j];
+            const double cost = main_cost + deep_cost(r, (N - n_cut + 32 * r.cb - 1) / (32 * r.cb) * ((R + 32 * r.rb - 1) / (32 * r.rb)) * S, steps);
+            if (best.code >= 0 && cost < best.cost) best = DeepPlan{i, j, n_cut, 1, steps * kDeepStep, cost};
+        }
+    }
+    return best;
+}
+
+template <bool TR>
+void deep_launch(int code, hipStream_t s, const DeepArgs &a, int samples, long n0, long n1)
+{
+    switch (code) {
+    case 0: return deep_go<2, 1, TR>(s, a, samples, (int)n0, (int)n1);
+    case 1: return deep_go<4, 1, TR>(s, a, samples, (int)n0, (int)n1);
+    case 2: return deep_go<6, 1, TR>(s, a, samples, (int)n0, (int)n1);
+    case 3: return deep_go<8, 1, TR>(s, a, samples, (int)n0, (int)n1);
+    case 4: return deep_go<10, 1, TR>(s, a, samples, (int)n0, (int)n1);
+    case 5: return deep_go<6, 2, TR>(s, a, samples, (int)n0, (int)n1);
+    case 6: return deep_go<8, 2, TR>(s, a, samples, (int)n0, (int)n1);
+    default:
+        if constexpr (!TR) deep_go<4, 2, false>(s, a, samples, (int)n0, (int)n1);
+    }
+}
+
+template <bool TR>
+void deep_run(const DeepPlan &p, hipStream_t s, DeepArgs a, int samples)
+{
+    a.parts = p.parts;
+    a.contract_per_part = p.contract_per_part;
+    deep_launch<TR>(p.code, s, a, samples, 0, p.n_cut);
+    if (p.rest_code >= 0) deep_launch<TR>(p.rest_code, s, a, samples, p.n_cut, a.outs);
+}
+
 // Whether the kernel above can address this problem (its windows take 32-bit byte offsets, its indices are 32-bit).
 inline bool slab_kernel_fits(long rows, long contract, long outs, long ld_in)
 {
@@ -772,7 +1168,6 @@ inline bool slab_kernel_fits(long rows, long contract, long outs, long ld_in)
            (unsigned long long)(rows + 2 * kSlabRows) * (outs + 128) * 4 < lim && (rows + kSlabRows - 1) / kSlabRows <= 65535;
 }
 
-constexpr int kComputeUnits = 256;
 constexpr int kSlabMinRows = 512;             // below, the kernels whose workgroups hold 256 rows
 // Least share of the chip's time that the tiles of a launch must fill, measured against the kernels for fewer rows on 130
 // layer shapes.  Forward with a shared x: wins from 0.6 on (1.1-2x; between 0.45 and 0.6 anything from 0.73x to 1.2x).
@@ -957,6 +1352,35 @@ inline SlabShape slab_input_grad_shape(const hot_linear_desc *d, bool dy_aligned
     return slab_shape_singles(d->rows, d->in_features, d->s_local, kSlabMinFillInputGrad, kSlabMinFillInputGradNarrow);
 }
 
+// Whether the kernel for a few hundred rows takes the layer: up to 704 rows always, beyond that where it beats the slab kernel's
+// shape by 3 % (a unit of that kernel's cost times its steps of 16 indices is 0.32 ns, measured 0.29-0.35 over its shapes) or
+// there is none.
+constexpr DeepPlan kNoDeepPlan = {-1, -1, 0, 1, 0, 0.0};
+
+inline bool deep_beats_slab(const DeepPlan &p, long rows, long contract, double slab_cost)
+{
+    return p.code >= 0 && (rows <= kDeepAlwaysRows || slab_cost == 0.0 || p.cost < 0.97 * (slab_cost * (double)((contract + kSlabK - 1) / kSlabK) * 3.2e-4 + 5.0));
+}
+
+inline DeepPlan deep_forward_plan(const hot_linear_desc *d)
+{
+    const DeepPlan p = deep_plan(d->rows, d->in_features, d->out_features, d->ldx, d->s_local, false, 0);
+    if (p.code < 0) return p;
+    const SlabForwardPlan slab = slab_forward_plan(d);
+    const double cost = (slab.two.waves ? slab.two.cost : 0.0) + (slab.one.waves ? slab.one.cost : 0.0);
+    return deep_beats_slab(p, d->rows, d->in_features, cost) ? p : kNoDeepPlan;
+}
+
+// ... and its input gradients (dy is the input, read in 16-byte quads)
+inline DeepPlan deep_input_grad_plan(const hot_linear_desc *d, bool dy_aligned, int64_t ws_bytes)
+{
+    if ((d->out_features & 3) != 0 || !dy_aligned) return kNoDeepPlan;
+    const DeepPlan p = deep_plan(d->rows, d->out_features, d->in_features, d->out_features, d->s_local, true, ws_bytes);
+    if (p.code < 0) return p;
+    const SlabShape slab = slab_input_grad_shape(d, true);
+    return deep_beats_slab(p, d->rows, d->out_features, slab.waves ? slab.cost : 0.0) ? p : kNoDeepPlan;
+}
+
 template <int RB, bool XS>
 void linear_go_st(int st, dim3 grid, int waves, hipStream_t s, const LinearArgs &a)
 {
@@ -1067,8 +1491,6 @@ constexpr int kWgradPartials = 34;   // per lane: 16 + 16 weight-gradient sums a
 // contiguous ranges, one per XCD.  The larger operand then enters one L2 only (two at a range boundary) and
 // the smaller one each L2 once, where the plain order had every XCD stream both (40 % L2 misses at 7260
 // rows).  Only locality depends on the round-robin placement, not the result.
-constexpr int kXcds = 8;
-
 constexpr int wgrad_max_split(int ob) { return kWgradMaxSplit / ob; }   // at most 60 KiB of LDS
 
 template <bool SPLIT, bool DEEP, int OB, bool PARTS = false>
@@ -3012,7 +3434,8 @@ int hot_linear_launch_shape(const hot_linear_desc *d, int which)
         return p.rb ? (p.split ? 100 : 0) + 10 * p.rb + p.smax : 0;
     }
     auto code = [](const SlabShape &h, int st) { return h.waves ? 100 * (h.rbw == 1 ? 2 : h.waves) + 10 * h.cbw + st : 0; };
-    if (which == 1) return code(slab_input_grad_shape(d, true), 1);
+    if (which == 1) return deep_input_grad_plan(d, true, 0).code >= 0 ? 0 : code(slab_input_grad_shape(d, true), 1);
+    if (deep_forward_plan(d).code >= 0) return 0;
     const SlabForwardPlan p = slab_forward_plan(d);
     return p.two.waves ? code(p.two, 2) + 1000 * (p.one.waves ? p.one.cbw : 0) : code(p.one, 1);
 }
@@ -3024,7 +3447,8 @@ int64_t hot_linear_backward_workspace_bytes(const hot_linear_desc *d)
     if (d->rows > (INT64_MAX / 64) / d->in_features || d->rows * d->in_features > (INT64_MAX / 64) / d->s_local) return HOT_EINVAL;
     const WgradShape w = wgrad_shape(d, -1);
     const int64_t for_weights = w.parts > 1 ? (int64_t)w.parts * wgrad_part_bytes(d) : 0;
-    const int x_parts = xgrad_parts(d, -1);
+    const DeepPlan deep = deep_input_grad_plan(d, true, -1);
+    const int x_parts = deep.code >= 0 ? deep.parts : xgrad_parts(d, -1);
     const int64_t for_inputs = x_parts > 1 ? (int64_t)x_parts * d->s_local * d->rows * d->in_features * (int64_t)sizeof(float) : 0;
     int64_t most = for_weights > for_inputs ? for_weights : for_inputs;     // the two kernels use it one after the other
     if (const RowPartsPlan plan = row_parts_plan(d, -1); plan.parts) {
@@ -3086,6 +3510,27 @@ int hot_linear_forward_rng(const hot_linear_desc *d, const hot_rng *rng, const f
     // Hundreds to thousands of rows on a layer that fills the chip with tiles of 512 rows: the kernel that stages x and the
     // drawn weights through LDS.  Samples that share x go two to a pass (they share every loaded row), an odd last one,
     // a single one and samples with inputs of their own one to a pass with tiles twice as wide.
+    if (const DeepPlan plan = deep_forward_plan(d); plan.code >= 0) {
+        DeepArgs b;
+        b.rows = d->rows;
+        b.contract = d->in_features;
+        b.outs = d->out_features;
+        b.ld_in = d->ldx;
+        b.in_sample_stride = d->x_sample_stride;
+        b.part_stride = 0;
+        b.n_begin = 0;
+        b.weight_quad0 = a.weight_quad0;
+        b.bias_quad0 = a.bias_quad0;
+        b.in = x;
+        b.mu_w = mu_w;
+        b.sigma_w = sigma_w;
+        b.mu_b = mu_b;
+        b.sigma_b = sigma_b;
+        b.out = y;
+        b.rng = r;
+        deep_run<false>(plan, s, b, d->s_local);
+        return hot_detail::note_hip(hipGetLastError());
+    }
     if (const SlabForwardPlan plan = slab_forward_plan(d); plan.two.waves || plan.one.waves) {
         SlabArgs b;
         b.rows = d->rows;
@@ -3287,6 +3732,30 @@ int hot_linear_backward_rng_ws(const hot_linear_desc *d, int32_t s_total, double
     // (a workspace that lets the kernel below cut the outputs into parts beats a four-wave launch that leaves a quarter of
     // its slots empty: 256 x 2160 x 8640, 136 workgroups of 256 rows x 32 inputs: the whole call 0.71 -> 0.53 ms)
     const int parts_at_hand = xgrad_parts(d, workspace ? workspace_bytes : 0);
+    if (const DeepPlan plan = deep_input_grad_plan(d, aligned16(dy), workspace ? workspace_bytes : 0); plan.code >= 0) {
+        DeepArgs b;
+        b.rows = d->rows;
+        b.contract = d->out_features;
+        b.outs = d->in_features;
+        b.ld_in = d->out_features;
+        b.in_sample_stride = d->rows * d->out_features;
+        b.part_stride = (long)d->s_local * d->rows * d->in_features;
+        b.n_begin = 0;
+        b.weight_quad0 = a.weight_quad0;
+        b.bias_quad0 = 0;
+        b.in = dy;
+        b.mu_w = mu_w;
+        b.sigma_w = sigma_w;
+        b.mu_b = b.sigma_b = nullptr;
+        b.out = plan.parts > 1 ? static_cast<float *>(workspace) : dx;
+        b.rng = r;
+        deep_run<true>(plan, s, b, d->s_local);
+        if (plan.parts > 1) {
+            const long quads = b.part_stride / 4;
+            hot_linear_dx_sum_kernel<<<dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, s>>>(dx, b.out, quads, plan.parts);
+        }
+        return hot_detail::note_hip(hipGetLastError());
+    }
     if (const SlabShape one = slab_input_grad_shape(d, aligned16(dy)); one.waves && !(parts_at_hand > 1 && one.waves == 4 && one.fill < 0.75)) {
         SlabArgs b;
         b.rows = d->rows;

@@ -1025,3 +1025,81 @@ def test_large_layer_weight_gradients_on_sampled_outputs(oracle, hot, rows, k, o
         err = np.abs(out[name].cpu().numpy()[o_sub].astype(np.float64) - w64)
         assert np.all(err <= 1e-5 * mag), f"{name}: worst {np.max(err / mag):.2e}"
         print("  %s worst error / magnitude sum: %.2e" % (name, np.max(err / mag)), flush=True)
+
+
+# (rows, contraction, outputs of the contraction, samples, per-sample input): the kernel for tens to hundreds of rows, every tile shape
+# it has (its cost model picks them in this order), as forward call and, with contraction and outputs exchanged, as input gradients.
+# Ragged rows (one row in the last block of 32, one block, a second row tile), a contraction with a last step of 4 indices and one of
+# whole rounds of the four waves, fewer steps than waves would share evenly, outputs that are no multiple of 32 or of 4
+DEEP_FORWARD = [(33, 164, 43, 1, False), (64, 128, 45, 3, True), (65, 128, 2069, 2, False), (129, 132, 4215, 1, False), (193, 260, 1358, 3, True),
+                (257, 164, 2705, 3, False), (129, 128, 8202, 1, False), (193, 128, 6148, 2, True), (65, 128, 8321, 3, False),
+                (321, 1028, 300, 2, True), (704, 324, 130, 1, False),
+                # the last outputs in a second launch of another shape (behind outputs 4096, 8192 and 5440)
+                (300, 516, 5493, 2, True), (255, 400, 8431, 2, False), (300, 408, 8261, 2, False)]
+DEEP_INPUT_GRAD = [(65, 256, 1588, 1, 0), (65, 324, 56, 1, 1), (65, 260, 1364, 3, 0), (65, 260, 676, 2, 1), (129, 260, 2072, 2, 0),
+                   (193, 256, 1396, 3, 0), (255, 600, 1212, 1, 1), (320, 1164, 1608, 1, 1), (129, 256, 8240, 1, 0), (320, 688, 1204, 1, 1),
+                   (255, 408, 6196, 2, 0), (255, 832, 2088, 1, 1), (300, 400, 8316, 1, 0), (255, 408, 8240, 2, 0)]
+
+
+def _materialised(hot, c, s, rng, w_off, b_off):
+    """The weights and biases of the draw as the flat forward call writes them, [s, o, k] and [s, o] in float64."""
+    o, k = c["mu_w"].shape
+    n = b_off + (o + 3) // 4 * 4
+    mu, sigma = torch.zeros(n, device=DEV), torch.full((n,), 0.5, device=DEV)
+    for off, name in ((w_off, "w"), (b_off, "b")):
+        mu[off:off + c["mu_" + name].numel()] = c["mu_" + name].reshape(-1)
+        sigma[off:off + c["mu_" + name].numel()] = c["sigma_" + name].reshape(-1)
+    plan = hot.hot_create(n, n, s, s, 1.0, 0)
+    w = torch.empty(s, n, device=DEV)
+    hot.hot_forward_rng(plan, rng, mu, sigma, w)
+    torch.cuda.synchronize()
+    hot.hot_destroy(plan)
+    return w[:, w_off:w_off + o * k].view(s, o, k).double(), w[:, b_off:b_off + o].double()
+
+
+def _deep_case(seed, o, k):
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    return g, {"mu_w": torch.randn(o, k, device=DEV, generator=g) * 0.1, "sigma_w": torch.rand(o, k, device=DEV, generator=g) * 0.05 + 0.01,
+               "mu_b": torch.randn(o, device=DEV, generator=g), "sigma_b": torch.rand(o, device=DEV, generator=g) + 0.1}
+
+
+@pytest.mark.parametrize("rows,k,o,s,xs", DEEP_FORWARD)
+def test_forward_at_tens_to_hundreds_of_rows_against_materialised_weights(hot, rows, k, o, s, xs):
+    """Within 1e-5 of the sum of the magnitudes of the addends, as the other forward kernels; rows of x have padding that holds NaN."""
+    print("case linear, tens to hundreds of rows", rows, k, o, s, xs, flush=True)
+    assert hot.hot_linear_launch_shape(rows, k, o, s, 0, per_sample_x=xs, ldx=k + 8) == 0
+    g, c = _deep_case(rows + o, o, k)
+    wide = torch.full((s, rows, k + 8) if xs else (rows, k + 8), float("nan"), device=DEV)
+    x = wide[..., :k]
+    x.copy_(torch.randn(x.shape, device=DEV, generator=g))
+    rng, w_off, b_off = hot.hot_rng(seed=41, step=3, first_sample=1), 8, 8 + (o * k + 3) // 4 * 4
+    guard = torch.full((s * rows * o + 64,), float("nan"), device=DEV)
+    y = guard[:s * rows * o].view(s, rows, o)
+    hot.hot_linear_forward_rng(rng, x, c["mu_w"], c["sigma_w"], c["mu_b"], c["sigma_b"], y, w_off, b_off)
+    w, b = _materialised(hot, c, s, rng, w_off, b_off)
+    assert bool(torch.isnan(guard[s * rows * o:]).all()), "written beyond y"
+    for i in range(s):
+        xi = (x[i] if xs else x).double()
+        want, mag = xi @ w[i].t() + b[i], xi.abs() @ w[i].abs().t() + b[i].abs()
+        assert bool(((y[i].double() - want).abs() <= 1e-5 * mag).all()), ((y[i].double() - want).abs() / mag).max().item()
+
+
+@pytest.mark.parametrize("rows,o,k,s,parts", DEEP_INPUT_GRAD)
+def test_input_gradients_at_tens_to_hundreds_of_rows_against_materialised_weights(hot, rows, o, k, s, parts):
+    """parts: with the workspace the call asks for (the contraction then cut into parts), else without one."""
+    print("case linear dx, tens to hundreds of rows", rows, o, k, s, parts, flush=True)
+    assert parts or hot.hot_linear_launch_shape(rows, k, o, s, 1) == 0
+    g, c = _deep_case(rows + k, o, k)
+    x, dy = torch.randn(rows, k, device=DEV, generator=g), torch.randn(s, rows, o, device=DEV, generator=g)
+    rng, w_off, b_off = hot.hot_rng(seed=43, step=3, first_sample=1), 8, 8 + (o * k + 3) // 4 * 4
+    guard = torch.full((s * rows * k + 64,), float("nan"), device=DEV)
+    dx = guard[:s * rows * k].view(s, rows, k)
+    ws = torch.full((hot.hot_linear_backward_workspace_bytes(rows, k, o, s) // 4 + 16,), float("nan"), device=DEV) if parts else None
+    hot.hot_linear_backward_rng(rng, x, dy, c["mu_w"], c["sigma_w"], None, None, torch.empty(o, k, device=DEV), torch.empty(o, k, device=DEV),
+                                None, None, dx, s, 100.0, hot.HOT_REDUCE_SUM, w_off, b_off, workspace=ws[:-16] if parts else None)
+    w, _ = _materialised(hot, c, s, rng, w_off, b_off)
+    assert bool(torch.isnan(guard[s * rows * k:]).all()), "written beyond dx"
+    assert ws is None or bool(torch.isnan(ws[-16:]).all()), "written beyond the workspace"
+    for i in range(s):
+        want, mag = dy[i].double() @ w[i], dy[i].double().abs() @ w[i].abs()
+        assert bool(((dx[i].double() - want).abs() <= 1e-5 * mag).all()), ((dx[i].double() - want).abs() / mag).max().item()
