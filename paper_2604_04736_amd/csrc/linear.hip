@@ -107,6 +107,7 @@ struct LinearArgs {
     long rows, in_features, out_features, ldx;
     long x_sample_stride;   // floats between the inputs of consecutive samples (0: one input for all)
     int s_loc;
+    int s_chunk;            // hot_linear_forward_kernel: samples per layer of the grid along z
     long weight_quad0;   // (weight_offset) / 4
     long bias_quad0;     // (bias_offset) / 4
     const float *x, *mu_w, *sigma_w, *mu_b, *sigma_b;
@@ -132,8 +133,10 @@ hot_linear_forward_kernel(LinearArgs a)
     const float *mu_row = a.mu_w + (o_ok ? o : 0) * K;
     const float *sg_row = a.sigma_w + (o_ok ? o : 0) * K;
     const long quad_row = a.weight_quad0 + ((o_ok ? o : 0) * K >> 2);
+    // grid z: the samples in chunks of s_chunk (a multiple of ST)
+    const int s_lo = (int)blockIdx.z * a.s_chunk, s_hi = s_lo + a.s_chunk < a.s_loc ? s_lo + a.s_chunk : a.s_loc;
 
-    for (int s0 = 0; s0 < a.s_loc; s0 += ST) {
+    for (int s0 = s_lo; s0 < s_hi; s0 += ST) {
         Acc16x16 mm[ST][RB];
 
         for (long kb = (long)wave * kInputsPerIter; kb < K; kb += (long)waves * kInputsPerIter) {
@@ -156,7 +159,7 @@ hot_linear_forward_kernel(LinearArgs a)
             }
 #pragma unroll
             for (int st = 0; st < ST; ++st) {
-                if (s0 + st < a.s_loc) {          // uniform over the wave
+                if (s0 + st < s_hi) {             // uniform over the wave
                     if constexpr (XS) {
                         const float *xs = a.x + (size_t)(s0 + st) * (size_t)a.x_sample_stride;
 #pragma unroll
@@ -222,7 +225,7 @@ hot_linear_forward_kernel(LinearArgs a)
 
 #pragma unroll
         for (int st = 0; st < ST; ++st) {
-            if (s0 + st < a.s_loc) {
+            if (s0 + st < s_hi) {
                 float bias = 0.0f;
                 if (a.mu_b && o_ok) {
                     const f4 e = eps_quad(a.bias_quad0 + (o >> 2), s0 + st, a.rng);
@@ -3492,6 +3495,7 @@ int hot_linear_forward_rng(const hot_linear_desc *d, const hot_rng *rng, const f
     a.ldx = d->ldx;
     a.x_sample_stride = d->x_sample_stride;
     a.s_loc = d->s_local;
+    a.s_chunk = d->s_local;
     a.weight_quad0 = d->weight_offset >> 2;
     a.bias_quad0 = mu_b ? d->bias_offset >> 2 : 0;
     a.x = x;
@@ -3576,7 +3580,7 @@ int hot_linear_forward_rng(const hot_linear_desc *d, const hot_rng *rng, const f
     // rows per workgroup: 16, 32 or 64 (one, two or four MFMA row tiles share every drawn weight)
     const int rb = d->rows > 32 ? 4 : (d->rows > 16 ? 2 : 1);
     // samples whose accumulators are live together (they share the loads of mu_W, sigma_W and x)
-    const int st = d->s_local >= 4 && four_samples_fit(rb, d->x_sample_stride != 0) ? 4 : (d->s_local >= 2 ? 2 : 1);
+    int st = d->s_local >= 4 && four_samples_fit(rb, d->x_sample_stride != 0) ? 4 : (d->s_local >= 2 ? 2 : 1);
     const long gx = (d->out_features + kColsPerWave - 1) / kColsPerWave;
     const long gy = (d->rows + kRowsPerTile * rb - 1) / (kRowsPerTile * rb);
     if (gx > 0x7fffffffL || gy > 65535) return HOT_EINVAL;
@@ -3587,7 +3591,19 @@ int hot_linear_forward_rng(const hot_linear_desc *d, const hot_rng *rng, const f
     while (waves < max_waves(rb) && gx * gy * waves < 8192 && 2L * waves <= k_blocks &&
            (size_t)(2 * waves - 1) * (size_t)(st * rb * 4) * 64 * sizeof(float) <= 65536)
         waves *= 2;
-    const dim3 grid((unsigned)gx, (unsigned)gy);
+    // Small layers leave most of the chip idle while one workgroup draws its samples one after the other (1 x 96 x 128 x 16
+    // samples: eight workgroups, 28 us of dependent instructions): the samples then go to workgroups of their own, one each while all
+    // waves fit on the chip at two per SIMD, else in as many chunks as do.
+    const long waves_all = gx * gy * waves;
+    a.s_chunk = (d->s_local + st - 1) / st * st;
+    if (waves_all * d->s_local <= 2048) {
+        st = 1;
+        a.s_chunk = 1;
+    } else if (2 * waves_all <= 2048) {
+        const int chunks = (int)(2048 / waves_all);
+        a.s_chunk = ((d->s_local + chunks - 1) / chunks + st - 1) / st * st;
+    }
+    const dim3 grid((unsigned)gx, (unsigned)gy, (unsigned)((d->s_local + a.s_chunk - 1) / a.s_chunk));
     if (rb == 4) linear_go<4>(st, grid, waves, s, a);
     else if (rb == 2) linear_go<2>(st, grid, waves, s, a);
     else linear_go<1>(st, grid, waves, s, a);

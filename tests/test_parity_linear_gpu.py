@@ -1103,3 +1103,18 @@ def test_input_gradients_at_tens_to_hundreds_of_rows_against_materialised_weight
     for i in range(s):
         want, mag = dy[i].double() @ w[i], dy[i].double().abs() @ w[i].abs()
         assert bool(((dx[i].double() - want).abs() <= 1e-5 * mag).all()), ((dx[i].double() - want).abs() / mag).max().item()
+
+
+# few rows and many samples: every sample in a workgroup of its own; samples in chunks (shared x: 4 + 4 + 1; own x: 4 + 4 + 1 by twos)
+@pytest.mark.parametrize("rows,k,o,s,xs", [(1, 96, 128, 16, False), (3, 68, 24, 7, True), (5, 1028, 530, 9, False), (5, 1028, 530, 9, True),
+                                           (20, 132, 40, 33, True)])
+def test_forward_of_many_samples_on_small_layers_against_materialised_weights(hot, rows, k, o, s, xs):
+    g, c = _deep_case(rows + o, o, k)
+    x = torch.randn((s, rows, k) if xs else (rows, k), device=DEV, generator=g)
+    rng, w_off, b_off = hot.hot_rng(seed=47, step=3, first_sample=1), 8, 8 + (o * k + 3) // 4 * 4
+    y = torch.full((s, rows, o), float("nan"), device=DEV)
+    hot.hot_linear_forward_rng(rng, x, c["mu_w"], c["sigma_w"], c["mu_b"], c["sigma_b"], y, w_off, b_off)
+    w, b = _materialised(hot, c, s, rng, w_off, b_off)
+    x3 = (x if xs else x.unsqueeze(0).expand(s, rows, k)).double()
+    want, mag = torch.matmul(x3, w.transpose(1, 2)) + b.unsqueeze(1), torch.matmul(x3.abs(), w.abs().transpose(1, 2)) + b.abs().unsqueeze(1)
+    assert bool(((y.double() - want).abs() <= 1e-5 * mag).all())
