@@ -539,6 +539,7 @@ hot_linear_slab_kernel(SlabArgs a)
     constexpr int WT = OUTS * KS;            // floats of one sample's weight tile
     constexpr int NX = WROWS / 16;           // load instructions per wave and step
     constexpr int QUADS = ST * OUTS * 4;     // quads drawn per step
+    constexpr bool EVERY = QUADS == 64 * WAVES;
     static_assert(QUADS <= 64 * WAVES && QUADS % 64 == 0, "whole waves draw");
     __shared__ __attribute__((aligned(16))) float xs0[WAVES * XW], xs1[WAVES * XW];
     // (BF: three planes of bf16 pieces instead of one of floats)
@@ -602,6 +603,7 @@ hot_linear_slab_kernel(SlabArgs a)
 #pragma unroll
         for (int j = 0; j < NX; ++j) x_off[j] = x_first[j];
         long d_quad = a.weight_quad0 + (d_flat >> 2);
+
         const bool d_live = d_ok && s0 + d_st < s_hi;
 
         // sends for mu and sigma of this thread's quad of the step that starts at cb0 (every call advances one step)
@@ -614,9 +616,12 @@ hot_linear_slab_kernel(SlabArgs a)
         };
         // draws that quad and puts it into the tile (every call advances one step; zeros beyond the layer's edges)
         auto put_w = [&](int cb0, lds_float *wsb) {
-            if (draws) {
+            // (Beyond the layer's edges mu and sigma have arrived as zeros.  Without the inner branch the scheduler may set the draw
+            // between matrix instructions; where only some waves draw the branch is faster: sixteen waves, 1024 x 8192^2 forward
+            // 1430 against 1495 us, but for the input gradients 1540 against 1480.)
+            if (EVERY || draws) {
                 f4 w4 = {0.0f, 0.0f, 0.0f, 0.0f};
-                if (d_live && cb0 < d_cols) {
+                if (EVERY || (WAVES == 16 && TR) || (d_live && cb0 < d_cols)) {
                     const f4 e = eps_quad(d_quad, s0 + d_st, a.rng);
 #pragma unroll
                     for (int c = 0; c < 4; ++c) w4[c] = __builtin_fmaf(sd4[c], e[c], m4[c]);
@@ -679,26 +684,53 @@ hot_linear_slab_kernel(SlabArgs a)
         // BF: one step on the bf16 matrix instruction.  The operands of the step are read (x as floats, the weights
         // as their three planes), x is cut into its pieces, and six products per block of 32 x 32 leave out only the
         // terms below 2^-24 of the full product; then the barrier, behind which the buffers just read are refilled.
+        // AHEAD: both row blocks are cut first, every block of weights is read once for the two of them, one block ahead of its
+        // products, and consecutive instructions go to different accumulators; it takes 24 to 36 registers more.  Measured:
+        // 64 output-samples in four waves 82 -> 77 us (16640 x 192 x 768), 128 in eight 246 -> 218 (7260 x 540 x 2160) and 267 -> 244
+        // (its transpose's input gradients), the input gradients of sixteen 1541 -> 1490 (1024 x 8192^2); but the forward call's
+        // sixteen waves spill (1439 -> 1488) and narrower tiles of eight, three waves to a SIMD, lose 3 %.
+        constexpr bool AHEAD = WAVES == 4 || CBW * ST == 4 || (WAVES == 16 && TR);
+        auto read_b = [&](int at, const lds_float *wsb, bf8 (&b)[3]) {      // at = st * CBW + cb
+            const volatile lds_bf8 *wp = (const volatile lds_bf8 *)((const lds_char *)wsb + ((at / CBW * OUTS + at % CBW * 32 + l32) * 32 + ((half ^ ((l32 >> 3) & 1)) << 4)));
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl) b[pl] = wp[pl * ST * OUTS * 2];
+        };
         auto step_bf = [&](int cb0, lds_float *xsb, lds_float *wsb) {
             read_ops(0, xsb, wsb);
             read_ops(1, xsb, wsb);
+            if constexpr (AHEAD) {
+                constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};
+                bf8 b[2][3], p[RBW][3];
+                read_b(0, wsb, b[0]);
 #pragma unroll
-            for (int rb = 0; rb < RBW; ++rb) {
-                bf8 a1, a2, a3;
-                split8_bf16(xa[0][rb], xa[1][rb], a1, a2, a3);
+                for (int rb = 0; rb < RBW; ++rb) split8_bf16(xa[0][rb], xa[1][rb], p[rb][0], p[rb][1], p[rb][2]);
 #pragma unroll
-                for (int st = 0; st < ST; ++st)
+                for (int at = 0; at < ST * CBW; ++at) {
+                    if (at + 1 < ST * CBW) read_b(at + 1, wsb, b[(at + 1) & 1]);
 #pragma unroll
-                    for (int cb = 0; cb < CBW; ++cb) {
-                        const volatile lds_bf8 *wp = (const volatile lds_bf8 *)((const lds_char *)wsb + ((st * OUTS + cb * 32 + l32) * 32 + ((half ^ ((l32 >> 3) & 1)) << 4)));
-                        const bf8 b1 = wp[0], b2 = wp[ST * OUTS * 2], b3 = wp[2 * ST * OUTS * 2];
-                        mm[st][rb][cb].mac(a3, b1);
-                        mm[st][rb][cb].mac(a2, b2);
-                        mm[st][rb][cb].mac(a1, b3);
-                        mm[st][rb][cb].mac(a2, b1);
-                        mm[st][rb][cb].mac(a1, b2);
-                        mm[st][rb][cb].mac(a1, b1);
-                    }
+                    for (int i = 0; i < 6; ++i)
+#pragma unroll
+                        for (int rb = 0; rb < RBW; ++rb) mm[at / CBW][rb][at % CBW].mac(p[rb][PA[i]], b[at & 1][PB[i]]);
+                }
+            } else {
+#pragma unroll
+                for (int rb = 0; rb < RBW; ++rb) {
+                    bf8 a1, a2, a3;
+                    split8_bf16(xa[0][rb], xa[1][rb], a1, a2, a3);
+#pragma unroll
+                    for (int st = 0; st < ST; ++st)
+#pragma unroll
+                        for (int cb = 0; cb < CBW; ++cb) {
+                            const volatile lds_bf8 *wp = (const volatile lds_bf8 *)((const lds_char *)wsb + ((st * OUTS + cb * 32 + l32) * 32 + ((half ^ ((l32 >> 3) & 1)) << 4)));
+                            const bf8 b1 = wp[0], b2 = wp[ST * OUTS * 2], b3 = wp[2 * ST * OUTS * 2];
+                            mm[st][rb][cb].mac(a3, b1);
+                            mm[st][rb][cb].mac(a2, b2);
+                            mm[st][rb][cb].mac(a1, b3);
+                            mm[st][rb][cb].mac(a2, b1);
+                            mm[st][rb][cb].mac(a1, b2);
+                            mm[st][rb][cb].mac(a1, b1);
+                        }
+                }
             }
             everything_arrived_then_barrier();
             put_w(cb0 + 2 * KS, wsb);
