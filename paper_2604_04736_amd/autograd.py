@@ -114,7 +114,7 @@ class BayesianLinear:
             dev = mu_w.device.index or 0
             sizes = [self.in_features * self.out_features] + ([self.out_features] if self.bias else [])
             self._kl_plans = [hot.hot_create(n, n, 1, 1, self.dataset_size, dev) for n in sizes]
-        out = torch.zeros(len(self._kl_plans), dtype=torch.float64, device=mu_w.device)
+        out = torch.empty(len(self._kl_plans), dtype=torch.float64, device=mu_w.device)       # (each call below writes its element)
         hot.hot_kl(self._kl_plans[0], mu_w.detach().reshape(-1), sigma_w.detach().reshape(-1), out[0:1])
         if self.bias:
             hot.hot_kl(self._kl_plans[1], mu_b.detach(), sigma_b.detach(), out[1:2])
