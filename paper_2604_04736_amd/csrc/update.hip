@@ -260,7 +260,6 @@ static int dropout_backward_impl(const hot_desc *d, const hot_rng *rng, double k
     Rng r;
     if (!make_rng(rng, d->s_local, r)) return HOT_EINVAL;
     const bool al = aligned16(grad_w) && aligned16(grad_mu) && (d->ld % 4 == 0);
-    const bool nt = (double)d->s_local * (double)d->ld * 4.0 >= 256.0 * 1048576.0;
     const double g = d->flags == HOT_REDUCE_NONE ? 1.0
                      : (d->flags == HOT_REDUCE_MEAN ? 1.0 / (double)d->s_local : 1.0 / (double)d->s_total);
     const dim3 grid(blocks_for((d->n_weights + 3) / 4)), block(kBlock);
@@ -268,9 +267,10 @@ static int dropout_backward_impl(const hot_desc *d, const hot_rng *rng, double k
     const DropMask dm = drop_mask(keep);
     const unsigned thr = dm.last_kept;
     const float inv = dm.inv_keep;
-    if (al && nt) hot_dropout_backward_kernel<true, true><<<grid, block, 0, s>>>(d->n_weights, d->ld, d->s_local, g, grad_w, grad_mu, r, thr, inv, period, unit_offset >> 2);
-    else if (al) hot_dropout_backward_kernel<true, false><<<grid, block, 0, s>>>(d->n_weights, d->ld, d->s_local, g, grad_w, grad_mu, r, thr, inv, period, unit_offset >> 2);
-    else hot_dropout_backward_kernel<false, false><<<grid, block, 0, s>>>(d->n_weights, d->ld, d->s_local, g, grad_w, grad_mu, r, thr, inv, period, unit_offset >> 2);
+    // (grad_w is read once, right after the network wrote it or, more often, something else: non-temporal loads whatever the size, as
+    // in hot_backward.  2.7 M weights x 16 samples, 172 MB: 50 -> 45 us against plain loads, which were kept below 256 MiB)
+    if (al) hot_dropout_backward_kernel<true, true><<<grid, block, 0, s>>>(d->n_weights, d->ld, d->s_local, g, grad_w, grad_mu, r, thr, inv, period, unit_offset >> 2);
+    else hot_dropout_backward_kernel<false, true><<<grid, block, 0, s>>>(d->n_weights, d->ld, d->s_local, g, grad_w, grad_mu, r, thr, inv, period, unit_offset >> 2);
     return hot_detail::note_hip(hipGetLastError());
 }
 
