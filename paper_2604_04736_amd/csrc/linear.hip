@@ -1098,7 +1098,7 @@ struct DeepShape {
     double us[4];
 };
 constexpr DeepShape kDeepShapes[] = {{2, 1, 4, {1.05, 1.9, 2.3, 2.9}}, {4, 1, 3, {1.1, 2.05, 2.8}}, {6, 1, 2, {1.5, 2.7}}, {8, 1, 2, {1.75, 3.8}}, {10, 1, 1, {2.3}},
-                                     {6, 2, 1, {2.2}}, {8, 2, 1, {3.0}}, {4, 2, 2, {2.1, 3.9}}};
+                                     {6, 2, 1, {2.6}}, {8, 2, 1, {3.0}}, {4, 2, 2, {2.1, 3.9}}};
 constexpr int kDeepCodes = sizeof(kDeepShapes) / sizeof(kDeepShapes[0]);
 constexpr int kDeepCodesTr = kDeepCodes - 1;        // (the last one's transposed draw spills its registers)
 

@@ -1034,7 +1034,7 @@ def test_large_layer_weight_gradients_on_sampled_outputs(oracle, hot, rows, k, o
 DEEP_FORWARD = [(33, 164, 43, 1, False), (64, 128, 45, 3, True), (65, 128, 2069, 2, False), (129, 132, 4215, 1, False), (193, 260, 1358, 3, True),
                 (257, 164, 2705, 3, False), (129, 128, 8202, 1, False), (193, 128, 6148, 2, True), (65, 128, 8321, 3, False),
                 (321, 1028, 300, 2, True), (704, 324, 130, 1, False),
-                # the last outputs in a second launch of another shape (behind outputs 4096, 8192 and 5440)
+                # hundreds of rows on wide layers; in the last two the outputs behind 8192 and 5440 go to a second launch of another shape
                 (300, 516, 5493, 2, True), (255, 400, 8431, 2, False), (300, 408, 8261, 2, False)]
 DEEP_INPUT_GRAD = [(65, 256, 1588, 1, 0), (65, 324, 56, 1, 1), (65, 260, 1364, 3, 0), (65, 260, 676, 2, 1), (129, 260, 2072, 2, 0),
                    (193, 256, 1396, 3, 0), (255, 600, 1212, 1, 1), (320, 1164, 1608, 1, 1), (129, 256, 8240, 1, 0), (320, 688, 1204, 1, 1),
