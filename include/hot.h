@@ -279,8 +279,9 @@ int hot_linear_forward_rng(const hot_linear_desc *desc, const hot_rng *rng, cons
  * scale the sums and add the KL part in fp32 (g * sum + k * mu, g * sum + k * (sigma - 1/sigma) with the hardware's
  * reciprocal: 1e-7 of each term), where hot_backward does it in fp64.  Against
  * library GEMMs for dx and G followed by hot_backward_rng the call is 1.1-3x faster up to tens of rows (with a
- * workspace, see below; 0.8-3x without) and at 1.08-1.25x for thousands of rows; between about 100 and 450 rows it
- * mostly stays behind on large layers (0.65-1.0x).
+ * workspace, see below; 0.8-3x without) and at 1.08-1.25x for thousands of rows; from 65 rows on the input gradients of
+ * layers with at least 256 outputs come from the forward call's kernel for tens to hundreds of rows (300 x 2160 x 8640, two
+ * samples: 486 -> 203 us for dx).
  */
 int hot_linear_backward_rng(const hot_linear_desc *desc, int32_t s_total, double dataset_size, uint32_t flags,
                             const hot_rng *rng, const float *x, const float *dy, const float *mu_w,
@@ -308,9 +309,12 @@ int hot_linear_launch_shape(const hot_linear_desc *desc, int which);
  * differs).  A layer with few weights and many rows (a ViT layer: 192 x 768 weights, 16 640 rows) has too
  * few 16-output x 64-input tiles to give every compute unit weight-gradient work, and the waves of one
  * workgroup are all that can add up the rows of a tile without memory.  With a workspace the rows are cut
- * into up to 16 parts for different workgroups; each part leaves its sums there and a second kernel adds
- * them in part order and finishes the gradients: deterministic, no atomics.  The input gradients use the
- * same memory afterwards where 256-row workgroups are too few for the chip (few inputs, around a thousand
+ * into parts for different workgroups; each part leaves its sums there and a second kernel adds
+ * them in a fixed order and finishes the gradients: deterministic, no atomics.  From 129 rows on (300 for one or two samples),
+ * where out_features is a multiple of 4 and the layer has fewer than 512 tiles of 128 x 128, the parts multiply bf16
+ * pieces and leave the raw product of each sample, so that every eps is drawn once (16640 x 192 x 768, two samples: 173 ->
+ * 75-85 us; 7260 x 2160 x 540: 435 -> 202).  The input gradients use the
+ * same memory afterwards where the tiles of dx are too few for the chip (few inputs, up to about a thousand
  * rows): the outputs they contract over are cut into parts, whose dx blocks a second kernel adds.
  * Up to 128 rows with dx wanted the workspace buys more: weight and input gradients then come from ONE pass
  * over the weights, every eps drawn once instead of once per kernel, and the draw is most of the time at so
