@@ -2330,73 +2330,73 @@ hot_linear_wgrad_row_parts_kernel(LinearGradArgs a, int parts, int chunk)
     // chunks before left in the workspace (the same thread holds the same sums every time).  What is sent for beyond the end
     // of a chunk are the first rows of the next.
     for (long c_lo = r_lo; c_lo < r_hi; c_lo += chunk) {
-    const long c_hi = c_lo + chunk < r_hi ? c_lo + chunk : r_hi;
-    Acc32x32 mm[NB][NS];
-    for (long r = c_lo + kRowPartRows * wave; r < c_hi; r += kRowPartRows * kRowPartWaves) {       // uniform over the wave
-        if (bias_tile) {
+        const long c_hi = c_lo + chunk < r_hi ? c_lo + chunk : r_hi;
+        Acc32x32 mm[NB][NS];
+        for (long r = c_lo + kRowPartRows * wave; r < c_hi; r += kRowPartRows * kRowPartWaves) {       // uniform over the wave
+            if (bias_tile) {
 #pragma unroll
-            for (int t = 0; t < 8; ++t)
+                for (int t = 0; t < 8; ++t)
 #pragma unroll
-                for (int j = 0; j < OB; ++j) col_sum[j] += XBIG ? sr[t][j % NS] : br[t][j];
-        }
-        bf8 b1[NB], b2[NB], b3[NB];
+                    for (int j = 0; j < OB; ++j) col_sum[j] += XBIG ? sr[t][j % NS] : br[t][j];
+            }
+            bf8 b1[NB], b2[NB], b3[NB];
 #pragma unroll
-        for (int i = 0; i < NB; ++i)
-            split8_bf16(f4{br[0][i], br[1][i], br[2][i], br[3][i]}, f4{br[4][i], br[5][i], br[6][i], br[7][i]}, b1[i], b2[i], b3[i]);
-        ask_big();
+            for (int i = 0; i < NB; ++i)
+                split8_bf16(f4{br[0][i], br[1][i], br[2][i], br[3][i]}, f4{br[4][i], br[5][i], br[6][i], br[7][i]}, b1[i], b2[i], b3[i]);
+            ask_big();
 #pragma unroll
-        for (int j = 0; j < NS; ++j) {
-            bf8 c1, c2, c3;
-            split8_bf16(f4{sr[0][j], sr[1][j], sr[2][j], sr[3][j]}, f4{sr[4][j], sr[5][j], sr[6][j], sr[7][j]}, c1, c2, c3);
-            if (j == NS - 1) ask_small();
+            for (int j = 0; j < NS; ++j) {
+                bf8 c1, c2, c3;
+                split8_bf16(f4{sr[0][j], sr[1][j], sr[2][j], sr[3][j]}, f4{sr[4][j], sr[5][j], sr[6][j], sr[7][j]}, c1, c2, c3);
+                if (j == NS - 1) ask_small();
 #pragma unroll
-            for (int i = 0; i < NB; ++i) {
-                // (x is the A operand: its index runs over the registers of a result)
-                auto mac = [&](const bf8 &b, const bf8 &c) {
-                    if constexpr (XBIG) mm[i][j].mac(b, c);
-                    else mm[i][j].mac(c, b);
-                };
-                mac(b3[i], c1);
-                mac(b2[i], c2);
-                mac(b1[i], c3);
-                mac(b2[i], c1);
-                mac(b1[i], c2);
-                mac(b1[i], c1);
+                for (int i = 0; i < NB; ++i) {
+                    // (x is the A operand: its index runs over the registers of a result)
+                    auto mac = [&](const bf8 &b, const bf8 &c) {
+                        if constexpr (XBIG) mm[i][j].mac(b, c);
+                        else mm[i][j].mac(c, b);
+                    };
+                    mac(b3[i], c1);
+                    mac(b2[i], c2);
+                    mac(b1[i], c3);
+                    mac(b2[i], c1);
+                    mac(b1[i], c2);
+                    mac(b1[i], c1);
+                }
             }
         }
-    }
-    const MfmaSettled settled;
+        const MfmaSettled settled;
 
-    // result register 4 q + c of a block: input index 8 q + 4 half + c, output index l32; input k0 + KB index + i, output o0 + OB index + j
-    float *const P = a.ws + (size_t)part * (size_t)row_part_floats(K, O, a.s_loc) + (size_t)s * (size_t)(O * K);
+        // result register 4 q + c of a block: input index 8 q + 4 half + c, output index l32; input k0 + KB index + i, output o0 + OB index + j
+        float *const P = a.ws + (size_t)part * (size_t)row_part_floats(K, O, a.s_loc) + (size_t)s * (size_t)(O * K);
 #pragma unroll
-    for (int j = 0; j < OB; ++j) {
-        float *mine = turn[wave];
+        for (int j = 0; j < OB; ++j) {
+            float *mine = turn[wave];
 #pragma unroll
-        for (int g = 0; g < 16; ++g) {
-            const int m = 8 * (g >> 2) + 4 * half + (g & 3);
-            typename Floats<KB>::V v;
+            for (int g = 0; g < 16; ++g) {
+                const int m = 8 * (g >> 2) + 4 * half + (g & 3);
+                typename Floats<KB>::V v;
 #pragma unroll
-            for (int i = 0; i < KB; ++i) v[i] = XBIG ? mm[i][j % NS].read(settled)[g] : mm[j][i % NS].read(settled)[g];
-            *reinterpret_cast<typename Floats<KB>::V *>(mine + l32 * PITCH + KB * m) = v;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int it = 0; it < KB; ++it) {
-            const int idx = it * 64 * kRowPartWaves + (int)threadIdx.x, row = idx / (TK / 4), quad = idx % (TK / 4);
-            f4 of_wave[kRowPartWaves], sum;
-#pragma unroll
-            for (int v = 0; v < kRowPartWaves; ++v) of_wave[v] = *reinterpret_cast<const f4 *>(turn[v] + row * PITCH + 4 * quad);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) sum[c] = (of_wave[0][c] + of_wave[1][c]) + (of_wave[2][c] + of_wave[3][c]);
-            const long o = o0 + OB * row + j, k = k0 + 4 * quad;
-            if (o < O && k < K) {
-                if (c_lo != r_lo) sum += load4<true, false>(P + o * K + k);
-                store4<true, false>(P + o * K + k, sum);
+                for (int i = 0; i < KB; ++i) v[i] = XBIG ? mm[i][j % NS].read(settled)[g] : mm[j][i % NS].read(settled)[g];
+                *reinterpret_cast<typename Floats<KB>::V *>(mine + l32 * PITCH + KB * m) = v;
             }
+            __syncthreads();
+#pragma unroll
+            for (int it = 0; it < KB; ++it) {
+                const int idx = it * 64 * kRowPartWaves + (int)threadIdx.x, row = idx / (TK / 4), quad = idx % (TK / 4);
+                f4 of_wave[kRowPartWaves], sum;
+#pragma unroll
+                for (int v = 0; v < kRowPartWaves; ++v) of_wave[v] = *reinterpret_cast<const f4 *>(turn[v] + row * PITCH + 4 * quad);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) sum[c] = (of_wave[0][c] + of_wave[1][c]) + (of_wave[2][c] + of_wave[3][c]);
+                const long o = o0 + OB * row + j, k = k0 + 4 * quad;
+                if (o < O && k < K) {
+                    if (c_lo != r_lo) sum += load4<true, false>(P + o * K + k);
+                    store4<true, false>(P + o * K + k, sum);
+                }
+            }
+            __syncthreads();
         }
-        __syncthreads();
-    }
     }
     if (bias_tile) {            // uniform over the workgroup
 #pragma unroll
