@@ -305,6 +305,18 @@ int hot_linear_backward_rng(const hot_linear_desc *desc, int32_t s_total, double
 int hot_linear_launch_shape(const hot_linear_desc *desc, int which);
 
 /*
+ * The same for the kernels that hot_linear_launch_shape answers 0 for (host arithmetic only; same passages of the paper).
+ * which = 0: hot_linear_forward_rng; 1: the input-gradient part of hot_linear_backward_rng_ws with workspace_bytes of workspace
+ * (0: none; negative: all that it asks for; dy taken to be 16-byte aligned).  Where the kernel for tens to hundreds of rows runs:
+ * 10 * (rows per workgroup / 32) + (outputs per workgroup / 32) of its launch, + 1000 * the same number of the second launch for
+ * the outputs left over (if there is one), + 1 000 000 * the parts that the contraction is cut into (1: not cut), e.g. 1021101.
+ * which = 2: weight gradients from row parts with that workspace: 10 * parts, + 1000 * the chunks in which a part is added up,
+ * + 1 with tiles of 128 inputs x 64 outputs (else 64 x 128).  0 where other kernels run.  HOT_EINVAL for a malformed
+ * desc or another `which`.
+ */
+int64_t hot_linear_kernel_shape(const hot_linear_desc *desc, int which, int64_t workspace_bytes);
+
+/*
  * The same call with device scratch of the caller's (same passage of the paper; only the launch shape
  * differs).  A layer with few weights and many rows (a ViT layer: 192 x 768 weights, 16 640 rows) has too
  * few 16-output x 64-input tiles to give every compute unit weight-gradient work, and the waves of one

@@ -31,12 +31,12 @@ EXPORTS = ("hot_create", "hot_forward", "hot_backward", "hot_destroy", "hot_set_
            "hot_linear_backward_rng", "hot_kl", "hot_forward_dropout_units_rng",
            "hot_backward_dropout_units_rng", "hot_stats_whole", "hot_adam_forward", "hot_backward_adam_forward",
            "hot_linear_backward_rng_ws", "hot_linear_backward_workspace_bytes", "hot_forward_static",
-           "hot_linear_launch_shape")
+           "hot_linear_launch_shape", "hot_linear_kernel_shape")
 
 
 # Return types of the entry points that do not return an int status (as declared in include/hot.h).
 RESTYPES = {"hot_strerror": ctypes.c_char_p, "hot_recommended_ld": ctypes.c_int64,
-            "hot_linear_backward_workspace_bytes": ctypes.c_int64}
+            "hot_linear_backward_workspace_bytes": ctypes.c_int64, "hot_linear_kernel_shape": ctypes.c_int64}
 
 
 class hot_desc(ctypes.Structure):
@@ -122,6 +122,8 @@ def lib() -> ctypes.CDLL:
     L.hot_linear_backward_rng_ws.restype = ctypes.c_int
     L.hot_linear_backward_workspace_bytes.argtypes = [ctypes.POINTER(hot_linear_desc)]
     L.hot_linear_launch_shape.argtypes = [ctypes.POINTER(hot_linear_desc), ctypes.c_int]
+    L.hot_linear_kernel_shape.argtypes = [ctypes.POINTER(hot_linear_desc), ctypes.c_int, ctypes.c_int64]
+    L.hot_linear_kernel_shape.restype = ctypes.c_int64
     L.hot_linear_backward_workspace_bytes.restype = ctypes.c_int64
     L.hot_adam_forward.argtypes = [vp, rp, ctypes.POINTER(hot_adam)] + [fp] * 10 + [vp, vp]
     L.hot_backward_adam.argtypes = [vp, rp, ctypes.POINTER(hot_adam)] + [fp] * 8 + [vp]
@@ -526,6 +528,19 @@ def hot_linear_launch_shape(rows: int, in_features: int, out_features: int, s_lo
     code = lib().hot_linear_launch_shape(ctypes.byref(d), which)
     if code < 0:
         _check_planless(int(code), "hot_linear_launch_shape")
+    return int(code)
+
+
+def hot_linear_kernel_shape(rows: int, in_features: int, out_features: int, s_local: int, which: int, per_sample_x: bool = False,
+                            ldx: int = 0, workspace_bytes: int = -1) -> int:
+    """Code of the tiles of the kernels for tens to hundreds of rows (which = 0: forward, 1: input gradients) or of the weight
+    gradients from row parts (which = 2), with workspace_bytes of workspace (negative: all that the layer asks for); see
+    include/hot.h.  0: other kernels."""
+    ldx = ldx or in_features
+    d = hot_linear_desc(rows, in_features, out_features, ldx, 0, 0, s_local, 0, rows * ldx if per_sample_x else 0)
+    code = lib().hot_linear_kernel_shape(ctypes.byref(d), which, workspace_bytes)
+    if code < 0:
+        _check_planless(int(code), "hot_linear_kernel_shape")
     return int(code)
 
 

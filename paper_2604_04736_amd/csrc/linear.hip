@@ -2570,11 +2570,17 @@ inline RowPartsPlan row_parts_plan(const hot_linear_desc *d, int64_t ws_bytes)
     return 2 * p.parts >= wanted.parts ? p : none;
 }
 
+// the chunks in which a part of a layer with `rows` rows is added up
+inline long row_part_chunks(long rows, const RowPartsPlan &p)
+{
+    return rows >= kRowPartLongRows ? (p.rows_per_part + kRowPartLongMost - 1) / kRowPartLongMost : 1;
+}
+
 void row_parts_go(const RowPartsPlan &p, hipStream_t s, const LinearGradArgs &a, long tiles)
 {
     const long per_xcd = (tiles * a.s_loc * p.parts + kXcds - 1) / kXcds;
     const dim3 grid((unsigned)(kXcds * per_xcd)), block(64 * kRowPartWaves);
-    const long chunks = a.rows >= kRowPartLongRows ? (p.rows_per_part + kRowPartLongMost - 1) / kRowPartLongMost : 1;
+    const long chunks = row_part_chunks(a.rows, p);
     const long step_rows = kRowPartRows * kRowPartWaves, chunk = ((p.rows_per_part + chunks - 1) / chunks + step_rows - 1) / step_rows * step_rows;
     if (p.xbig) hot_linear_wgrad_row_parts_kernel<true><<<grid, block, 0, s>>>(a, p.parts, (int)chunk);
     else hot_linear_wgrad_row_parts_kernel<false><<<grid, block, 0, s>>>(a, p.parts, (int)chunk);
@@ -3473,6 +3479,19 @@ int hot_linear_launch_shape(const hot_linear_desc *d, int which)
     if (deep_forward_plan(d).code >= 0) return 0;
     const SlabForwardPlan p = slab_forward_plan(d);
     return p.two.waves ? code(p.two, 2) + 1000 * (p.one.waves ? p.one.cbw : 0) : code(p.one, 1);
+}
+
+int64_t hot_linear_kernel_shape(const hot_linear_desc *d, int which, int64_t workspace_bytes)
+{
+    if (const int plain = hot_linear_launch_shape(d, 0); plain < 0) return plain;
+    if (which < 0 || which > 2) return HOT_EINVAL;
+    if (which == 2) {
+        const RowPartsPlan p = row_parts_plan(d, workspace_bytes);
+        return p.parts ? 1000 * (int64_t)row_part_chunks(d->rows, p) + 10 * p.parts + (p.xbig ? 1 : 0) : 0;
+    }
+    const DeepPlan p = which == 0 ? deep_forward_plan(d) : deep_input_grad_plan(d, true, workspace_bytes);
+    auto code = [](int i) { return i < 0 ? 0 : 10 * kDeepShapes[i].rb + kDeepShapes[i].cb; };
+    return p.code < 0 ? 0 : 1000000 * (int64_t)p.parts + 1000 * code(p.rest_code) + code(p.code);
 }
 
 int64_t hot_linear_backward_workspace_bytes(const hot_linear_desc *d)

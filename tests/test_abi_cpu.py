@@ -147,6 +147,24 @@ def test_one_pass_backward_shape_query_and_its_workspace(hot):
     assert hot.hot_linear_launch_shape(16, 2160, 8640, 2, 2) == 12 and hot.hot_linear_launch_shape(64, 8192, 8192, 2, 2) == 112
 
 
+def test_kernel_shape_query(hot):
+    """Host arithmetic only: what hot_linear_launch_shape answers 0 for, the tiles, parts and chunks of it."""
+    assert hot.hot_linear_kernel_shape(300, 2160, 8640, 2, 0, per_sample_x=True) == 1021101      # 320 x 32, the rest 64 x 32
+    assert hot.hot_linear_launch_shape(300, 2160, 8640, 2, 0, per_sample_x=True) == 0
+    assert hot.hot_linear_kernel_shape(7260, 540, 2160, 2, 0) == 0                               # (another kernel)
+    assert hot.hot_linear_kernel_shape(500, 1024, 4096, 1, 1) // 1000000 > 1                     # dx in parts
+    assert hot.hot_linear_kernel_shape(500, 1024, 4096, 1, 1, workspace_bytes=0) // 1000000 <= 1
+    code = hot.hot_linear_kernel_shape(16640, 192, 768, 2, 2)
+    parts, chunks = code % 1000 // 10, code // 1000
+    assert code % 10 == 0 and parts > 1 and chunks >= -(-16640 // parts) / 832                   # 64 inputs x 128 outputs, 208 rows a wave
+    assert hot.hot_linear_kernel_shape(16640, 192, 768, 2, 2, workspace_bytes=0) == 0
+    for which in (-1, 3):
+        with pytest.raises(hot.HotError):
+            hot.hot_linear_kernel_shape(300, 2160, 8640, 2, which)
+    with pytest.raises(hot.HotError):
+        hot.hot_linear_kernel_shape(300, 2162, 8640, 2, 0)
+
+
 def test_host_only_entry_points(hot):
     assert hot.hot_version() == 302
     assert hot.hot_strerror(0) == "success"
