@@ -2502,10 +2502,11 @@ constexpr long kRowPartMinWeights = 8192, kRowPartAnyWeightsRows = 512;     // (
 constexpr long kRowPartMaxTileCount = 512;
 constexpr int kRowPartMaxParts = 64;
 constexpr int64_t kRowPartMaxBytes = (int64_t)256 << 20, kRowPartSmallBytes = (int64_t)8 << 20;
-// The bf16 matrix instruction rounds every accumulation towards zero, so errors grow with the rows a wave adds up: 16640 x 192 x
-// 768, 2-norm against 64 bits: 3.2e-7 at 297 rows, 3.0e-7 at 245, 2.7e-7 at 198 (the fp32 instruction with 260: 3.0e-7).  From 8192
-// rows on, where the first kernel also cuts many parts, a wave takes at most 208 before its sums leave the registers.
-constexpr long kRowPartLongRows = 8192, kRowPartLongMost = 208 * kRowPartWaves;
+// The bf16 matrix instruction rounds its accumulations to one side (the mean error is negative for sums of either sign, -1.4e-7 of
+// the mean magnitude at 8191 rows in four waves), so errors grow with the rows a wave adds up, 2-norm against 64 bits: 16640 x 192 x 768 3.2e-7 at 297 rows, 3.0e-7 at 245, 2.7e-7 at 198 (the fp32 instruction with 260: 3.0e-7).  So after at most
+// 208 rows a wave's sums leave the registers: 7260 x 2160 x 540 x 8 samples with 1815 rows to a wave 6.0e-7, with 208 3.0e-7 (the
+// fp32 instruction 5.4e-7; 825 -> 922 us, the fp32 instruction 1512), 4673 x 888 x 208 x 8 4.5e-7 -> 2.8e-7 (3.2e-7).
+constexpr long kRowPartMostRows = 208;
 
 inline bool row_parts_suit(const hot_linear_desc *d)
 {
@@ -2570,17 +2571,10 @@ inline RowPartsPlan row_parts_plan(const hot_linear_desc *d, int64_t ws_bytes)
     return 2 * p.parts >= wanted.parts ? p : none;
 }
 
-// the chunks in which a part of a layer with `rows` rows is added up
-inline long row_part_chunks(long rows, const RowPartsPlan &p)
-{
-    return rows >= kRowPartLongRows ? (p.rows_per_part + kRowPartLongMost - 1) / kRowPartLongMost : 1;
-}
-
-void row_parts_go(const RowPartsPlan &p, hipStream_t s, const LinearGradArgs &a, long tiles)
+void row_parts_go(const RowPartsPlan &p, long chunks, hipStream_t s, const LinearGradArgs &a, long tiles)
 {
     const long per_xcd = (tiles * a.s_loc * p.parts + kXcds - 1) / kXcds;
     const dim3 grid((unsigned)(kXcds * per_xcd)), block(64 * kRowPartWaves);
-    const long chunks = row_part_chunks(a.rows, p);
     const long step_rows = kRowPartRows * kRowPartWaves, chunk = ((p.rows_per_part + chunks - 1) / chunks + step_rows - 1) / step_rows * step_rows;
     if (p.xbig) hot_linear_wgrad_row_parts_kernel<true><<<grid, block, 0, s>>>(a, p.parts, (int)chunk);
     else hot_linear_wgrad_row_parts_kernel<false><<<grid, block, 0, s>>>(a, p.parts, (int)chunk);
@@ -3461,6 +3455,19 @@ WgradShape wgrad_shape(const hot_linear_desc *d, int64_t ws_bytes)
     return wgrad_shape_with(d, ws_bytes, false);
 }
 
+// The chunks in which a row part of `p` is added up.  Besides the bound on a wave's rows: where the kernel that would run otherwise
+// splits the rows finely (eight waves to a tile), its sums are half as long as those of four waves here, and so many one-sided
+// roundings are worse than its own (648 x 2032 x 156 x 4 samples: 2.0e-7 against 1.8e-7, 540 x 4080 x 36 x 8 2.1e-7 against
+// 1.9e-7); with at most 3/2 of its rows to a sum they are not (1.5e-7 and 1.7e-7; 31 -> 35 us each).
+inline long row_part_chunks(const hot_linear_desc *d, const RowPartsPlan &p, int64_t ws_bytes)
+{
+    const WgradShape w = wgrad_shape(d, ws_bytes);
+    const long theirs = w.tile ? d->rows : (d->rows + (long)w.split * w.parts - 1) / ((long)w.split * w.parts);
+    const long most = theirs * 3 / 2 < kRowPartMostRows ? theirs * 3 / 2 : kRowPartMostRows;
+    const long rows = (most < kRowPartRows ? kRowPartRows : most / kRowPartRows * kRowPartRows) * kRowPartWaves;
+    return (p.rows_per_part + rows - 1) / rows;
+}
+
 }  // namespace
 
 extern "C" {
@@ -3487,7 +3494,7 @@ int64_t hot_linear_kernel_shape(const hot_linear_desc *d, int which, int64_t wor
     if (which < 0 || which > 2) return HOT_EINVAL;
     if (which == 2) {
         const RowPartsPlan p = row_parts_plan(d, workspace_bytes);
-        return p.parts ? 1000 * (int64_t)row_part_chunks(d->rows, p) + 10 * p.parts + (p.xbig ? 1 : 0) : 0;
+        return p.parts ? 1000 * (int64_t)row_part_chunks(d, p, workspace_bytes) + 10 * p.parts + (p.xbig ? 1 : 0) : 0;
     }
     const DeepPlan p = which == 0 ? deep_forward_plan(d) : deep_input_grad_plan(d, true, workspace_bytes);
     auto code = [](int i) { return i < 0 ? 0 : 10 * kDeepShapes[i].rb + kDeepShapes[i].cb; };
@@ -3758,7 +3765,7 @@ int hot_linear_backward_rng_ws(const hot_linear_desc *d, int32_t s_total, double
     if (const RowPartsPlan plan = row_parts_plan(d, workspace ? workspace_bytes : 0); plan.parts) {
         a.ws = static_cast<float *>(workspace);
         a.rows_per_part = plan.rows_per_part;
-        row_parts_go(plan, s, a, plan.xbig ? row_part_tiles<true>(d) : row_part_tiles<false>(d));
+        row_parts_go(plan, row_part_chunks(d, plan, workspace ? workspace_bytes : 0), s, a, plan.xbig ? row_part_tiles<true>(d) : row_part_tiles<false>(d));
     } else if (shape.tile) {
         wgrad_tile_go(s, a, wgrad_tile_count(d));
     } else {

@@ -1118,3 +1118,54 @@ def test_forward_of_many_samples_on_small_layers_against_materialised_weights(ho
     x3 = (x if xs else x.unsqueeze(0).expand(s, rows, k)).double()
     want, mag = torch.matmul(x3, w.transpose(1, 2)) + b.unsqueeze(1), torch.matmul(x3.abs(), w.abs().transpose(1, 2)) + b.abs().unsqueeze(1)
     assert bool(((y.double() - want).abs() <= 1e-5 * mag).all())
+
+
+# ------------------------------------------------------------------ the bf16 pieces against the fp32 instruction
+
+def _backward(hot, rng, x, dy, c, dx, workspace, s):
+    o, k = c["mu_w"].shape
+    out = [torch.full((o, k), float("nan"), device=DEV) for _ in range(2)]
+    hot.hot_linear_backward_rng(rng, x, dy, c["mu_w"], c["sigma_w"], None, None, out[0], out[1], None, None, dx, s, 1e30,
+                                hot.HOT_REDUCE_NONE, 0, 0, workspace=workspace)
+    return out
+
+
+def _workspace(hot, rows, k, o, s):
+    return torch.empty(max(hot.hot_linear_backward_workspace_bytes(rows, k, o, s) // 4, 4), device=DEV)
+
+
+def _distance(got, want):
+    return ((got.double() - want).norm() / want.norm()).item()
+
+
+# parts of a thousand rows and more; four waves where the other kernel splits the rows over eight
+@pytest.mark.parametrize("rows,k,o,s", [(4673, 888, 208, 8), (6151, 2048, 632, 3), (648, 2032, 156, 4), (540, 4080, 36, 8)])
+@pytest.mark.parametrize("positive", [False, True])
+def test_weight_gradients_from_row_parts_are_no_less_accurate(hot, rows, k, o, s, positive):
+    """Row parts (bf16 pieces, accumulations rounded to one side) against the kernel on the fp32 instruction with a workspace,
+    which the first o - 1 outputs alone go to: the 2-norm distance from 64 bits may not be larger (2 % for what both share, the
+    rounding of the sums over parts and samples).  One unit in the last place, 2^-23, is as good as any distance: the last
+    additions (chunks, waves, parts, samples: four to five roundings of 2^-24 / sqrt(3) each, 7e-8) round that much whichever
+    instruction formed the products, and sums of one sign end there with either (7.4e-8 against 6.8e-8)."""
+    assert hot.hot_linear_kernel_shape(rows, k, o, s, 2)
+    g, c = _deep_case(rows + o, o, k)
+    x, dy = torch.randn(s, rows, k, device=DEV, generator=g), torch.randn(s, rows, o, device=DEV, generator=g)
+    if positive:
+        x, dy = x.abs(), dy.abs()
+    rng = hot.hot_rng(seed=53, step=3, first_sample=1)
+    unit = dict(mu_w=torch.zeros(o, k, device=DEV), sigma_w=torch.ones(o, k, device=DEV),
+                mu_b=torch.zeros(o, device=DEV), sigma_b=torch.ones(o, device=DEV))
+    eps, _ = _materialised(hot, unit, s, rng, 0, o * k)
+    want = [torch.zeros(o, k, device=DEV, dtype=torch.float64) for _ in range(2)]
+    for i in range(s):
+        P = dy[i].double().t() @ x[i].double()
+        want[0] += P
+        want[1] += P * eps[i]
+    parts = _backward(hot, rng, x, dy, c, None, _workspace(hot, rows, k, o, s), s)
+    fewer = {"mu_w": c["mu_w"][:o - 1], "sigma_w": c["sigma_w"][:o - 1]}
+    assert hot.hot_linear_kernel_shape(rows, k, o - 1, s, 2) == 0
+    plain = _backward(hot, rng, x, dy[:, :, :o - 1].contiguous(), fewer, None, _workspace(hot, rows, k, o - 1, s), s)
+    for a, b, w in zip(parts, plain, [w[:o - 1] for w in want]):
+        a = a[:o - 1]
+        print("distance from 64 bits: row parts %.2e, fp32 instruction %.2e" % (_distance(a, w), _distance(b, w)), flush=True)
+        assert _distance(a, w) <= max(1.02 * _distance(b, w), 2.0 ** -23)
