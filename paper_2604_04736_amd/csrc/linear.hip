@@ -3509,7 +3509,9 @@ int64_t hot_linear_backward_workspace_bytes(const hot_linear_desc *d)
     const WgradShape w = wgrad_shape(d, -1);
     const int64_t for_weights = w.parts > 1 ? (int64_t)w.parts * wgrad_part_bytes(d) : 0;
     const DeepPlan deep = deep_input_grad_plan(d, true, -1);
-    const int x_parts = deep.code >= 0 ? deep.parts : xgrad_parts(d, -1);
+    // (a dy off the 16-byte grid goes to the kernel whose waves share the draws: enough for its parts too)
+    const int deep_parts = deep.code >= 0 ? deep.parts : 1, other_parts = xgrad_parts(d, -1);
+    const int x_parts = deep_parts > other_parts ? deep_parts : other_parts;
     const int64_t for_inputs = x_parts > 1 ? (int64_t)x_parts * d->s_local * d->rows * d->in_features * (int64_t)sizeof(float) : 0;
     int64_t most = for_weights > for_inputs ? for_weights : for_inputs;     // the two kernels use it one after the other
     if (const RowPartsPlan plan = row_parts_plan(d, -1); plan.parts) {

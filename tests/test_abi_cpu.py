@@ -147,6 +147,13 @@ def test_one_pass_backward_shape_query_and_its_workspace(hot):
     assert hot.hot_linear_launch_shape(16, 2160, 8640, 2, 2) == 12 and hot.hot_linear_launch_shape(64, 8192, 8192, 2, 2) == 112
 
 
+def test_workspace_query_covers_a_dy_off_the_16_byte_grid(hot):
+    """Such a dy goes to the kernel that cuts the outputs into up to eight parts of dx, whatever the one for aligned rows takes."""
+    for rows, k, o, s, parts in [(371, 540, 1368, 4, 8), (1084, 296, 1344, 4, 8), (487, 332, 1092, 8, 8), (193, 2068, 1024, 3, 8)]:
+        assert 0 < hot.hot_linear_kernel_shape(rows, k, o, s, 1) // 1000000 < parts
+        assert hot.hot_linear_backward_workspace_bytes(rows, k, o, s) >= parts * s * rows * k * 4
+
+
 def test_kernel_shape_query(hot):
     """Host arithmetic only: what hot_linear_launch_shape answers 0 for, the tiles, parts and chunks of it."""
     assert hot.hot_linear_kernel_shape(300, 2160, 8640, 2, 0, per_sample_x=True) == 1021101      # 320 x 32, the rest 64 x 32
