@@ -1130,23 +1130,29 @@ constexpr long kDeepMinContract = 128, kDeepMinContractTr = 256, kDeepMinWorkgro
 constexpr int kDeepMaxParts = 16;
 constexpr int64_t kDeepMaxBytes = (int64_t)256 << 20;
 
-// R rows, C contraction indices, N outputs; ws_bytes: as in wgrad_shape (0: no parts)
-inline DeepPlan deep_plan(long R, long C, long N, long ld_in, int S, bool tr, int64_t ws_bytes)
+// Whether the kernel can take a problem of R rows, C contraction indices and N outputs, and is worth a look there.
+inline bool deep_fits(long R, long C, long N, long ld_in, int S, bool tr)
+{
+    if (R < (tr ? kDeepMinRowsTr : kDeepMinRows) || C < (tr ? kDeepMinContractTr : kDeepMinContract) || S > 65535) return false;
+    constexpr long kIndexMost = 1L << 29;                // (so that the products below stay within 64 bits)
+    if (R > kIndexMost || C > kIndexMost || N > kIndexMost || ld_in > kIndexMost) return false;
+    const unsigned long long lim = 0x7FFFFFF0ull;
+    if ((unsigned long long)(R + 640) * ld_in * 4 >= lim || (unsigned long long)(C + 256) * (N + 64) * 4 >= 2 * lim) return false;
+    return (N + 31) / 32 * ((R + 127) / 128) <= 0x3fffffffL / ((long)S * (tr ? kDeepMaxParts : 1));      // (tiles are counted in 32 bits)
+}
+
+// ws_bytes: as in wgrad_shape (0: no parts); least_parts: the fewest parts allowed
+inline DeepPlan deep_plan(long R, long C, long N, long ld_in, int S, bool tr, int64_t ws_bytes, int least_parts)
 {
     DeepPlan best = {-1, -1, 0, 1, 0, 0.0};
-    if (R < (tr ? kDeepMinRowsTr : kDeepMinRows) || C < (tr ? kDeepMinContractTr : kDeepMinContract) || S > 65535) return best;
-    constexpr long kIndexMost = 1L << 29;                // (so that the products below stay within 64 bits)
-    if (R > kIndexMost || C > kIndexMost || N > kIndexMost || ld_in > kIndexMost) return best;
-    const unsigned long long lim = 0x7FFFFFF0ull;
-    if ((unsigned long long)(R + 640) * ld_in * 4 >= lim || (unsigned long long)(C + 256) * (N + 64) * 4 >= 2 * lim) return best;
-    if ((N + 31) / 32 * ((R + 127) / 128) > 0x3fffffffL / ((long)S * (tr ? kDeepMaxParts : 1))) return best;      // (tiles are counted in 32 bits)
+    if (!deep_fits(R, C, N, ld_in, S, tr)) return best;
     const int64_t block_bytes = (int64_t)S * R * N * (int64_t)sizeof(float);
     const int64_t budget = ws_bytes < 0 || ws_bytes > kDeepMaxBytes ? kDeepMaxBytes : ws_bytes;
     for (int i = 0; i < (tr ? kDeepCodesTr : kDeepCodes); ++i) {
         const DeepShape &h = kDeepShapes[i];
         const long row_tiles = (R + 32 * h.rb - 1) / (32 * h.rb), col_tiles = (N + 32 * h.cb - 1) / (32 * h.cb);
         const long per_col = row_tiles * S;             // workgroups of one column of tiles
-        for (int parts = 1; parts <= (tr ? kDeepMaxParts : 1); ++parts) {
+        for (int parts = least_parts; parts <= (tr ? kDeepMaxParts : 1); ++parts) {
             if (parts > 1 && parts * block_bytes > budget) break;
             const long per_part = ((C + parts - 1) / parts + kDeepStep - 1) / kDeepStep * kDeepStep;
             if (parts > 1 && (per_part * (parts - 1) >= C || per_part < 2 * kDeepStep)) continue;
@@ -1155,6 +1161,7 @@ inline DeepPlan deep_plan(long R, long C, long N, long ld_in, int S, bool tr, in
             if (parts > 1) cost += 4.0 + (double)(parts + 1) * (double)block_bytes / 4e6;
             if (best.code < 0 || cost < best.cost) best = DeepPlan{i, -1, N, parts, per_part, cost};
         }
+        if (least_parts > 1) continue;
         // whole rounds of this shape, and what is left over in the shape that does it fastest
         const long steps = (C + kDeepStep - 1) / kDeepStep, round = (long)kComputeUnits * h.resident;
         const long main_tiles = col_tiles * per_col / round * round / per_col;
@@ -1399,21 +1406,11 @@ inline bool deep_beats_slab(const DeepPlan &p, long rows, long contract, double 
 
 inline DeepPlan deep_forward_plan(const hot_linear_desc *d)
 {
-    const DeepPlan p = deep_plan(d->rows, d->in_features, d->out_features, d->ldx, d->s_local, false, 0);
+    const DeepPlan p = deep_plan(d->rows, d->in_features, d->out_features, d->ldx, d->s_local, false, 0, 1);
     if (p.code < 0) return p;
     const SlabForwardPlan slab = slab_forward_plan(d);
     const double cost = (slab.two.waves ? slab.two.cost : 0.0) + (slab.one.waves ? slab.one.cost : 0.0);
     return deep_beats_slab(p, d->rows, d->in_features, cost) ? p : kNoDeepPlan;
-}
-
-// ... and its input gradients (dy is the input, read in 16-byte quads)
-inline DeepPlan deep_input_grad_plan(const hot_linear_desc *d, bool dy_aligned, int64_t ws_bytes)
-{
-    if ((d->out_features & 3) != 0 || !dy_aligned) return kNoDeepPlan;
-    const DeepPlan p = deep_plan(d->rows, d->out_features, d->in_features, d->out_features, d->s_local, true, ws_bytes);
-    if (p.code < 0) return p;
-    const SlabShape slab = slab_input_grad_shape(d, true);
-    return deep_beats_slab(p, d->rows, d->out_features, slab.waves ? slab.cost : 0.0) ? p : kNoDeepPlan;
 }
 
 template <int RB, bool XS>
@@ -3380,6 +3377,87 @@ int xgrad_parts(const hot_linear_desc *d, int64_t ws_bytes)
     return parts;
 }
 
+// The launch shapes of the two kernels above without parts: 64 * rb rows per workgroup of the kernel whose waves share the
+// draws (rb == 0: it does not run), 16 * rb rows and `waves` shares of the contraction of the other.
+struct XgradShape {
+    int rb, waves;
+    long gy;            // row blocks
+};
+
+inline XgradShape xgrad_rows_shape(const hot_linear_desc *d)
+{
+    // Rows per workgroup: 64 x cand.  All workgroups of these shapes are resident at once and those that share a
+    // compute unit share its SIMDs, so the kernel takes (most workgroups on one compute unit) x (one workgroup's
+    // work): per step 512 x cand matrix cycles per wave plus about 900 for the draw and the rest.  The count that
+    // minimises the product wins: 7260 rows x 540 inputs x 2 samples are 522 workgroups of 256 rows (three on ten
+    // compute units, two on the others: a third of the chip's time idle) but 684 of 192 rows (0.48 -> 0.40 ms).
+    XgradShape best = {0, 1, 0};
+    long best_cost = 0;
+    const long k_groups = (d->in_features + 63) / 64;
+    for (int cand = d->rows >= 256 ? 4 : 0; cand >= 1; --cand) {
+        const long gy = (d->rows + 64 * cand - 1) / (64 * cand);
+        const long wgs = k_groups * gy * d->s_local;
+        if (gy > 65535 || wgs < 256) continue;     // (none fits: the other kernel, 15 % faster than 64-row workgroups there)
+        const long cost = ((wgs + 255) / 256) * (512L * cand + 900);
+        if (best.rb == 0 || cost < best_cost) {
+            best = XgradShape{cand, 1, gy};
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
+inline XgradShape xgrad_shape(const hot_linear_desc *d)
+{
+    // Row tiles per workgroup: more of them share each drawn weight, fewer of them give more
+    // workgroups and more waves per workgroup.  Take the most sharing that still puts a wave on
+    // every SIMD of the chip (1024), else whatever yields the most waves.
+    const long k_groups = (d->in_features + 63) / 64;
+    const long o_blocks = (d->out_features + kXgradOutputsPerStep - 1) / kXgradOutputsPerStep;
+    XgradShape best = {1, 1, 0};
+    long most = -1;
+    for (int cand = d->rows > 32 ? 4 : (d->rows > 16 ? 2 : 1); cand >= 1; cand >>= 1) {
+        const long gy = (d->rows + kRowsPerTile * cand - 1) / (kRowsPerTile * cand);
+        int waves = 1;
+        while (waves < max_waves(cand) && k_groups * gy * d->s_local * waves < 8192 && 2L * waves <= o_blocks &&
+               (size_t)(2 * waves - 1) * (size_t)(cand * 16) * 64 * sizeof(float) <= 65536)
+            waves *= 2;
+        const long total = k_groups * gy * d->s_local * waves;
+        if (total > most) {
+            most = total;
+            best = XgradShape{cand, waves, gy};
+        }
+        if (total >= 1024) break;
+    }
+    return best;
+}
+
+// Whether the slab kernel takes the input gradients (where the kernel for tens to hundreds of rows does not).  A workspace that
+// lets the kernel above cut the outputs into parts beats a four-wave launch that leaves a quarter of its slots empty
+// (256 x 2160 x 8640, 136 workgroups of 256 rows x 32 inputs: the whole call 0.71 -> 0.53 ms).
+inline bool xgrad_by_slab(const SlabShape &one, int parts_at_hand)
+{
+    return one.waves && !(parts_at_hand > 1 && one.waves == 4 && one.fill < 0.75);
+}
+
+// Whether the kernel for tens to hundreds of rows takes the input gradients (dy is its input, read in 16-byte quads).  Its four waves
+// and the parts share an output's sum.  In bf16 pieces, with six roundings to 16 products, a sum ends 0.83-0.88 times as far from
+// 64 bits as on the fp32 instruction in as many shares (measured at 33 to 2500 rows), so it needs as many shares as the kernel
+// has that would run otherwise: with four against sixteen (81 x 2048 x 3624) the distance was 4.7e-7 against 2.8e-7.
+inline DeepPlan deep_input_grad_plan(const hot_linear_desc *d, bool dy_aligned, int64_t ws_bytes)
+{
+    if ((d->out_features & 3) != 0 || !dy_aligned ||
+        !deep_fits(d->rows, d->out_features, d->in_features, d->out_features, d->s_local, true))
+        return kNoDeepPlan;
+    const SlabShape slab = slab_input_grad_shape(d, true);
+    const int parts_at_hand = xgrad_parts(d, ws_bytes);
+    const int shares = xgrad_by_slab(slab, parts_at_hand) ? 1 : parts_at_hand > 1 ? parts_at_hand : xgrad_rows_shape(d).rb ? 1 : xgrad_shape(d).waves;
+    const DeepPlan p = deep_plan(d->rows, d->out_features, d->in_features, d->out_features, d->s_local, true, ws_bytes,
+                                 (shares + kDeepWaves - 1) / kDeepWaves);
+    if (p.code < 0) return p;
+    return deep_beats_slab(p, d->rows, d->out_features, slab.waves ? slab.cost : 0.0) ? p : kNoDeepPlan;
+}
+
 // Launch shape of the weight-gradient kernel.
 struct WgradShape {
     long tiles, rows_per_part;
@@ -3792,21 +3870,8 @@ int hot_linear_backward_rng_ws(const hot_linear_desc *d, int32_t s_total, double
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return hot_detail::note_hip(e);
     if (!dx) return HOT_OK;
 
-    // Row tiles per workgroup: more of them share each drawn weight, fewer of them give more
-    // workgroups and more waves per workgroup.  Take the most sharing that still puts a wave on
-    // every SIMD of the chip (1024), else whatever yields the most waves.
-    const long o_blocks = (d->out_features + kXgradOutputsPerStep - 1) / kXgradOutputsPerStep;
-    auto waves_for = [&](int rb_, long gy_) {
-        int w = 1;
-        while (w < max_waves(rb_) && k_groups * gy_ * d->s_local * w < 8192 && 2L * w <= o_blocks &&
-               (size_t)(2 * w - 1) * (size_t)(rb_ * 16) * 64 * sizeof(float) <= 65536)
-            w *= 2;
-        return w;
-    };
     // Hundreds to thousands of rows on a layer whose dx fills the chip with tiles of 512 rows: the kernel of the forward pass
     // with dy as its input and the weight tile drawn transposed (rows of dy are read in 16-byte quads).
-    // (a workspace that lets the kernel below cut the outputs into parts beats a four-wave launch that leaves a quarter of
-    // its slots empty: 256 x 2160 x 8640, 136 workgroups of 256 rows x 32 inputs: the whole call 0.71 -> 0.53 ms)
     const int parts_at_hand = xgrad_parts(d, workspace ? workspace_bytes : 0);
     if (const DeepPlan plan = deep_input_grad_plan(d, aligned16(dy), workspace ? workspace_bytes : 0); plan.code >= 0) {
         DeepArgs b;
@@ -3832,7 +3897,7 @@ int hot_linear_backward_rng_ws(const hot_linear_desc *d, int32_t s_total, double
         }
         return hot_detail::note_hip(hipGetLastError());
     }
-    if (const SlabShape one = slab_input_grad_shape(d, aligned16(dy)); one.waves && !(parts_at_hand > 1 && one.waves == 4 && one.fill < 0.75)) {
+    if (const SlabShape one = slab_input_grad_shape(d, aligned16(dy)); xgrad_by_slab(one, parts_at_hand)) {
         SlabArgs b;
         b.rows = d->rows;
         b.contract = d->out_features;
@@ -3851,8 +3916,7 @@ int hot_linear_backward_rng_ws(const hot_linear_desc *d, int32_t s_total, double
         slab_go_singles<true, true>(one, s, b, 0, d->s_local);
         return hot_detail::note_hip(hipGetLastError());
     }
-    // many rows: the workgroup-shared draw, with as many rows per workgroup (256, 128, 64) as still give every
-    // compute unit a workgroup
+    // many rows: the workgroup-shared draw
     if (const int x_parts = parts_at_hand; x_parts > 1) {
         // too few 256-row workgroups: the outputs are cut into parts, summed from the workspace afterwards
         a.ws = static_cast<float *>(workspace);
@@ -3864,52 +3928,19 @@ int hot_linear_backward_rng_ws(const hot_linear_desc *d, int32_t s_total, double
         hot_linear_dx_sum_kernel<<<dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, s>>>(dx, a.ws, quads, x_parts);
         return hot_detail::note_hip(hipGetLastError());
     }
-    if (d->rows >= 256) {
-        // Rows per workgroup: 64 x cand.  All workgroups of these shapes are resident at once and those that share a
-        // compute unit share its SIMDs, so the kernel takes (most workgroups on one compute unit) x (one workgroup's
-        // work): per step 512 x cand matrix cycles per wave plus about 900 for the draw and the rest.  The count that
-        // minimises the product wins: 7260 rows x 540 inputs x 2 samples are 522 workgroups of 256 rows (three on ten
-        // compute units, two on the others: a third of the chip's time idle) but 684 of 192 rows (0.48 -> 0.40 ms).
-        int best = 0;
-        long best_cost = 0, best_gy = 0;
-        for (int cand = 4; cand >= 1; --cand) {
-            const long gy_c = (d->rows + 64 * cand - 1) / (64 * cand);
-            const long wgs = k_groups * gy_c * d->s_local;
-            if (gy_c > 65535 || wgs < 256) continue;     // (none fits: the kernel below, 15 % faster than 64-row workgroups there)
-            const long cost = ((wgs + 255) / 256) * (512L * cand + 900);
-            if (best == 0 || cost < best_cost) {
-                best = cand;
-                best_cost = cost;
-                best_gy = gy_c;
-            }
-        }
-        if (best) {
-            const dim3 grid((unsigned)k_groups, (unsigned)best_gy, (unsigned)d->s_local);
-            if (best == 4) hot_linear_xgrad_rows_kernel<4><<<grid, dim3(256), 0, s>>>(a);
-            else if (best == 3) hot_linear_xgrad_rows_kernel<3><<<grid, dim3(256), 0, s>>>(a);
-            else if (best == 2) hot_linear_xgrad_rows_kernel<2><<<grid, dim3(256), 0, s>>>(a);
-            else hot_linear_xgrad_rows_kernel<1><<<grid, dim3(256), 0, s>>>(a);
-            return hot_detail::note_hip(hipGetLastError());
-        }
+    if (const XgradShape h = xgrad_rows_shape(d); h.rb) {
+        const dim3 grid((unsigned)k_groups, (unsigned)h.gy, (unsigned)d->s_local);
+        if (h.rb == 4) hot_linear_xgrad_rows_kernel<4><<<grid, dim3(256), 0, s>>>(a);
+        else if (h.rb == 3) hot_linear_xgrad_rows_kernel<3><<<grid, dim3(256), 0, s>>>(a);
+        else if (h.rb == 2) hot_linear_xgrad_rows_kernel<2><<<grid, dim3(256), 0, s>>>(a);
+        else hot_linear_xgrad_rows_kernel<1><<<grid, dim3(256), 0, s>>>(a);
+        return hot_detail::note_hip(hipGetLastError());
     }
-    int rb = 1, waves = 1;
-    long gy = 0, best = -1;
-    for (int cand = d->rows > 32 ? 4 : (d->rows > 16 ? 2 : 1); cand >= 1; cand >>= 1) {
-        const long gy_c = (d->rows + kRowsPerTile * cand - 1) / (kRowsPerTile * cand);
-        const int w_c = waves_for(cand, gy_c);
-        const long total = k_groups * gy_c * d->s_local * w_c;
-        if (total > best) {
-            best = total;
-            rb = cand;
-            waves = w_c;
-            gy = gy_c;
-        }
-        if (total >= 1024) break;
-    }
-    const dim3 grid((unsigned)k_groups, (unsigned)gy, (unsigned)d->s_local);
-    if (rb == 4) xgrad_go<4>(grid, waves, s, a);
-    else if (rb == 2) xgrad_go<2>(grid, waves, s, a);
-    else xgrad_go<1>(grid, waves, s, a);
+    const XgradShape h = xgrad_shape(d);
+    const dim3 grid((unsigned)k_groups, (unsigned)h.gy, (unsigned)d->s_local);
+    if (h.rb == 4) xgrad_go<4>(grid, h.waves, s, a);
+    else if (h.rb == 2) xgrad_go<2>(grid, h.waves, s, a);
+    else xgrad_go<1>(grid, h.waves, s, a);
     return hot_detail::note_hip(hipGetLastError());
 }
 

@@ -1169,3 +1169,24 @@ def test_weight_gradients_from_row_parts_are_no_less_accurate(hot, rows, k, o, s
         a = a[:o - 1]
         print("distance from 64 bits: row parts %.2e, fp32 instruction %.2e" % (_distance(a, w), _distance(b, w)), flush=True)
         assert _distance(a, w) <= max(1.02 * _distance(b, w), 2.0 ** -23)
+
+
+# the kernel that runs otherwise splits the contraction over 8 or 16 waves; with a workspace: in few parts, in many
+@pytest.mark.parametrize("rows,o,k,s,workspace", [(81, 3624, 2048, 1, False), (122, 2048, 832, 2, False), (224, 7096, 264, 4, False),
+                                                  (400, 768, 192, 8, True), (1837, 580, 300, 2, True), (139, 768, 4096, 1, True)])
+def test_input_gradients_at_tens_to_hundreds_of_rows_are_no_less_accurate(hot, rows, o, k, s, workspace):
+    """The same for the input gradients, against the kernel on the fp32 instruction (which a dy off the 16-byte grid goes to)."""
+    g, c = _deep_case(rows + k, o, k)
+    x = torch.randn(rows, k, device=DEV, generator=g)
+    flat = torch.randn(s * rows * o + 1, device=DEV, generator=g)
+    off = flat[1:].view(s, rows, o)
+    rng = hot.hot_rng(seed=59, step=3, first_sample=1)
+    w, _ = _materialised(hot, c, s, rng, 0, o * k)
+    want = torch.stack([off[i].double() @ w[i] for i in range(s)])
+    got = []
+    for dy in (off.clone(), off):
+        dx = torch.full((s, rows, k), float("nan"), device=DEV)
+        _backward(hot, rng, x, dy, c, dx, _workspace(hot, rows, k, o, s) if workspace else None, s)
+        got.append(_distance(dx, want))
+    print("distance from 64 bits: %.2e, on the fp32 instruction %.2e" % tuple(got), flush=True)
+    assert got[0] <= 1.02 * got[1]
