@@ -858,6 +858,28 @@ __device__ __forceinline__ void philox_rounds(u4 &c, unsigned k0, unsigned k1)
     }
 }
 
+// An infinite factor, and one beyond the largest bf16 number, has no bf16 pieces: the products of what they give are NaN.  So where
+// a sum of the kernel below is NaN it is formed again from fp32 products, over the indices c_lo .. c_hi - 1 (a NaN among the
+// factors ends it).
+template <bool TR>
+__device__ __forceinline__ float deep_plain_sum(const DeepArgs &a, int s, int row, int n, int c_lo, int c_hi)
+{
+    const float *in = a.in + (size_t)s * (size_t)a.in_sample_stride + (size_t)row * (size_t)a.ld_in;
+    float sum = 0.0f;
+#pragma unroll 1
+    for (int c = c_lo; c < c_hi && sum == sum; c += TR ? 1 : 4) {
+        const long flat = TR ? (long)c * a.outs + n : (long)n * a.contract + c;
+        const f4 e = eps_quad(a.weight_quad0 + (flat >> 2), s, a.rng);
+        if constexpr (TR) {
+            sum = __builtin_fmaf(in[c], __builtin_fmaf(a.sigma_w[flat], pick4_of(e, n & 3), a.mu_w[flat]), sum);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sum = __builtin_fmaf(in[c + i], __builtin_fmaf(a.sigma_w[flat + i], e[i], a.mu_w[flat + i]), sum);
+        }
+    }
+    return sum;
+}
+
 template <int RB, int CB, bool TR>
 __global__ void __launch_bounds__(64 * kDeepWaves, RB * CB <= 2 ? 4 : RB * CB <= 4 ? 3 : (RB * CB <= 8 ? 2 : 1))
 hot_linear_deep_kernel(DeepArgs a)
@@ -1056,6 +1078,7 @@ hot_linear_deep_kernel(DeepArgs a)
     float bias = 0.0f;
     if (!TR && a.mu_b && n < N) bias = __builtin_fmaf(a.sigma_b[n], pick4_of(eps_quad(a.bias_quad0 + (n >> 2), s, a.rng), n & 3), a.mu_b[n]);
     float *const dst = a.out + (size_t)part * (size_t)a.part_stride + (size_t)s * (size_t)R * (size_t)N;
+    bool special = false;
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
         __syncthreads();
@@ -1074,7 +1097,19 @@ hot_linear_deep_kernel(DeepArgs a)
 #pragma unroll
             for (int w = 0; w < kDeepWaves; ++w) v[w] = ((const lds_float *)lds)[w * (32 * RP) + row * RP + col];
             const int at = r0 + 32 * rb + row;
-            if (at < R && n < N) dst[(size_t)at * (size_t)N + (size_t)n] = (v[0] + v[1]) + (v[2] + v[3]) + bias;
+            if (at < R && n < N) {
+                const float sum = (v[0] + v[1]) + (v[2] + v[3]) + bias;
+                special |= sum != sum;
+                dst[(size_t)at * (size_t)N + (size_t)n] = sum;
+            }
+        }
+    }
+    if (special) {          // (a loop of its own, so that no accumulator lives through it: each thread looks at what it stored)
+#pragma unroll 1
+        for (int i = 0; i < RB * (OUTS / 8); ++i) {
+            const int at = r0 + i * (256 / OUTS) + (int)threadIdx.x / OUTS;
+            float *const y = dst + (size_t)at * (size_t)N + (size_t)n;
+            if (at < R && n < N && *y != *y) *y = deep_plain_sum<TR>(a, s, at, n, c_lo, c_hi) + bias;
         }
     }
 }
@@ -2270,6 +2305,21 @@ struct Floats<4> {
 // floats of one part's share of the workspace: per sample the weights, then the biases (a multiple of four, so that quads stay aligned)
 inline __host__ __device__ long row_part_floats(long K, long O, int s_loc) { return (O * K + ((O + 3) & ~3L)) * s_loc; }
 
+// Those of four sums over the rows r_lo .. r_hi - 1 that the bf16 pieces left as NaN, from fp32 products (see deep_plain_sum).
+__device__ __forceinline__ void row_parts_plain_sums(const LinearGradArgs &a, int s, long o, long k, long r_lo, long r_hi, float *p)
+{
+    const float *x = a.x + (size_t)s * (size_t)a.x_sample_stride + (size_t)k;
+    const float *dy = a.dy + (size_t)s * (size_t)a.rows * (size_t)a.out_features + (size_t)o;
+#pragma unroll 1
+    for (int c = 0; c < 4; ++c) {
+        if (p[c] == p[c]) continue;
+        float sum = 0.0f;
+#pragma unroll 1
+        for (long r = r_lo; r < r_hi && sum == sum; ++r) sum = __builtin_fmaf(dy[(size_t)r * (size_t)a.out_features], x[(size_t)r * (size_t)a.ldx + (size_t)c], sum);
+        p[c] = sum;
+    }
+}
+
 template <bool XBIG>
 __global__ void __launch_bounds__(64 * kRowPartWaves, 2)
 hot_linear_wgrad_row_parts_kernel(LinearGradArgs a, int parts, int chunk)
@@ -2323,6 +2373,7 @@ hot_linear_wgrad_row_parts_kernel(LinearGradArgs a, int parts, int chunk)
     };
     ask_big();
     ask_small();
+    unsigned long long special = 0;       // the lanes that met a NaN
     // A long part is added up in chunks of `chunk` rows (a multiple of 64), each into accumulators of its own and then to what the
     // chunks before left in the workspace (the same thread holds the same sums every time).  What is sent for beyond the end
     // of a chunk are the first rows of the next.
@@ -2391,8 +2442,18 @@ hot_linear_wgrad_row_parts_kernel(LinearGradArgs a, int parts, int chunk)
                     if (c_lo != r_lo) sum += load4<true, false>(P + o * K + k);
                     store4<true, false>(P + o * K + k, sum);
                 }
+                special |= __builtin_amdgcn_ballot_w64(!(sum[0] == sum[0] && sum[1] == sum[1] && sum[2] == sum[2] && sum[3] == sum[3]));
             }
             __syncthreads();
+        }
+    }
+    if (special) {              // (in a loop of its own, as in the kernel for tens to hundreds of rows)
+        float *const P = a.ws + (size_t)part * (size_t)row_part_floats(K, O, a.s_loc) + (size_t)s * (size_t)(O * K);
+#pragma unroll 1
+        for (int i = 0; i < OB * KB; ++i) {
+            const int idx = i % KB * 64 * kRowPartWaves + (int)threadIdx.x;
+            const long o = o0 + OB * (idx / (TK / 4)) + i / KB, k = k0 + 4 * (idx % (TK / 4));
+            if (o < O && k < K) row_parts_plain_sums(a, s, o, k, r_lo, r_hi, P + o * K + k);
         }
     }
     if (bias_tile) {            // uniform over the workgroup

@@ -1190,3 +1190,56 @@ def test_input_gradients_at_tens_to_hundreds_of_rows_are_no_less_accurate(hot, r
         got.append(_distance(dx, want))
     print("distance from 64 bits: %.2e, on the fp32 instruction %.2e" % tuple(got), flush=True)
     assert got[0] <= 1.02 * got[1]
+
+
+MOST = torch.finfo(torch.float32).max
+
+
+@pytest.mark.parametrize("rows,k,o,s", [(40, 132, 4200, 2), (70, 256, 2100, 2), (300, 260, 1400, 2)])
+def test_forward_of_infinite_and_huge_inputs(hot, rows, k, o, s):
+    """Infinities, NaN and the type's lowest and highest values among the inputs give what fp32 products give."""
+    assert hot.hot_linear_kernel_shape(rows, k, o, s, 0, per_sample_x=True)
+    g, c = _deep_case(rows + o, o, k)
+    x = torch.randn(s, rows, k, device=DEV, generator=g)
+    for i, v in enumerate((float("inf"), -float("inf"), float("nan"), -MOST, MOST)):
+        x[i % s, (7 * i + 3) % rows, (13 * i) % k] = v
+    x[1, rows - 1, 5], x[1, rows - 1, k - 1] = float("inf"), -float("inf")
+    rng, b_off = hot.hot_rng(seed=61, step=3, first_sample=1), (o * k + 3) // 4 * 4
+    y = torch.full((s, rows, o), float("nan"), device=DEV)
+    hot.hot_linear_forward_rng(rng, x, c["mu_w"], c["sigma_w"], c["mu_b"], c["sigma_b"], y, 0, b_off)
+    w, b = _materialised(hot, c, s, rng, 0, b_off)
+    for i in range(s):
+        want = x[i].double() @ w[i].t() + b[i]
+        _same_where_special(y[i], want, x[i].double().abs() @ w[i].abs().t() + b[i].abs())
+
+
+def _same_where_special(got, want, magnitude):
+    """NaN and infinities in the same places; else within 1e-5 of the magnitude sum (finite there)."""
+    got, special = got.double(), ~torch.isfinite(want)
+    assert torch.equal(torch.isnan(got), torch.isnan(want))
+    infinite = torch.isinf(want)
+    assert infinite.any() and torch.equal(got[infinite], want[infinite])
+    assert bool(((got - want).abs()[~special] <= 1e-5 * magnitude[~special]).all())
+
+
+def test_backward_of_infinite_and_huge_gradients(hot):
+    """The same for the input gradients (dy) and the weight gradients from row parts (x and dy)."""
+    rows, k, o, s = 320, 800, 600, 2
+    assert hot.hot_linear_kernel_shape(rows, k, o, s, 1) and hot.hot_linear_kernel_shape(rows, k, o, s, 2)
+    g, c = _deep_case(rows + o, o, k)
+    x, dy = torch.randn(s, rows, k, device=DEV, generator=g), torch.randn(s, rows, o, device=DEV, generator=g)
+    for i in range(s):
+        for j, v in enumerate((float("inf"), float("nan"), -float("inf"), MOST / 1024, -MOST)):
+            dy[i, 67 * j + 3, 131 * j + i] = v
+            x[i, 61 * j + 9, 97 * j + 2 * i] = v
+        x[i, 67 * 4 + 3] *= 0.1           # (so that what the largest values give stays finite)
+        dy[i, 61 * 4 + 9] *= 0.1
+    rng = hot.hot_rng(seed=67, step=3, first_sample=1)
+    dx = torch.full((s, rows, k), 0.0, device=DEV)
+    gmu, gsig = _backward(hot, rng, x, dy, c, dx, _workspace(hot, rows, k, o, s), s)
+    w, _ = _materialised(hot, c, s, rng, 0, o * k)
+    for i in range(s):
+        _same_where_special(dx[i], dy[i].double() @ w[i], dy[i].double().abs() @ w[i].abs())
+    P = [dy[i].double().t() @ x[i].double() for i in range(s)]
+    mag = [dy[i].double().abs().t() @ x[i].double().abs() for i in range(s)]
+    _same_where_special(gmu, sum(P), sum(mag))
