@@ -1164,6 +1164,7 @@ constexpr long kDeepMinRows = 33, kDeepMinRowsTr = 65, kDeepAlwaysRows = 704;
 constexpr long kDeepMinContract = 128, kDeepMinContractTr = 256, kDeepMinWorkgroupsTr = 100;
 constexpr int kDeepMaxParts = 16;
 constexpr int64_t kDeepMaxBytes = (int64_t)256 << 20;
+constexpr long kDeepMostTiles = (1L << 24) - kXcds;
 
 // Whether the kernel can take a problem of R rows, C contraction indices and N outputs, and is worth a look there.
 inline bool deep_fits(long R, long C, long N, long ld_in, int S, bool tr)
@@ -1173,7 +1174,9 @@ inline bool deep_fits(long R, long C, long N, long ld_in, int S, bool tr)
     if (R > kIndexMost || C > kIndexMost || N > kIndexMost || ld_in > kIndexMost) return false;
     const unsigned long long lim = 0x7FFFFFF0ull;
     if ((unsigned long long)(R + 640) * ld_in * 4 >= lim || (unsigned long long)(C + 256) * (N + 64) * 4 >= 2 * lim) return false;
-    return (N + 31) / 32 * ((R + 127) / 128) <= 0x3fffffffL / ((long)S * (tr ? kDeepMaxParts : 1));      // (tiles are counted in 32 bits)
+    // One workgroup of 256 threads per tile, in one dimension of the grid, which holds fewer than 2^32 threads.  (Parts need not be
+    // counted: what they leave in the workspace bounds them to far fewer tiles.)
+    return (N + 31) / 32 * ((R + 63) / 64) <= kDeepMostTiles / S;
 }
 
 // ws_bytes: as in wgrad_shape (0: no parts); least_parts: the fewest parts allowed

@@ -147,6 +147,13 @@ def test_one_pass_backward_shape_query_and_its_workspace(hot):
     assert hot.hot_linear_launch_shape(16, 2160, 8640, 2, 2) == 12 and hot.hot_linear_launch_shape(64, 8192, 8192, 2, 2) == 112
 
 
+def test_tiles_that_one_grid_dimension_cannot_hold_go_to_other_kernels(hot):
+    """A dimension of a grid holds fewer than 2^32 threads, and the kernel for tens to hundreds of rows has 256 to a tile."""
+    for which, rows, k, o, few, many in [(0, 64, 128, 2_700_000, 198, 199), (0, 40, 128, 2_700_000, 198, 199), (1, 65, 2_080_000, 256, 128, 130)]:
+        assert hot.hot_linear_kernel_shape(rows, k, o, few, which, workspace_bytes=0) > 0
+        assert hot.hot_linear_kernel_shape(rows, k, o, many, which, workspace_bytes=0) == 0
+
+
 def test_workspace_query_covers_a_dy_off_the_16_byte_grid(hot):
     """Such a dy goes to the kernel that cuts the outputs into up to eight parts of dx, whatever the one for aligned rows takes."""
     for rows, k, o, s, parts in [(371, 540, 1368, 4, 8), (1084, 296, 1344, 4, 8), (487, 332, 1092, 8, 8), (193, 2068, 1024, 3, 8)]:
