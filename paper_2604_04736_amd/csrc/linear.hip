@@ -135,6 +135,7 @@ hot_linear_forward_kernel(LinearArgs a)
     const long quad_row = a.weight_quad0 + ((o_ok ? o : 0) * K >> 2);
     // grid z: the samples in chunks of s_chunk (a multiple of ST)
     const int s_lo = (int)blockIdx.z * a.s_chunk, s_hi = s_lo + a.s_chunk < a.s_loc ? s_lo + a.s_chunk : a.s_loc;
+    const float *const x = a.x + (size_t)s_lo * (size_t)a.x_sample_stride;       // (not XS: of all this workgroup's samples)
 
     for (int s0 = s_lo; s0 < s_hi; s0 += ST) {
         Acc16x16 mm[ST][RB];
@@ -152,7 +153,7 @@ hot_linear_forward_kernel(LinearArgs a)
 #pragma unroll
                     for (int rb = 0; rb < RB; ++rb) {
                         const long row = r0 + kRowsPerTile * rb + n;
-                        xa[rb][h] = (row < R && k + 4 * h < K) ? load4<true, false>(a.x + row * a.ldx + k + 4 * h)
+                        xa[rb][h] = (row < R && k + 4 * h < K) ? load4<true, false>(x + row * a.ldx + k + 4 * h)
                                                                 : f4{0.0f, 0.0f, 0.0f, 0.0f};
                     }
                 }
@@ -1442,8 +1443,25 @@ inline bool deep_beats_slab(const DeepPlan &p, long rows, long contract, double 
     return p.code >= 0 && (rows <= kDeepAlwaysRows || slab_cost == 0.0 || p.cost < 0.97 * (slab_cost * (double)((contract + kSlabK - 1) / kSlabK) * 3.2e-4 + 5.0));
 }
 
+// Whether a forward call is left to the first kernel above: where that has at most one workgroup (64 rows x 16 outputs, one
+// sample) per compute unit.  A workgroup of either waits for one dependent chain per step there, and the first kernel's
+// four waves step over 128 indices in 1.3 us, those of the kernel for tens to hundreds of rows over 64 in 1.0 to 1.6.  Measured on 360
+// layers: up to 256 workgroups 1.2x on average (63 x 6480 x 1172 x 1: 82 us against 135, 312 x 6816 x 72 x 1 86 against 139; at
+// worst 0.95x), from 257 to 512 0.9x, but for long sums over at most 64 rows, where both draw as often (52 x 8192 x 6264 x 1:
+// 214 against 237, 38 x 6228 x 2160 x 2 119 against 128).
+constexpr long kLongContract = 6000;
+
+inline bool few_first_kernel_workgroups(const hot_linear_desc *d)
+{
+    const long gx = (d->out_features + kColsPerWave - 1) / kColsPerWave, gy = (d->rows + 4 * kRowsPerTile - 1) / (4 * kRowsPerTile);
+    if (gx > 2 * kComputeUnits || gy > kComputeUnits) return false;
+    const long wgs = gx * gy * d->s_local;
+    return wgs <= kComputeUnits || (wgs <= 2 * kComputeUnits && gy == 1 && d->s_local <= 2 && d->in_features > kLongContract);
+}
+
 inline DeepPlan deep_forward_plan(const hot_linear_desc *d)
 {
+    if (few_first_kernel_workgroups(d)) return kNoDeepPlan;
     const DeepPlan p = deep_plan(d->rows, d->in_features, d->out_features, d->ldx, d->s_local, false, 0, 1);
     if (p.code < 0) return p;
     const SlabForwardPlan slab = slab_forward_plan(d);
@@ -1466,7 +1484,8 @@ void linear_go_st(int st, dim3 grid, int waves, hipStream_t s, const LinearArgs 
 template <int RB>
 void linear_go(int st, dim3 grid, int waves, hipStream_t s, const LinearArgs &a)
 {
-    if (a.x_sample_stride != 0) linear_go_st<RB, true>(st, grid, waves, s, a);
+    // (a workgroup with one sample has one input: 129 x 3648 x 540 x 1 51 -> 47 us)
+    if (a.x_sample_stride != 0 && a.s_chunk > 1) linear_go_st<RB, true>(st, grid, waves, s, a);
     else linear_go_st<RB, false>(st, grid, waves, s, a);
 }
 
@@ -3797,12 +3816,14 @@ int hot_linear_forward_rng(const hot_linear_desc *d, const hot_rng *rng, const f
     // samples: eight workgroups, 28 us of dependent instructions): the samples then go to workgroups of their own, one each while all
     // waves fit on the chip at two per SIMD, else in as many chunks as do.
     const long waves_all = gx * gy * waves;
+    // (a second wave per SIMD gains the four-tile workgroups nothing: their pairs of samples stay together)
+    const long room = rb == 4 && d->s_local == 2 ? 1024 : 2048;
     a.s_chunk = (d->s_local + st - 1) / st * st;
-    if (waves_all * d->s_local <= 2048) {
+    if (waves_all * d->s_local <= room) {
         st = 1;
         a.s_chunk = 1;
-    } else if (2 * waves_all <= 2048) {
-        const int chunks = (int)(2048 / waves_all);
+    } else if (2 * waves_all <= room) {
+        const int chunks = (int)(room / waves_all);
         a.s_chunk = ((d->s_local + chunks - 1) / chunks + st - 1) / st * st;
     }
     const dim3 grid((unsigned)gx, (unsigned)gy, (unsigned)((d->s_local + a.s_chunk - 1) / a.s_chunk));

@@ -154,6 +154,14 @@ def test_tiles_that_one_grid_dimension_cannot_hold_go_to_other_kernels(hot):
         assert hot.hot_linear_kernel_shape(rows, k, o, many, which, workspace_bytes=0) == 0
 
 
+def test_layers_of_few_workgroups_stay_with_the_first_kernel(hot):
+    """64 rows x 16 outputs x one sample each: up to one for every compute unit (256), with long sums up to two."""
+    for rows, k, o, few, many in [(63, 6480, 1172, 3, 4), (312, 6816, 72, 10, 11), (97, 7328, 164, 11, 12), (40, 2048, 4096, 1, 2),
+                                  (52, 8192, 4096, 2, 3), (52, 8192, 8192, 1, 2)]:
+        assert hot.hot_linear_kernel_shape(rows, k, o, few, 0) == 0 == hot.hot_linear_launch_shape(rows, k, o, few, 0)
+        assert hot.hot_linear_kernel_shape(rows, k, o, many, 0) > 0
+
+
 def test_workspace_query_covers_a_dy_off_the_16_byte_grid(hot):
     """Such a dy goes to the kernel that cuts the outputs into up to eight parts of dx, whatever the one for aligned rows takes."""
     for rows, k, o, s, parts in [(371, 540, 1368, 4, 8), (1084, 296, 1344, 4, 8), (487, 332, 1092, 8, 8), (193, 2068, 1024, 3, 8)]:
