@@ -1127,14 +1127,15 @@ void deep_go(hipStream_t s, DeepArgs a, int samples, int n_begin, int n_end)
 }
 
 // The shapes of the kernel above and what they cost: microseconds per step of a workgroup with 1 .. `resident` workgroups on its
-// compute unit (as many as registers and LDS admit).  Measured on layers of 16 to 128 steps; the model ranks shapes, and picks
-// the number of parts.
+// compute unit (as many as registers and LDS admit), and of a round of workgroups besides its steps (the first loads, the sums
+// through LDS, the stores).  Measured on layers of 3 to 128 steps; the model ranks shapes, and picks the number of parts.
 struct DeepShape {
     int rb, cb, resident;
     double us[4];
+    double start;
 };
-constexpr DeepShape kDeepShapes[] = {{2, 1, 4, {1.05, 1.9, 2.3, 2.9}}, {4, 1, 3, {1.1, 2.05, 2.8}}, {6, 1, 2, {1.5, 2.7}}, {8, 1, 2, {1.75, 3.8}}, {10, 1, 1, {2.3}},
-                                     {6, 2, 1, {2.6}}, {8, 2, 1, {3.0}}, {4, 2, 2, {2.1, 3.9}}};
+constexpr DeepShape kDeepShapes[] = {{2, 1, 4, {1.05, 1.9, 2.3, 2.9}, 4.0}, {4, 1, 3, {1.1, 2.05, 2.8}, 5.0}, {6, 1, 2, {1.5, 2.7}, 6.0}, {8, 1, 2, {1.75, 3.8}, 7.0},
+                                     {10, 1, 1, {2.3}, 9.0}, {6, 2, 1, {2.6}, 11.0}, {8, 2, 1, {3.0}, 13.0}, {4, 2, 2, {2.1, 3.9}, 6.0}};
 constexpr int kDeepCodes = sizeof(kDeepShapes) / sizeof(kDeepShapes[0]);
 constexpr int kDeepCodesTr = kDeepCodes - 1;        // (the last one's transposed draw spills its registers)
 
@@ -1144,7 +1145,7 @@ struct DeepPlan {
     long n_cut;
     int parts;
     long contract_per_part;
-    double cost;
+    double cost;            // what shapes and parts are ranked by
 };
 
 inline double deep_cost(const DeepShape &h, long wgs, long steps)
@@ -1159,9 +1160,8 @@ inline double deep_cost(const DeepShape &h, long wgs, long steps)
 // 84 us, 300: 655 -> 210, 256 x 8192^2 590 -> 400, 64 x 1024^2 x 8 95 -> 21; at 16 rows 59 -> 79, so fewer stay), input gradients from
 // 65 (below, the other kernel draws as few weights and has more waves: 0.87-1.04x), both given two (four) steps of contraction per
 // wave and, without parts, 100 workgroups for the input gradients (below, the other kernel's up to sixteen waves per tile win:
-// 200 x 192 x 768 27 -> 32).  From 705 rows on the kernel above shares every draw among as many rows: there the cheaper one by
-// the two models runs (900 x 2160 x 8640 534 -> 476, 2048 x 1024^2 71 -> 60, 7260 x 540 x 2160 206 against 301 stays).
-constexpr long kDeepMinRows = 33, kDeepMinRowsTr = 65, kDeepAlwaysRows = 704;
+// 200 x 192 x 768 27 -> 32).  Where the kernel above runs too, the faster one by the two models (deep_beats_slab).
+constexpr long kDeepMinRows = 33, kDeepMinRowsTr = 65;
 constexpr long kDeepMinContract = 128, kDeepMinContractTr = 256, kDeepMinWorkgroupsTr = 100;
 constexpr int kDeepMaxParts = 16;
 constexpr int64_t kDeepMaxBytes = (int64_t)256 << 20;
@@ -1433,30 +1433,70 @@ inline SlabShape slab_input_grad_shape(const hot_linear_desc *d, bool dy_aligned
     return slab_shape_singles(d->rows, d->in_features, d->s_local, kSlabMinFillInputGrad, kSlabMinFillInputGradNarrow);
 }
 
-// Whether the kernel for a few hundred rows takes the layer: up to 704 rows always, beyond that where it beats the slab kernel's
-// shape by 3 % (a unit of that kernel's cost times its steps of 16 indices is 0.32 ns, measured 0.29-0.35 over its shapes) or
-// there is none.
 constexpr DeepPlan kNoDeepPlan = {-1, -1, 0, 1, 0, 0.0};
 
-inline bool deep_beats_slab(const DeepPlan &p, long rows, long contract, double slab_cost)
+// What a plan takes, in microseconds, to compare it with other kernels: shapes are ranked with 5 us for the start of every round,
+// as they were measured; here it is the shape's own.  And every column of tiles reads the whole input: one that the L2 caches cannot
+// hold (inputs: how many differ among the samples) comes at 5.3 TB/s (1387 x 1964 x 540 x 8 samples with inputs of their own: 1.5 GB,
+// 296 us, where the steps alone would take 188; 2019 x 2108 x 768 x 2: 0.82 GB, 149 us).
+constexpr double kInputTooLarge = 20e6, kInputBytesPerUs = 5.3e6;
+
+inline double deep_time(const DeepPlan &p, long R, long C, long N, long S, long inputs)
 {
-    return p.code >= 0 && (rows <= kDeepAlwaysRows || slab_cost == 0.0 || p.cost < 0.97 * (slab_cost * (double)((contract + kSlabK - 1) / kSlabK) * 3.2e-4 + 5.0));
+    long col_tiles = 0;
+    double t = p.cost;
+    auto add = [&](int code, long n) {
+        const DeepShape &h = kDeepShapes[code];
+        const long cols = (n + 32 * h.cb - 1) / (32 * h.cb), wgs = cols * ((R + 32 * h.rb - 1) / (32 * h.rb)) * S * p.parts;
+        const long round = (long)kComputeUnits * h.resident;
+        t += (double)((wgs + round - 1) / round) * (h.start - 5.0);
+        col_tiles += cols;
+    };
+    add(p.code, p.n_cut);
+    if (p.rest_code >= 0) add(p.rest_code, N - p.n_cut);
+    const double bytes = (double)R * (double)C * 4.0;
+    const double reads = bytes * (double)inputs > kInputTooLarge ? bytes * (double)(S * col_tiles) / kInputBytesPerUs : 0.0;
+    return t > reads ? t : reads;
+}
+
+// What a launch of the slab kernel takes, in microseconds: a unit of its cost times its steps of 16 indices is 0.32 ns, more or less
+// of it by shape, fitted to 200 layers of 65 to 3500 rows and 128 to 4096 inputs (st: samples per pass).
+inline double slab_time(const SlabShape &h, int st, long contract)
+{
+    if (!h.waves) return 0.0;
+    const int wide = h.cbw * st;
+    double share = 1.1, start = 5.0;                                     // 256 rows x 32 outputs
+    if (h.waves == 4 && h.rbw == 1) start = 6.0;                         // 128 rows
+    else if (h.waves == 4 && st == 2) share = 0.78, start = 7.0;
+    else if (h.waves == 4 && wide == 2) share = 0.86, start = 10.0;
+    else if (h.waves == 8 && wide == 1) share = 1.3, start = 6.0;
+    else if (h.waves == 8 && wide == 2) share = 0.92, start = 7.0;
+    else if (h.waves == 8) share = 0.8, start = 11.0;
+    else if (h.waves == 16) share = 0.85, start = 18.0;
+    return share * h.cost * (double)((contract + kSlabK - 1) / kSlabK) * 3.2e-4 + start;
+}
+
+// Whether the kernel for tens to hundreds of rows takes a layer that the slab kernel could take (slab: that one's time, 0: it could
+// not).  Of 205 layers where either runs the models leave one more than 6 % behind the faster (245 x 644 x 6107 x 2 samples: 42 us
+// against 38); with the kernel for fewer rows up to 704 rows always, layers of few inputs and many outputs lost
+// (493 x 236 x 8192 x 4: 94 against 67, 658 x 192 x 8048 x 4 134 against 74).
+inline bool deep_beats_slab(const DeepPlan &p, long R, long C, long N, long S, long inputs, double slab)
+{
+    return p.code >= 0 && (slab == 0.0 || deep_time(p, R, C, N, S, inputs) < slab);
 }
 
 // Whether a forward call is left to the first kernel above: where that has at most one workgroup (64 rows x 16 outputs, one
 // sample) per compute unit.  A workgroup of either waits for one dependent chain per step there, and the first kernel's
-// four waves step over 128 indices in 1.3 us, those of the kernel for tens to hundreds of rows over 64 in 1.0 to 1.6.  Measured on 360
-// layers: up to 256 workgroups 1.2x on average (63 x 6480 x 1172 x 1: 82 us against 135, 312 x 6816 x 72 x 1 86 against 139; at
-// worst 0.95x), from 257 to 512 0.9x, but for long sums over at most 64 rows, where both draw as often (52 x 8192 x 6264 x 1:
-// 214 against 237, 38 x 6228 x 2160 x 2 119 against 128).
-constexpr long kLongContract = 6000;
-
+// four waves step over 128 indices in 1.3 us, those of the kernel for tens to hundreds of rows over 64 in 1.0 to 1.6.  Measured
+// on 360 layers: up to 256 workgroups 1.2x on average (63 x 6480 x 1172 x 1: 82 us against 135, 312 x 6816 x 72 x 1 86 against 139;
+// at worst 0.95x), from 257 to 512 0.9x, but for long sums (52 x 8192 x 6264 x 1: 214 against 237, 769 x 7712 x 252 x 2 150 against
+// 171, 99 x 7192 x 1148 x 2 134 against 151; one sample up to 5000 inputs 1.05x the other way).
 inline bool few_first_kernel_workgroups(const hot_linear_desc *d)
 {
     const long gx = (d->out_features + kColsPerWave - 1) / kColsPerWave, gy = (d->rows + 4 * kRowsPerTile - 1) / (4 * kRowsPerTile);
-    if (gx > 2 * kComputeUnits || gy > kComputeUnits) return false;
+    if (gx > 2 * kComputeUnits || gy > 2 * kComputeUnits) return false;
     const long wgs = gx * gy * d->s_local;
-    return wgs <= kComputeUnits || (wgs <= 2 * kComputeUnits && gy == 1 && d->s_local <= 2 && d->in_features > kLongContract);
+    return wgs <= kComputeUnits || (wgs <= 2 * kComputeUnits && d->s_local <= 2 && d->in_features > (d->s_local == 2 ? 4000 : 6000));
 }
 
 inline DeepPlan deep_forward_plan(const hot_linear_desc *d)
@@ -1465,8 +1505,8 @@ inline DeepPlan deep_forward_plan(const hot_linear_desc *d)
     const DeepPlan p = deep_plan(d->rows, d->in_features, d->out_features, d->ldx, d->s_local, false, 0, 1);
     if (p.code < 0) return p;
     const SlabForwardPlan slab = slab_forward_plan(d);
-    const double cost = (slab.two.waves ? slab.two.cost : 0.0) + (slab.one.waves ? slab.one.cost : 0.0);
-    return deep_beats_slab(p, d->rows, d->in_features, cost) ? p : kNoDeepPlan;
+    const double time = slab_time(slab.two, 2, d->in_features) + slab_time(slab.one, 1, d->in_features);
+    return deep_beats_slab(p, d->rows, d->in_features, d->out_features, d->s_local, d->x_sample_stride != 0 ? d->s_local : 1, time) ? p : kNoDeepPlan;
 }
 
 template <int RB, bool XS>
@@ -3538,7 +3578,7 @@ inline DeepPlan deep_input_grad_plan(const hot_linear_desc *d, bool dy_aligned, 
     const DeepPlan p = deep_plan(d->rows, d->out_features, d->in_features, d->out_features, d->s_local, true, ws_bytes,
                                  (shares + kDeepWaves - 1) / kDeepWaves);
     if (p.code < 0) return p;
-    return deep_beats_slab(p, d->rows, d->out_features, slab.waves ? slab.cost : 0.0) ? p : kNoDeepPlan;
+    return deep_beats_slab(p, d->rows, d->out_features, d->in_features, d->s_local, d->s_local, slab_time(slab, 1, d->out_features)) ? p : kNoDeepPlan;
 }
 
 // Launch shape of the weight-gradient kernel.

@@ -162,6 +162,18 @@ def test_layers_of_few_workgroups_stay_with_the_first_kernel(hot):
         assert hot.hot_linear_kernel_shape(rows, k, o, many, 0) > 0
 
 
+def test_layers_on_which_the_slab_kernel_is_faster_stay_with_it(hot):
+    """Few inputs and many outputs (a round of tiles of the kernel for fewer rows starts too slowly for its few steps), inputs of
+    each sample's own that no cache holds (it reads them once per column of narrower tiles)."""
+    for rows, k, o, s in [(493, 236, 8192, 4), (658, 192, 8048, 4), (665, 304, 4300, 2), (1387, 1964, 540, 8)]:
+        assert hot.hot_linear_kernel_shape(rows, k, o, s, 0, per_sample_x=True) == 0
+        assert hot.hot_linear_launch_shape(rows, k, o, s, 0, per_sample_x=True) > 0
+    for rows, k, o, s in [(422, 5148, 408, 4), (1142, 1024, 4428, 4), (2107, 2068, 1572, 3)]:
+        assert hot.hot_linear_kernel_shape(rows, k, o, s, 1, workspace_bytes=0) == 0 < hot.hot_linear_launch_shape(rows, k, o, s, 1)
+    for rows, k, o, s in [(499, 1420, 3276, 3), (790, 5204, 1968, 2), (1067, 596, 192, 8)]:
+        assert hot.hot_linear_kernel_shape(rows, k, o, s, 0, per_sample_x=True) > 0
+
+
 def test_workspace_query_covers_a_dy_off_the_16_byte_grid(hot):
     """Such a dy goes to the kernel that cuts the outputs into up to eight parts of dx, whatever the one for aligned rows takes."""
     for rows, k, o, s, parts in [(371, 540, 1368, 4, 8), (1084, 296, 1344, 4, 8), (487, 332, 1092, 8, 8), (193, 2068, 1024, 3, 8)]:

@@ -1027,18 +1027,38 @@ def test_large_layer_weight_gradients_on_sampled_outputs(oracle, hot, rows, k, o
         print("  %s worst error / magnitude sum: %.2e" % (name, np.max(err / mag)), flush=True)
 
 
-# (rows, contraction, outputs of the contraction, samples, per-sample input): the kernel for tens to hundreds of rows, every tile shape
-# it has (its cost model picks them in this order), as forward call and, with contraction and outputs exchanged, as input gradients.
-# Ragged rows (one row in the last block of 32, one block, a second row tile), a contraction with a last step of 4 indices and one of
-# whole rounds of the four waves, fewer steps than waves would share evenly, outputs that are no multiple of 32 or of 4
-DEEP_FORWARD = [(33, 164, 43, 1, False), (64, 128, 45, 3, True), (65, 128, 2069, 2, False), (129, 132, 4215, 1, False), (193, 260, 1358, 3, True),
-                (257, 164, 2705, 3, False), (129, 128, 8202, 1, False), (193, 128, 6148, 2, True), (65, 128, 8321, 3, False),
-                (321, 1028, 300, 2, True), (704, 324, 130, 1, False),
-                # hundreds of rows on wide layers; in the last two the outputs behind 8192 and 5440 go to a second launch of another shape
-                (300, 516, 5493, 2, True), (255, 400, 8431, 2, False), (300, 408, 8261, 2, False)]
-DEEP_INPUT_GRAD = [(65, 256, 1588, 1, 0), (65, 324, 56, 1, 1), (65, 260, 1364, 3, 0), (65, 260, 676, 2, 1), (129, 260, 2072, 2, 0),
-                   (193, 256, 1396, 3, 0), (255, 600, 1212, 1, 1), (320, 1164, 1608, 1, 1), (129, 256, 8240, 1, 0), (320, 688, 1204, 1, 1),
-                   (255, 408, 6196, 2, 0), (255, 832, 2088, 1, 1), (300, 400, 8316, 1, 0), (255, 408, 8240, 2, 0)]
+# (rows, contraction, outputs of the contraction, samples, per-sample input, hot_linear_kernel_shape): the kernel for tens to hundreds
+# of rows, every tile shape it has, alone and with a second launch of another shape for the outputs left over, as forward call
+# and, with contraction and outputs exchanged, as input gradients (parts: with the workspace).  Ragged rows (one row in the last
+# block of 32, one block, a second row tile), a contraction with a last step of 4 indices and one of whole rounds of the four
+# waves, outputs that are no multiple of 32 or of 4; 0: layers at the edge that go to other kernels
+DEEP_FORWARD = [(33, 164, 43, 1, False, 0), (64, 128, 45, 3, True, 0), (65, 128, 2069, 2, False, 1000041),
+                (129, 132, 4215, 1, False, 1000061), (193, 260, 1358, 3, True, 1000081), (257, 164, 2705, 3, False, 1000101),
+                (129, 128, 8202, 1, False, 1000062), (193, 128, 6148, 2, True, 0), (65, 128, 8321, 3, False, 1000042),
+                (321, 1028, 300, 2, True, 0), (704, 324, 130, 1, False, 0), (300, 516, 5493, 2, True, 1000061),
+                (255, 400, 8431, 2, False, 1021082), (300, 408, 8261, 2, False, 1101042), (33, 164, 4243, 1, True, 1000021),
+                (65, 132, 2243, 1, False, 1000021), (193, 144, 4507, 3, False, 1000082), (257, 1028, 4190, 2, True, 1021101),
+                (385, 168, 8470, 2, False, 1021082), (640, 396, 3608, 3, False, 1041042), (257, 528, 3601, 3, False, 1041101)]
+DEEP_INPUT_GRAD = [(65, 256, 1588, 1, 0, 0), (65, 324, 56, 1, 1, 0), (65, 260, 1364, 3, 0, 0), (65, 260, 676, 2, 1, 0),
+                   (129, 260, 2072, 2, 0, 0), (193, 256, 1396, 3, 0, 1000081), (255, 600, 1212, 1, 1, 5000081),
+                   (320, 1164, 1608, 1, 1, 5000101), (129, 256, 8240, 1, 0, 1000062), (320, 688, 1204, 1, 1, 6000101),
+                   (255, 408, 6196, 2, 0, 0), (255, 832, 2088, 1, 1, 7000082), (300, 400, 8316, 1, 0, 1000041), (255, 408, 8240, 2, 0, 0),
+                   (129, 304, 520, 2, 1, 1000021), (65, 392, 36, 1, 1, 4000021), (129, 292, 2796, 1, 1, 1000041),
+                   (65, 412, 344, 3, 1, 4000041), (129, 292, 2492, 2, 1, 1000061), (129, 904, 164, 3, 1, 8000061),
+                   (129, 288, 2760, 3, 1, 1000062), (193, 304, 1380, 3, 1, 1000081), (385, 508, 6328, 1, 1, 1000082),
+                   (385, 640, 396, 3, 1, 5000082), (257, 256, 1852, 3, 1, 1000101), (193, 352, 5516, 3, 0, 1021082),
+                   (257, 488, 3072, 3, 1, 1021101), (257, 516, 5388, 2, 0, 1041101), (129, 604, 2056, 1, 1, 5000062)]
+
+
+def test_every_tile_shape_for_tens_to_hundreds_of_rows_is_among_the_cases():
+    """Alone or as the first launch, and with one sample's contraction cut and whole."""
+    tiles = {21, 41, 61, 81, 101, 62, 82}
+    assert {case[-1] % 1000 for case in DEEP_FORWARD} == tiles | {42, 0}
+    for few in (True, False):
+        assert {case[-1] % 1000 for case in DEEP_INPUT_GRAD if case[-1] and (case[-1] // 1000000 > 1) == few} == tiles
+    for cases in (DEEP_FORWARD, DEEP_INPUT_GRAD):
+        rest = {case[-1] % 1000000 for case in cases if case[-1] % 1000000 > 1000}
+        assert len(rest) >= 3 and 21101 in rest
 
 
 def _materialised(hot, c, s, rng, w_off, b_off):
@@ -1063,11 +1083,11 @@ def _deep_case(seed, o, k):
                "mu_b": torch.randn(o, device=DEV, generator=g), "sigma_b": torch.rand(o, device=DEV, generator=g) + 0.1}
 
 
-@pytest.mark.parametrize("rows,k,o,s,xs", DEEP_FORWARD)
-def test_forward_at_tens_to_hundreds_of_rows_against_materialised_weights(hot, rows, k, o, s, xs):
+@pytest.mark.parametrize("rows,k,o,s,xs,shape", DEEP_FORWARD)
+def test_forward_at_tens_to_hundreds_of_rows_against_materialised_weights(hot, rows, k, o, s, xs, shape):
     """Within 1e-5 of the sum of the magnitudes of the addends, as the other forward kernels; rows of x have padding that holds NaN."""
     print("case linear, tens to hundreds of rows", rows, k, o, s, xs, flush=True)
-    assert hot.hot_linear_launch_shape(rows, k, o, s, 0, per_sample_x=xs, ldx=k + 8) == 0
+    assert hot.hot_linear_kernel_shape(rows, k, o, s, 0, per_sample_x=xs, ldx=k + 8) == shape
     g, c = _deep_case(rows + o, o, k)
     wide = torch.full((s, rows, k + 8) if xs else (rows, k + 8), float("nan"), device=DEV)
     x = wide[..., :k]
@@ -1084,11 +1104,11 @@ def test_forward_at_tens_to_hundreds_of_rows_against_materialised_weights(hot, r
         assert bool(((y[i].double() - want).abs() <= 1e-5 * mag).all()), ((y[i].double() - want).abs() / mag).max().item()
 
 
-@pytest.mark.parametrize("rows,o,k,s,parts", DEEP_INPUT_GRAD)
-def test_input_gradients_at_tens_to_hundreds_of_rows_against_materialised_weights(hot, rows, o, k, s, parts):
+@pytest.mark.parametrize("rows,o,k,s,parts,shape", DEEP_INPUT_GRAD)
+def test_input_gradients_at_tens_to_hundreds_of_rows_against_materialised_weights(hot, rows, o, k, s, parts, shape):
     """parts: with the workspace the call asks for (the contraction then cut into parts), else without one."""
     print("case linear dx, tens to hundreds of rows", rows, o, k, s, parts, flush=True)
-    assert parts or hot.hot_linear_launch_shape(rows, k, o, s, 1) == 0
+    assert hot.hot_linear_kernel_shape(rows, k, o, s, 1, workspace_bytes=-1 if parts else 0) == shape
     g, c = _deep_case(rows + k, o, k)
     x, dy = torch.randn(rows, k, device=DEV, generator=g), torch.randn(s, rows, o, device=DEV, generator=g)
     rng, w_off, b_off = hot.hot_rng(seed=43, step=3, first_sample=1), 8, 8 + (o * k + 3) // 4 * 4
