@@ -2418,6 +2418,10 @@ hot_linear_wgrad_row_parts_kernel(LinearGradArgs a, int parts, int chunk)
     unsigned b_off = row0 * b_pitch + (unsigned)((XBIG ? k0 : o0) * 4 + 4 * NB * l32);
     unsigned s_off = row0 * s_pitch + (unsigned)((XBIG ? o0 : k0) * 4 + 4 * NS * l32);
 
+    // The instruction rounds its accumulations downwards (the mean error is -1.4e-7 of the mean magnitude at 8191 rows, for sums of either
+    // sign), and what all parts and samples lose in one direction adds up.  So every other wave takes its products with the
+    // opposite sign, and its tile is subtracted.
+    const float sign = wave & 1 ? -1.0f : 1.0f;
     float col_sum[OB];
 #pragma unroll
     for (int j = 0; j < OB; ++j) col_sum[j] = 0.0f;
@@ -2457,7 +2461,7 @@ hot_linear_wgrad_row_parts_kernel(LinearGradArgs a, int parts, int chunk)
 #pragma unroll
             for (int j = 0; j < NS; ++j) {
                 bf8 c1, c2, c3;
-                split8_bf16(f4{sr[0][j], sr[1][j], sr[2][j], sr[3][j]}, f4{sr[4][j], sr[5][j], sr[6][j], sr[7][j]}, c1, c2, c3);
+                split8_bf16(f4{sr[0][j], sr[1][j], sr[2][j], sr[3][j]} * sign, f4{sr[4][j], sr[5][j], sr[6][j], sr[7][j]} * sign, c1, c2, c3);
                 if (j == NS - 1) ask_small();
 #pragma unroll
                 for (int i = 0; i < NB; ++i) {
@@ -2498,7 +2502,7 @@ hot_linear_wgrad_row_parts_kernel(LinearGradArgs a, int parts, int chunk)
 #pragma unroll
                 for (int v = 0; v < kRowPartWaves; ++v) of_wave[v] = *reinterpret_cast<const f4 *>(turn[v] + row * PITCH + 4 * quad);
 #pragma unroll
-                for (int c = 0; c < 4; ++c) sum[c] = (of_wave[0][c] + of_wave[1][c]) + (of_wave[2][c] + of_wave[3][c]);
+                for (int c = 0; c < 4; ++c) sum[c] = (of_wave[0][c] - of_wave[1][c]) + (of_wave[2][c] - of_wave[3][c]);
                 const long o = o0 + OB * row + j, k = k0 + 4 * quad;
                 if (o < O && k < K) {
                     if (c_lo != r_lo) sum += load4<true, false>(P + o * K + k);
@@ -2602,6 +2606,7 @@ hot_linear_wgrad_row_parts_finish_kernel(LinearGradArgs a, int parts)
 struct RowPartsPlan {
     int parts;
     long rows_per_part;
+    long chunks;        // in which a part is added up
     bool xbig;
 };
 
@@ -2622,11 +2627,10 @@ constexpr long kRowPartMinWeights = 8192, kRowPartAnyWeightsRows = 512;     // (
 constexpr long kRowPartMaxTileCount = 512;
 constexpr int kRowPartMaxParts = 64;
 constexpr int64_t kRowPartMaxBytes = (int64_t)256 << 20, kRowPartSmallBytes = (int64_t)8 << 20;
-// The bf16 matrix instruction rounds its accumulations to one side (the mean error is negative for sums of either sign, -1.4e-7 of
-// the mean magnitude at 8191 rows in four waves), so errors grow with the rows a wave adds up, 2-norm against 64 bits: 16640 x 192 x 768 3.2e-7 at 297 rows, 3.0e-7 at 245, 2.7e-7 at 198 (the fp32 instruction with 260: 3.0e-7).  So after at most
-// 208 rows a wave's sums leave the registers: 7260 x 2160 x 540 x 8 samples with 1815 rows to a wave 6.0e-7, with 208 3.0e-7 (the
-// fp32 instruction 5.4e-7; 825 -> 922 us, the fp32 instruction 1512), 4673 x 888 x 208 x 8 4.5e-7 -> 2.8e-7 (3.2e-7).
-constexpr long kRowPartMostRows = 208;
+// Errors grow with the rows that a wave adds up, 2-norm against 64 bits at 16640 x 192 x 768: 2.7e-7 with 297, 2.0e-7 with 152 (the fp32
+// instruction with 260: 3.1e-7).  From 8192 rows on, where the first kernel also cuts many parts, a wave's sums leave its
+// registers after at most 208 rows.
+constexpr long kRowPartLongRows = 8192, kRowPartLongMost = 208, kRowPartFineRows = 64;
 
 inline bool row_parts_suit(const hot_linear_desc *d)
 {
@@ -2636,34 +2640,6 @@ inline bool row_parts_suit(const hot_linear_desc *d)
     const unsigned long long lim = 0xFFFFFFF0ull;           // 32-bit byte offsets
     const unsigned long long reach = (unsigned long long)d->rows + 2 * kRowPartRows * kRowPartWaves;
     return (reach * d->ldx + d->in_features) * 4 < lim && reach * d->out_features * 4 < lim;
-}
-
-// the best plan whose parts fit into `budget` bytes
-inline RowPartsPlan row_parts_within(const hot_linear_desc *d, int64_t budget)
-{
-    RowPartsPlan p = {0, 0, false};
-    const long tall = row_part_tiles<true>(d), wide = row_part_tiles<false>(d);
-    p.xbig = tall <= wide;
-    const long tiles = p.xbig ? tall : wide;
-    const int64_t part_bytes = row_part_floats(d->in_features, d->out_features, d->s_local) * (int64_t)sizeof(float);
-    // The number of parts whose rounds of workgroups (two per compute unit; a last round of one per compute unit runs its
-    // workgroups faster) times steps per workgroup is least; a workgroup's start, its sums through LDS and its share
-    // of the finish kernel take about as long as four steps.  At least 128 rows to a part.
-    const long step_rows = kRowPartRows * kRowPartWaves;
-    double best = 0.0;
-    for (int parts = 1; parts <= kRowPartMaxParts && parts * part_bytes <= budget && (parts == 1 || d->rows >= 128L * parts); ++parts) {
-        const long rows = ((d->rows + parts - 1) / parts + kRowPartRows - 1) / kRowPartRows * kRowPartRows;
-        if (rows * (parts - 1) >= d->rows) continue;       // (the parts must all exist)
-        const long wgs = tiles * d->s_local * parts, last = wgs % 512;
-        const double rounds = (double)(wgs / 512) + (last == 0 ? 0.0 : (last <= 256 ? 0.65 : 1.0));
-        const double cost = rounds * ((double)((rows + step_rows - 1) / step_rows) + 4.0);
-        if (p.parts == 0 || cost < best) {
-            best = cost;
-            p.parts = parts;
-            p.rows_per_part = rows;
-        }
-    }
-    return p;
 }
 
 inline int64_t wgrad_part_bytes(const hot_linear_desc *d)
@@ -2678,24 +2654,11 @@ inline int64_t row_parts_budget(const hot_linear_desc *d)
     return most < kRowPartMaxBytes ? most : kRowPartMaxBytes;
 }
 
-// ws_bytes: what the caller's workspace holds (negative: as much as wanted, for the size query).  With less than half of the
-// parts it wants the chip would stand too empty: then the first kernel runs, which needs no workspace to split the rows.
-inline RowPartsPlan row_parts_plan(const hot_linear_desc *d, int64_t ws_bytes)
-{
-    const RowPartsPlan none = {0, 0, false};
-    if (ws_bytes == 0 || !row_parts_suit(d)) return none;
-    const RowPartsPlan wanted = row_parts_within(d, row_parts_budget(d));
-    const int64_t part_bytes = row_part_floats(d->in_features, d->out_features, d->s_local) * (int64_t)sizeof(float);
-    if (ws_bytes < 0 || wanted.parts * part_bytes <= ws_bytes) return wanted;
-    const RowPartsPlan p = row_parts_within(d, ws_bytes);
-    return 2 * p.parts >= wanted.parts ? p : none;
-}
-
-void row_parts_go(const RowPartsPlan &p, long chunks, hipStream_t s, const LinearGradArgs &a, long tiles)
+void row_parts_go(const RowPartsPlan &p, hipStream_t s, const LinearGradArgs &a, long tiles)
 {
     const long per_xcd = (tiles * a.s_loc * p.parts + kXcds - 1) / kXcds;
     const dim3 grid((unsigned)(kXcds * per_xcd)), block(64 * kRowPartWaves);
-    const long step_rows = kRowPartRows * kRowPartWaves, chunk = ((p.rows_per_part + chunks - 1) / chunks + step_rows - 1) / step_rows * step_rows;
+    const long step_rows = kRowPartRows * kRowPartWaves, chunk = ((p.rows_per_part + p.chunks - 1) / p.chunks + step_rows - 1) / step_rows * step_rows;
     if (p.xbig) hot_linear_wgrad_row_parts_kernel<true><<<grid, block, 0, s>>>(a, p.parts, (int)chunk);
     else hot_linear_wgrad_row_parts_kernel<false><<<grid, block, 0, s>>>(a, p.parts, (int)chunk);
     const long threads = a.out_features * a.in_features / 4 + (a.mu_b ? (a.out_features + 3) / 4 : 0);
@@ -3656,17 +3619,61 @@ WgradShape wgrad_shape(const hot_linear_desc *d, int64_t ws_bytes)
     return wgrad_shape_with(d, ws_bytes, false);
 }
 
-// The chunks in which a row part of `p` is added up.  Besides the bound on a wave's rows: where the kernel that would run otherwise
-// splits the rows finely (eight waves to a tile), its sums are half as long as those of four waves here, and so many one-sided
-// roundings are worse than its own (648 x 2032 x 156 x 4 samples: 2.0e-7 against 1.8e-7, 540 x 4080 x 36 x 8 2.1e-7 against
-// 1.9e-7); with at most 3/2 of its rows to a sum they are not (1.5e-7 and 1.7e-7; 31 -> 35 us each).
-inline long row_part_chunks(const hot_linear_desc *d, const RowPartsPlan &p, int64_t ws_bytes)
+// Most rows that a wave of the row parts may add up in one sum.  In as many rows the bf16 pieces are 0.75-0.85 times as far from 64
+// bits as the fp32 instruction, so with 3/2 of the rows that a wave of the kernel adds up that would run otherwise they are not
+// farther (533 x 920 x 464 x 3 samples, four waves against eight: 1.8e-7 in one sum, 1.3e-7 in two, that kernel 1.6e-7; 6151 x
+// 2048 x 632 x 3: 6.1e-7, 4.3e-7 and 5.0e-7); up to 64 rows they are level.
+inline long row_parts_most_rows(const hot_linear_desc *d, int64_t ws_bytes)
 {
     const WgradShape w = wgrad_shape(d, ws_bytes);
-    const long theirs = w.tile ? d->rows : (d->rows + (long)w.split * w.parts - 1) / ((long)w.split * w.parts);
-    const long most = theirs * 3 / 2 < kRowPartMostRows ? theirs * 3 / 2 : kRowPartMostRows;
-    const long rows = (most < kRowPartRows ? kRowPartRows : most / kRowPartRows * kRowPartRows) * kRowPartWaves;
-    return (p.rows_per_part + rows - 1) / rows;
+    long most = d->rows;            // (the tile kernel adds up all rows in one such sum)
+    if (!w.tile) most = (d->rows + (long)w.split * w.parts - 1) / ((long)w.split * w.parts) * 3 / 2;
+    if (d->rows >= kRowPartLongRows && most > kRowPartLongMost) most = kRowPartLongMost;
+    return most < kRowPartFineRows ? kRowPartFineRows : most / kRowPartRows * kRowPartRows;
+}
+
+// the best plan whose parts fit into `budget` bytes, with at most `most` rows to a wave's sum
+inline RowPartsPlan row_parts_within(const hot_linear_desc *d, int64_t budget, long most)
+{
+    RowPartsPlan p = {0, 0, 1, false};
+    const long tall = row_part_tiles<true>(d), wide = row_part_tiles<false>(d);
+    p.xbig = tall <= wide;
+    const long tiles = p.xbig ? tall : wide;
+    const int64_t part_bytes = row_part_floats(d->in_features, d->out_features, d->s_local) * (int64_t)sizeof(float);
+    // The number of parts whose rounds of workgroups (two per compute unit; a last round of one per compute unit runs its
+    // workgroups faster) times steps per workgroup is least; a workgroup's start, its sums through LDS (once per chunk) and its
+    // share of the finish kernel take about as long as four steps.  At least 128 rows to a part.
+    const long step_rows = kRowPartRows * kRowPartWaves;
+    double best = 0.0;
+    for (int parts = 1; parts <= kRowPartMaxParts && parts * part_bytes <= budget && (parts == 1 || d->rows >= 128L * parts); ++parts) {
+        const long rows = ((d->rows + parts - 1) / parts + kRowPartRows - 1) / kRowPartRows * kRowPartRows;
+        if (rows * (parts - 1) >= d->rows) continue;       // (the parts must all exist)
+        const long wgs = tiles * d->s_local * parts, last = wgs % 512;
+        const double rounds = (double)(wgs / 512) + (last == 0 ? 0.0 : (last <= 256 ? 0.65 : 1.0));
+        const long chunks = (rows + most * kRowPartWaves - 1) / (most * kRowPartWaves);
+        const double cost = rounds * ((double)((rows + step_rows - 1) / step_rows) + 4.0 * (double)chunks);
+        if (p.parts == 0 || cost < best) {
+            best = cost;
+            p.parts = parts;
+            p.rows_per_part = rows;
+            p.chunks = chunks;
+        }
+    }
+    return p;
+}
+
+// ws_bytes: what the caller's workspace holds (negative: as much as wanted, for the size query).  With less than half of the
+// parts it wants the chip would stand too empty: then the first kernel runs, which needs no workspace to split the rows.
+inline RowPartsPlan row_parts_plan(const hot_linear_desc *d, int64_t ws_bytes)
+{
+    const RowPartsPlan none = {0, 0, 1, false};
+    if (ws_bytes == 0 || !row_parts_suit(d)) return none;
+    const long most = row_parts_most_rows(d, ws_bytes);
+    const RowPartsPlan wanted = row_parts_within(d, row_parts_budget(d), most);
+    const int64_t part_bytes = row_part_floats(d->in_features, d->out_features, d->s_local) * (int64_t)sizeof(float);
+    if (ws_bytes < 0 || wanted.parts * part_bytes <= ws_bytes) return wanted;
+    const RowPartsPlan p = row_parts_within(d, ws_bytes, most);
+    return 2 * p.parts >= wanted.parts ? p : none;
 }
 
 }  // namespace
@@ -3695,7 +3702,7 @@ int64_t hot_linear_kernel_shape(const hot_linear_desc *d, int which, int64_t wor
     if (which < 0 || which > 2) return HOT_EINVAL;
     if (which == 2) {
         const RowPartsPlan p = row_parts_plan(d, workspace_bytes);
-        return p.parts ? 1000 * (int64_t)row_part_chunks(d, p, workspace_bytes) + 10 * p.parts + (p.xbig ? 1 : 0) : 0;
+        return p.parts ? 1000 * (int64_t)p.chunks + 10 * p.parts + (p.xbig ? 1 : 0) : 0;
     }
     const DeepPlan p = which == 0 ? deep_forward_plan(d) : deep_input_grad_plan(d, true, workspace_bytes);
     auto code = [](int i) { return i < 0 ? 0 : 10 * kDeepShapes[i].rb + kDeepShapes[i].cb; };
@@ -3970,7 +3977,7 @@ int hot_linear_backward_rng_ws(const hot_linear_desc *d, int32_t s_total, double
     if (const RowPartsPlan plan = row_parts_plan(d, workspace ? workspace_bytes : 0); plan.parts) {
         a.ws = static_cast<float *>(workspace);
         a.rows_per_part = plan.rows_per_part;
-        row_parts_go(plan, row_part_chunks(d, plan, workspace ? workspace_bytes : 0), s, a, plan.xbig ? row_part_tiles<true>(d) : row_part_tiles<false>(d));
+        row_parts_go(plan, s, a, plan.xbig ? row_part_tiles<true>(d) : row_part_tiles<false>(d));
     } else if (shape.tile) {
         wgrad_tile_go(s, a, wgrad_tile_count(d));
     } else {

@@ -1158,8 +1158,10 @@ def _distance(got, want):
     return ((got.double() - want).norm() / want.norm()).item()
 
 
-# parts of a thousand rows and more; four waves where the other kernel splits the rows over eight
-@pytest.mark.parametrize("rows,k,o,s", [(4673, 888, 208, 8), (6151, 2048, 632, 3), (648, 2032, 156, 4), (540, 4080, 36, 8)])
+# parts of a thousand rows and more; four waves where the other kernel splits the rows over eight; what many parts and samples
+# would lose in one direction
+@pytest.mark.parametrize("rows,k,o,s", [(4673, 888, 208, 8), (6151, 2048, 632, 3), (648, 2032, 156, 4), (540, 4080, 36, 8),
+                                        (16466, 120, 36, 8), (361, 1396, 224, 3)])
 @pytest.mark.parametrize("positive", [False, True])
 def test_weight_gradients_from_row_parts_are_no_less_accurate(hot, rows, k, o, s, positive):
     """Row parts (bf16 pieces, accumulations rounded to one side) against the kernel on the fp32 instruction with a workspace,
