@@ -2624,6 +2624,14 @@ inline long row_part_tiles(const hot_linear_desc *d)
 // 128 x 128 and more stay with the kernel above this one: level with it (0.96-1.08x), it needs no workspace.
 constexpr long kRowPartMinRows = 129, kRowPartAlwaysRows = 300, kRowPartMinRowSamples = 600;
 constexpr long kRowPartMinWeights = 8192, kRowPartAnyWeightsRows = 512;     // (one or two tiles need that many rows to be worth two launches)
+// From 8192 to 2^18 weights the products are too few to pay for a second launch with one or two samples and fewer than 1200 rows
+// of them (581 x 540 x 380 x 1: 13.3 against 15.2 us, 317 x 124 x 1448 x 2 14.0 against 15.2; of 90 such layers 1.03x on
+// average), nor do they where half of every tile has no outputs (544 x 7756 x 32 x 2: 18.2 against 20.4).  From 8192 rows on the
+// other kernel cuts the rows of up to 2^17 weights into four parts, from 16384 on its waves outnumber the chip's slots: between
+// them it is as fast on one sample (8300 x 192 x 128 x 1: 23.3 against 25.9, 12000 x 100 x 300 level, 16640 x 192^2 42.9 against 31.0).
+constexpr long kRowPartFewRowSamples = 1200, kRowPartManyWeights = 1L << 18;
+constexpr long kRowPartNarrow = 32, kRowPartNarrowRows = 1000;
+constexpr long kRowPartOneSampleRows = 8192, kRowPartOneSampleRowsEnd = 12000, kRowPartOneSampleWeights = 1L << 17;
 constexpr long kRowPartMaxTileCount = 512;
 constexpr int kRowPartMaxParts = 64;
 constexpr int64_t kRowPartMaxBytes = (int64_t)256 << 20, kRowPartSmallBytes = (int64_t)8 << 20;
@@ -2637,6 +2645,11 @@ inline bool row_parts_suit(const hot_linear_desc *d)
     if (d->rows < kRowPartMinRows || (d->rows < kRowPartAlwaysRows && d->rows * d->s_local < kRowPartMinRowSamples)) return false;
     if (d->rows < kRowPartAnyWeightsRows && d->in_features * d->out_features < kRowPartMinWeights) return false;
     if ((d->out_features & 3) || wgrad_tile_count(d) >= kRowPartMaxTileCount) return false;       // (rows of dy are read in 16-byte quads)
+    if (const long weights = d->in_features * d->out_features; weights > kRowPartMinWeights) {
+        if (weights < kRowPartManyWeights && d->s_local <= 2 && d->rows * d->s_local < kRowPartFewRowSamples) return false;
+        if (d->out_features <= kRowPartNarrow && d->rows < kRowPartNarrowRows && d->s_local <= 4) return false;
+        if (weights < kRowPartOneSampleWeights && d->s_local == 1 && d->rows >= kRowPartOneSampleRows && d->rows < kRowPartOneSampleRowsEnd) return false;
+    }
     const unsigned long long lim = 0xFFFFFFF0ull;           // 32-bit byte offsets
     const unsigned long long reach = (unsigned long long)d->rows + 2 * kRowPartRows * kRowPartWaves;
     return (reach * d->ldx + d->in_features) * 4 < lim && reach * d->out_features * 4 < lim;

@@ -174,6 +174,15 @@ def test_layers_on_which_the_slab_kernel_is_faster_stay_with_it(hot):
         assert hot.hot_linear_kernel_shape(rows, k, o, s, 0, per_sample_x=True) > 0
 
 
+def test_weight_gradients_of_small_layers_stay_with_one_launch(hot):
+    """Row parts take two: few weights with few rows of one or two samples, half-empty tiles, one sample of 8192 to 12000 rows."""
+    for rows, k, o, s in [(581, 540, 380, 1), (1199, 92, 112, 1), (317, 124, 1448, 2), (544, 7756, 32, 2), (8300, 192, 128, 1)]:
+        assert hot.hot_linear_kernel_shape(rows, k, o, s, 2) == 0
+    for rows, k, o, s in [(581, 540, 500, 1), (1200, 92, 112, 1), (617, 124, 1448, 2), (544, 7756, 36, 2), (544, 7756, 32, 5),
+                          (12000, 192, 128, 1), (8300, 192, 128, 2)]:
+        assert hot.hot_linear_kernel_shape(rows, k, o, s, 2) > 0
+
+
 def test_workspace_query_covers_a_dy_off_the_16_byte_grid(hot):
     """Such a dy goes to the kernel that cuts the outputs into up to eight parts of dx, whatever the one for aligned rows takes."""
     for rows, k, o, s, parts in [(371, 540, 1368, 4, 8), (1084, 296, 1344, 4, 8), (487, 332, 1092, 8, 8), (193, 2068, 1024, 3, 8)]:
