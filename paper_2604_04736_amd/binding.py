@@ -235,9 +235,12 @@ def _mat(t: torch.Tensor, s: int, n: int, ld: int, dev: int, name: str) -> int:
     return t.data_ptr()
 
 
+# The stream's handle itself where this torch gives it: torch.cuda.current_stream builds a Stream object around it first (1.2 us).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(dev: int) -> int:
-    # (the handle itself: torch.cuda.current_stream builds a Stream object around it first, 1.2 us)
-    return torch._C._cuda_getCurrentRawStream(dev)
+    return _raw_stream(dev) if _raw_stream is not None else torch.cuda.current_stream(dev).cuda_stream
 
 
 _STAY = contextlib.nullcontext()

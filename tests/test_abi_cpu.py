@@ -297,6 +297,17 @@ def test_binding_error_objects(hot):
     assert e.value.code == hot.HOT_ENOMEM and "memory" in str(e.value)
 
 
+def test_stream_handle_without_the_private_query(hot, monkeypatch):
+    """A torch that does not give the raw handle: the public stream object's."""
+    import types
+    import torch
+    monkeypatch.setattr(hot, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda dev: types.SimpleNamespace(cuda_stream=100 + dev))
+    assert hot._stream(3) == 103
+    monkeypatch.setattr(hot, "_raw_stream", lambda dev: 200 + dev)
+    assert hot._stream(3) == 203
+
+
 def test_device_code_has_no_packed_instructions(tmp_path):
     """The library is built with packed fp32 arithmetic switched off, and the one kernel version that made
     the compiler emit a packed move (v_pk_mov_b32, to rotate vectors read from LDS) returned sporadic wrong
