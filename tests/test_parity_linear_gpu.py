@@ -350,7 +350,7 @@ def test_fused_layer_backward_matches_oracle(oracle, hot, rows, k, o, s, xs, bia
 WITH_WORKSPACE = [(4200, 64, 48, 2, False, True, False, 1.0, True), (17000, 36, 20, 3, True, True, False, 1.0, True),
                   (17000, 36, 20, 2, False, False, False, 0.3, True), (17000, 36, 20, 2, False, True, False, 0.01, False),
                   (2100, 516, 1840, 1, False, True, False, 1.0, True), (300, 64, 48, 2, False, True, False, 1.0, False),
-                  # rows enough for wide tiles through parts: all of the workspace, a part of it, too little for any part
+                  # rows enough for parts, wide tiles: all of the workspace, a part of it, too little for any part
                   (8200, 256, 512, 1, False, True, False, 1.0, True), (8200, 256, 512, 1, False, True, False, 0.3, True),
                   (8200, 256, 512, 1, False, True, False, 0.05, False),
                   # input gradients on too few 256-row workgroups: the outputs cut into parts (ragged last part; a
@@ -359,15 +359,21 @@ WITH_WORKSPACE = [(4200, 64, 48, 2, False, True, False, 1.0, True), (17000, 36, 
                   (1030, 132, 700, 2, False, True, True, 0.6, True), (1030, 132, 700, 2, False, True, True, 0.1, False),
                   # ... from 129 rows on (one 256-row workgroup per 64 inputs, its last waves without rows)
                   (200, 132, 700, 2, False, True, True, 1.0, True),
-                  # the shape on which one accumulator register was once read before the matrix pipeline had written it
+                  # a layer on which one accumulator register was once read before the matrix pipeline had written it
                   # (a partial last row block in a tile without biases; the kernels now wait explicitly)
-                  (19549, 84, 1744, 1, False, True, False, 1.0, True)]
+                  (19549, 84, 1744, 1, False, True, False, 1.0, True),
+                  # the weight gradients above that use the workspace come from row parts in bf16 pieces; outputs that are no multiple
+                  # of four stay with the parts of the kernel on the fp32 instruction: narrow tiles, wide tiles with all of
+                  # the workspace and a part of it, and the layer of the accumulator register
+                  (17000, 36, 18, 3, True, True, False, 1.0, True), (17000, 36, 18, 2, False, False, False, 0.3, True),
+                  (8200, 256, 510, 1, False, True, False, 1.0, True), (8200, 256, 510, 1, False, True, False, 0.3, True),
+                  (19549, 84, 1742, 1, False, True, False, 1.0, True)]
 
 
 @pytest.mark.parametrize("rows,k,o,s,xs,bias,want_dx,fraction,used", WITH_WORKSPACE)
 def test_backward_with_a_workspace_matches_oracle(oracle, hot, rows, k, o, s, xs, bias, want_dx, fraction, used):
     """hot_linear_backward_rng_ws.  Weight gradients of few tiles and many rows: the rows cut into parts over
-    workgroups, partial sums in the caller's workspace, added in part order by a second kernel.  Input gradients
+    workgroups, partial sums in the caller's workspace, added in a fixed order by a second kernel.  Input gradients
     on too few workgroups: the outputs cut into parts the same way.  Everything against the oracle to the same
     bound as without a workspace; a workspace smaller than asked for (fewer parts, or none) and a shape that
     wants none give the same; the workspace is the only memory written besides the outputs."""
@@ -398,14 +404,30 @@ def test_backward_in_one_pass_matches_oracle(oracle, hot, rows, k, o, s, xs, bia
 
 # Weight gradients from row parts on the bf16 matrix instruction: the fewest rows (129, samples making up for them) and
 # ragged tiles; one exact tile of 128 inputs x 64 outputs and of 64 x 128; a layer narrower than any tile; rows that leave
-# the last wave of the last part one row or none; enough rows for the bound on a wave's rows; half of the workspace
+# the last wave of the last part one row or none; half of the workspace
 ROW_PARTS = [(129, 132, 260, 5, True, True, 1.0), (300, 128, 64, 2, False, True, 1.0), (300, 64, 128, 2, True, False, 1.0),
              (512, 8, 12, 1, False, True, 1.0), (577, 260, 68, 3, True, True, 1.0), (1041, 128, 516, 2, False, True, 0.5),
              (8195, 36, 44, 2, True, True, 1.0), (1025, 200, 4, 1, False, False, 1.0)]
+# A part added up in chunks, which each add to what the chunk before left in the workspace (x 1000 in the shape's code): both
+# orientations of the tile (the code's last digit), two, three and four chunks, the last of them ragged, parts of few and of many rows
+ROW_PART_CHUNKS = [(275, 124, 68, 3, True, True, 0.5, 2011), (260, 24, 360, 3, False, True, 0.5, 2010), (17835, 8, 564, 5, False, True, 1.0, 2200),
+                   (18525, 8, 1144, 5, False, True, 1.0, 3110), (15926, 804, 8, 4, True, True, 0.5, 3091), (10072, 1532, 8, 5, False, False, 0.5, 4041)]
+
+
+def _workspace_given(hot, rows, k, o, s, fraction):
+    """floats of a workspace of that fraction of what the layer asks for"""
+    return max(int(hot.hot_linear_backward_workspace_bytes(rows, k, o, s) * fraction) // 16 * 4, 4)
 
 
 @pytest.mark.parametrize("rows,k,o,s,xs,bias,fraction", ROW_PARTS)
 def test_weight_gradients_from_row_parts_match_oracle(oracle, hot, rows, k, o, s, xs, bias, fraction):
+    assert hot.hot_linear_kernel_shape(rows, k, o, s, 2, xs, workspace_bytes=4 * _workspace_given(hot, rows, k, o, s, fraction)) // 1000 == 1
+    _backward_with_a_workspace(oracle, hot, rows, k, o, s, xs, bias, False, fraction, True)
+
+
+@pytest.mark.parametrize("rows,k,o,s,xs,bias,fraction,shape", ROW_PART_CHUNKS)
+def test_weight_gradients_from_row_parts_in_chunks_match_oracle(oracle, hot, rows, k, o, s, xs, bias, fraction, shape):
+    assert hot.hot_linear_kernel_shape(rows, k, o, s, 2, xs, workspace_bytes=4 * _workspace_given(hot, rows, k, o, s, fraction)) == shape
     _backward_with_a_workspace(oracle, hot, rows, k, o, s, xs, bias, False, fraction, True)
 
 
@@ -441,7 +463,7 @@ def _backward_with_a_workspace(oracle, hot, rows, k, o, s, xs, bias, want_dx, fr
     s_total, dsize = 2 * s, 800.0
     want_bytes = hot.hot_linear_backward_workspace_bytes(rows, k, o, s)
     assert (want_bytes > 0) == ((used or fraction <= 0.1) if wants_none is None else not wants_none), want_bytes
-    n_ws = max(int(want_bytes * fraction) // 16 * 4, 4)
+    n_ws = _workspace_given(hot, rows, k, o, s, fraction)
     ws = torch.full((n_ws + 8,), float("nan"), device=DEV)
     t = {n: torch.from_numpy(c[n]).to(DEV) for n in ("x", "mu_w", "sigma_w", "mu_b", "sigma_b")}
     out = {"gmw": torch.full((o, k), float("nan"), device=DEV), "gsw": torch.full((o, k), float("nan"), device=DEV),
