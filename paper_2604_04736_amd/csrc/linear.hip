@@ -1469,7 +1469,7 @@ inline double slab_time(const SlabShape &h, int st, long contract)
     if (h.waves == 4 && h.rbw == 1) start = 6.0;                         // 128 rows
     else if (h.waves == 4 && st == 2) share = 0.78, start = 7.0;
     else if (h.waves == 4 && wide == 2) share = 0.86, start = 10.0;
-    else if (h.waves == 8 && wide == 1) share = 1.3, start = 6.0;
+    else if (h.waves == 8 && wide == 1) share = h.cost > 3000.0 ? 1.0 : 1.3, start = 6.0;       // (1.3: alone on its compute unit)
     else if (h.waves == 8 && wide == 2) share = 0.92, start = 7.0;
     else if (h.waves == 8) share = 0.8, start = 11.0;
     else if (h.waves == 16) share = 0.85, start = 18.0;

@@ -168,7 +168,7 @@ def test_layers_on_which_the_slab_kernel_is_faster_stay_with_it(hot):
     for rows, k, o, s in [(493, 236, 8192, 4), (658, 192, 8048, 4), (665, 304, 4300, 2), (1387, 1964, 540, 8)]:
         assert hot.hot_linear_kernel_shape(rows, k, o, s, 0, per_sample_x=True) == 0
         assert hot.hot_linear_launch_shape(rows, k, o, s, 0, per_sample_x=True) > 0
-    for rows, k, o, s in [(422, 5148, 408, 4), (1142, 1024, 4428, 4), (2107, 2068, 1572, 3)]:
+    for rows, k, o, s in [(422, 5148, 408, 4), (1142, 1024, 4428, 4), (2107, 2068, 1572, 3), (7260, 540, 2160, 2)]:
         assert hot.hot_linear_kernel_shape(rows, k, o, s, 1, workspace_bytes=0) == 0 < hot.hot_linear_launch_shape(rows, k, o, s, 1)
     for rows, k, o, s in [(499, 1420, 3276, 3), (790, 5204, 1968, 2), (1067, 596, 192, 8)]:
         assert hot.hot_linear_kernel_shape(rows, k, o, s, 0, per_sample_x=True) > 0
