@@ -220,19 +220,23 @@ int hot_last_hip_error(const hot_plan *plan);
  * row-major; mu_b, sigma_b: [out_features] or both NULL; y: [s_local, rows, out_features]
  * packed, out.  All DEVICE pointers; x, mu_W, sigma_W 16-byte aligned; in_features, ldx,
  * weight_offset, bias_offset multiples of 4.  The contraction runs on the matrix cores at fp32
- * accuracy: on the fp32 instructions (v_mfma_f32_16x16x4_f32, v_mfma_f32_32x32x2_f32), or, in the tiles of 256 rows
- * and more, on v_mfma_f32_32x32x16_bf16 with every product formed from three bf16 pieces of both factors (six
- * partial products; what they leave out is below 3 * 2^-24 of a product; measured errors up to 7e-7 of the sum of
- * addend magnitudes, against 3e-7 on the fp32 instruction; a factor below about 1e-33 in magnitude has pieces
- * below bf16's normal range, which the instruction may flush, and an infinite factor gives NaN, not infinity).
+ * accuracy: on the fp32 instructions (v_mfma_f32_16x16x4_f32, v_mfma_f32_32x32x2_f32), or on v_mfma_f32_32x32x16_bf16 with
+ * every product formed from three bf16 pieces of both factors (six partial products; what they leave out is below 3 * 2^-24
+ * of a product; errors of both are up to 3 to 7e-7 of the sum of addend magnitudes, by the length of a wave's sum).  bf16 pieces
+ * are what may run: forward from 33 rows and 128 inputs on (hot_linear_kernel_shape with which = 0 or hot_linear_launch_shape
+ * with 0 tells where, but for the latter's codes 2xx), input gradients from 65 rows and 256 outputs on (the same with 1), weight
+ * gradients from 129 rows on (large layers, and those that a workspace cuts into row parts).  There a factor below about 1e-33 in
+ * magnitude has pieces below bf16's normal range, which the instruction may flush.  An infinite factor, or one above the
+ * largest bf16 number (3.39e38), gives NaN in the tiles that hot_linear_launch_shape tells of (2xx apart) and in the weight gradients of
+ * large layers; elsewhere, bf16 pieces or not, it gives what fp32 products give.
  * Runs on the current device, asynchronous on `stream`.
- * Up to 32 rows a wave draws the weights it multiplies for those rows.  From 33 rows on (layers of at least 128 inputs) one wave
- * holds all of a workgroup's 64 to 320 rows and draws every weight once for them (2160 x 8640, two samples: 84 us at 64 rows,
- * 210 at 300; 172 TFLOP/s of fp32 work at 256 rows x 8192^2); from about 700 rows on, on layers that fill the chip,
- * tiles of 256, 512 or 1024 rows x 32 to 128 outputs, whose four, eight or sixteen waves share every draw through LDS and take x
- * from memory straight into it (hot_linear_launch_shape tells; tiles of 128 and 256 rows also serve fewer rows on layers
- * of fewer inputs), at 120-190 TFLOP/s of fp32 work.  What the other kernels cannot take goes, from 256 rows on, to one whose
- * four waves share the draws, else to the first.
+ * Up to 32 rows, and wherever 64-row x 16-output tiles of all samples are at most one per compute unit, a wave draws the weights
+ * it multiplies.  From 33 rows on (layers of at least 128 inputs) one wave holds all of a workgroup's 64 to 320 rows and draws every
+ * weight once for them (2160 x 8640, two samples: 83 us at 64 rows, 215 at 300; 170 TFLOP/s of fp32 work at 256 rows x 8192^2);
+ * where they are faster, tiles of 256, 512 or 1024 rows x 32 to 128 outputs, whose four, eight or sixteen waves share every
+ * draw through LDS and take x from memory straight into it (many rows on layers that fill the chip, fewer on layers of few inputs and
+ * many outputs, there also tiles of 128 rows), at 120-190 TFLOP/s of fp32 work.  What the other kernels cannot take goes, from
+ * 256 rows on, to one whose four waves share the draws, else to the first.
  */
 typedef struct hot_linear_desc {
     int64_t rows;          /* R >= 1: rows of x (batch x tokens) */
@@ -267,10 +271,11 @@ int hot_linear_forward_rng(const hot_linear_desc *desc, const hot_rng *rng, cons
  * when x is shared (the caller adds them up), or NULL to skip it (a first layer); with dx, rows <=
  * 1 048 560 and s_local <= 65 535 (grid limits; HOT_EINVAL beyond, before anything runs).  Other arguments
  * and rules as for hot_linear_forward_rng.  Every weight is drawn once per sample (and per wave that
- * shares its tile) for the weight gradients, and for dx once per block of 64 rows, or, from 65 rows
- * on, once per workgroup of 64 to 320 rows, or, where tiles of 512 or 1024 rows fill the chip, once per such tile (the
- * forward pass's kernels with dy as their input; they need out_features to be a multiple of 4 and dy 16-byte
- * aligned; else from 256 rows on once per workgroup of 64 to 256 rows, whose waves share the draws through LDS).  Large layers
+ * shares its tile) for the weight gradients, and for dx once per block of 64 rows, or, from 65 rows on where it splits a sum
+ * into as many shares as the kernel for those (a workspace lets it), once per workgroup of 64 to 320 rows, or, where tiles of 512 or
+ * 1024 rows are faster, once per such tile (the forward pass's kernels with dy as their input; they need out_features to be
+ * a multiple of 4 and dy 16-byte aligned; else from 256 rows on once per workgroup of 64 to 256 rows, whose waves share the
+ * draws through LDS).  Large layers
  * (from 129 rows on, at least 512 tiles of 128 inputs x 128 outputs, or from 256 rows on at least 140) take their
  * weight gradients from a kernel that stages x and dy through LDS and multiplies bf16 pieces of both, as the
  * forward call's large tiles do (up to 180 TFLOP/s of fp32 work); it needs out_features to
@@ -279,9 +284,8 @@ int hot_linear_forward_rng(const hot_linear_desc *desc, const hot_rng *rng, cons
  * scale the sums and add the KL part in fp32 (g * sum + k * mu, g * sum + k * (sigma - 1/sigma) with the hardware's
  * reciprocal: 1e-7 of each term), where hot_backward does it in fp64.  Against
  * library GEMMs for dx and G followed by hot_backward_rng the call is 1.1-3x faster up to tens of rows (with a
- * workspace, see below; 0.8-3x without) and at 1.08-1.25x for thousands of rows; from 65 rows on the input gradients of
- * layers with at least 256 outputs come from the forward call's kernel for tens to hundreds of rows (300 x 2160 x 8640, two
- * samples: 486 -> 203 us for dx).
+ * workspace, see below; 0.8-3x without) and at 1.03-1.3x for thousands of rows (1.5-2.5x with a workspace).  300 x 2160 x 8640
+ * with two samples takes 0.43 ms with a workspace and 0.49 without.
  */
 int hot_linear_backward_rng(const hot_linear_desc *desc, int32_t s_total, double dataset_size, uint32_t flags,
                             const hot_rng *rng, const float *x, const float *dy, const float *mu_w,
@@ -322,10 +326,12 @@ int64_t hot_linear_kernel_shape(const hot_linear_desc *desc, int which, int64_t 
  * few 16-output x 64-input tiles to give every compute unit weight-gradient work, and the waves of one
  * workgroup are all that can add up the rows of a tile without memory.  With a workspace the rows are cut
  * into parts for different workgroups; each part leaves its sums there and a second kernel adds
- * them in a fixed order and finishes the gradients: deterministic, no atomics.  From 129 rows on (300 for one or two samples),
- * where out_features is a multiple of 4 and the layer has fewer than 512 tiles of 128 x 128, the parts multiply bf16
- * pieces and leave the raw product of each sample, so that every eps is drawn once (16640 x 192 x 768, two samples: 173 ->
- * 75-85 us; 7260 x 2160 x 540: 435 -> 202).  The input gradients use the
+ * them in a fixed order and finishes the gradients: deterministic, no atomics.  Where out_features is a multiple of 4 and the
+ * layer has fewer than 512 tiles of 128 x 128, the parts multiply bf16 pieces and leave the raw product of each sample, so that
+ * every eps is drawn once (16640 x 192 x 768, two samples: 150 -> 74 us; 7260 x 2160 x 540: 382 -> 205): from 300 rows on, from 129 on
+ * if rows x samples are at least 600; below 512 rows from 8192 weights on, and not where one launch is faster (8192 to 2^18
+ * weights with fewer than 1200 rows of one or two samples, up to 32 outputs, one sample of 8192 to 12000 rows;
+ * hot_linear_kernel_shape with which = 2 tells).  The input gradients use the
  * same memory afterwards where the tiles of dx are too few for the chip (few inputs, up to about a thousand
  * rows): the outputs they contract over are cut into parts, whose dx blocks a second kernel adds.
  * Up to 128 rows with dx wanted the workspace buys more: weight and input gradients then come from ONE pass

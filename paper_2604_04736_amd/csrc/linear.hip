@@ -17,12 +17,13 @@
 // order, and every 128-byte line of mu_W, sigma_W and x is consumed by one iteration.
 //
 // Kernels of this file, by regime:
-//   forward   hot_linear_forward_kernel        up to a few hundred rows: every wave draws what it multiplies
-//             hot_linear_forward_rows_kernel   from 256 rows: four waves x 64 rows share every draw through LDS
-//             hot_linear_slab_kernel           from 256 rows on layers that fill the chip: 256 to 1024 rows x 32 to 128 outputs per
-//                                              workgroup, x loaded straight into LDS, the drawn weights shared through it,
-//                                              v_mfma_f32_32x32x2_f32; also the input gradients of such layers
-//             hot_linear_deep_kernel           tens to hundreds of rows (and more on small layers): a wave holds all rows of its
+//   forward   hot_linear_forward_kernel        up to 32 rows, and layers that do not fill the chip: every wave draws what it multiplies
+//             hot_linear_forward_rows_kernel   from 256 rows: four waves x 64 rows share every draw through LDS; where neither of the
+//                                              next two runs (fewer than 128 inputs, operands beyond their 32-bit offsets)
+//             hot_linear_slab_kernel           many rows on layers that fill the chip: 256 to 1024 rows x 32 to 128 outputs per
+//                                              workgroup, x loaded straight into LDS, the drawn weights shared through it, bf16 pieces
+//                                              on v_mfma_f32_32x32x16_bf16 (128 rows: v_mfma_f32_32x32x2_f32); also input gradients
+//             hot_linear_deep_kernel           tens to hundreds of rows, and more where it is faster: a wave holds all rows of its
 //                                              workgroup, the waves split the contraction; also the input gradients
 //   backward  hot_linear_wgrad_kernel          weight and bias gradients (per-sample G never stored); variants for
 //                                              few tiles (waves split the rows), many rows (operands prefetched,
@@ -31,8 +32,9 @@
 //                                              x and dy loaded straight into LDS
 //             hot_linear_wgrad_row_parts_kernel  the same for smaller layers and many rows, with a workspace: the rows cut into
 //                                              parts, bf16 pieces straight from memory, no LDS before the last sum
-//             hot_linear_xgrad_kernel          input gradients up to a few hundred rows
-//             hot_linear_xgrad_rows_kernel     input gradients from 256 rows: shared draws, as in the forward kernel
+//             hot_linear_xgrad_kernel          input gradients where few workgroups are left to it: up to 16 waves split a sum
+//             hot_linear_xgrad_rows_kernel     input gradients from 256 rows: shared draws, as in the forward kernel; with a
+//                                              workspace from 129 rows on in parts (both where the forward kernels above do not run)
 #include <hip/hip_runtime.h>
 
 #include "hot.h"
@@ -1156,8 +1158,8 @@ inline double deep_cost(const DeepShape &h, long wgs, long steps)
     return t + 4.0;
 }
 
-// Where it runs, measured against the other kernels on 60 layer shapes: forward from 33 rows on (64 x 2160 x 8640 x 2 samples 130 ->
-// 84 us, 300: 655 -> 210, 256 x 8192^2 590 -> 400, 64 x 1024^2 x 8 95 -> 21; at 16 rows 59 -> 79, so fewer stay), input gradients from
+// Where it runs, measured against the other kernels on 60 layer shapes: forward from 33 rows on (64 x 2160 x 8640 x 2 samples 133 ->
+// 83 us, 300: 638 -> 215, 256 x 8192^2 592 -> 403, 64 x 1024^2 x 8 93 -> 22; at 16 rows 59 -> 79, so fewer stay), input gradients from
 // 65 (below, the other kernel draws as few weights and has more waves: 0.87-1.04x), both given two (four) steps of contraction per
 // wave and, without parts, 100 workgroups for the input gradients (below, the other kernel's up to sixteen waves per tile win:
 // 200 x 192 x 768 27 -> 32).  Where the kernel above runs too, the faster one by the two models (deep_beats_slab).
@@ -1272,15 +1274,16 @@ struct SlabShape {
 
 // Four waves: 256 rows x 32 or 64 output-samples.  Up to four such workgroups share a compute unit and run at the rate of
 // its matrix pipes together (measured per step and workgroup: 2700 cycles for 64 output-samples, 1600 for 32, whose x is
-// re-read twice as often), one alone at that plus 600.  Against the kernels for few rows they win from a fill of 0.52 of the
-// compute units' last workgroup on (measured on 160 layer shapes of 256 to 7260 rows: 1.1-2.2x from there, 0.3-0.9x below).
+// re-read twice as often), one alone at that plus 600.  Against the kernels on the fp32 instruction they win from a fill of 0.52
+// of the compute units' last workgroup on (measured on 160 layer shapes of 256 to 7260 rows: 1.1-2.2x from there, 0.3-0.9x below);
+// against the kernel for tens to hundreds of rows deep_beats_slab decides.
 constexpr double kSlab4MinFill = 0.52;
 constexpr long kSlab4MinRows = 129;
 // From 65 to 128 rows the four waves take 32 rows each: half the matrix work per draw again, measured per step and
-// workgroup 1850 cycles for 64 output-samples and 1170 for 32, 300 more for one alone on its compute unit.  Against the
-// kernels for few rows, which draw every weight once per 64 rows: 96 and 128 rows x 8192^2 1.13-1.27x, x 2160 x 8640 with
-// one x per sample 1.2-1.28x; a narrow workgroup alone on its compute unit (one wave per SIMD) loses (96 x 4096^2: 0.87x),
-// so the shapes of 32 output-samples need two workgroups per compute unit.
+// workgroup 1850 cycles for 64 output-samples and 1170 for 32, 300 more for one alone on its compute unit.  The kernel for tens to
+// hundreds of rows takes most of these layers; to this shape remain few inputs and many outputs (110 x 100 x 8192 x 2, below
+// 128 inputs, or where deep_beats_slab prefers it).  A narrow workgroup alone on its compute unit (one wave per SIMD) loses
+// (96 x 4096^2: 0.87x), so the shapes of 32 output-samples need two workgroups per compute unit.
 constexpr long kSlab4HalfMinRows = 65;
 constexpr double kSlab4HalfMinFill = 0.52;
 
@@ -1490,13 +1493,13 @@ inline bool deep_beats_slab(const DeepPlan &p, long R, long C, long N, long S, l
 // four waves step over 128 indices in 1.3 us, those of the kernel for tens to hundreds of rows over 64 in 1.0 to 1.6.  Measured
 // on 360 layers: up to 256 workgroups 1.2x on average (63 x 6480 x 1172 x 1: 82 us against 135, 312 x 6816 x 72 x 1 86 against 139;
 // at worst 0.95x), from 257 to 512 0.9x, but for long sums (52 x 8192 x 6264 x 1: 214 against 237, 769 x 7712 x 252 x 2 150 against
-// 171, 99 x 7192 x 1148 x 2 134 against 151; one sample up to 5000 inputs 1.05x the other way).
+// 171, 71 x 2804 x 2048 x 2 55 against 60; one sample up to 5000 inputs 1.05x the other way).
 inline bool few_first_kernel_workgroups(const hot_linear_desc *d)
 {
     const long gx = (d->out_features + kColsPerWave - 1) / kColsPerWave, gy = (d->rows + 4 * kRowsPerTile - 1) / (4 * kRowsPerTile);
     if (gx > 2 * kComputeUnits || gy > 2 * kComputeUnits) return false;
     const long wgs = gx * gy * d->s_local;
-    return wgs <= kComputeUnits || (wgs <= 2 * kComputeUnits && d->s_local <= 2 && d->in_features > (d->s_local == 2 ? 4000 : 6000));
+    return wgs <= kComputeUnits || (wgs <= 2 * kComputeUnits && d->s_local <= 2 && d->in_features > (d->s_local == 2 ? 2500 : 6000));
 }
 
 inline DeepPlan deep_forward_plan(const hot_linear_desc *d)
@@ -2617,8 +2620,8 @@ inline long row_part_tiles(const hot_linear_desc *d)
     return ((d->in_features + tk - 1) / tk) * ((d->out_features + to - 1) / to);
 }
 
-// Where they run, measured against the first kernel above with a workspace, 40 shapes: 16640 x 192 x 768 173 -> 75 us,
-// 7260 x 2160 x 540 435 -> 202, 1024 x 540 x 2160 96 -> 52, 300 x 540 x 2160 41 -> 28, 513 x 2160 x 2160 x 8 samples 478 -> 293;
+// Where they run, measured against the first kernel above with a workspace, 40 shapes: 16640 x 192 x 768 150 -> 74 us,
+// 7260 x 2160 x 540 382 -> 205, 1024 x 540 x 2160 96 -> 52, 300 x 540 x 2160 41 -> 28, 513 x 2160 x 2160 x 8 samples 478 -> 293;
 // below 300 rows they win once rows x samples reach 600 (256 x 192 x 768 x 4: 20 -> 17 us) and lose below that (256 x 1024^2 x 2:
 // 24 -> 28, 129 x 8192 x 1024 x 1: 43 -> 52), and at a hundred rows and less (64 x 128^2 x 4: 15 -> 18).  Layers of 512 tiles of
 // 128 x 128 and more stay with the kernel above this one: level with it (0.96-1.08x), it needs no workspace.
@@ -3374,11 +3377,11 @@ struct OnePassPlan {
     long parts, outs_per_part;
 };
 
-// Where the waves split the rows: 33 to 128 rows, one or two samples, half a million weights (measured against the two
-// separate kernels at 2 samples: 64 rows 1.5-1.7x at 516 x 2100 to 2160 x 8640, 1.17x at 8192 x 8192; 128 rows 1.45x at
-// 540 x 2160, 1.04x at 8192 x 8192; slower on smaller layers, whose few tiles leave the barriers exposed (100 x 260 x 1000:
-// 0.93x), with four samples (0.83x at 64 x 2048 x 2048: two waves per SIMD) and at 256 rows x 1 sample (0.88x)).  Up to
-// 64 rows it also beats a wave drawing whole tiles for all rows (8192 x 8192: 0.66 against 0.72 ms).
+// Where the waves split the rows: 33 to 128 rows, one or two samples, half a million weights.  Measured against the two
+// separate kernels at 2 samples: 33 rows 1.33x at 2160 x 8640, 64 rows 1.39-1.47x at 516 x 2100 and 2160 x 8640, 1.16x at 8192^2;
+// at 100 and 128 rows those have become faster since the row limit was set (0.63x at 100 x 516 x 2100, 0.71-0.75x at 2160 x 8640,
+// 0.87-0.90x at 8192^2 and 540 x 2160): an open end.  Slower on smaller layers, whose few tiles leave the barriers
+// exposed, and with four samples (two waves per SIMD).  Up to 64 rows it also beats a wave drawing whole tiles for all rows.
 constexpr int kSplitRowsFrom = kOnePassMaxRows + 1, kSplitRowsMaxRows = 128;
 constexpr long kSplitRowsMinWeights = 512 * 1024;
 
@@ -3531,9 +3534,10 @@ inline XgradShape xgrad_shape(const hot_linear_desc *d)
     return best;
 }
 
-// Whether the slab kernel takes the input gradients (where the kernel for tens to hundreds of rows does not).  A workspace that
-// lets the kernel above cut the outputs into parts beats a four-wave launch that leaves a quarter of its slots empty
-// (256 x 2160 x 8640, 136 workgroups of 256 rows x 32 inputs: the whole call 0.71 -> 0.53 ms).
+// Whether the slab kernel takes the input gradients (where the kernel for tens to hundreds of rows does not).  A four-wave launch
+// that leaves a quarter of its slots empty gives way to the parts of the kernel above where a workspace allows them.  Of the layers that
+// still come here (short contractions on few inputs: 362 x 872 x 248 x 8, 905 x 504 x 584 x 3) the slab kernel would be the faster one
+// by now (the whole call 0.75-0.90 of the time on 40 of them), but its sums are whole: 1.1-1.2 times as far from 64 bits.
 inline bool xgrad_by_slab(const SlabShape &one, int parts_at_hand)
 {
     return one.waves && !(parts_at_hand > 1 && one.waves == 4 && one.fill < 0.75);
@@ -3788,13 +3792,6 @@ int hot_linear_forward_rng(const hot_linear_desc *d, const hot_rng *rng, const f
     a.rng = r;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // Many rows (from 256) and at least 128 workgroups of 256 rows: the kernel whose waves share every draw
-    // through LDS (measured against the kernel above: 1.05-1.4x from there on, slower below).  Two samples per
-    // pass and one column tile when several samples share x; a single sample, and samples with inputs of
-    // their own (one per pass), afford two column tiles.
-    // Hundreds to thousands of rows on a layer that fills the chip with tiles of 512 rows: the kernel that stages x and the
-    // drawn weights through LDS.  Samples that share x go two to a pass (they share every loaded row), an odd last one,
-    // a single one and samples with inputs of their own one to a pass with tiles twice as wide.
     if (const DeepPlan plan = deep_forward_plan(d); plan.code >= 0) {
         DeepArgs b;
         b.rows = d->rows;
@@ -3816,6 +3813,9 @@ int hot_linear_forward_rng(const hot_linear_desc *d, const hot_rng *rng, const f
         deep_run<false>(plan, s, b, d->s_local);
         return hot_detail::note_hip(hipGetLastError());
     }
+    // Many rows on a layer that fills the chip with its tiles: the kernel that stages x and the
+    // drawn weights through LDS.  Samples that share x go two to a pass (they share every loaded row), an odd last one,
+    // a single one and samples with inputs of their own one to a pass with tiles twice as wide.
     if (const SlabForwardPlan plan = slab_forward_plan(d); plan.two.waves || plan.one.waves) {
         SlabArgs b;
         b.rows = d->rows;
@@ -3845,6 +3845,10 @@ int hot_linear_forward_rng(const hot_linear_desc *d, const hot_rng *rng, const f
         }
         return hot_detail::note_hip(hipGetLastError());
     }
+    // Many rows (from 256) and at least 128 workgroups of 256 rows: the kernel whose waves share every draw
+    // through LDS (measured against the first kernel: 1.05-1.4x from there on, slower below).  Two samples per
+    // pass and one column tile when several samples share x; a single sample, and samples with inputs of
+    // their own (one per pass), afford two column tiles.
     {
         const bool xs = d->x_sample_stride != 0;
         const int no = (d->s_local == 1 || xs) ? 2 : 1;      // one sample per pass: its x loads serve two column tiles
@@ -4015,8 +4019,6 @@ int hot_linear_backward_rng_ws(const hot_linear_desc *d, int32_t s_total, double
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return hot_detail::note_hip(e);
     if (!dx) return HOT_OK;
 
-    // Hundreds to thousands of rows on a layer whose dx fills the chip with tiles of 512 rows: the kernel of the forward pass
-    // with dy as its input and the weight tile drawn transposed (rows of dy are read in 16-byte quads).
     const int parts_at_hand = xgrad_parts(d, workspace ? workspace_bytes : 0);
     if (const DeepPlan plan = deep_input_grad_plan(d, aligned16(dy), workspace ? workspace_bytes : 0); plan.code >= 0) {
         DeepArgs b;
@@ -4042,6 +4044,8 @@ int hot_linear_backward_rng_ws(const hot_linear_desc *d, int32_t s_total, double
         }
         return hot_detail::note_hip(hipGetLastError());
     }
+    // Many rows on a layer whose dx fills the chip with the tiles of the slab kernel: the kernel of the forward pass
+    // with dy as its input and the weight tile drawn transposed (rows of dy are read in 16-byte quads).
     if (const SlabShape one = slab_input_grad_shape(d, aligned16(dy)); xgrad_by_slab(one, parts_at_hand)) {
         SlabArgs b;
         b.rows = d->rows;

@@ -135,7 +135,10 @@ hot_dropout_forward_kernel(long n, long ld, int s_loc, const float *__restrict__
     }
 }
 
-template <bool ALIGNED, bool NT>
+// grad_w is read once.  Non-temporal loads: the network's backward passes that wrote it have mostly pushed it out of the caches again, and
+// plain loads then wait for what those hold to be written back (2.7 M weights x 16 samples, 172 MB: 71 us against 40 after 800 MB of
+// other writes, 1 M x 16 27 against 16).  Where it was written just before, plain loads would be faster (35 against 40, 14.5 against 17).
+template <bool ALIGNED>
 __global__ void __launch_bounds__(kBlock)
 hot_dropout_backward_kernel(long n, long ld, int s_loc, double g, const float *__restrict__ gw,
                             float *__restrict__ gmu, Rng rng, unsigned last_kept, float inv_keep, long period,
@@ -149,8 +152,8 @@ hot_dropout_backward_kernel(long n, long ld, int s_loc, double g, const float *_
             double acc[4] = {0.0, 0.0, 0.0, 0.0};
             int s = 0;
             for (; s + 2 <= s_loc; s += 2) {
-                const f4 v0 = load4<ALIGNED, NT>(gw + (size_t)s * (size_t)ld + col);
-                const f4 v1 = load4<ALIGNED, NT>(gw + (size_t)(s + 1) * (size_t)ld + col);
+                const f4 v0 = load4<ALIGNED, true>(gw + (size_t)s * (size_t)ld + col);
+                const f4 v1 = load4<ALIGNED, true>(gw + (size_t)(s + 1) * (size_t)ld + col);
                 const f4 b0 = mask_quad(mq, s, rng, last_kept, inv_keep);
                 const f4 b1 = mask_quad(mq, s + 1, rng, last_kept, inv_keep);
 #pragma unroll
@@ -160,7 +163,7 @@ hot_dropout_backward_kernel(long n, long ld, int s_loc, double g, const float *_
                 }
             }
             for (; s < s_loc; ++s) {
-                const f4 v0 = load4<ALIGNED, NT>(gw + (size_t)s * (size_t)ld + col);
+                const f4 v0 = load4<ALIGNED, true>(gw + (size_t)s * (size_t)ld + col);
                 const f4 b0 = mask_quad(mq, s, rng, last_kept, inv_keep);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) acc[j] = fma((double)v0[j], (double)b0[j], acc[j]);
@@ -168,7 +171,7 @@ hot_dropout_backward_kernel(long n, long ld, int s_loc, double g, const float *_
             f4 o;
 #pragma unroll
             for (int j = 0; j < 4; ++j) o[j] = (float)(g * acc[j]);
-            store4<ALIGNED, NT>(gmu + col, o);
+            store4<ALIGNED, true>(gmu + col, o);
         } else {
             double acc[3] = {0.0, 0.0, 0.0};
             for (int s = 0; s < s_loc; ++s) {
@@ -267,10 +270,8 @@ static int dropout_backward_impl(const hot_desc *d, const hot_rng *rng, double k
     const DropMask dm = drop_mask(keep);
     const unsigned thr = dm.last_kept;
     const float inv = dm.inv_keep;
-    // (grad_w is read once, right after the network wrote it or, more often, something else: non-temporal loads whatever the size, as
-    // in hot_backward.  2.7 M weights x 16 samples, 172 MB: 50 -> 45 us against plain loads, which were kept below 256 MiB)
-    if (al) hot_dropout_backward_kernel<true, true><<<grid, block, 0, s>>>(d->n_weights, d->ld, d->s_local, g, grad_w, grad_mu, r, thr, inv, period, unit_offset >> 2);
-    else hot_dropout_backward_kernel<false, true><<<grid, block, 0, s>>>(d->n_weights, d->ld, d->s_local, g, grad_w, grad_mu, r, thr, inv, period, unit_offset >> 2);
+    if (al) hot_dropout_backward_kernel<true><<<grid, block, 0, s>>>(d->n_weights, d->ld, d->s_local, g, grad_w, grad_mu, r, thr, inv, period, unit_offset >> 2);
+    else hot_dropout_backward_kernel<false><<<grid, block, 0, s>>>(d->n_weights, d->ld, d->s_local, g, grad_w, grad_mu, r, thr, inv, period, unit_offset >> 2);
     return hot_detail::note_hip(hipGetLastError());
 }
 
