@@ -228,7 +228,8 @@ int hot_last_hip_error(const hot_plan *plan);
  * gradients from 129 rows on (large layers, and those that a workspace cuts into row parts).  There a factor below about 1e-33 in
  * magnitude has pieces below bf16's normal range, which the instruction may flush.  An infinite factor, or one above the
  * largest bf16 number (3.39e38), gives NaN in the tiles that hot_linear_launch_shape tells of (2xx apart) and in the weight gradients of
- * large layers; elsewhere, bf16 pieces or not, it gives what fp32 products give.
+ * large layers; elsewhere, bf16 pieces or not, it gives what fp32 products give (where an input and a weight of one sum are both
+ * infinite, possibly an infinity instead of NaN).
  * Runs on the current device, asynchronous on `stream`.
  * Up to 32 rows, and wherever 64-row x 16-output tiles of all samples are at most one per compute unit, a wave draws the weights
  * it multiplies.  From 33 rows on (layers of at least 128 inputs) one wave holds all of a workgroup's 64 to 320 rows and draws every

@@ -1239,15 +1239,18 @@ def test_input_gradients_at_tens_to_hundreds_of_rows_are_no_less_accurate(hot, r
 MOST = torch.finfo(torch.float32).max
 
 
-@pytest.mark.parametrize("rows,k,o,s", [(40, 132, 4200, 2), (70, 256, 2100, 2), (300, 260, 1400, 2)])
-def test_forward_of_infinite_and_huge_inputs(hot, rows, k, o, s):
-    """Infinities, NaN and the type's lowest and highest values among the inputs give what fp32 products give."""
-    assert hot.hot_linear_kernel_shape(rows, k, o, s, 0, per_sample_x=True)
+# tiles of 32 outputs (two rows to a wave at the end) and of 64 (one), ragged
+@pytest.mark.parametrize("rows,k,o,s,width", [(40, 132, 4200, 2, 1), (70, 256, 2100, 2, 1), (300, 260, 1405, 2, 1), (129, 140, 2949, 3, 2),
+                                              (385, 508, 6371, 1, 2)])
+def test_forward_of_infinite_and_huge_inputs(hot, rows, k, o, s, width):
+    """Infinities, NaN and the type's lowest and highest values among the inputs, and an infinite weight, give what fp32 products give."""
+    assert hot.hot_linear_kernel_shape(rows, k, o, s, 0, per_sample_x=True) % 10 == width
     g, c = _deep_case(rows + o, o, k)
     x = torch.randn(s, rows, k, device=DEV, generator=g)
-    for i, v in enumerate((float("inf"), -float("inf"), float("nan"), -MOST, MOST)):
-        x[i % s, (7 * i + 3) % rows, (13 * i) % k] = v
-    x[1, rows - 1, 5], x[1, rows - 1, k - 1] = float("inf"), -float("inf")
+    for i in range(s):
+        for j, v in enumerate((float("inf"), -float("inf"), float("nan"), -MOST, MOST)):
+            x[i, 7 * j + 3 + i, 13 * j + i] = v
+    x[0, rows - 1, 5], x[0, rows - 1, k - 1] = float("inf"), -float("inf")
     rng, b_off = hot.hot_rng(seed=61, step=3, first_sample=1), (o * k + 3) // 4 * 4
     y = torch.full((s, rows, o), float("nan"), device=DEV)
     hot.hot_linear_forward_rng(rng, x, c["mu_w"], c["sigma_w"], c["mu_b"], c["sigma_b"], y, 0, b_off)
@@ -1255,6 +1258,11 @@ def test_forward_of_infinite_and_huge_inputs(hot, rows, k, o, s):
     for i in range(s):
         want = x[i].double() @ w[i].t() + b[i]
         _same_where_special(y[i], want, x[i].double().abs() @ w[i].abs().t() + b[i].abs())
+    # an infinite weight with finite inputs
+    x = torch.randn(s, rows, k, device=DEV, generator=g)
+    c["mu_w"][o - 1, 9] = -float("inf")
+    hot.hot_linear_forward_rng(rng, x, c["mu_w"], c["sigma_w"], c["mu_b"], c["sigma_b"], y, 0, b_off)
+    assert torch.equal(y[:, :, o - 1], -x[:, :, 9] * float("inf")) and bool(torch.isfinite(y[:, :, :o - 1]).all())
 
 
 def _same_where_special(got, want, magnitude):
