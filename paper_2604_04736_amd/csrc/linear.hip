@@ -137,7 +137,6 @@ hot_linear_forward_kernel(LinearArgs a)
     const long quad_row = a.weight_quad0 + ((o_ok ? o : 0) * K >> 2);
     // grid z: the samples in chunks of s_chunk (a multiple of ST)
     const int s_lo = (int)blockIdx.z * a.s_chunk, s_hi = s_lo + a.s_chunk < a.s_loc ? s_lo + a.s_chunk : a.s_loc;
-    const float *const x = a.x + (size_t)s_lo * (size_t)a.x_sample_stride;       // (not XS: of all this workgroup's samples)
 
     for (int s0 = s_lo; s0 < s_hi; s0 += ST) {
         Acc16x16 mm[ST][RB];
@@ -155,7 +154,7 @@ hot_linear_forward_kernel(LinearArgs a)
 #pragma unroll
                     for (int rb = 0; rb < RB; ++rb) {
                         const long row = r0 + kRowsPerTile * rb + n;
-                        xa[rb][h] = (row < R && k + 4 * h < K) ? load4<true, false>(x + row * a.ldx + k + 4 * h)
+                        xa[rb][h] = (row < R && k + 4 * h < K) ? load4<true, false>(a.x + row * a.ldx + k + 4 * h)
                                                                 : f4{0.0f, 0.0f, 0.0f, 0.0f};
                     }
                 }
@@ -1551,8 +1550,8 @@ void linear_go_st(int st, dim3 grid, int waves, hipStream_t s, const LinearArgs 
 template <int RB>
 void linear_go(int st, dim3 grid, int waves, hipStream_t s, const LinearArgs &a)
 {
-    // (a workgroup with one sample has one input: 129 x 3648 x 540 x 1 51 -> 47 us)
-    if (a.x_sample_stride != 0 && a.s_chunk > 1) linear_go_st<RB, true>(st, grid, waves, s, a);
+    // (one sample has one input: 129 x 3648 x 540 x 1 51 -> 47 us)
+    if (a.x_sample_stride != 0 && a.s_loc > 1) linear_go_st<RB, true>(st, grid, waves, s, a);
     else linear_go_st<RB, false>(st, grid, waves, s, a);
 }
 
