@@ -1503,12 +1503,12 @@ inline double slab_time(const SlabShape &h, int st, long contract)
 }
 
 // Whether the kernel for tens to hundreds of rows takes a layer that the slab kernel could take (slab: that one's time, 0: it could
-// not).  Of 205 layers where either runs the models leave one more than 6 % behind the faster (245 x 644 x 6107 x 2 samples: 42 us
-// against 38); with the kernel for fewer rows up to 704 rows always, layers of few inputs and many outputs lost
-// (493 x 236 x 8192 x 4: 94 against 67, 658 x 192 x 8048 x 4 134 against 74).
+// not), unless the models are too close to tell.  Of 1000 layers where either runs they leave three more than 6 % behind the faster
+// (245 x 644 x 6107 x 2 samples: 42 us against 38); with the kernel for fewer rows up to 704 rows always, layers of few inputs and many
+// outputs lost (493 x 236 x 8192 x 4: 94 against 67, 658 x 192 x 8048 x 4 134 against 74).
 inline bool deep_beats_slab(const DeepPlan &p, long R, long C, long N, long S, long inputs, double slab)
 {
-    return p.code >= 0 && (slab == 0.0 || deep_time(p, R, C, N, S, inputs) < slab);
+    return p.code >= 0 && (slab == 0.0 || deep_time(p, R, C, N, S, inputs) < 0.96 * slab);
 }
 
 // Whether a forward call is left to the first kernel above: where that has at most one workgroup (64 rows x 16 outputs, one

@@ -1067,7 +1067,7 @@ DEEP_INPUT_GRAD = [(65, 256, 1588, 1, 0, 0), (65, 324, 56, 1, 1, 0), (65, 260, 1
                    (255, 408, 6196, 2, 0, 0), (255, 832, 2088, 1, 1, 7000082), (300, 400, 8316, 1, 0, 1000041), (255, 408, 8240, 2, 0, 0),
                    (129, 304, 520, 2, 1, 1000021), (65, 392, 36, 1, 1, 4000021), (129, 292, 2796, 1, 1, 1000041),
                    (65, 412, 344, 3, 1, 4000041), (129, 292, 2492, 2, 1, 1000061), (129, 904, 164, 3, 1, 8000061),
-                   (129, 288, 2760, 3, 1, 1000062), (193, 304, 1380, 3, 1, 1000081), (385, 508, 6328, 1, 1, 1000082),
+                   (129, 288, 2760, 3, 1, 1000062), (193, 304, 1380, 3, 1, 1000081), (385, 508, 6328, 1, 1, 0), (193, 628, 4104, 3, 0, 1000082),
                    (385, 640, 396, 3, 1, 5000082), (257, 256, 1852, 3, 1, 1000101), (193, 352, 5516, 3, 0, 1021082),
                    (257, 488, 3072, 3, 1, 1021101), (257, 516, 5388, 2, 0, 1041101), (129, 604, 2056, 1, 1, 5000062)]
 
@@ -1241,7 +1241,7 @@ MOST = torch.finfo(torch.float32).max
 
 # tiles of 32 outputs (two rows to a wave at the end) and of 64 (one), ragged
 @pytest.mark.parametrize("rows,k,o,s,width", [(40, 132, 4200, 2, 1), (70, 256, 2100, 2, 1), (300, 260, 1405, 2, 1), (129, 140, 2949, 3, 2),
-                                              (385, 508, 6371, 1, 2)])
+                                              (385, 628, 6196, 1, 2)])
 def test_forward_of_infinite_and_huge_inputs(hot, rows, k, o, s, width):
     """Infinities, NaN and the type's lowest and highest values among the inputs, and an infinite weight, give what fp32 products give."""
     assert hot.hot_linear_kernel_shape(rows, k, o, s, 0, per_sample_x=True) % 10 == width
