@@ -1295,3 +1295,62 @@ def test_backward_of_infinite_and_huge_gradients(hot):
     P = [dy[i].double().t() @ x[i].double() for i in range(s)]
     mag = [dy[i].double().abs().t() @ x[i].double().abs() for i in range(s)]
     _same_where_special(gmu, sum(P), sum(mag))
+
+
+# The kernels that multiply fp16 pieces: the contraction of the slab kernel's launch shapes from 80 on (76: bf16 pieces), forward and input
+# gradients, weight gradients in tiles (from 512 rows on) and in row parts (256 rows to a sum and more), tile edges among the sizes.
+F16_FORWARD = [(1030, 76, 4100, 2, False), (1030, 80, 4100, 2, False), (1030, 84, 4100, 2, True), (2050, 532, 2052, 2, False), (7260, 100, 540, 2, True),
+               (1025, 300, 9000, 1, True), (300, 100, 7001, 2, False), (300, 100, 7001, 1, True), (513, 260, 8190, 3, False)]
+F16_BACKWARD = [(1030, 4096, 76, 2), (1030, 4096, 80, 2), (1030, 4100, 300, 2), (2050, 2052, 532, 2), (7260, 540, 100, 2), (3000, 260, 212, 1),
+                (300, 7004, 100, 2), (511, 3000, 3004, 1), (512, 3000, 3004, 2)]
+
+
+@pytest.mark.parametrize("rows,k,o,s,own", F16_FORWARD)
+def test_forward_from_fp16_pieces_over_many_decades(hot, rows, k, o, s, own):
+    """Values of one block of sixteen indices within a few decades, blocks eight decades apart (the weights the other way, so that every
+    block counts), rows and outputs twenty decades apart.  Bound: 2^-22 left out, 2^-23 of cutting per factor, and the roundings of the
+    accumulations, which grow with the blocks added up."""
+    g, c = _deep_case(rows + o, o, k)
+    f = 10.0 ** (8.0 * torch.rand((k + 15) // 16, device=DEV, generator=g) - 4.0).repeat_interleave(16)[:k]
+    x = torch.randn(*((s, rows, k) if own else (rows, k)), device=DEV, generator=g) * f
+    x = x * 10.0 ** (20.0 * torch.rand(rows, 1, device=DEV, generator=g) - 10.0)
+    x[..., rows // 2, :] = 0.0
+    x[..., 16:32] = x[..., 16:32] * (torch.rand(16, device=DEV, generator=g) < 0.5)
+    per_out = 10.0 ** (20.0 * torch.rand(o, 1, device=DEV, generator=g) - 10.0)
+    c["mu_w"], c["sigma_w"] = c["mu_w"] / f * per_out, c["sigma_w"] / f * per_out
+    c["mu_b"], c["sigma_b"] = c["mu_b"] * 0.0, c["sigma_b"] * 1e-30
+    rng, b_off = hot.hot_rng(seed=71, step=2, first_sample=1), (o * k + 3) // 4 * 4
+    y = torch.full((s, rows, o), float("nan"), device=DEV)
+    hot.hot_linear_forward_rng(rng, x.contiguous(), c["mu_w"].contiguous(), c["sigma_w"].contiguous(), c["mu_b"], c["sigma_b"], y, 0, b_off)
+    w, b = _materialised(hot, c, s, rng, 0, b_off)
+    for i in range(s):
+        xi = (x[i] if own else x).double()
+        worst = float(((y[i] - (xi @ w[i].t() + b[i])).abs() / (xi.abs() @ w[i].abs().t() + b[i].abs())).max())
+        assert worst <= 2.0 ** -22 + 2 * 2.0 ** -23 + (k // 16 + 4) * 2.0 ** -24, worst
+
+
+@pytest.mark.parametrize("rows,k,o,s", F16_BACKWARD)
+def test_backward_from_fp16_pieces_over_many_decades(hot, rows, k, o, s):
+    """The same for the input gradients (blocks of outputs) and the weight gradients (blocks of rows, x and dy against each other)."""
+    g, c = _deep_case(rows + o, o, k)
+    f = 10.0 ** (8.0 * torch.rand((rows + 15) // 16, device=DEV, generator=g) - 4.0).repeat_interleave(16)[:rows, None]
+    h = 10.0 ** (8.0 * torch.rand((o + 15) // 16, device=DEV, generator=g) - 4.0).repeat_interleave(16)[:o]
+    x = torch.randn(s, rows, k, device=DEV, generator=g) * f * 10.0 ** (10.0 * torch.rand(k, device=DEV, generator=g) - 5.0)
+    dy = torch.randn(s, rows, o, device=DEV, generator=g) / f * h
+    x[:, rows // 2:rows // 2 + 40] = 0.0
+    c["mu_w"], c["sigma_w"] = (c["mu_w"] / h[:, None]).contiguous(), (c["sigma_w"] / h[:, None]).contiguous()
+    rng = hot.hot_rng(seed=73, step=2, first_sample=1)
+    dx = torch.full((s, rows, k), float("nan"), device=DEV)
+    gmu, gsig = _backward(hot, rng, x, dy, c, dx, _workspace(hot, rows, k, o, s), s)
+    w, _ = _materialised(hot, c, s, rng, 0, o * k)
+    eps = [(w[i] - c["mu_w"].double()) / c["sigma_w"].double() for i in range(s)]
+    for i in range(s):
+        worst = float(((dx[i] - dy[i].double() @ w[i]).abs() / (dy[i].double().abs() @ w[i].abs())).max())
+        assert worst <= 2.0 ** -22 + 2 * 2.0 ** -23 + (o // 16 + 4) * 2.0 ** -24, worst
+    P = [dy[i].double().t() @ x[i].double() for i in range(s)]
+    mag = [dy[i].double().abs().t() @ x[i].double().abs() for i in range(s)]
+    bound = 2.0 ** -22 + 2 * 2.0 ** -23 + (rows // 16 + 4) * 2.0 ** -24
+    assert float(((gmu - sum(P)).abs() / sum(mag)).max()) <= bound
+    # (eps is recovered from the rounded weights, up to 2^-24 |w| / sigma and what its own product rounds)
+    wide = sum(m * (bound * e.abs() + 2.0 ** -23 * w[i].abs() / c["sigma_w"].double()) for i, (m, e) in enumerate(zip(mag, eps)))
+    assert bool(((gsig - sum(p * e for p, e in zip(P, eps))).abs() <= wide).all())
