@@ -507,13 +507,13 @@ __device__ __forceinline__ void split8_bf16(const f4 &a, const f4 &b, bf8 &p1, b
 // block's largest or smaller keeps fewer than its 24 bits, its error stays below 2^-38 of that largest value.
 // Distance from 64 bits against the six bf16 products, normal values (8000 x k x 2048, 8000 x 4096 x o): sums over 192 indices
 // 0.83, 128 0.89, 96 0.93, 64 1.03, 32 1.3 (the instruction adds products of 22 bits with less room than products of 16), 540 and more
-// 0.72-0.8: half as many roundings.  Hence kF16MinSum; in row parts kF16MinRowSum rows to a sum of four waves (64 per wave; 1.09
-// where a wave adds up 16 rows).  Time: 7260 x 540 x 2160 x 2 input gradients, 2160 to 540, 306 -> 184 us, forward 225 -> 194;
+// 0.72-0.8: half as many roundings.  Hence kF16MinSum.  In row parts the scales and the longer end of a sum pay from about a thousand rows to
+// a sum of four waves on (1452 rows 250 -> 199 us, 2000 141 -> 134; 554 rows 56 -> 64, 594 69 -> 66 one way round and 64 -> 69 the other).  Time: 7260 x 540 x 2160 x 2 input gradients, 2160 to 540, 306 -> 184 us, forward 225 -> 194;
 // 1024 x 8192^2 x 2 forward 1429 -> 1325, input gradients 1490 -> 1190, weight gradients 1790 -> 1520; row parts of 7260 x 540 x
-// 2160 x 2 250 -> 199, of 300 x 2160 x 8640 x 2 341 -> 277.  A fourth product x2 w2 costs 5-10 % and takes 3-5 % off the error of short sums only.
+// 2160 x 2 250 -> 199.  A fourth product x2 w2 costs 5-10 % and takes 3-5 % off the error of short sums only.
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 
-constexpr long kF16MinSum = 80, kF16MinRowSum = 256;
+constexpr long kF16MinSum = 80, kF16MinRowSum = 1024;
 constexpr float kF16Limit = 65000.0f;      // above it a scaled factor gets a new scale (the largest fp16 number is 65504)
 constexpr float kF16Low = 4.0f;              // so does a block whose largest scaled magnitude lies below it
 constexpr int kF16Raise = 32;                // see F16Scale

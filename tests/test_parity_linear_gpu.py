@@ -1298,7 +1298,7 @@ def test_backward_of_infinite_and_huge_gradients(hot):
 
 
 # The kernels that multiply fp16 pieces: the contraction of the slab kernel's launch shapes from 80 on (76: bf16 pieces), forward and input
-# gradients, weight gradients in tiles (from 512 rows on) and in row parts (256 rows to a sum and more), tile edges among the sizes.
+# gradients, weight gradients in tiles (from 512 rows on) and in row parts (1024 rows to a sum and more), tile edges among the sizes.
 F16_FORWARD = [(1030, 76, 4100, 2, False), (1030, 80, 4100, 2, False), (1030, 84, 4100, 2, True), (2050, 532, 2052, 2, False), (7260, 100, 540, 2, True),
                (1025, 300, 9000, 1, True), (300, 100, 7001, 2, False), (300, 100, 7001, 1, True), (513, 260, 8190, 3, False)]
 F16_BACKWARD = [(1030, 4096, 76, 2), (1030, 4096, 80, 2), (1030, 4100, 300, 2), (2050, 2052, 532, 2), (7260, 540, 100, 2), (3000, 260, 212, 1),
