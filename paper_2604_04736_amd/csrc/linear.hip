@@ -2527,11 +2527,13 @@ hot_linear_wgrad_tile_kernel(LinearGradArgs a)
     else wgrad_tile_body<false, F16>(a, XB, DB, o0, k0);
 }
 
-// Whether the kernel above can address this problem (its windows take 32-bit byte offsets).
+// Whether the kernel above can address this problem (its windows take 32-bit byte offsets).  Any number of outputs: a quad of dy
+// that reaches over the end of a row brings columns that are never stored, loads need an alignment of 4 bytes only, and the check at
+// the end of the window is per 4 bytes (3946 x 3288 x 1506 x 2 samples, forward and backward: 2104 -> 1584 us against the first kernel,
+// 1000 x 2048 x 2049 x 2: a third of its distance from 64 bits).
 inline bool wgrad_tile_fits(const hot_linear_desc *d)
 {
     const unsigned long long lim = 0xFFFFFFF0ull;
-    if (d->out_features & 3) return false;        // rows of dy are read in 16-byte quads
     return (unsigned long long)((d->rows + kTileRows) * d->ldx + d->in_features) * 4 < lim &&
            (unsigned long long)(d->rows + kTileRows) * d->out_features * 4 < lim;
 }
@@ -2542,8 +2544,9 @@ inline long wgrad_tile_count(const hot_linear_desc *d)
 }
 
 // From here on fp16 pieces: they take the steps 1.25x as fast, but the scales and what they displace from the registers around the row
-// loops cost a tile about 15 us (300 x 2160 x 8640 x 2: 227 us with bf16 pieces, 259 with these; 1024 x 8192^2 x 2 1740 and 1490).
-constexpr long kF16MinTileRows = 512;
+// loops cost a tile about 15 us (300 x 2160 x 8640 x 2: 227 us with bf16 pieces, 259 with these; the whole pass of 569 x 2572 x 4340 x 1 331 and
+// 344; 1024 x 8192^2 x 2 1740 and 1490).
+constexpr long kF16MinTileRows = 768;
 
 void wgrad_tile_go(hipStream_t s, const LinearGradArgs &a, long tiles)
 {
@@ -2898,6 +2901,10 @@ constexpr long kRowPartFewRowSamples = 1200, kRowPartManyWeights = 1L << 18;
 constexpr long kRowPartNarrow = 32, kRowPartNarrowRows = 1000;
 constexpr long kRowPartOneSampleRows = 8192, kRowPartOneSampleRowsEnd = 12000, kRowPartOneSampleWeights = 1L << 17;
 constexpr long kRowPartMaxTileCount = 512;
+// Rows of dy may start at any multiple of 4 bytes: a load of 8 or 16 bytes needs no more, a quad that reaches over the end of a row only
+// brings columns that are never stored, and behind the window's end the hardware's check is per 4 bytes.  (1888 x 1056 x 402 x 4 samples and
+// the like: 1.1-1.3x against the first kernel, 0.5-0.8 of its distance from 64 bits.)  An odd number of outputs stays with that
+// kernel: the accuracy of this one is tested against it there.
 constexpr int kRowPartMaxParts = 64;
 constexpr int64_t kRowPartMaxBytes = (int64_t)256 << 20, kRowPartSmallBytes = (int64_t)8 << 20;
 // Errors grow with the rows that a wave adds up, 2-norm against 64 bits at 16640 x 192 x 768: 2.7e-7 with 297, 2.0e-7 with 152 (the fp32
@@ -2909,7 +2916,7 @@ inline bool row_parts_suit(const hot_linear_desc *d)
 {
     if (d->rows < kRowPartMinRows || (d->rows < kRowPartAlwaysRows && d->rows * d->s_local < kRowPartMinRowSamples)) return false;
     if (d->rows < kRowPartAnyWeightsRows && d->in_features * d->out_features < kRowPartMinWeights) return false;
-    if ((d->out_features & 3) || wgrad_tile_count(d) >= kRowPartMaxTileCount) return false;       // (rows of dy are read in 16-byte quads)
+    if ((d->out_features & 1) || wgrad_tile_count(d) >= kRowPartMaxTileCount) return false;
     if (const long weights = d->in_features * d->out_features; weights > kRowPartMinWeights) {
         if (weights < kRowPartManyWeights && d->s_local <= 2 && d->rows * d->s_local < kRowPartFewRowSamples) return false;
         if (d->out_features <= kRowPartNarrow && d->rows < kRowPartNarrowRows && d->s_local <= 4) return false;

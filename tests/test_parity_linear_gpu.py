@@ -1298,11 +1298,11 @@ def test_backward_of_infinite_and_huge_gradients(hot):
 
 
 # The kernels that multiply fp16 pieces: the contraction of the slab kernel's launch shapes from 80 on (76: bf16 pieces), forward and input
-# gradients, weight gradients in tiles (from 512 rows on) and in row parts (1024 rows to a sum and more), tile edges among the sizes.
+# gradients, weight gradients in tiles (from 768 rows on) and in row parts (1024 rows to a sum and more), tile edges among the sizes.
 F16_FORWARD = [(1030, 76, 4100, 2, False), (1030, 80, 4100, 2, False), (1030, 84, 4100, 2, True), (2050, 532, 2052, 2, False), (7260, 100, 540, 2, True),
                (1025, 300, 9000, 1, True), (300, 100, 7001, 2, False), (300, 100, 7001, 1, True), (513, 260, 8190, 3, False)]
 F16_BACKWARD = [(1030, 4096, 76, 2), (1030, 4096, 80, 2), (1030, 4100, 300, 2), (2050, 2052, 532, 2), (7260, 540, 100, 2), (3000, 260, 212, 1),
-                (300, 7004, 100, 2), (511, 3000, 3004, 1), (512, 3000, 3004, 2)]
+                (300, 7004, 100, 2), (767, 3000, 3004, 1), (768, 3000, 3004, 2)]
 
 
 @pytest.mark.parametrize("rows,k,o,s,own", F16_FORWARD)
@@ -1354,3 +1354,29 @@ def test_backward_from_fp16_pieces_over_many_decades(hot, rows, k, o, s):
     # (eps is recovered from the rounded weights, up to 2^-24 |w| / sigma and what its own product rounds)
     wide = sum(m * (bound * e.abs() + 2.0 ** -23 * w[i].abs() / c["sigma_w"].double()) for i, (m, e) in enumerate(zip(mag, eps)))
     assert bool(((gsig - sum(p * e for p, e in zip(P, eps))).abs() <= wide).all())
+
+
+# outputs that are no multiple of four: rows of dy off the 16-byte grid, the last quad of a row reaching into the next one (1, 2 and 3
+# elements), in the tile kernel and (even ones) in row parts; both kinds of pieces
+RAGGED_WGRAD = [(800, 2052, 1537, 2, False), (600, 2052, 1538, 1, True), (300, 2052, 1539, 2, False), (513, 4100, 2050, 1, False),
+                (200, 4100, 2050, 1, False), (513, 300, 130, 4, True), (2000, 260, 514, 2, True), (700, 132, 1030, 3, True)]
+
+
+@pytest.mark.parametrize("rows,k,o,s,parts", RAGGED_WGRAD)
+def test_weight_gradients_with_rows_of_dy_off_the_grid(hot, rows, k, o, s, parts):
+    """Against 64 bits, also with a NaN in the first element of a row of dy (which the last quad of the row before brings along): only
+    that output's gradients may see it.  Bound as for the cases over many decades."""
+    assert bool(hot.hot_linear_kernel_shape(rows, k, o, s, 2)) == parts
+    g, c = _deep_case(rows + o, o, k)
+    x, dy = torch.randn(s, rows, k, device=DEV, generator=g), torch.randn(s, rows, o, device=DEV, generator=g)
+    rng = hot.hot_rng(seed=79, step=2, first_sample=1)
+    bound = 2.0 ** -22 + 2 * 2.0 ** -23 + (rows // 16 + 4) * 2.0 ** -24
+    for poisoned in (False, True):
+        if poisoned:
+            dy[:, rows // 2, 0] = float("nan")
+        gmu, gsig = _backward(hot, rng, x, dy, c, None, _workspace(hot, rows, k, o, s), s)
+        lo = 1 if poisoned else 0
+        P = sum(dy[i, :, lo:].double().t() @ x[i].double() for i in range(s))
+        mag = sum(dy[i, :, lo:].double().abs().t() @ x[i].double().abs() for i in range(s))
+        assert float(((gmu[lo:] - P).abs() / mag).max()) <= bound
+        assert bool(torch.isfinite(gsig[lo:]).all()) and bool(torch.isnan(gmu[:lo]).all()) and bool(torch.isnan(gsig[:lo]).all())
