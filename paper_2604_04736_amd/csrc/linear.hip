@@ -2217,6 +2217,59 @@ constexpr int kTileRows = 16;         // rows per step
 constexpr int kTurnPitch = 36;        // floats per row of a wave's 32 x 32 block on its way out (16-byte aligned rows)
 
 
+// Those of four sums over the rows r_lo .. r_hi - 1 that the pieces left as NaN, from fp32 products (see deep_plain_sum).
+__device__ __forceinline__ void row_parts_plain_sums(const LinearGradArgs &a, int s, long o, long k, long r_lo, long r_hi, float *p)
+{
+    const float *x = a.x + (size_t)s * (size_t)a.x_sample_stride + (size_t)k;
+    const float *dy = a.dy + (size_t)s * (size_t)a.rows * (size_t)a.out_features + (size_t)o;
+#pragma unroll 1
+    for (int c = 0; c < 4; ++c) {
+        if (p[c] == p[c]) continue;
+        float sum = 0.0f;
+#pragma unroll 1
+        for (long r = r_lo; r < r_hi && sum == sum; ++r) sum = __builtin_fmaf(dy[(size_t)r * (size_t)a.out_features], x[(size_t)r * (size_t)a.ldx + (size_t)c], sum);
+        p[c] = sum;
+    }
+}
+
+// The weight gradients (o, k .. k + 3) that the tile kernel left as NaN, all samples again from fp32 products.
+__device__ __forceinline__ void wgrad_tile_plain(const LinearGradArgs &a, long o, long k)
+{
+    const long at = o * a.in_features + k;
+    f4 om = load4<true, false>(a.gmu_w + at), os = load4<true, false>(a.gsig_w + at);
+    float again[4], gm[4] = {0.0f, 0.0f, 0.0f, 0.0f}, gs[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    bool any = false;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const bool bad = om[c] != om[c] || os[c] != os[c];
+        any |= bad;
+        again[c] = bad ? __builtin_nanf("") : 0.0f;       // (what row_parts_plain_sums takes for a sum to form)
+    }
+    if (!any) return;
+#pragma unroll 1
+    for (int s = 0; s < a.s_loc; ++s) {
+        float p[4] = {again[0], again[1], again[2], again[3]};
+        row_parts_plain_sums(a, s, o, k, 0, a.rows, p);
+        const f4 e = eps_quad(a.weight_quad0 + (at >> 2), s, a.rng);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            gm[c] += p[c];
+            gs[c] = __builtin_fmaf(p[c], e[c], gs[c]);
+        }
+    }
+    const f4 m4 = load4<true, false>(a.mu_w + at), sd4 = load4<true, false>(a.sigma_w + at);
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+        if (again[c] != again[c]) {
+            float pm, ps;
+            finish_pair(gm[c], gs[c], m4[c], sd4[c], (float)a.g, (float)a.k, pm, ps);
+            om[c] = pm;
+            os[c] = ps;
+        }
+    store4<true, false>(a.gmu_w + at, om);
+    store4<true, false>(a.gsig_w + at, os);
+}
+
 // WHOLE: every 32 x 32 block of the workgroup's tile reaches into the layer (no block is skipped, no column masked).
 // XB, DB: the four buffers of 16 rows x 128 columns of x and of dy.
 // F16: two fp16 pieces to a factor, else three bf16 pieces.
@@ -2386,6 +2439,7 @@ __device__ __forceinline__ void wgrad_tile_body(const LinearGradArgs &a, lds_flo
     // pairs before left in the gradient arrays (the same thread holds the same weights every time); the last pair
     // applies the scale and the KL part.
     float gb_m[2] = {0.0f, 0.0f}, gb_s[2] = {0.0f, 0.0f};
+    unsigned long long special = 0;          // the lanes that met a NaN
     lds_float *const mine = XB[wave];        // a buffer per wave for turning its blocks on their way out
     for (int s0 = 0; s0 < a.s_loc; s0 += 2) {
         const bool two = s0 + 1 < a.s_loc, first = s0 == 0, last = s0 + 2 >= a.s_loc;
@@ -2462,6 +2516,8 @@ __device__ __forceinline__ void wgrad_tile_body(const LinearGradArgs &a, lds_flo
                         }
                         store4<true, false>(a.gmu_w + at, om);
                         store4<true, false>(a.gsig_w + at, os);
+                        const f4 both = om + os;       // (NaN wherever either is; infinities of two signs only cost a look)
+                        special |= __builtin_amdgcn_ballot_w64(!(both[0] == both[0] && both[1] == both[1] && both[2] == both[2] && both[3] == both[3]));
                     }
                 }
             }
@@ -2482,6 +2538,15 @@ __device__ __forceinline__ void wgrad_tile_body(const LinearGradArgs &a, lds_flo
             }
         }
         everything_arrived_then_barrier();       // (the buffers go back to the rows of the next pair)
+    }
+    // An infinite factor, and one whose pieces overflow, leaves NaN where fp32 products give infinity or a number (in a loop of its own, so
+    // that no accumulator lives through it; the thread that stored a quad looks at it again).
+    if (special) {
+#pragma unroll 1
+        for (int n = 0; n < 16; ++n) {
+            const long oo = o0 + 64 * wo + 32 * (n >> 2 & 1) + 8 * (n & 3) + (lane >> 3), k = k0 + 64 * wk + 32 * (n >> 3) + 4 * (lane & 7);
+            if (oo < O && k < K) wgrad_tile_plain(a, oo, k);
+        }
     }
     if (bias_wave && half == 0) {
 #pragma unroll
@@ -2590,21 +2655,6 @@ struct Floats<4> {
 
 // floats of one part's share of the workspace: per sample the weights, then the biases (a multiple of four, so that quads stay aligned)
 inline __host__ __device__ long row_part_floats(long K, long O, int s_loc) { return (O * K + ((O + 3) & ~3L)) * s_loc; }
-
-// Those of four sums over the rows r_lo .. r_hi - 1 that the bf16 pieces left as NaN, from fp32 products (see deep_plain_sum).
-__device__ __forceinline__ void row_parts_plain_sums(const LinearGradArgs &a, int s, long o, long k, long r_lo, long r_hi, float *p)
-{
-    const float *x = a.x + (size_t)s * (size_t)a.x_sample_stride + (size_t)k;
-    const float *dy = a.dy + (size_t)s * (size_t)a.rows * (size_t)a.out_features + (size_t)o;
-#pragma unroll 1
-    for (int c = 0; c < 4; ++c) {
-        if (p[c] == p[c]) continue;
-        float sum = 0.0f;
-#pragma unroll 1
-        for (long r = r_lo; r < r_hi && sum == sum; ++r) sum = __builtin_fmaf(dy[(size_t)r * (size_t)a.out_features], x[(size_t)r * (size_t)a.ldx + (size_t)c], sum);
-        p[c] = sum;
-    }
-}
 
 // F16: two fp16 pieces to a factor, else three bf16 pieces.
 template <bool XBIG, bool F16>

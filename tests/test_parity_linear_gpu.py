@@ -1380,3 +1380,19 @@ def test_weight_gradients_with_rows_of_dy_off_the_grid(hot, rows, k, o, s, parts
         mag = sum(dy[i, :, lo:].double().abs().t() @ x[i].double().abs() for i in range(s))
         assert float(((gmu[lo:] - P).abs() / mag).max()) <= bound
         assert bool(torch.isfinite(gsig[lo:]).all()) and bool(torch.isnan(gmu[:lo]).all()) and bool(torch.isnan(gsig[:lo]).all())
+
+
+@pytest.mark.parametrize("rows,k,o,s", [(800, 2052, 1537, 2), (300, 2052, 1539, 3)])
+def test_tile_weight_gradients_of_infinite_and_huge_values(hot, rows, k, o, s):
+    """Infinities, NaN and the type's extremes in x and dy, in the tile kernel (both kinds of pieces, an odd last sample): what fp32 products give."""
+    assert hot.hot_linear_kernel_shape(rows, k, o, s, 2) == 0
+    g, c = _deep_case(rows + o, o, k)
+    x, dy = torch.randn(s, rows, k, device=DEV, generator=g), torch.randn(s, rows, o, device=DEV, generator=g)
+    for j, v in enumerate((float("inf"), float("nan"), -float("inf"), MOST / 1024, -MOST)):
+        dy[0, 59 * j + 3, 131 * j] = v
+        x[s - 1, 47 * j + 9, 97 * j + 2] = v
+    x[0, 59 * 4 + 3] *= 0.1           # (so that what the largest values give stays finite)
+    dy[s - 1, 47 * 4 + 9] *= 0.1
+    gmu, _ = _backward(hot, hot.hot_rng(seed=89, step=3, first_sample=1), x, dy, c, None, _workspace(hot, rows, k, o, s), s)
+    P = [dy[i].double().t() @ x[i].double() for i in range(s)]
+    _same_where_special(gmu, sum(P), sum(dy[i].double().abs().t() @ x[i].double().abs() for i in range(s)))
