@@ -21,8 +21,8 @@
 //             hot_linear_forward_rows_kernel   from 256 rows: four waves x 64 rows share every draw through LDS; where neither of the
 //                                              next two runs (fewer than 128 inputs, operands beyond their 32-bit offsets)
 //             hot_linear_slab_kernel           many rows on layers that fill the chip: 256 to 1024 rows x 32 to 128 outputs per
-//                                              workgroup, x loaded straight into LDS, the drawn weights shared through it, bf16 pieces
-//                                              on v_mfma_f32_32x32x16_bf16 (128 rows: v_mfma_f32_32x32x2_f32); also input gradients
+//                                              workgroup, x loaded straight into LDS, the drawn weights shared through it, pieces on
+//                                              v_mfma_f32_32x32x16_f16 or _bf16 (128 rows: v_mfma_f32_32x32x2_f32); also input gradients
 //             hot_linear_deep_kernel           tens to hundreds of rows, and more where it is faster: a wave holds all rows of its
 //                                              workgroup, the waves split the contraction; also the input gradients
 //   backward  hot_linear_wgrad_kernel          weight and bias gradients (per-sample G never stored); variants for
@@ -31,7 +31,7 @@
 //             hot_linear_wgrad_tile_kernel     the same for large layers: 128 inputs x 128 outputs per workgroup, rows of
 //                                              x and dy loaded straight into LDS
 //             hot_linear_wgrad_row_parts_kernel  the same for smaller layers and many rows, with a workspace: the rows cut into
-//                                              parts, bf16 pieces straight from memory, no LDS before the last sum
+//                                              parts, pieces straight from memory, no LDS before the last sum
 //             hot_linear_xgrad_kernel          input gradients where few workgroups are left to it: up to 16 waves split a sum
 //             hot_linear_xgrad_rows_kernel     input gradients from 256 rows: shared draws, as in the forward kernel; with a
 //                                              workspace from 129 rows on in parts (both where the forward kernels above do not run)
@@ -97,9 +97,11 @@ public:
         if constexpr (N == 4) v_ = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, v_, 0, 0, 0);
         else v_ = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, v_, 0, 0, 0);
     }
-    // the same over sixteen contraction indices of bf16 operands (32 x 32 blocks only)
-    __device__ __forceinline__ void mac(bf8 a, bf8 b) { v_ = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, v_, 0, 0, 0); }
-    __device__ __forceinline__ void mac(h8 a, h8 b) { v_ = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, v_, 0, 0, 0); }
+    // the same over sixteen contraction indices of bf16 or fp16 operands (32 x 32 blocks only)
+#define HOT_MFMA_32X32X16(type) __builtin_amdgcn_mfma_f32_32x32x16_##type
+    __device__ __forceinline__ void mac(bf8 a, bf8 b) { v_ = HOT_MFMA_32X32X16(bf16)(a, b, v_, 0, 0, 0); }
+    __device__ __forceinline__ void mac(h8 a, h8 b) { v_ = HOT_MFMA_32X32X16(f16)(a, b, v_, 0, 0, 0); }
+#undef HOT_MFMA_32X32X16
     __device__ __forceinline__ V read(const MfmaSettled &) const { return v_; }
     __device__ __forceinline__ void scale(const MfmaSettled &, int i, float f) { v_[i] *= f; }
     __device__ __forceinline__ void shift(const MfmaSettled &, int i, int e) { v_[i] = __builtin_amdgcn_ldexpf(v_[i], e); }
@@ -2623,8 +2625,8 @@ void wgrad_tile_go(hipStream_t s, const LinearGradArgs &a, long tiles)
 
 // ---------------------------------------------------------------------------------
 // Weight gradients of layers with few tiles and many rows, given a workspace: the rows are cut into parts for different
-// workgroups, as in the PARTS runs of the first kernel above, but the products are formed from bf16 pieces (see
-// split2_bf16), and what a part leaves in the workspace is the raw product P_s of each sample: eps is drawn once per
+// workgroups, as in the PARTS runs of the first kernel above, but the products are formed from pieces (see
+// split2_bf16, split2_f16), and what a part leaves in the workspace is the raw product P_s of each sample: eps is drawn once per
 // weight and sample by the finish kernel instead of once per part and wave.
 //
 // A wave owns a tile of 128 x 64 (BIG x SMALL blocks of 32; XBIG: 128 inputs x 64 outputs, else 64 inputs x 128 outputs) and
