@@ -709,9 +709,9 @@ def sampled_linear_lines(hot, torch, dev, iters: int = 20):
         del x, mu, sg, y, y2, w
     out["note"] = ("TFLOPs counts the layer's 2 S R K O fp32 operations. From 33 rows on most forward calls, from 65 on many input "
                    "gradients (hot_linear_kernel_shape and hot_linear_launch_shape tell) form every product from three bf16 pieces of both factors on v_mfma_f32_32x32x16_bf16 (six of "
-                   "the nine partial products: fp32 accuracy at 6/16 of the cycles of v_mfma_f32_32x32x2_f32) or, where sums are long, from two scaled fp16 pieces (three products), so "
+                   "the nine partial products: fp32 accuracy at 6/16 of the cycles of v_mfma_f32_32x32x2_f32), so "
                    "frac_of_fp32_mfma_peak, which prices against the fp32 instruction's 157.3 TFLOP/s, can exceed 1; against "
-                   "the 16-bit peak divided by six or three products the ceiling is 417 or 833 TFLOP/s. The weight gradients of large layers (tiles of "
+                   "the bf16 peak divided by six products the ceiling is 417 TFLOP/s. The weight gradients of large layers (tiles of "
                    "128 x 128), and those that a workspace cuts into row parts, are formed the same way; the other weight-gradient kernels use the fp32 instructions.")
     return out
 

@@ -220,18 +220,15 @@ int hot_last_hip_error(const hot_plan *plan);
  * row-major; mu_b, sigma_b: [out_features] or both NULL; y: [s_local, rows, out_features]
  * packed, out.  All DEVICE pointers; x, mu_W, sigma_W 16-byte aligned; in_features, ldx,
  * weight_offset, bias_offset multiples of 4.  The contraction runs on the matrix cores at fp32
- * accuracy: on the fp32 instructions (v_mfma_f32_16x16x4_f32, v_mfma_f32_32x32x2_f32), or on v_mfma_f32_32x32x16_bf16 or _f16 with
+ * accuracy: on the fp32 instructions (v_mfma_f32_16x16x4_f32, v_mfma_f32_32x32x2_f32), or on v_mfma_f32_32x32x16_bf16 with
  * every product formed from three bf16 pieces of both factors (six partial products; what they leave out is below 3 * 2^-24
- * of a product) or from two fp16 pieces of the factors scaled by powers of two (three partial products, below 2^-22; sums of 80 terms and
- * more in the shapes of hot_linear_launch_shape, weight gradients in large tiles from 768 rows and in row parts from 1024 rows to a sum);
- * errors of all are up to 3 to 7e-7 of the sum of addend magnitudes, by the length of a wave's sum.  Pieces
+ * of a product; errors of both are up to 3 to 7e-7 of the sum of addend magnitudes, by the length of a wave's sum).  bf16 pieces
  * are what may run: forward from 33 rows and 128 inputs on (hot_linear_kernel_shape with which = 0 or hot_linear_launch_shape
  * with 0 tells where, but for the latter's codes 2xx), input gradients from 65 rows and 256 outputs on (the same with 1), weight
  * gradients from 129 rows on (large layers, and those that a workspace cuts into row parts).  There a factor below about 1e-33 in
- * magnitude has bf16 pieces below the normal range, which the instruction may flush, and one below 2^-16 of the largest of its row
- * or column among the same sixteen terms of a sum has fp16 pieces with an error of up to 2^-38 of that largest.  An infinite factor, or
- * where bf16 pieces run one above their largest number (3.39e38), gives NaN in the tiles that hot_linear_launch_shape tells of (2xx
- * apart); elsewhere, pieces or not, it gives what fp32 products give (where an input and a weight of one sum are both
+ * magnitude has pieces below bf16's normal range, which the instruction may flush.  An infinite factor, or one above the
+ * largest bf16 number (3.39e38), gives NaN in the tiles that hot_linear_launch_shape tells of (2xx apart);
+ * elsewhere, bf16 pieces or not, it gives what fp32 products give (where an input and a weight of one sum are both
  * infinite, possibly an infinity instead of NaN).
  * Runs on the current device, asynchronous on `stream`.
  * Up to 32 rows, and wherever 64-row x 16-output tiles of all samples are at most one per compute unit, a wave draws the weights
@@ -281,7 +278,7 @@ int hot_linear_forward_rng(const hot_linear_desc *desc, const hot_rng *rng, cons
  * a multiple of 4 and dy 16-byte aligned; else from 256 rows on once per workgroup of 64 to 256 rows, whose waves share the
  * draws through LDS).  Large layers
  * (from 129 rows on, at least 512 tiles of 128 inputs x 128 outputs, or from 256 rows on at least 140) take their
- * weight gradients from a kernel that stages x and dy through LDS and multiplies pieces of both, as the
+ * weight gradients from a kernel that stages x and dy through LDS and multiplies bf16 pieces of both, as the
  * forward call's large tiles do (up to 180 TFLOP/s of fp32 work); it needs
  * rows * max(ldx, out_features) * 4 below 4 GiB, else the first kernel runs; with more
  * than two samples it adds up pairs of samples in grad_mu_w and grad_sigma_w themselves.  All of these kernels
@@ -331,7 +328,7 @@ int64_t hot_linear_kernel_shape(const hot_linear_desc *desc, int which, int64_t 
  * workgroup are all that can add up the rows of a tile without memory.  With a workspace the rows are cut
  * into parts for different workgroups; each part leaves its sums there and a second kernel adds
  * them in a fixed order and finishes the gradients: deterministic, no atomics.  Where out_features is even and the
- * layer has fewer than 512 tiles of 128 x 128, the parts multiply pieces and leave the raw product of each sample, so that
+ * layer has fewer than 512 tiles of 128 x 128, the parts multiply bf16 pieces and leave the raw product of each sample, so that
  * every eps is drawn once (16640 x 192 x 768, two samples: 150 -> 74 us; 7260 x 2160 x 540: 382 -> 205): from 300 rows on, from 129 on
  * if rows x samples are at least 600; below 512 rows from 8192 weights on, and not where one launch is faster (8192 to 2^18
  * weights with fewer than 1200 rows of one or two samples, up to 32 outputs, one sample of 8192 to 12000 rows;

@@ -21,8 +21,8 @@
 //             hot_linear_forward_rows_kernel   from 256 rows: four waves x 64 rows share every draw through LDS; where neither of the
 //                                              next two runs (fewer than 128 inputs, operands beyond their 32-bit offsets)
 //             hot_linear_slab_kernel           many rows on layers that fill the chip: 256 to 1024 rows x 32 to 128 outputs per
-//                                              workgroup, x loaded straight into LDS, the drawn weights shared through it, pieces on
-//                                              v_mfma_f32_32x32x16_f16 or _bf16 (128 rows: v_mfma_f32_32x32x2_f32); also input gradients
+//                                              workgroup, x loaded straight into LDS, the drawn weights shared through it, bf16 pieces
+//                                              on v_mfma_f32_32x32x16_bf16 (128 rows: v_mfma_f32_32x32x2_f32); also input gradients
 //             hot_linear_deep_kernel           tens to hundreds of rows, and more where it is faster: a wave holds all rows of its
 //                                              workgroup, the waves split the contraction; also the input gradients
 //   backward  hot_linear_wgrad_kernel          weight and bias gradients (per-sample G never stored); variants for
@@ -31,7 +31,7 @@
 //             hot_linear_wgrad_tile_kernel     the same for large layers: 128 inputs x 128 outputs per workgroup, rows of
 //                                              x and dy loaded straight into LDS
 //             hot_linear_wgrad_row_parts_kernel  the same for smaller layers and many rows, with a workspace: the rows cut into
-//                                              parts, pieces straight from memory, no LDS before the last sum
+//                                              parts, bf16 pieces straight from memory, no LDS before the last sum
 //             hot_linear_xgrad_kernel          input gradients where few workgroups are left to it: up to 16 waves split a sum
 //             hot_linear_xgrad_rows_kernel     input gradients from 256 rows: shared draws, as in the forward kernel; with a
 //                                              workspace from 129 rows on in parts (both where the forward kernels above do not run)
@@ -79,7 +79,6 @@ struct MfmaSettled {
 
 typedef float f16v __attribute__((ext_vector_type(16)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
-typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 
 template <class V, int N>
 class MfmaAcc {
@@ -97,14 +96,9 @@ public:
         if constexpr (N == 4) v_ = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, v_, 0, 0, 0);
         else v_ = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, v_, 0, 0, 0);
     }
-    // the same over sixteen contraction indices of bf16 or fp16 operands (32 x 32 blocks only)
-#define HOT_MFMA_32X32X16(type) __builtin_amdgcn_mfma_f32_32x32x16_##type
-    __device__ __forceinline__ void mac(bf8 a, bf8 b) { v_ = HOT_MFMA_32X32X16(bf16)(a, b, v_, 0, 0, 0); }
-    __device__ __forceinline__ void mac(h8 a, h8 b) { v_ = HOT_MFMA_32X32X16(f16)(a, b, v_, 0, 0, 0); }
-#undef HOT_MFMA_32X32X16
+    // the same over sixteen contraction indices of bf16 operands (32 x 32 blocks only)
+    __device__ __forceinline__ void mac(bf8 a, bf8 b) { v_ = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, v_, 0, 0, 0); }
     __device__ __forceinline__ V read(const MfmaSettled &) const { return v_; }
-    __device__ __forceinline__ void scale(const MfmaSettled &, int i, float f) { v_[i] *= f; }
-    __device__ __forceinline__ void shift(const MfmaSettled &, int i, int e) { v_[i] = __builtin_amdgcn_ldexpf(v_[i], e); }
 };
 typedef MfmaAcc<f4, 4> Acc16x16;        // v_mfma_f32_16x16x4_f32: four result registers per lane
 typedef MfmaAcc<f16v, 16> Acc32x32;     // v_mfma_f32_32x32x2_f32: sixteen
@@ -501,121 +495,6 @@ __device__ __forceinline__ void split8_bf16(const f4 &a, const f4 &b, bf8 &p1, b
     p3 = __builtin_bit_cast(bf8, q3);
 }
 
-// The same from two fp16 pieces of eleven significant bits: x s = x1 + x2 up to 2^-23 |x s|, and x1 w1 + (x1 w2 + x2 w1) leaves out
-// terms of at most 2^-22 |x w|, of either sign: three products instead of six.  fp16's exponents reach from 2^-24 to 2^15 only, so each
-// row or column of an operand has a scale s, a power of two, that follows its values: the largest magnitude of a block of sixteen
-// contraction indices lies between 4 and 65000 once scaled, and where a block asks for another scale the sums so far are
-// multiplied by the quotient (exact; measured on normal values: once, in the first block).  A value 2^-16 times the
-// block's largest or smaller keeps fewer than its 24 bits, its error stays below 2^-38 of that largest value.
-// Distance from 64 bits against the six bf16 products, normal values (8000 x k x 2048, 8000 x 4096 x o): sums over 192 indices
-// 0.83, 128 0.89, 96 0.93, 64 1.03, 32 1.3 (the instruction adds products of 22 bits with less room than products of 16), 540 and more
-// 0.72-0.8: half as many roundings.  Hence kF16MinSum.  In row parts the scales and the longer end of a sum pay from about a thousand rows to
-// a sum of four waves on (1452 rows 250 -> 199 us, 2000 141 -> 134; 554 rows 56 -> 64, 594 69 -> 66 one way round and 64 -> 69 the other).  Time: 7260 x 540 x 2160 x 2 input gradients, 2160 to 540, 306 -> 184 us, forward 225 -> 194;
-// 1024 x 8192^2 x 2 forward 1429 -> 1325, input gradients 1490 -> 1190, weight gradients 1790 -> 1520; row parts of 7260 x 540 x
-// 2160 x 2 250 -> 199.  A fourth product x2 w2 costs 5-10 % and takes 3-5 % off the error of short sums only.
-typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-
-constexpr long kF16MinSum = 80, kF16MinRowSum = 1024;
-constexpr float kF16Limit = 65000.0f;      // above it a scaled factor gets a new scale (the largest fp16 number is 65504)
-constexpr float kF16Low = 4.0f;              // so does a block whose largest scaled magnitude lies below it
-constexpr int kF16Raise = 32;                // see F16Scale
-constexpr float kF16FirstScale = 0x1p127f; // before the first factor that is not zero
-
-// the power of two that takes `biggest` (at least 0) to 2^13 .. 2^14 (numbers below 2^-114: 2^127)
-__device__ __forceinline__ float f16_scale(float biggest)
-{
-    const int e = (int)(__builtin_bit_cast(unsigned, biggest) >> 23);
-    return __builtin_bit_cast(float, (unsigned)(267 - e < 254 ? 267 - e : 254) << 23);
-}
-// 2^a / 2^b for two such scales
-__device__ __forceinline__ float f16_scale_ratio(float a, float b)
-{
-    return __builtin_amdgcn_ldexpf(1.0f, (int)(__builtin_bit_cast(unsigned, a) >> 23) - (int)(__builtin_bit_cast(unsigned, b) >> 23));
-}
-__device__ __forceinline__ float max_abs4(f4 v)
-{
-    return __builtin_fmaxf(__builtin_fmaxf(__builtin_fabsf(v[0]), __builtin_fabsf(v[1])), __builtin_fmaxf(__builtin_fabsf(v[2]), __builtin_fabsf(v[3])));
-}
-
-// the exponent field of such a scale (a product of scaled factors is 2^(their sum - 254) times the product)
-__device__ __forceinline__ int f16_scale_bits(float s) { return (int)(__builtin_bit_cast(unsigned, s) >> 23); }
-// whether a block's largest scaled magnitude asks for another scale (a block of zeros does not, nor does NaN)
-__device__ __forceinline__ bool f16_leaves(float t) { return t > kF16Limit || (t < kF16Low && t != 0.0f); }
-// The scale of one row or column of an operand, in lanes l and l + 32, which hold different contraction indices of it.
-struct F16Scale {
-    float now = kF16FirstScale, lowest = kF16FirstScale;
-    // takes in the largest magnitude of the next block; returns what the sums so far are to be multiplied by.  A scale is raised to
-    // at most 2^kF16Raise times the lowest that the sums have had, so that they stay in range.  POISON: NaN where values in one sum lie
-    // further apart than 2^100 (the kernels that ask for it form such sums again from fp32 products).
-    template <bool POISON>
-    __device__ __forceinline__ float next(float biggest)
-    {
-        const float both = __builtin_fmaxf(biggest, __shfl_xor(biggest, 32, 64)), old = now;
-        if (f16_leaves(both * old)) {
-            const float wanted = f16_scale(both);
-            const int apart = f16_scale_bits(wanted) - f16_scale_bits(lowest);
-            if (POISON && lowest != kF16FirstScale && (apart > 100 || apart < -100)) return __builtin_nanf("");
-            now = apart > kF16Raise ? __builtin_ldexpf(lowest, kF16Raise) : wanted;
-            lowest = __builtin_fminf(lowest, now);
-        }
-        return f16_scale_ratio(now, old);
-    }
-};
-// the row (of the first operand) that register i of a 32 x 32 result belongs to; its column (of the second) is lane % 32
-__device__ __forceinline__ int mfma_row(int i, int half) { return 8 * (i >> 2) + 4 * half + (i & 3); }
-__device__ __forceinline__ void rescale_rows(Acc32x32 &m, const MfmaSettled &settled, float f, int half)
-{
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        m.scale(settled, i, __shfl(f, mfma_row(i, half), 64));
-        __builtin_amdgcn_sched_barrier(0);       // (one factor at a time: hoisted, they would take registers from the loop around this branch)
-    }
-}
-__device__ __forceinline__ void rescale_columns(Acc32x32 &m, const MfmaSettled &settled, float f)
-{
-#pragma unroll
-    for (int i = 0; i < 16; ++i) m.scale(settled, i, f);
-}
-
-// the two pieces of two scaled floats, packed
-__device__ __forceinline__ void split2_f16(float x0, float x1, float s0, float s1, unsigned &p1, unsigned &p2)
-{
-    const h2 a = __builtin_convertvector(f2{x0 * s0, x1 * s1}, h2);
-    p1 = __builtin_bit_cast(unsigned, a);
-    p2 = __builtin_bit_cast(unsigned, __builtin_convertvector(f2{__builtin_fmaf(x0, s0, -(float)a[0]), __builtin_fmaf(x1, s1, -(float)a[1])}, h2));
-}
-__device__ __forceinline__ void split8_f16(const f4 &a, const f4 &b, float s, h8 &p1, h8 &p2)
-{
-    u4 q1, q2;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        unsigned t1, t2;
-        split2_f16(j < 2 ? a[2 * j] : b[2 * j - 4], j < 2 ? a[2 * j + 1] : b[2 * j - 3], s, s, t1, t2);
-        q1[j] = t1;
-        q2[j] = t2;
-    }
-    p1 = __builtin_bit_cast(h8, q1);
-    p2 = __builtin_bit_cast(h8, q2);
-}
-
-// The two ways of cutting: what a piece vector is, how many there are, and the products kept, smallest first.
-template <bool F16>
-struct Cut {
-    typedef bf8 V;
-    static constexpr int PIECES = 3, PRODUCTS = 6;
-    static constexpr int A[6] = {2, 1, 0, 1, 0, 0}, B[6] = {0, 1, 2, 0, 1, 0};
-    static __device__ __forceinline__ void split8(const f4 &a, const f4 &b, float, V (&p)[3]) { split8_bf16(a, b, p[0], p[1], p[2]); }
-    static __device__ __forceinline__ void split2(float x0, float x1, float, float, unsigned (&p)[3]) { split2_bf16(x0, x1, p[0], p[1], p[2]); }
-};
-template <>
-struct Cut<true> {
-    typedef h8 V;
-    static constexpr int PIECES = 2, PRODUCTS = 3;
-    static constexpr int A[3] = {1, 0, 0}, B[3] = {0, 1, 0};
-    static __device__ __forceinline__ void split8(const f4 &a, const f4 &b, float s, V (&p)[2]) { split8_f16(a, b, s, p[0], p[1]); }
-    static __device__ __forceinline__ void split2(float x0, float x1, float s0, float s1, unsigned (&p)[2]) { split2_f16(x0, x1, s0, s1, p[0], p[1]); }
-};
-
 // What the kernel works on: out_s[row][n] = sum_c in_s[row][c] W_s(n, c) + bias_s[n] with W_s drawn.  Forward (TR = false):
 // in = x, c runs over the layer's inputs, n over its outputs, weight (n, c) has flat index n * C + c (the generator's
 // quads run along c).  Input gradients (TR = true): in = dy, c runs over the layer's outputs, n over its inputs, weight
@@ -647,19 +526,14 @@ __device__ __forceinline__ int slab_swizzle(int r) { return ((r >> 1) & 3) ^ ((r
 // every sample has an input of its own (then ST = 1).
 // RBW: blocks of 32 rows per wave; one only with four waves (128 rows per workgroup, for 65 to 128 rows: half the matrix
 // work per draw again).
-// F16: two fp16 pieces to a factor, else three bf16 pieces (64 rows per wave) or the fp32 instruction (32 rows).
-template <int WAVES, int CBW, int ST, bool OWN, bool TR, int RBW, bool F16>
-__global__ void __launch_bounds__(64 * WAVES, CBW * ST <= 2 ? (RBW == 2 && WAVES != 16 ? 3 : 4) : 2)
+template <int WAVES, int CBW, int ST, bool OWN, bool TR, int RBW = 2, bool BF = (RBW == 2)>
+__global__ void __launch_bounds__(64 * WAVES, CBW * ST <= 2 ? (BF && WAVES != 16 ? 3 : 4) : 2)
 hot_linear_slab_kernel(SlabArgs a)
 {
     static_assert(ST == 1 || ST == 2, "one or two samples per pass");
     static_assert(!OWN || ST == 1, "one input per sample: one sample per pass");
     static_assert(WAVES == 8 || ((WAVES == 16 || WAVES == 4) && CBW * ST <= 2), "sixteen waves have 128 registers each, and so have four: four such workgroups share a compute unit");
     static_assert(RBW == 2 || (RBW == 1 && WAVES == 4), "32 rows per wave only in workgroups of four waves");
-    static_assert(RBW == 2 || !F16, "32 rows per wave: the fp32 instruction");
-    constexpr bool CUT = RBW == 2;
-    typedef Cut<F16> C_;
-    constexpr int PL = C_::PIECES;
     constexpr int WROWS = 32 * RBW, OUTS = 32 * CBW, KS = kSlabK;
     constexpr int XW = WROWS * KS;           // floats of a wave's region of x
     constexpr int WT = OUTS * KS;            // floats of one sample's weight tile
@@ -668,9 +542,8 @@ hot_linear_slab_kernel(SlabArgs a)
     constexpr bool EVERY = QUADS == 64 * WAVES;
     static_assert(QUADS <= 64 * WAVES && QUADS % 64 == 0, "whole waves draw");
     __shared__ __attribute__((aligned(16))) float xs0[WAVES * XW], xs1[WAVES * XW];
-    // (CUT: planes of 16-bit pieces instead of one of floats; F16: then the scale of every output's weights)
-    constexpr int WFLOATS = ST * (CUT ? WT * PL / 2 + (F16 ? OUTS : 0) : WT);
-    __shared__ __attribute__((aligned(16))) float ws0[WFLOATS], ws1[WFLOATS];
+    // (BF: three planes of bf16 pieces instead of one of floats)
+    __shared__ __attribute__((aligned(16))) float ws0[ST * WT * (BF ? 3 : 2) / 2], ws1[ST * WT * (BF ? 3 : 2) / 2];
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int l32 = lane & 31, half = lane >> 5;
@@ -697,16 +570,15 @@ hot_linear_slab_kernel(SlabArgs a)
     // indices cb0 + d_c (.. + 3 if not TR)
     const bool draws = t < QUADS;
     const int d_st = t / (OUTS * 4), d_idx = t % (OUTS * 4);
-    // (F16: all contraction indices of an output are drawn in one wave, so that it can give them one scale)
-    const int d_n = !TR ? d_idx >> 2 : F16 ? 16 * (d_idx >> 6) + 4 * (d_idx & 3) : 4 * (d_idx % (OUTS / 4));
-    const int d_c = !TR ? 4 * (d_idx & 3) : F16 ? (d_idx & 63) >> 2 : d_idx / (OUTS / 4);
+    const int d_n = TR ? 4 * (d_idx % (OUTS / 4)) : d_idx >> 2;
+    const int d_c = TR ? d_idx / (OUTS / 4) : 4 * (d_idx & 3);
     const bool d_ok = draws && n0 + d_n < N;
     const int d_cols = C - d_c;
     const long d_flat = TR ? (long)d_c * N + n0 + d_n : (long)(n0 + d_n) * C + d_c;
     const unsigned w_step = TR ? (unsigned)(KS * N * 4) : (unsigned)(KS * 4);      // bytes from one step's quad to the next
-    int d_put[TR ? 4 : 1];                   // where the drawn weights go in the tile (floats; CUT: bytes within a plane)
-    if constexpr (CUT) {
-        // A plane holds, per sample and output, 32 bytes: two chunks of eight pieces, chunk h with the contraction indices
+    int d_put[TR ? 4 : 1];                   // where the drawn weights go in the tile (floats; BF: bytes within a plane)
+    if constexpr (BF) {
+        // A plane holds, per sample and output, 32 bytes: two chunks of eight bf16, chunk h with the contraction indices
         // 4 h .. 4 h + 3 and 8 + 4 h .. 8 + 4 h + 3 (what lanes 32 h .. 32 h + 31 feed to one matrix instruction), stored
         // as chunk h ^ bit 3 of the output (so that 16 consecutive outputs spread over all banks).
         const int h = (d_c >> 2) & 1, part = d_c >> 3;
@@ -736,10 +608,6 @@ hot_linear_slab_kernel(SlabArgs a)
 
         // sends for mu and sigma of this thread's quad of the step that starts at cb0 (every call advances one step)
         f4 m4, sd4;
-        float d_scale[TR ? 4 : 1];           // F16: the scale of the outputs that this thread draws for
-#pragma unroll
-        for (int e = 0; e < (TR ? 4 : 1); ++e) d_scale[e] = kF16FirstScale;
-        unsigned d_lowest = 0xFEFEFEFEu;     // the exponent fields of the lowest that they have been, a byte each
         auto ask_w = [&](int cb0) {
             const int off = (int)((d_ok && cb0 < d_cols) ? w_off : kOutside);
             m4 = window_load4<false>(mu_win, off);
@@ -758,46 +626,18 @@ hot_linear_slab_kernel(SlabArgs a)
 #pragma unroll
                     for (int c = 0; c < 4; ++c) w4[c] = __builtin_fmaf(sd4[c], e[c], m4[c]);
                 }
-                if constexpr (CUT) {
-                    // An output's scale follows the weights drawn for it (see F16Scale; the waves learn of it with the tile).  Its block lies in
-                    // 4 lanes, or with TR in 16, one weight each: there single small weights must not ask, so they do from far below only.
-                    if constexpr (F16) {
-                        bool over = false;
+                if constexpr (BF) {
+                    // three bf16 pieces of every weight (see split2_bf16): a quad along the contraction is 8 bytes per plane
+                    unsigned pc[3][2];
+                    split2_bf16(w4[0], w4[1], pc[0][0], pc[1][0], pc[2][0]);
+                    split2_bf16(w4[2], w4[3], pc[0][1], pc[1][1], pc[2][1]);
 #pragma unroll
-                        for (int e = 0; e < (TR ? 4 : 1); ++e) {
-                            const float t = (TR ? __builtin_fabsf(w4[e]) : max_abs4(w4)) * d_scale[e];
-                            over |= TR ? t > kF16Limit || (t < 0x1p-7f && t != 0.0f) : f16_leaves(t);
-                        }
-                        if (__any(over)) {
-#pragma unroll
-                            for (int e = 0; e < (TR ? 4 : 1); ++e) {
-                                float big = TR ? __builtin_fabsf(w4[e]) : max_abs4(w4);
-#pragma unroll
-                                for (int d = TR ? 4 : 1; d < (TR ? 64 : 4); d *= 2) big = __builtin_fmaxf(big, __shfl_xor(big, d, 64));
-                                if (f16_leaves(big * d_scale[e])) {
-                                    const int low = (int)(d_lowest >> (8 * e) & 255u), wanted = f16_scale_bits(f16_scale(big));
-                                    const int bits = wanted < low + kF16Raise ? wanted : low + kF16Raise;
-                                    d_scale[e] = __builtin_bit_cast(float, (unsigned)bits << 23);
-                                    if (bits < low) d_lowest = (d_lowest & ~(255u << (8 * e))) | (unsigned)bits << (8 * e);
-                                }
-                            }
-                        }
-                        if (d_c == 0) {
-#pragma unroll
-                            for (int e = 0; e < (TR ? 4 : 1); ++e) wsb[ST * WT + d_st * OUTS + d_n + e] = d_scale[e];
-                        }
-                    }
-                    // the pieces of every weight: a quad along the contraction is 8 bytes per plane
-                    unsigned lo[PL], hi[PL];
-                    C_::split2(w4[0], w4[1], d_scale[0], d_scale[TR ? 1 : 0], lo);
-                    C_::split2(w4[2], w4[3], d_scale[TR ? 2 : 0], d_scale[TR ? 3 : 0], hi);
-#pragma unroll
-                    for (int pl = 0; pl < PL; ++pl) {
+                    for (int pl = 0; pl < 3; ++pl) {
                         lds_char *plane = (lds_char *)wsb + pl * (ST * OUTS * 32);
-                        if constexpr (!TR) *(lds_u2 *)(plane + d_put[0]) = u2{lo[pl], hi[pl]};
+                        if constexpr (!TR) *(lds_u2 *)(plane + d_put[0]) = u2{pc[pl][0], pc[pl][1]};
                         else {
 #pragma unroll
-                            for (int e = 0; e < 4; ++e) *(lds_ushort *)(plane + d_put[e]) = (unsigned short)((e < 2 ? lo[pl] : hi[pl]) >> (16 * (e & 1)));
+                            for (int e = 0; e < 4; ++e) *(lds_ushort *)(plane + d_put[e]) = (unsigned short)(pc[pl][e >> 1] >> (16 * (e & 1)));
                         }
                     }
                 } else if constexpr (!TR) *(lds_f4 *)(wsb + d_put[0]) = w4;
@@ -824,7 +664,7 @@ hot_linear_slab_kernel(SlabArgs a)
             const volatile lds_f4 *wp = (const volatile lds_f4 *)(wsb + op_off[k8]);
 #pragma unroll
             for (int rb = 0; rb < RBW; ++rb) xa[k8][rb] = xp[rb * 128];
-            if constexpr (!CUT) {
+            if constexpr (!BF) {
 #pragma unroll
                 for (int st = 0; st < ST; ++st)
 #pragma unroll
@@ -841,93 +681,55 @@ hot_linear_slab_kernel(SlabArgs a)
 #pragma unroll
                         for (int cb = 0; cb < CBW; ++cb) mm[st][rb][cb].mac(xa[k8][rb][i], wb[k8][st][cb][i]);
         };
-        // CUT: one step on the 16-bit matrix instruction.  The operands of the step are read (x as floats, the weights as their
-        // planes), x is cut into its pieces, and the products of a block of 32 x 32 leave out only the terms below 2^-22 (three bf16
-        // pieces: 2^-24) of the full one; then the barrier, behind which the buffers just read are refilled.
+        // BF: one step on the bf16 matrix instruction.  The operands of the step are read (x as floats, the weights
+        // as their three planes), x is cut into its pieces, and six products per block of 32 x 32 leave out only the
+        // terms below 2^-24 of the full product; then the barrier, behind which the buffers just read are refilled.
         // AHEAD: both row blocks are cut first, every block of weights is read once for the two of them, one block ahead of its
-        // products, and consecutive instructions go to different accumulators; sixteen waves have no registers for that.
-        constexpr bool AHEAD = WAVES == 4 || CBW * ST == 4 || (F16 && WAVES == 8);
-        F16Scale x_scale[RBW];                      // of this lane's row of every row block
-        float w_scale[ST * CBW];                    // of its output of every block
+        // products, and consecutive instructions go to different accumulators; it takes 24 to 36 registers more.  Measured:
+        // 64 output-samples in four waves 82 -> 77 us (16640 x 192 x 768), 128 in eight 246 -> 218 (7260 x 540 x 2160) and 267 -> 244
+        // (its transpose's input gradients), the input gradients of sixteen 1541 -> 1490 (1024 x 8192^2); but the forward call's
+        // sixteen waves spill (1439 -> 1488) and narrower tiles of eight, three waves to a SIMD, lose 3 %.
+        constexpr bool AHEAD = WAVES == 4 || CBW * ST == 4 || (WAVES == 16 && TR);
+        auto read_b = [&](int at, const lds_float *wsb, bf8 (&b)[3]) {      // at = st * CBW + cb
+            const volatile lds_bf8 *wp = (const volatile lds_bf8 *)((const lds_char *)wsb + ((at / CBW * OUTS + at % CBW * 32 + l32) * 32 + ((half ^ ((l32 >> 3) & 1)) << 4)));
 #pragma unroll
-        for (int at = 0; at < ST * CBW; ++at) w_scale[at] = kF16FirstScale;
-        auto read_b = [&](int at, const lds_float *wsb, typename C_::V (&b)[PL]) {      // at = st * CBW + cb
-            typedef __attribute__((address_space(3))) typename C_::V lds_v;
-            const volatile lds_v *wp = (const volatile lds_v *)((const lds_char *)wsb + ((at * 32 + l32) * 32 + ((half ^ ((l32 >> 3) & 1)) << 4)));
-#pragma unroll
-            for (int pl = 0; pl < PL; ++pl) b[pl] = wp[pl * ST * OUTS * 2];
+            for (int pl = 0; pl < 3; ++pl) b[pl] = wp[pl * ST * OUTS * 2];
         };
-        // this step's scales of the weights, and of the rows of a block: where one differs from the last step's, the sums so far take it
-        auto rescale_w = [&](const lds_float *wsb) {
-            float now[ST * CBW];
-            bool moved = false;
-#pragma unroll
-            for (int at = 0; at < ST * CBW; ++at) {
-                now[at] = ((const volatile lds_float *)wsb)[ST * WT + at * 32 + l32];
-                moved |= now[at] != w_scale[at];
-            }
-            if (__any(moved)) {
-                const MfmaSettled settled;
-#pragma unroll
-                for (int at = 0; at < ST * CBW; ++at) {
-                    const float f = f16_scale_ratio(now[at], w_scale[at]);
-                    w_scale[at] = now[at];
-#pragma unroll
-                    for (int rb = 0; rb < RBW; ++rb) rescale_columns(mm[at / CBW][rb][at % CBW], settled, f);
-                }
-            }
-        };
-        auto rescale_x = [&](int rb) {
-            const float big = __builtin_fmaxf(max_abs4(xa[0][rb]), max_abs4(xa[1][rb]));
-            if (__any(f16_leaves(big * x_scale[rb].now))) {
-                const MfmaSettled settled;
-                const float f = x_scale[rb].template next<false>(big);
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const float fi = __shfl(f, mfma_row(i, half), 64);
-#pragma unroll
-                    for (int at = 0; at < ST * CBW; ++at) mm[at / CBW][rb][at % CBW].scale(settled, i, fi);
-                }
-            }
-        };
-        auto step_cut = [&](int cb0, lds_float *xsb, lds_float *wsb) {
+        auto step_bf = [&](int cb0, lds_float *xsb, lds_float *wsb) {
+            read_ops(0, xsb, wsb);
+            read_ops(1, xsb, wsb);
             if constexpr (AHEAD) {
-                typename C_::V b[2][PL], p[RBW][PL];
-                read_ops(0, xsb, wsb);
-                read_ops(1, xsb, wsb);
-                if constexpr (F16) {
-                    rescale_w(wsb);
-#pragma unroll
-                    for (int rb = 0; rb < RBW; ++rb) rescale_x(rb);
-                }
+                constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};
+                bf8 b[2][3], p[RBW][3];
                 read_b(0, wsb, b[0]);
 #pragma unroll
-                for (int rb = 0; rb < RBW; ++rb) C_::split8(xa[0][rb], xa[1][rb], x_scale[rb].now, p[rb]);
+                for (int rb = 0; rb < RBW; ++rb) split8_bf16(xa[0][rb], xa[1][rb], p[rb][0], p[rb][1], p[rb][2]);
 #pragma unroll
                 for (int at = 0; at < ST * CBW; ++at) {
                     if (at + 1 < ST * CBW) read_b(at + 1, wsb, b[(at + 1) & 1]);
 #pragma unroll
-                    for (int i = 0; i < C_::PRODUCTS; ++i)
+                    for (int i = 0; i < 6; ++i)
 #pragma unroll
-                        for (int rb = 0; rb < RBW; ++rb) mm[at / CBW][rb][at % CBW].mac(p[rb][C_::A[i]], b[at & 1][C_::B[i]]);
+                        for (int rb = 0; rb < RBW; ++rb) mm[at / CBW][rb][at % CBW].mac(p[rb][PA[i]], b[at & 1][PB[i]]);
                 }
             } else {
 #pragma unroll
                 for (int rb = 0; rb < RBW; ++rb) {
-                    typename C_::V p[PL], b[PL];
+                    bf8 a1, a2, a3;
+                    split8_bf16(xa[0][rb], xa[1][rb], a1, a2, a3);
 #pragma unroll
-                    for (int k8 = 0; k8 < 2; ++k8) xa[k8][rb] = ((const volatile lds_f4 *)(xsb + wave * XW + op_off[k8]))[rb * 128];
-                    if constexpr (F16) {
-                        if (rb == 0) rescale_w(wsb);
-                        rescale_x(rb);
-                    }
-                    C_::split8(xa[0][rb], xa[1][rb], x_scale[rb].now, p);
+                    for (int st = 0; st < ST; ++st)
 #pragma unroll
-                    for (int at = 0; at < ST * CBW; ++at) {
-                        read_b(at, wsb, b);
-#pragma unroll
-                        for (int i = 0; i < C_::PRODUCTS; ++i) mm[at / CBW][rb][at % CBW].mac(p[C_::A[i]], b[C_::B[i]]);
-                    }
+                        for (int cb = 0; cb < CBW; ++cb) {
+                            const volatile lds_bf8 *wp = (const volatile lds_bf8 *)((const lds_char *)wsb + ((st * OUTS + cb * 32 + l32) * 32 + ((half ^ ((l32 >> 3) & 1)) << 4)));
+                            const bf8 b1 = wp[0], b2 = wp[ST * OUTS * 2], b3 = wp[2 * ST * OUTS * 2];
+                            mm[st][rb][cb].mac(a3, b1);
+                            mm[st][rb][cb].mac(a2, b2);
+                            mm[st][rb][cb].mac(a1, b3);
+                            mm[st][rb][cb].mac(a2, b1);
+                            mm[st][rb][cb].mac(a1, b2);
+                            mm[st][rb][cb].mac(a1, b1);
+                        }
                 }
             }
             everything_arrived_then_barrier();
@@ -955,10 +757,10 @@ hot_linear_slab_kernel(SlabArgs a)
         put_w(KS, W1);
         ask_w(2 * KS);
         everything_arrived_then_barrier();
-        if constexpr (CUT) {
+        if constexpr (BF) {
             for (int cb0 = 0; cb0 < C; cb0 += 2 * KS) {
-                step_cut(cb0, X0, W0);
-                step_cut(cb0 + KS, X1, W1);
+                step_bf(cb0, X0, W0);
+                step_bf(cb0 + KS, X1, W1);
             }
         } else {
             read_ops(0, X0, W0);
@@ -991,12 +793,7 @@ hot_linear_slab_kernel(SlabArgs a)
 #pragma unroll
                         for (int i = 0; i < 16; ++i) {
                             const int row = r0w + 32 * rb + 8 * (i >> 2) + (i & 3);
-                            float sum = acc[i];
-                            if constexpr (F16) {
-                                const int x_bits = __shfl(f16_scale_bits(x_scale[rb].now), mfma_row(i, half), 64);
-                                sum = __builtin_amdgcn_ldexpf(sum, 254 - x_bits - f16_scale_bits(w_scale[st * CBW + cb]));
-                            }
-                            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, sum + bias), out_win,
+                            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, acc[i] + bias), out_win,
                                                                   (n_ok && row < R) ? (int)(((unsigned)row * (unsigned)N + (unsigned)n) * 4u) : (int)kOutside, 0, 0);
                         }
                     }
@@ -1568,13 +1365,7 @@ void slab_go(hipStream_t s, SlabArgs a, int s_begin, int s_end)
     a.s_end = s_end;
     const dim3 grid((unsigned)((a.outs + 32 * CBW - 1) / (32 * CBW)), (unsigned)((a.rows + 32 * RBW * WAVES - 1) / (32 * RBW * WAVES)),
                     (unsigned)((s_end - s_begin + ST - 1) / ST));
-    if constexpr (RBW == 2) {
-        if (a.contract >= kF16MinSum) {
-            hot_linear_slab_kernel<WAVES, CBW, ST, OWN, TR, RBW, true><<<grid, dim3(64 * WAVES), 0, s>>>(a);
-            return;
-        }
-    }
-    hot_linear_slab_kernel<WAVES, CBW, ST, OWN, TR, RBW, false><<<grid, dim3(64 * WAVES), 0, s>>>(a);
+    hot_linear_slab_kernel<WAVES, CBW, ST, OWN, TR, RBW><<<grid, dim3(64 * WAVES), 0, s>>>(a);
 }
 
 // one sample per pass, in the shape chosen
@@ -2219,7 +2010,7 @@ constexpr int kTileRows = 16;         // rows per step
 constexpr int kTurnPitch = 36;        // floats per row of a wave's 32 x 32 block on its way out (16-byte aligned rows)
 
 
-// Those of four sums over the rows r_lo .. r_hi - 1 that the pieces left as NaN, from fp32 products (see deep_plain_sum).
+// Those of four sums over the rows r_lo .. r_hi - 1 that the bf16 pieces left as NaN, from fp32 products (see deep_plain_sum).
 __device__ __forceinline__ void row_parts_plain_sums(const LinearGradArgs &a, int s, long o, long k, long r_lo, long r_hi, float *p)
 {
     const float *x = a.x + (size_t)s * (size_t)a.x_sample_stride + (size_t)k;
@@ -2274,11 +2065,9 @@ __device__ __forceinline__ void wgrad_tile_plain(const LinearGradArgs &a, long o
 
 // WHOLE: every 32 x 32 block of the workgroup's tile reaches into the layer (no block is skipped, no column masked).
 // XB, DB: the four buffers of 16 rows x 128 columns of x and of dy.
-// F16: two fp16 pieces to a factor, else three bf16 pieces.
-template <bool WHOLE, bool F16>
+template <bool WHOLE>
 __device__ __forceinline__ void wgrad_tile_body(const LinearGradArgs &a, lds_float *const (&XB)[4], lds_float *const (&DB)[4], long o0, long k0)
 {
-    typedef Cut<F16> C_;
     constexpr int WK = 2, TK = kTileSide, TO = kTileSide;         // 2 x 2 waves of 64 inputs x 64 outputs
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -2319,7 +2108,7 @@ __device__ __forceinline__ void wgrad_tile_body(const LinearGradArgs &a, lds_flo
     const int rows = (int)R;
 
     // The products of one sample over all rows, into the accumulators mm (and the column sums of dy into sb).
-    // A step is 16 rows, the contraction block of the 16-bit matrix instructions (see split2_bf16, split2_f16): lanes 0-31 hold the even rows of a
+    // A step is 16 rows, the contraction block of the bf16 matrix instruction (see split2_bf16): lanes 0-31 hold the even rows of a
     // column, lanes 32-63 the odd ones, on both sides alike.  Four buffers, loads three steps ahead.  Step i (buffers i % 4):
     // read its operands, cut them, multiply; wait for the loads of step i + 1 (sent for two steps ago; those of step i + 2 may
     // still be on their way), barrier; send for step i + 3 (its buffers held step i - 1, read for the last time before this
@@ -2362,26 +2151,6 @@ __device__ __forceinline__ void wgrad_tile_body(const LinearGradArgs &a, lds_flo
                     bv[p][i] = db[2 * p * TO + 32 * i];
                 }
         };
-        // the scales of this lane's columns of x and of dy in the two blocks of each (both halves of the wave hold the same)
-        F16Scale x_scale[2], d_scale[2];
-        auto rescale = [&](const float (&v)[P][2], F16Scale (&scale)[2], bool of_x) {
-            float big[2];
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-                big[i] = __builtin_fmaxf(max_abs4(f4{v[0][i], v[1][i], v[2][i], v[3][i]}), max_abs4(f4{v[4][i], v[5][i], v[6][i], v[7][i]}));
-            if (__any(f16_leaves(big[0] * scale[0].now) || f16_leaves(big[1] * scale[1].now))) {
-                const MfmaSettled settled;
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    const float f = scale[i].next<false>(big[i]);
-#pragma unroll
-                    for (int j = 0; j < 2; ++j) {
-                        if (of_x) rescale_rows(mm[i][j], settled, f, half);
-                        else rescale_columns(mm[j][i], settled, f);
-                    }
-                }
-            }
-        };
 
         request(XB[0], DB[0], rows);
         request(XB[1], DB[1], rows - kTileRows);
@@ -2398,40 +2167,29 @@ __device__ __forceinline__ void wgrad_tile_body(const LinearGradArgs &a, lds_flo
                         sb[1] += bv[p][1];
                     }
                 }
-                if constexpr (F16) {
-                    rescale(av, x_scale, true);
-                    rescale(bv, d_scale, false);
-                }
-                typename C_::V ap[2][C_::PIECES];
+                bf8 a1[2], a2[2], a3[2];
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
-                    C_::split8(f4{av[0][i], av[1][i], av[2][i], av[3][i]}, f4{av[4][i], av[5][i], av[6][i], av[7][i]}, x_scale[i].now, ap[i]);
+                    split8_bf16(f4{av[0][i], av[1][i], av[2][i], av[3][i]}, f4{av[4][i], av[5][i], av[6][i], av[7][i]}, a1[i], a2[i], a3[i]);
 #pragma unroll
                 for (int j = 0; j < 2; ++j) {
-                    typename C_::V bp[C_::PIECES];
-                    C_::split8(f4{bv[0][j], bv[1][j], bv[2][j], bv[3][j]}, f4{bv[4][j], bv[5][j], bv[6][j], bv[7][j]}, d_scale[j].now, bp);
+                    bf8 b1, b2, b3;
+                    split8_bf16(f4{bv[0][j], bv[1][j], bv[2][j], bv[3][j]}, f4{bv[4][j], bv[5][j], bv[6][j], bv[7][j]}, b1, b2, b3);
 #pragma unroll
                     for (int i = 0; i < 2; ++i)
                         if (WHOLE || ok[i][j]) {
-#pragma unroll
-                            for (int n = 0; n < C_::PRODUCTS; ++n) mm[i][j].mac(ap[i][C_::A[n]], bp[C_::B[n]]);
+                            mm[i][j].mac(a3[i], b1);
+                            mm[i][j].mac(a2[i], b2);
+                            mm[i][j].mac(a1[i], b3);
+                            mm[i][j].mac(a2[i], b1);
+                            mm[i][j].mac(a1[i], b2);
+                            mm[i][j].mac(a1[i], b1);
                         }
                 }
                 asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(XI + DI) : "memory");
                 request(XB[(b + 3) % 4], DB[(b + 3) % 4], left - 3 * kTileRows);
                 left -= kTileRows;
             }
-        }
-        if constexpr (F16) {
-            const MfmaSettled settled;
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int g = 0; g < 16; ++g) {
-                    const int x_bits = __shfl(f16_scale_bits(x_scale[i].now), mfma_row(g, half), 64);
-#pragma unroll
-                    for (int j = 0; j < 2; ++j) mm[i][j].shift(settled, g, 254 - x_bits - f16_scale_bits(d_scale[j].now));
-                }
         }
         everything_arrived_then_barrier();       // every wave is done with the buffers
     };
@@ -2564,7 +2322,6 @@ __device__ __forceinline__ void wgrad_tile_body(const LinearGradArgs &a, lds_flo
     }
 }
 
-template <bool F16>
 __global__ void __launch_bounds__(256, 2)
 hot_linear_wgrad_tile_kernel(LinearGradArgs a)
 {
@@ -2590,8 +2347,8 @@ hot_linear_wgrad_tile_kernel(LinearGradArgs a)
     const long o0 = (8 * (band < bands ? band : bands) + within % height) * TO;
     const long k0 = (within / height) * TK;
     // (uniform over the workgroup, so all its waves meet at the same barriers)
-    if (k0 + TK <= K && o0 + TO <= O) wgrad_tile_body<true, F16>(a, XB, DB, o0, k0);
-    else wgrad_tile_body<false, F16>(a, XB, DB, o0, k0);
+    if (k0 + TK <= K && o0 + TO <= O) wgrad_tile_body<true>(a, XB, DB, o0, k0);
+    else wgrad_tile_body<false>(a, XB, DB, o0, k0);
 }
 
 // Whether the kernel above can address this problem (its windows take 32-bit byte offsets).  Any number of outputs: a quad of dy
@@ -2610,23 +2367,16 @@ inline long wgrad_tile_count(const hot_linear_desc *d)
     return ((d->in_features + kTileSide - 1) / kTileSide) * ((d->out_features + kTileSide - 1) / kTileSide);
 }
 
-// From here on fp16 pieces: they take the steps 1.25x as fast, but the scales and what they displace from the registers around the row
-// loops cost a tile about 15 us (300 x 2160 x 8640 x 2: 227 us with bf16 pieces, 259 with these; the whole pass of 569 x 2572 x 4340 x 1 331 and
-// 344; 1024 x 8192^2 x 2 1740 and 1490).
-constexpr long kF16MinTileRows = 768;
-
 void wgrad_tile_go(hipStream_t s, const LinearGradArgs &a, long tiles)
 {
     const long per_xcd = (tiles + kXcds - 1) / kXcds;
-    const dim3 grid((unsigned)(kXcds * per_xcd));
-    if (a.rows >= kF16MinTileRows) hot_linear_wgrad_tile_kernel<true><<<grid, dim3(256), 0, s>>>(a);
-    else hot_linear_wgrad_tile_kernel<false><<<grid, dim3(256), 0, s>>>(a);
+    hot_linear_wgrad_tile_kernel<<<dim3((unsigned)(kXcds * per_xcd)), dim3(256), 0, s>>>(a);
 }
 
 // ---------------------------------------------------------------------------------
 // Weight gradients of layers with few tiles and many rows, given a workspace: the rows are cut into parts for different
-// workgroups, as in the PARTS runs of the first kernel above, but the products are formed from pieces (see
-// split2_bf16, split2_f16), and what a part leaves in the workspace is the raw product P_s of each sample: eps is drawn once per
+// workgroups, as in the PARTS runs of the first kernel above, but the products are formed from bf16 pieces (see
+// split2_bf16), and what a part leaves in the workspace is the raw product P_s of each sample: eps is drawn once per
 // weight and sample by the finish kernel instead of once per part and wave.
 //
 // A wave owns a tile of 128 x 64 (BIG x SMALL blocks of 32; XBIG: 128 inputs x 64 outputs, else 64 inputs x 128 outputs) and
@@ -2658,8 +2408,7 @@ struct Floats<4> {
 // floats of one part's share of the workspace: per sample the weights, then the biases (a multiple of four, so that quads stay aligned)
 inline __host__ __device__ long row_part_floats(long K, long O, int s_loc) { return (O * K + ((O + 3) & ~3L)) * s_loc; }
 
-// F16: two fp16 pieces to a factor, else three bf16 pieces.
-template <bool XBIG, bool F16>
+template <bool XBIG>
 __global__ void __launch_bounds__(64 * kRowPartWaves, 2)
 hot_linear_wgrad_row_parts_kernel(LinearGradArgs a, int parts, int chunk)
 {
@@ -2667,10 +2416,7 @@ hot_linear_wgrad_row_parts_kernel(LinearGradArgs a, int parts, int chunk)
     constexpr int TK = 32 * KB, TO = 32 * OB, PITCH = TK + 4;
     typedef Floats<NB> LB;
     typedef Floats<NS> LS;
-    typedef Cut<F16> C_;
-    constexpr int PL = C_::PIECES;
     __shared__ __attribute__((aligned(16))) float turn[kRowPartWaves][32 * PITCH];
-    __shared__ __attribute__((aligned(16))) int x_bits[kRowPartWaves][F16 ? TK : 1];      // F16: of the scales of a wave's columns of x
     const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const long K = a.in_features, O = a.out_features, R = a.rows;
@@ -2717,7 +2463,6 @@ hot_linear_wgrad_row_parts_kernel(LinearGradArgs a, int parts, int chunk)
         for (int t = 0; t < 8; ++t) sr[t] = LS::load(s_win, s_off + (unsigned)t * s_pitch);
         s_off += (unsigned)(kRowPartRows * kRowPartWaves) * s_pitch;
     };
-    F16Scale b_scale[NB], s_scale[NS];       // of this lane's columns (both halves of the wave hold the same)
     ask_big();
     ask_small();
     unsigned long long special = 0;       // the lanes that met a NaN
@@ -2734,68 +2479,33 @@ hot_linear_wgrad_row_parts_kernel(LinearGradArgs a, int parts, int chunk)
 #pragma unroll
                     for (int j = 0; j < OB; ++j) col_sum[j] += XBIG ? sr[t][j % NS] : br[t][j];
             }
-            if constexpr (F16) {
-                float b_big[NB];
-                bool over = false;
-#pragma unroll
-                for (int i = 0; i < NB; ++i) {
-                    b_big[i] = __builtin_fmaxf(max_abs4(f4{br[0][i], br[1][i], br[2][i], br[3][i]}), max_abs4(f4{br[4][i], br[5][i], br[6][i], br[7][i]}));
-                    over |= f16_leaves(b_big[i] * b_scale[i].now);
-                }
-                if (__any(over)) {
-                    const MfmaSettled settled;
-#pragma unroll
-                    for (int i = 0; i < NB; ++i) {
-                        const float f = b_scale[i].template next<true>(b_big[i]);
-#pragma unroll
-                        for (int j = 0; j < NS; ++j) {
-                            if constexpr (XBIG) rescale_rows(mm[i][j], settled, f, half);
-                            else rescale_columns(mm[i][j], settled, f);
-                        }
-                    }
-                }
-            }
-            typename C_::V bp[NB][PL];
+            bf8 b1[NB], b2[NB], b3[NB];
 #pragma unroll
             for (int i = 0; i < NB; ++i)
-                C_::split8(f4{br[0][i], br[1][i], br[2][i], br[3][i]}, f4{br[4][i], br[5][i], br[6][i], br[7][i]}, b_scale[i].now, bp[i]);
+                split8_bf16(f4{br[0][i], br[1][i], br[2][i], br[3][i]}, f4{br[4][i], br[5][i], br[6][i], br[7][i]}, b1[i], b2[i], b3[i]);
             ask_big();
 #pragma unroll
             for (int j = 0; j < NS; ++j) {
-                f4 lo = {sr[0][j], sr[1][j], sr[2][j], sr[3][j]}, hi = {sr[4][j], sr[5][j], sr[6][j], sr[7][j]};
-                if constexpr (F16) {
-                    const float s_big = __builtin_fmaxf(max_abs4(lo), max_abs4(hi));
-                    if (__any(f16_leaves(s_big * s_scale[j].now))) {
-                        const MfmaSettled settled;
-                        const float f = s_scale[j].template next<true>(s_big);
-#pragma unroll
-                        for (int i = 0; i < NB; ++i) {
-                            if constexpr (XBIG) rescale_columns(mm[i][j], settled, f);
-                            else rescale_rows(mm[i][j], settled, f, half);
-                        }
-                    }
-                } else {
-                    lo *= sign;
-                    hi *= sign;
-                }
-                typename C_::V cp[PL];
-                C_::split8(lo, hi, s_scale[j].now * sign, cp);
+                bf8 c1, c2, c3;
+                split8_bf16(f4{sr[0][j], sr[1][j], sr[2][j], sr[3][j]} * sign, f4{sr[4][j], sr[5][j], sr[6][j], sr[7][j]} * sign, c1, c2, c3);
                 if (j == NS - 1) ask_small();
 #pragma unroll
-                for (int i = 0; i < NB; ++i)
+                for (int i = 0; i < NB; ++i) {
                     // (x is the A operand: its index runs over the registers of a result)
-#pragma unroll
-                    for (int n = 0; n < C_::PRODUCTS; ++n) {
-                        if constexpr (XBIG) mm[i][j].mac(bp[i][C_::A[n]], cp[C_::B[n]]);
-                        else mm[i][j].mac(cp[C_::B[n]], bp[i][C_::A[n]]);
-                    }
+                    auto mac = [&](const bf8 &b, const bf8 &c) {
+                        if constexpr (XBIG) mm[i][j].mac(b, c);
+                        else mm[i][j].mac(c, b);
+                    };
+                    mac(b3[i], c1);
+                    mac(b2[i], c2);
+                    mac(b1[i], c3);
+                    mac(b2[i], c1);
+                    mac(b1[i], c2);
+                    mac(b1[i], c1);
+                }
             }
         }
         const MfmaSettled settled;
-        if constexpr (F16) {
-#pragma unroll
-            for (int i = 0; i < KB; ++i) x_bits[wave][KB * l32 + i] = f16_scale_bits(XBIG ? b_scale[i].now : s_scale[i % NS].now);
-        }
 
         // result register 4 q + c of a block: input index 8 q + 4 half + c, output index l32; input k0 + KB index + i, output o0 + OB index + j
         float *const P = a.ws + (size_t)part * (size_t)row_part_floats(K, O, a.s_loc) + (size_t)s * (size_t)(O * K);
@@ -2804,14 +2514,10 @@ hot_linear_wgrad_row_parts_kernel(LinearGradArgs a, int parts, int chunk)
             float *mine = turn[wave];
 #pragma unroll
             for (int g = 0; g < 16; ++g) {
-                const int m = mfma_row(g, half);
+                const int m = 8 * (g >> 2) + 4 * half + (g & 3);
                 typename Floats<KB>::V v;
 #pragma unroll
-                for (int i = 0; i < KB; ++i) {
-                    v[i] = XBIG ? mm[i][j % NS].read(settled)[g] : mm[j][i % NS].read(settled)[g];
-                    if constexpr (F16)
-                        v[i] = __builtin_amdgcn_ldexpf(v[i], 254 - x_bits[wave][KB * m + i] - f16_scale_bits(XBIG ? s_scale[j % NS].now : b_scale[j % NB].now));
-                }
+                for (int i = 0; i < KB; ++i) v[i] = XBIG ? mm[i][j % NS].read(settled)[g] : mm[j][i % NS].read(settled)[g];
                 *reinterpret_cast<typename Floats<KB>::V *>(mine + l32 * PITCH + KB * m) = v;
             }
             __syncthreads();
@@ -2996,11 +2702,8 @@ void row_parts_go(const RowPartsPlan &p, hipStream_t s, const LinearGradArgs &a,
     const long per_xcd = (tiles * a.s_loc * p.parts + kXcds - 1) / kXcds;
     const dim3 grid((unsigned)(kXcds * per_xcd)), block(64 * kRowPartWaves);
     const long step_rows = kRowPartRows * kRowPartWaves, chunk = ((p.rows_per_part + p.chunks - 1) / p.chunks + step_rows - 1) / step_rows * step_rows;
-    const bool f16 = (chunk < p.rows_per_part ? chunk : p.rows_per_part) >= kF16MinRowSum;
-    if (p.xbig && f16) hot_linear_wgrad_row_parts_kernel<true, true><<<grid, block, 0, s>>>(a, p.parts, (int)chunk);
-    else if (p.xbig) hot_linear_wgrad_row_parts_kernel<true, false><<<grid, block, 0, s>>>(a, p.parts, (int)chunk);
-    else if (f16) hot_linear_wgrad_row_parts_kernel<false, true><<<grid, block, 0, s>>>(a, p.parts, (int)chunk);
-    else hot_linear_wgrad_row_parts_kernel<false, false><<<grid, block, 0, s>>>(a, p.parts, (int)chunk);
+    if (p.xbig) hot_linear_wgrad_row_parts_kernel<true><<<grid, block, 0, s>>>(a, p.parts, (int)chunk);
+    else hot_linear_wgrad_row_parts_kernel<false><<<grid, block, 0, s>>>(a, p.parts, (int)chunk);
     const long threads = a.out_features * a.in_features / 4 + (a.mu_b ? (a.out_features + 3) / 4 : 0);
     hot_linear_wgrad_row_parts_finish_kernel<<<dim3((unsigned)((threads + 63) / 64)), dim3(64), 0, s>>>(a, p.parts);
 }

@@ -1396,3 +1396,85 @@ def test_tile_weight_gradients_of_infinite_and_huge_values(hot, rows, k, o, s):
     gmu, _ = _backward(hot, hot.hot_rng(seed=89, step=3, first_sample=1), x, dy, c, None, _workspace(hot, rows, k, o, s), s)
     P = [dy[i].double().t() @ x[i].double() for i in range(s)]
     _same_where_special(gmu, sum(P), sum(dy[i].double().abs().t() @ x[i].double().abs() for i in range(s)))
+
+
+# Factors of very different size in one sum, the large one beside a small partner or none: in every sixteen terms (at any of their
+# places) or once in a sum, early, in the middle, late.  What the pieces leave out and the accumulations round is relative to the products,
+# 2^-24 (3 + sqrt(six roundings for sixteen terms)) of the magnitude sum (8 for 3: biases, waves and parts add up on top), however
+# large a factor is whose partner is not.
+MIXED = [("each", 1e7), ("each", 1e9), ("first", 1e12), ("first", 1e30), ("middle", 1e22), ("last", 1e30)]
+
+
+def _mixed(big, small, dim, where, factor):
+    """Scales along `dim` of two tensors that are contracted over it: up in the first, down by as much (or to zero) in the second."""
+    n = big.shape[dim]
+    at = {"each": torch.arange(0, n, 16) + torch.arange((n + 15) // 16) % 16, "first": torch.tensor([3]), "middle": torch.tensor([n // 2]), "last": torch.tensor([n - 2])}[where]
+    at = at[at < n].to(DEV)
+    up, down = torch.ones(n, device=DEV), torch.ones(n, device=DEV)
+    up[at], down[at] = factor, (1.0 / factor if where == "each" else 0.0)
+    return up, down
+
+
+def _mixed_bound(n):
+    return 2.0 ** -24 * (8 + (6 * n / 16) ** 0.5)
+
+
+@pytest.mark.parametrize("rows,k,o,s,own,shape", [(2040, 100, 4092, 2, False, 1621), (2040, 532, 4092, 1, True, 821), (1530, 84, 5400, 2, False, 822),
+                                                  (1530, 84, 10800, 1, False, 841), (300, 100, 3702, 2, False, 412), (7260, 532, 540, 2, False, 812)])
+@pytest.mark.parametrize("large_weights", [False, True])
+def test_forward_of_factors_of_very_different_size(hot, rows, k, o, s, own, shape, large_weights):
+    assert hot.hot_linear_launch_shape(rows, k, o, s, 0, per_sample_x=own) == shape
+    worst = {}
+    for where, factor in MIXED:
+        g, c = _deep_case(rows + o, o, k)
+        x = torch.randn(*((s, rows, k) if own else (rows, k)), device=DEV, generator=g)
+        up, down = _mixed(x, c["mu_w"], 1, where, factor) if not own else _mixed(x[0], c["mu_w"], 1, where, factor)
+        w_by, x_by = (up, down) if large_weights else (down, up)
+        x, c["mu_w"], c["sigma_w"] = x * x_by, c["mu_w"] * w_by, c["sigma_w"] * w_by
+        rng, b_off = hot.hot_rng(seed=97, step=2, first_sample=1), (o * k + 3) // 4 * 4
+        y = torch.full((s, rows, o), float("nan"), device=DEV)
+        hot.hot_linear_forward_rng(rng, x, c["mu_w"], c["sigma_w"], c["mu_b"], c["sigma_b"], y, 0, b_off)
+        w, b = _materialised(hot, c, s, rng, 0, b_off)
+        for i in range(s):
+            xi = (x[i] if own else x).double()
+            e = float(((y[i] - (xi @ w[i].t() + b[i])).abs() / (xi.abs() @ w[i].abs().t() + b[i].abs())).max())
+            worst[where, factor] = max(worst.get((where, factor), 0.0), e)
+    print("  worst error / magnitude sum:", {m: "%.1e" % e for m, e in worst.items()}, "allowed %.1e" % _mixed_bound(k), flush=True)
+    assert all(e <= _mixed_bound(k) for e in worst.values())
+
+
+# (launch shape of the input gradients or 0, kernel shape of the weight gradients with a workspace: 0 tiles, else row parts)
+@pytest.mark.parametrize("rows,k,o,s,dx_shape,w_shape", [(7260, 2160, 540, 2, 841, 1051), (4673, 888, 208, 8, 421, 2021), (2040, 4092, 100, 2, 1621, 1041),
+                                                         (1530, 7000, 84, 2, 821, 1021), (1030, 3000, 3004, 1, 0, 0), (800, 3000, 3002, 2, 0, 0)])
+@pytest.mark.parametrize("large_first", [True, False])
+def test_backward_of_factors_of_very_different_size(hot, rows, k, o, s, dx_shape, w_shape, large_first):
+    """large_first: dy against the weights (input gradients), x against dy (weight gradients); else the other way round."""
+    assert hot.hot_linear_launch_shape(rows, k, o, s, 1, per_sample_x=True) == dx_shape
+    assert hot.hot_linear_kernel_shape(rows, k, o, s, 2, per_sample_x=True) == w_shape
+    worst = {}
+    rng = hot.hot_rng(seed=101, step=2, first_sample=1)
+    for where, factor in MIXED:
+        g, c = _deep_case(rows + o, o, k)
+        dy = torch.randn(s, rows, o, device=DEV, generator=g)
+        x = torch.randn(s, rows, k, device=DEV, generator=g)
+        up, down = _mixed(dy[0], c["mu_w"], 1, where, factor)
+        d_by, w_by = (up, down) if large_first else (down, up)
+        d2, c2 = dy * d_by, {"mu_w": c["mu_w"] * w_by[:, None], "sigma_w": c["sigma_w"] * w_by[:, None]}
+        c2["mu_b"], c2["sigma_b"] = c["mu_b"], c["sigma_b"]
+        dx = torch.full((s, rows, k), float("nan"), device=DEV)
+        _backward(hot, rng, x, d2, c2, dx, _workspace(hot, rows, k, o, s), s)
+        w, _ = _materialised(hot, c2, s, rng, 0, o * k)
+        for i in range(s):
+            e = float(((dx[i] - d2[i].double() @ w[i]).abs() / (d2[i].double().abs() @ w[i].abs())).max())
+            worst["dx", where, factor] = max(worst.get(("dx", where, factor), 0.0), e / _mixed_bound(o))
+        del d2, dx, w
+        up, down = _mixed(x[0], dy[0], 0, where, factor)
+        x_by, d_by = (up, down) if large_first else (down, up)
+        x2, d2 = x * x_by[:, None], dy * d_by[:, None]
+        gmu, _ = _backward(hot, rng, x2, d2, c, None, _workspace(hot, rows, k, o, s), s)
+        P = sum(d2[i].double().t() @ x2[i].double() for i in range(s))
+        mag = sum(d2[i].double().abs().t() @ x2[i].double().abs() for i in range(s))
+        worst["dw", where, factor] = float(((gmu - P).abs() / mag).max()) / _mixed_bound(rows)
+        del x2, d2, P, mag
+    print("  worst error / allowed:", {m: "%.1e" % e for m, e in worst.items()}, flush=True)
+    assert all(e <= 1.0 for e in worst.values())
