@@ -2010,63 +2010,79 @@ constexpr int kTileRows = 16;         // rows per step
 constexpr int kTurnPitch = 36;        // floats per row of a wave's 32 x 32 block on its way out (16-byte aligned rows)
 
 
-// Those of four sums over the rows r_lo .. r_hi - 1 that the bf16 pieces left as NaN, from fp32 products (see deep_plain_sum).
-__device__ __forceinline__ void row_parts_plain_sums(const LinearGradArgs &a, int s, long o, long k, long r_lo, long r_hi, float *p)
+// The weight gradients of a wave's 64 inputs x 64 outputs (from k0, o0) that the tile kernel left as NaN, again from fp32 products on
+// the matrix instruction: an infinite factor, and one whose pieces overflow, leaves NaN where those give infinity or a number.
+// Rows straight from memory, a block of 32 x 32 at a time and only those that hold a NaN.  Called by whole waves.  What it takes is
+// bounded by the layer: every gradient again (a row of dy that is NaN) makes 1024 x 2560 x 2560 x 2 samples 0.21 -> 1.4 ms, 300 x 2160 x
+// 8640 x 2 0.24 -> 1.4, 2048 x 4096 x 4096 x 2 0.8 -> 5.5 (a lane to each sum and a load to each factor: 36, 17 and 159).
+__device__ __forceinline__ void wgrad_tile_again(const LinearGradArgs &a, long o0, long k0)
 {
-    const float *x = a.x + (size_t)s * (size_t)a.x_sample_stride + (size_t)k;
-    const float *dy = a.dy + (size_t)s * (size_t)a.rows * (size_t)a.out_features + (size_t)o;
+    const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
+    const long K = a.in_features, O = a.out_features;
+    const int R = (int)a.rows;
 #pragma unroll 1
-    for (int c = 0; c < 4; ++c) {
-        if (p[c] == p[c]) continue;
-        float sum = 0.0f;
-#pragma unroll 1
-        for (long r = r_lo; r < r_hi && sum == sum; ++r) sum = __builtin_fmaf(dy[(size_t)r * (size_t)a.out_features], x[(size_t)r * (size_t)a.ldx + (size_t)c], sum);
-        p[c] = sum;
-    }
-}
-
-// The weight gradients (o, k .. k + 3) that the tile kernel left as NaN, all samples again from fp32 products.
-__device__ __forceinline__ void wgrad_tile_plain(const LinearGradArgs &a, long o, long k)
-{
-    const long at = o * a.in_features + k;
-    f4 om = load4<true, false>(a.gmu_w + at), os = load4<true, false>(a.gsig_w + at);
-    float again[4], gm[4] = {0.0f, 0.0f, 0.0f, 0.0f}, gs[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    bool any = false;
+    for (int n = 0; n < 4; ++n) {
+        const long k = k0 + 32 * (n >> 1), o = o0 + 32 * (n & 1) + l32;
+        auto inside = [&](int q) { return o < O && k + 8 * q + 4 * half < K; };
+        auto at = [&](int q) { return o * K + k + 8 * q + 4 * half; };
+        unsigned bad = 0;                       // bit 4 q + c: weight (o, k + 8 q + 4 half + c)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const bool bad = om[c] != om[c] || os[c] != os[c];
-        any |= bad;
-        again[c] = bad ? __builtin_nanf("") : 0.0f;       // (what row_parts_plain_sums takes for a sum to form)
-    }
-    if (!any) return;
-#pragma unroll 1
-    for (int s = 0; s < a.s_loc; ++s) {
-        float p[4] = {again[0], again[1], again[2], again[3]};
-        row_parts_plain_sums(a, s, o, k, 0, a.rows, p);
-        const f4 e = eps_quad(a.weight_quad0 + (at >> 2), s, a.rng);
+        for (int q = 0; q < 4; ++q)
+            if (inside(q)) {
+                const f4 om = load4<true, false>(a.gmu_w + at(q)), os = load4<true, false>(a.gsig_w + at(q));
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            gm[c] += p[c];
-            gs[c] = __builtin_fmaf(p[c], e[c], gs[c]);
+                for (int c = 0; c < 4; ++c) bad |= (om[c] != om[c] || os[c] != os[c] ? 1u : 0u) << (4 * q + c);
+            }
+        if (__builtin_amdgcn_ballot_w64(bad != 0) == 0) continue;
+        float gm[16] = {}, gs[16] = {};
+#pragma unroll 1
+        for (int s = 0; s < a.s_loc; ++s) {
+            // (columns outside the layer and rows behind the last take the nearest ones; the latter count as zeros)
+            const float *x = a.x + (size_t)s * (size_t)a.x_sample_stride + (size_t)(k + l32 < K ? k + l32 : K - 1);
+            const float *dy = a.dy + (size_t)s * (size_t)R * (size_t)O + (size_t)(o < O ? o : O - 1);
+            Acc32x32 m;
+#pragma unroll 1
+            for (int r0 = half; r0 < R + half; r0 += 16) {
+                float xv[8], dv[8];
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    const int r = r0 + 2 * t, from = r < R ? r : R - 1;
+                    xv[t] = x[(size_t)from * (size_t)a.ldx];
+                    dv[t] = dy[(size_t)from * (size_t)O];
+                    xv[t] = r < R ? xv[t] : 0.0f;
+                    dv[t] = r < R ? dv[t] : 0.0f;
+                }
+#pragma unroll
+                for (int t = 0; t < 8; ++t) m.mac(xv[t], dv[t]);
+            }
+            const MfmaSettled settled;
+            const f16v p = m.read(settled);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (inside(q)) {
+                    const f4 e = eps_quad(a.weight_quad0 + (at(q) >> 2), s, a.rng);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        gm[4 * q + c] += p[4 * q + c];
+                        gs[4 * q + c] = __builtin_fmaf(p[4 * q + c], e[c], gs[4 * q + c]);
+                    }
+                }
         }
-    }
-    const f4 m4 = load4<true, false>(a.mu_w + at), sd4 = load4<true, false>(a.sigma_w + at);
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
-        if (again[c] != again[c]) {
-            float pm, ps;
-            finish_pair(gm[c], gs[c], m4[c], sd4[c], (float)a.g, (float)a.k, pm, ps);
-            om[c] = pm;
-            os[c] = ps;
-        }
-    store4<true, false>(a.gmu_w + at, om);
-    store4<true, false>(a.gsig_w + at, os);
+        for (int q = 0; q < 4; ++q)
+            if (inside(q)) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (bad >> (4 * q + c) & 1u)
+                        finish_pair(gm[4 * q + c], gs[4 * q + c], a.mu_w[at(q) + c], a.sigma_w[at(q) + c], (float)a.g, (float)a.k, a.gmu_w[at(q) + c], a.gsig_w[at(q) + c]);
+            }
+    }
 }
 
 // WHOLE: every 32 x 32 block of the workgroup's tile reaches into the layer (no block is skipped, no column masked).
-// XB, DB: the four buffers of 16 rows x 128 columns of x and of dy.
+// XB, DB: the four buffers of 16 rows x 128 columns of x and of dy.  Returns whether the wave left a NaN.
 template <bool WHOLE>
-__device__ __forceinline__ void wgrad_tile_body(const LinearGradArgs &a, lds_float *const (&XB)[4], lds_float *const (&DB)[4], long o0, long k0)
+__device__ __forceinline__ bool wgrad_tile_body(const LinearGradArgs &a, lds_float *const (&XB)[4], lds_float *const (&DB)[4], long o0, long k0)
 {
     constexpr int WK = 2, TK = kTileSide, TO = kTileSide;         // 2 x 2 waves of 64 inputs x 64 outputs
     const int t = threadIdx.x, lane = t & 63;
@@ -2199,7 +2215,7 @@ __device__ __forceinline__ void wgrad_tile_body(const LinearGradArgs &a, lds_flo
     // pairs before left in the gradient arrays (the same thread holds the same weights every time); the last pair
     // applies the scale and the KL part.
     float gb_m[2] = {0.0f, 0.0f}, gb_s[2] = {0.0f, 0.0f};
-    unsigned long long special = 0;          // the lanes that met a NaN
+    float special = 0.0f;                    // NaN once this lane has left a NaN (or an infinity, which only costs a look) in the last pass
     lds_float *const mine = XB[wave];        // a buffer per wave for turning its blocks on their way out
     for (int s0 = 0; s0 < a.s_loc; s0 += 2) {
         const bool two = s0 + 1 < a.s_loc, first = s0 == 0, last = s0 + 2 >= a.s_loc;
@@ -2208,6 +2224,7 @@ __device__ __forceinline__ void wgrad_tile_body(const LinearGradArgs &a, lds_flo
         all_rows(s0, m0, sb0);
         if (two) all_rows(s0 + 1, m1, sb1);
         const MfmaSettled settled;
+        special = 0.0f;                      // (not kept through the row loops)
 
         long o0e = o0 + 64 * wo, k0e = k0 + 64 * wk;
         asm volatile("" : "+v"(o0e), "+v"(k0e));       // (so that the addresses below are formed here, not ahead of the row loops)
@@ -2276,8 +2293,10 @@ __device__ __forceinline__ void wgrad_tile_body(const LinearGradArgs &a, lds_flo
                         }
                         store4<true, false>(a.gmu_w + at, om);
                         store4<true, false>(a.gsig_w + at, os);
-                        const f4 both = om + os;       // (NaN wherever either is; infinities of two signs only cost a look)
-                        special |= __builtin_amdgcn_ballot_w64(!(both[0] == both[0] && both[1] == both[1] && both[2] == both[2] && both[3] == both[3]));
+                        // (a product that is not finite shows in os; looking at om as well, or in lane masks, costs the row loops
+                        // registers: 300 x 2160 x 8640 x 2 230 us, 235 and 239)
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) special = __builtin_fmaf(os[c], 0.0f, special);
                     }
                 }
             }
@@ -2299,15 +2318,6 @@ __device__ __forceinline__ void wgrad_tile_body(const LinearGradArgs &a, lds_flo
         }
         everything_arrived_then_barrier();       // (the buffers go back to the rows of the next pair)
     }
-    // An infinite factor, and one whose pieces overflow, leaves NaN where fp32 products give infinity or a number (in a loop of its own, so
-    // that no accumulator lives through it; the thread that stored a quad looks at it again).
-    if (special) {
-#pragma unroll 1
-        for (int n = 0; n < 16; ++n) {
-            const long oo = o0 + 64 * wo + 32 * (n >> 2 & 1) + 8 * (n & 3) + (lane >> 3), k = k0 + 64 * wk + 32 * (n >> 3) + 4 * (lane & 7);
-            if (oo < O && k < K) wgrad_tile_plain(a, oo, k);
-        }
-    }
     if (bias_wave && half == 0) {
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
@@ -2320,6 +2330,7 @@ __device__ __forceinline__ void wgrad_tile_body(const LinearGradArgs &a, lds_flo
             }
         }
     }
+    return __builtin_amdgcn_ballot_w64(special != special) != 0;
 }
 
 __global__ void __launch_bounds__(256, 2)
@@ -2347,8 +2358,14 @@ hot_linear_wgrad_tile_kernel(LinearGradArgs a)
     const long o0 = (8 * (band < bands ? band : bands) + within % height) * TO;
     const long k0 = (within / height) * TK;
     // (uniform over the workgroup, so all its waves meet at the same barriers)
-    if (k0 + TK <= K && o0 + TO <= O) wgrad_tile_body<true>(a, XB, DB, o0, k0);
-    else wgrad_tile_body<false>(a, XB, DB, o0, k0);
+    const bool special = k0 + TK <= K && o0 + TO <= O ? wgrad_tile_body<true>(a, XB, DB, o0, k0) : wgrad_tile_body<false>(a, XB, DB, o0, k0);
+    if (special) {
+        // (the arguments read once more, so that none is kept for this through the row loops; the last barrier's wait covers the wave's own stores)
+        unsigned long long args = (unsigned long long)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(args));
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        wgrad_tile_again(*reinterpret_cast<const LinearGradArgs *>(args), o0 + 64 * (wave / 2), k0 + 64 * (wave % 2));
+    }
 }
 
 // Whether the kernel above can address this problem (its windows take 32-bit byte offsets).  Any number of outputs: a quad of dy
@@ -2407,6 +2424,21 @@ struct Floats<4> {
 
 // floats of one part's share of the workspace: per sample the weights, then the biases (a multiple of four, so that quads stay aligned)
 inline __host__ __device__ long row_part_floats(long K, long O, int s_loc) { return (O * K + ((O + 3) & ~3L)) * s_loc; }
+
+// Those of four sums over the rows r_lo .. r_hi - 1 that the bf16 pieces left as NaN, from fp32 products (see deep_plain_sum).
+__device__ __forceinline__ void row_parts_plain_sums(const LinearGradArgs &a, int s, long o, long k, long r_lo, long r_hi, float *p)
+{
+    const float *x = a.x + (size_t)s * (size_t)a.x_sample_stride + (size_t)k;
+    const float *dy = a.dy + (size_t)s * (size_t)a.rows * (size_t)a.out_features + (size_t)o;
+#pragma unroll 1
+    for (int c = 0; c < 4; ++c) {
+        if (p[c] == p[c]) continue;
+        float sum = 0.0f;
+#pragma unroll 1
+        for (long r = r_lo; r < r_hi && sum == sum; ++r) sum = __builtin_fmaf(dy[(size_t)r * (size_t)a.out_features], x[(size_t)r * (size_t)a.ldx + (size_t)c], sum);
+        p[c] = sum;
+    }
+}
 
 template <bool XBIG>
 __global__ void __launch_bounds__(64 * kRowPartWaves, 2)

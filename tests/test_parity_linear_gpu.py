@@ -1478,3 +1478,31 @@ def test_backward_of_factors_of_very_different_size(hot, rows, k, o, s, dx_shape
         del x2, d2, P, mag
     print("  worst error / allowed:", {m: "%.1e" % e for m, e in worst.items()}, flush=True)
     assert all(e <= 1.0 for e in worst.values())
+
+
+# whole tiles and ragged ones; a row of dy that is NaN touches every gradient, late in the sum
+@pytest.mark.parametrize("rows,k,o,s", [(1024, 2560, 2560, 2), (1024, 2560, 2561, 2)])
+def test_tile_weight_gradients_of_a_row_that_is_nan_take_bounded_time(hot, rows, k, o, s):
+    """Sums that are NaN are formed again; that goes through the rows again at the fp32 instruction's rate, some 7 times as long as without a
+    NaN (20 allowed; a lane to a sum took 180 times)."""
+    g, c = _deep_case(rows + o, o, k)
+    x, dy = torch.randn(rows, k, device=DEV, generator=g), torch.randn(s, rows, o, device=DEV, generator=g)
+    rng = hot.hot_rng(seed=103, step=2, first_sample=1)
+
+    def fastest():
+        times = []
+        for _ in range(4):
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            begin.record()
+            gmu, gsig = _backward(hot, rng, x, dy, c, None, None, s)
+            end.record()
+            torch.cuda.synchronize()
+            times.append(begin.elapsed_time(end))
+        return min(times), gmu, gsig
+
+    clean, _, _ = fastest()
+    dy[0, rows - 2] = float("nan")
+    again, gmu, gsig = fastest()
+    print("  %.3f ms, with a row that is NaN %.3f" % (clean, again), flush=True)
+    assert bool(torch.isnan(gmu).all()) and bool(torch.isnan(gsig).all())
+    assert again <= 20.0 * clean
