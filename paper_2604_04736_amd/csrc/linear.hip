@@ -2362,7 +2362,9 @@ hot_linear_wgrad_tile_kernel(LinearGradArgs a)
     if (special) {
         // (the arguments read once more, so that none is kept for this through the row loops; the last barrier's wait covers the wave's own stores)
         unsigned long long args = (unsigned long long)__builtin_amdgcn_kernarg_segment_ptr();
+#ifdef __OPTIMIZE__       // (without optimisation nothing is kept anyhow, and the address is in no scalar register)
         asm volatile("" : "+s"(args));
+#endif
         const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         wgrad_tile_again(*reinterpret_cast<const LinearGradArgs *>(args), o0 + 64 * (wave / 2), k0 + 64 * (wave % 2));
     }
