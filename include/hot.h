@@ -280,7 +280,8 @@ int hot_linear_forward_rng(const hot_linear_desc *desc, const hot_rng *rng, cons
  * (from 129 rows on, at least 512 tiles of 128 inputs x 128 outputs, or from 256 rows on at least 140) take their
  * weight gradients from a kernel that stages x and dy through LDS and multiplies bf16 pieces of both, as the
  * forward call's large tiles do (up to 180 TFLOP/s of fp32 work); it needs
- * rows * max(ldx, out_features) * 4 below 4 GiB, else the first kernel runs; with more
+ * rows * max(ldx, out_features) * 4 below 4 GiB and, with out_features no multiple of 4, at least 230 tiles (below 450 rows 320,
+ * below 208 rows 1100) and as many rows to a sum in the first kernel, else the first kernel runs; with more
  * than two samples it adds up pairs of samples in grad_mu_w and grad_sigma_w themselves.  All of these kernels
  * scale the sums and add the KL part in fp32 (g * sum + k * mu, g * sum + k * (sigma - 1/sigma) with the hardware's
  * reciprocal: 1e-7 of each term), where hot_backward does it in fp64.  Against

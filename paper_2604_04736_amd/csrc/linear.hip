@@ -2372,8 +2372,7 @@ hot_linear_wgrad_tile_kernel(LinearGradArgs a)
 
 // Whether the kernel above can address this problem (its windows take 32-bit byte offsets).  Any number of outputs: a quad of dy
 // that reaches over the end of a row brings columns that are never stored, loads need an alignment of 4 bytes only, and the check at
-// the end of the window is per 4 bytes (3946 x 3288 x 1506 x 2 samples, forward and backward: 2104 -> 1584 us against the first kernel,
-// 1000 x 2048 x 2049 x 2: a third of its distance from 64 bits).
+// the end of the window is per 4 bytes.  (Where such layers take it: wgrad_shape.)
 inline bool wgrad_tile_fits(const hot_linear_desc *d)
 {
     const unsigned long long lim = 0xFFFFFFF0ull;
@@ -3673,6 +3672,19 @@ WgradShape wgrad_shape_with(const hot_linear_desc *d, int64_t ws_bytes, bool wid
     return w;
 }
 
+// the least tiles with which the tile kernel takes outputs that are no multiple of four (measured in wgrad_shape)
+inline long wgrad_tile_ragged_tiles(long rows) { return rows >= 450 ? 230 : rows >= 208 ? 320 : 1100; }
+
+// the shape of the kernel above
+WgradShape wgrad_first_shape(const hot_linear_desc *d, int64_t ws_bytes)
+{
+    if (ws_bytes != 0 && d->rows >= 8192) {     // with parts, smaller layers afford the wide tiles too (16640 x 192 x 768: 51 -> 57 TFLOP/s)
+        const WgradShape w = wgrad_shape_with(d, ws_bytes, true);
+        if (w.parts > 1) return w;              // (else the workspace was too small for that)
+    }
+    return wgrad_shape_with(d, ws_bytes, false);
+}
+
 WgradShape wgrad_shape(const hot_linear_desc *d, int64_t ws_bytes)
 {
     // Large layers at hundreds of rows and more: the kernel with tiles of 128 x 128.  Two workgroups share a compute
@@ -3683,18 +3695,21 @@ WgradShape wgrad_shape(const hot_linear_desc *d, int64_t ws_bytes)
     // the chip better, as do few-tile layers whose rows a workspace spreads over the chip).
     const long tile_count = wgrad_tile_count(d);
     const bool fills = tile_count >= 512 || (tile_count >= 140 && d->rows >= 256 && !(ws_bytes != 0 && d->rows >= 8192));
-    if (wgrad_tile_fits(d) && d->rows >= kSlab4MinRows && fills) {
+    // Rows of dy off the 16-byte grid: only where the kernel above adds up all rows in one sum too (there this one is 0.82-0.88 times as far
+    // from 64 bits; against two shorter sums 1.2 times, 1517 x 6448 x 1397 x 4 samples 5.0e-7 and 6.2e-7, against four 1.85 times), and
+    // where it is faster.  From 450 rows and 230 tiles on 1.03-2.1x (788 x 1340 x 3429 x 3 290 -> 244 us, 473 x 5560 x 6805 x 2 1246 ->
+    // 584; 455 x 272 x 8421 x 4, 198 tiles, 143 -> 155; 440 x 3964 x 1051 x 1, 279, 57 -> 60), from 208 rows and 320 tiles on 1.01-1.8x (212 x 1632 x 5714 x 4 242 -> 210; 332 x
+    // 788 x 4859 x 2, 266 tiles, 76 -> 86), with fewer rows from 1100 tiles on 1.04-1.5x (134 x 7800 x 1149 x 3, 549, 122 -> 159).
+    const WgradShape first = wgrad_first_shape(d, ws_bytes);
+    const bool suits = (d->out_features & 3) == 0 || (first.split * first.parts == 1 && tile_count >= wgrad_tile_ragged_tiles(d->rows));
+    if (wgrad_tile_fits(d) && d->rows >= kSlab4MinRows && fills && suits) {
         WgradShape w = wgrad_shape_with(d, 0, false);
         w.parts = 1;
         w.rows_per_part = 0;
         w.tile = true;
         return w;
     }
-    if (ws_bytes != 0 && d->rows >= 8192) {     // with parts, smaller layers afford the wide tiles too (16640 x 192 x 768: 51 -> 57 TFLOP/s)
-        const WgradShape w = wgrad_shape_with(d, ws_bytes, true);
-        if (w.parts > 1) return w;              // (else the workspace was too small for that)
-    }
-    return wgrad_shape_with(d, ws_bytes, false);
+    return first;
 }
 
 // Most rows that a wave of the row parts may add up in one sum.  In as many rows the bf16 pieces are 0.75-0.85 times as far from 64
