@@ -2426,21 +2426,6 @@ struct Floats<4> {
 // floats of one part's share of the workspace: per sample the weights, then the biases (a multiple of four, so that quads stay aligned)
 inline __host__ __device__ long row_part_floats(long K, long O, int s_loc) { return (O * K + ((O + 3) & ~3L)) * s_loc; }
 
-// Those of four sums over the rows r_lo .. r_hi - 1 that the bf16 pieces left as NaN, from fp32 products (see deep_plain_sum).
-__device__ __forceinline__ void row_parts_plain_sums(const LinearGradArgs &a, int s, long o, long k, long r_lo, long r_hi, float *p)
-{
-    const float *x = a.x + (size_t)s * (size_t)a.x_sample_stride + (size_t)k;
-    const float *dy = a.dy + (size_t)s * (size_t)a.rows * (size_t)a.out_features + (size_t)o;
-#pragma unroll 1
-    for (int c = 0; c < 4; ++c) {
-        if (p[c] == p[c]) continue;
-        float sum = 0.0f;
-#pragma unroll 1
-        for (long r = r_lo; r < r_hi && sum == sum; ++r) sum = __builtin_fmaf(dy[(size_t)r * (size_t)a.out_features], x[(size_t)r * (size_t)a.ldx + (size_t)c], sum);
-        p[c] = sum;
-    }
-}
-
 template <bool XBIG>
 __global__ void __launch_bounds__(64 * kRowPartWaves, 2)
 hot_linear_wgrad_row_parts_kernel(LinearGradArgs a, int parts, int chunk)
@@ -2498,7 +2483,6 @@ hot_linear_wgrad_row_parts_kernel(LinearGradArgs a, int parts, int chunk)
     };
     ask_big();
     ask_small();
-    unsigned long long special = 0;       // the lanes that met a NaN
     // A long part is added up in chunks of `chunk` rows (a multiple of 64), each into accumulators of its own and then to what the
     // chunks before left in the workspace (the same thread holds the same sums every time).  What is sent for beyond the end
     // of a chunk are the first rows of the next.
@@ -2567,18 +2551,8 @@ hot_linear_wgrad_row_parts_kernel(LinearGradArgs a, int parts, int chunk)
                     if (c_lo != r_lo) sum += load4<true, false>(P + o * K + k);
                     store4<true, false>(P + o * K + k, sum);
                 }
-                special |= __builtin_amdgcn_ballot_w64(!(sum[0] == sum[0] && sum[1] == sum[1] && sum[2] == sum[2] && sum[3] == sum[3]));
             }
             __syncthreads();
-        }
-    }
-    if (special) {              // (in a loop of its own, as in the kernel for tens to hundreds of rows)
-        float *const P = a.ws + (size_t)part * (size_t)row_part_floats(K, O, a.s_loc) + (size_t)s * (size_t)(O * K);
-#pragma unroll 1
-        for (int i = 0; i < OB * KB; ++i) {
-            const int idx = i % KB * 64 * kRowPartWaves + (int)threadIdx.x;
-            const long o = o0 + OB * (idx / (TK / 4)) + i / KB, k = k0 + 4 * (idx % (TK / 4));
-            if (o < O && k < K) row_parts_plain_sums(a, s, o, k, r_lo, r_hi, P + o * K + k);
         }
     }
     if (bias_tile) {            // uniform over the workgroup
@@ -2596,6 +2570,50 @@ hot_linear_wgrad_row_parts_kernel(LinearGradArgs a, int parts, int chunk)
                  (size_t)s * (size_t)((O + 3) & ~3L) + (size_t)o0 + threadIdx.x] = sum;
         }
     }
+}
+
+// Quad q of a sample's sums where the parts add up to NaN: parts that hold a NaN (an infinite factor, and one whose pieces overflow, leaves
+// one) are formed again there, from fp32 products.  A wave's lanes read consecutive quads of a row of x and the same factor of dy.
+// A row of dy that is NaN, late in a part, makes 7260 x 2160 x 540 x 2 samples 0.22 -> 0.60 ms and 16640 x 192 x 768 x 2 0.086 -> 0.23; in
+// the kernel above, a lane to each sum with rows across its lanes, it was 25.7 and 4.7.
+__device__ __forceinline__ f4 row_parts_again(const LinearGradArgs &a, int s, long q, int parts, const float *theirs, size_t per_part)
+{
+    const long K = a.in_features, O = a.out_features, o = 4 * q / K, k = 4 * q - o * K;
+    const float *x = a.x + (size_t)s * (size_t)a.x_sample_stride + (size_t)k, *dy = a.dy + (size_t)s * (size_t)a.rows * (size_t)O + (size_t)o;
+    f4 P = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+    for (int p = 0; p < parts; ++p) {
+        f4 u = load4<true, false>(theirs + (size_t)p * per_part);
+        if (u[0] != u[0] || u[1] != u[1] || u[2] != u[2] || u[3] != u[3]) {
+            const long lo = p * a.rows_per_part, hi = lo + a.rows_per_part < a.rows ? lo + a.rows_per_part : a.rows;
+            f4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+            bool open = true;                   // a sum that is to be formed again is not NaN so far
+#pragma unroll 1
+            for (long r = lo; r < hi && open; r += 4) {
+                f4 xv[4];
+                float dv[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const size_t from = (size_t)(r + t < hi ? r + t : hi - 1);
+                    xv[t] = load4<true, false>(x + from * (size_t)a.ldx);
+                    dv[t] = dy[from * (size_t)O];
+                }
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        if (r + t < hi) v[c] = __builtin_fmaf(dv[t], xv[t][c], v[c]);
+                open = false;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) open |= u[c] != u[c] && v[c] == v[c];
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) u[c] = u[c] != u[c] ? v[c] : u[c];
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) P[c] += u[c];
+    }
+    return P;
 }
 
 // Adds the parts in a fixed order, draws eps and finishes the gradients: thread q owns quad q of the O*K weights, the threads
@@ -2628,6 +2646,7 @@ hot_linear_wgrad_row_parts_finish_kernel(LinearGradArgs a, int parts)
             }
 #pragma unroll
         for (int c = 0; c < 4; ++c) P[c] = (of[0][c] + of[1][c]) + (of[2][c] + of[3][c]);
+        if (weights && (P[0] != P[0] || P[1] != P[1] || P[2] != P[2] || P[3] != P[3])) P = row_parts_again(a, s, q, parts, theirs, per_part);
         const f4 e = eps_quad(weights ? a.weight_quad0 + q : a.bias_quad0 + b, s, a.rng);
 #pragma unroll
         for (int c = 0; c < 4; ++c) {

@@ -1480,11 +1480,13 @@ def test_backward_of_factors_of_very_different_size(hot, rows, k, o, s, dx_shape
     assert all(e <= 1.0 for e in worst.values())
 
 
-# whole tiles and ragged ones; a row of dy that is NaN touches every gradient, late in the sum
-@pytest.mark.parametrize("rows,k,o,s", [(1024, 2560, 2560, 2), (1024, 2560, 2561, 2)])
-def test_tile_weight_gradients_of_a_row_that_is_nan_take_bounded_time(hot, rows, k, o, s):
-    """Sums that are NaN are formed again; that goes through the rows again at the fp32 instruction's rate, some 7 times as long as without a
-    NaN (20 allowed; a lane to a sum took 180 times)."""
+# tiles, whole and ragged, and row parts; a row of dy that is NaN touches every gradient, late in the sum
+@pytest.mark.parametrize("rows,k,o,s,parts", [(1024, 2560, 2560, 2, False), (1000, 2560, 2561, 2, False), (7260, 2160, 540, 2, True), (3000, 888, 206, 4, True)])
+def test_weight_gradients_of_a_row_that_is_nan_take_bounded_time(hot, rows, k, o, s, parts):
+    """Sums that are NaN are formed again; that goes through the rows again at the fp32 instruction's rate or with coalesced loads, some 7 and
+    3 times as long as without a NaN (20 allowed; a lane to a sum took 180 and 120 times)."""
+    assert not parts or hot.hot_linear_kernel_shape(rows, k, o, s, 2) > 0
+    workspace = _workspace(hot, rows, k, o, s) if parts else None
     g, c = _deep_case(rows + o, o, k)
     x, dy = torch.randn(rows, k, device=DEV, generator=g), torch.randn(s, rows, o, device=DEV, generator=g)
     rng = hot.hot_rng(seed=103, step=2, first_sample=1)
@@ -1494,7 +1496,7 @@ def test_tile_weight_gradients_of_a_row_that_is_nan_take_bounded_time(hot, rows,
         for _ in range(4):
             begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
             begin.record()
-            gmu, gsig = _backward(hot, rng, x, dy, c, None, None, s)
+            gmu, gsig = _backward(hot, rng, x, dy, c, None, workspace, s)
             end.record()
             torch.cuda.synchronize()
             times.append(begin.elapsed_time(end))
