@@ -1297,19 +1297,29 @@ def test_backward_of_infinite_and_huge_gradients(hot):
     _same_where_special(gmu, sum(P), sum(mag))
 
 
-# The kernels that multiply fp16 pieces: the contraction of the slab kernel's launch shapes from 80 on (76: bf16 pieces), forward and input
-# gradients, weight gradients in tiles (from 768 rows on) and in row parts (1024 rows to a sum and more), tile edges among the sizes.
-F16_FORWARD = [(1030, 76, 4100, 2, False), (1030, 80, 4100, 2, False), (1030, 84, 4100, 2, True), (2050, 532, 2052, 2, False), (7260, 100, 540, 2, True),
-               (1025, 300, 9000, 1, True), (300, 100, 7001, 2, False), (300, 100, 7001, 1, True), (513, 260, 8190, 3, False)]
-F16_BACKWARD = [(1030, 4096, 76, 2), (1030, 4096, 80, 2), (1030, 4100, 300, 2), (2050, 2052, 532, 2), (7260, 540, 100, 2), (3000, 260, 212, 1),
-                (300, 7004, 100, 2), (767, 3000, 3004, 1), (768, 3000, 3004, 2)]
+def _pieces_bound(n):
+    """Of a sum over n products, relative to its magnitude sum: the pieces leave out 3 * 2^-24 of a product, each of six accumulations for
+    sixteen products rounds by 2^-24 of what has been added up, in no particular direction (their square root), and five more
+    roundings (bias, waves, parts, samples, the result) come on top."""
+    return 2.0 ** -24 * (8 + (6 * n / 16) ** 0.5)
 
 
-@pytest.mark.parametrize("rows,k,o,s,own", F16_FORWARD)
-def test_forward_from_fp16_pieces_over_many_decades(hot, rows, k, o, s, own):
+# Blocks of sixteen indices many decades apart, against the kernels that cut both factors into pieces: with the launch shape of the forward
+# call or the input gradients (0: smaller tiles run) and the kernel shape of the weight gradients with a workspace (0: tiles of 128 x
+# 128, else row parts: 1000 x chunks + 10 x parts + orientation).  Tile edges among the sizes; 1460 rows to a part in the last of row parts.
+DECADES_FORWARD = [(1030, 76, 4100, 2, False, 412), (1030, 80, 4100, 2, False, 412), (1030, 84, 4100, 2, True, 421), (2050, 532, 2052, 2, False, 412),
+                   (7260, 100, 540, 2, True, 811), (1025, 300, 9000, 1, True, 421), (300, 100, 7001, 2, False, 0), (300, 100, 7001, 1, True, 0),
+                   (513, 260, 8190, 3, False, 1412), (2040, 100, 4092, 2, True, 1621), (1530, 84, 10800, 1, False, 841), (1530, 84, 5400, 2, False, 822)]
+DECADES_BACKWARD = [(1030, 4096, 76, 2, 411, 1021), (1030, 4096, 80, 2, 411, 1021), (1030, 4100, 300, 2, 421, 1031), (2050, 2052, 532, 2, 411, 1031),
+                    (7260, 540, 100, 2, 811, 1130), (3000, 260, 212, 1, 0, 1160), (300, 7004, 100, 2, 0, 1011), (767, 3000, 3004, 1, 0, 0),
+                    (768, 3000, 3004, 2, 0, 0), (2040, 4092, 100, 2, 1621, 1041), (7260, 2160, 540, 2, 841, 1051)]
+
+
+@pytest.mark.parametrize("rows,k,o,s,own,shape", DECADES_FORWARD)
+def test_forward_from_pieces_over_many_decades(hot, rows, k, o, s, own, shape):
     """Values of one block of sixteen indices within a few decades, blocks eight decades apart (the weights the other way, so that every
-    block counts), rows and outputs twenty decades apart.  Bound: 2^-22 left out, 2^-23 of cutting per factor, and the roundings of the
-    accumulations, which grow with the blocks added up."""
+    block counts), rows and outputs twenty decades apart."""
+    assert hot.hot_linear_launch_shape(rows, k, o, s, 0, per_sample_x=own) == shape
     g, c = _deep_case(rows + o, o, k)
     f = 10.0 ** (8.0 * torch.rand((k + 15) // 16, device=DEV, generator=g) - 4.0).repeat_interleave(16)[:k]
     x = torch.randn(*((s, rows, k) if own else (rows, k)), device=DEV, generator=g) * f
@@ -1326,12 +1336,14 @@ def test_forward_from_fp16_pieces_over_many_decades(hot, rows, k, o, s, own):
     for i in range(s):
         xi = (x[i] if own else x).double()
         worst = float(((y[i] - (xi @ w[i].t() + b[i])).abs() / (xi.abs() @ w[i].abs().t() + b[i].abs())).max())
-        assert worst <= 2.0 ** -22 + 2 * 2.0 ** -23 + (k // 16 + 4) * 2.0 ** -24, worst
+        assert worst <= _pieces_bound(k), worst
 
 
-@pytest.mark.parametrize("rows,k,o,s", F16_BACKWARD)
-def test_backward_from_fp16_pieces_over_many_decades(hot, rows, k, o, s):
+@pytest.mark.parametrize("rows,k,o,s,dx_shape,w_shape", DECADES_BACKWARD)
+def test_backward_from_pieces_over_many_decades(hot, rows, k, o, s, dx_shape, w_shape):
     """The same for the input gradients (blocks of outputs) and the weight gradients (blocks of rows, x and dy against each other)."""
+    assert hot.hot_linear_launch_shape(rows, k, o, s, 1, per_sample_x=True) == dx_shape
+    assert hot.hot_linear_kernel_shape(rows, k, o, s, 2, per_sample_x=True) == w_shape
     g, c = _deep_case(rows + o, o, k)
     f = 10.0 ** (8.0 * torch.rand((rows + 15) // 16, device=DEV, generator=g) - 4.0).repeat_interleave(16)[:rows, None]
     h = 10.0 ** (8.0 * torch.rand((o + 15) // 16, device=DEV, generator=g) - 4.0).repeat_interleave(16)[:o]
@@ -1346,31 +1358,34 @@ def test_backward_from_fp16_pieces_over_many_decades(hot, rows, k, o, s):
     eps = [(w[i] - c["mu_w"].double()) / c["sigma_w"].double() for i in range(s)]
     for i in range(s):
         worst = float(((dx[i] - dy[i].double() @ w[i]).abs() / (dy[i].double().abs() @ w[i].abs())).max())
-        assert worst <= 2.0 ** -22 + 2 * 2.0 ** -23 + (o // 16 + 4) * 2.0 ** -24, worst
+        assert worst <= _pieces_bound(o), worst
     P = [dy[i].double().t() @ x[i].double() for i in range(s)]
     mag = [dy[i].double().abs().t() @ x[i].double().abs() for i in range(s)]
-    bound = 2.0 ** -22 + 2 * 2.0 ** -23 + (rows // 16 + 4) * 2.0 ** -24
+    bound = _pieces_bound(rows)
     assert float(((gmu - sum(P)).abs() / sum(mag)).max()) <= bound
     # (eps is recovered from the rounded weights, up to 2^-24 |w| / sigma and what its own product rounds)
     wide = sum(m * (bound * e.abs() + 2.0 ** -23 * w[i].abs() / c["sigma_w"].double()) for i, (m, e) in enumerate(zip(mag, eps)))
     assert bool(((gsig - sum(p * e for p, e in zip(P, eps))).abs() <= wide).all())
 
 
-# outputs that are no multiple of four: rows of dy off the 16-byte grid, the last quad of a row reaching into the next one (1, 2 and 3
-# elements), in the tile kernel and (even ones) in row parts; both kinds of pieces
-RAGGED_WGRAD = [(800, 2052, 1537, 2, False), (600, 2052, 1538, 1, True), (300, 2052, 1539, 2, False), (513, 4100, 2050, 1, False),
-                (200, 4100, 2050, 1, False), (513, 300, 130, 4, True), (2000, 260, 514, 2, True), (700, 132, 1030, 3, True)]
+# Outputs that are no multiple of four: rows of dy off the 16-byte grid, the last quad of a row reaching into the next one (1, 2 and 3
+# elements), in row parts (even ones), in the tile kernel (the second to last line: 230 tiles and more, below 450 rows 320, below 208
+# rows 1100) and in the first kernel
+RAGGED_WGRAD = [(800, 2052, 1537, 2, False), (600, 2052, 1538, 1, True), (300, 2052, 1539, 2, False), (200, 4100, 2050, 1, False),
+                (513, 300, 130, 4, True), (2000, 260, 514, 2, True), (700, 132, 1030, 3, True),
+                (513, 4100, 2050, 1, False), (513, 4100, 2051, 1, False), (300, 2500, 2179, 2, False), (150, 4612, 4097, 1, False),
+                (800, 2948, 1537, 2, False)]
 
 
 @pytest.mark.parametrize("rows,k,o,s,parts", RAGGED_WGRAD)
 def test_weight_gradients_with_rows_of_dy_off_the_grid(hot, rows, k, o, s, parts):
     """Against 64 bits, also with a NaN in the first element of a row of dy (which the last quad of the row before brings along): only
-    that output's gradients may see it.  Bound as for the cases over many decades."""
+    that output's gradients may see it."""
     assert bool(hot.hot_linear_kernel_shape(rows, k, o, s, 2)) == parts
     g, c = _deep_case(rows + o, o, k)
     x, dy = torch.randn(s, rows, k, device=DEV, generator=g), torch.randn(s, rows, o, device=DEV, generator=g)
     rng = hot.hot_rng(seed=79, step=2, first_sample=1)
-    bound = 2.0 ** -22 + 2 * 2.0 ** -23 + (rows // 16 + 4) * 2.0 ** -24
+    bound = _pieces_bound(rows)
     for poisoned in (False, True):
         if poisoned:
             dy[:, rows // 2, 0] = float("nan")
@@ -1382,9 +1397,10 @@ def test_weight_gradients_with_rows_of_dy_off_the_grid(hot, rows, k, o, s, parts
         assert bool(torch.isfinite(gsig[lo:]).all()) and bool(torch.isnan(gmu[:lo]).all()) and bool(torch.isnan(gsig[:lo]).all())
 
 
-@pytest.mark.parametrize("rows,k,o,s", [(800, 2052, 1537, 2), (300, 2052, 1539, 3)])
+# the first kernel, and tiles: ragged, with an odd last sample, aligned
+@pytest.mark.parametrize("rows,k,o,s", [(800, 2052, 1537, 2), (300, 2052, 1539, 3), (800, 2948, 1537, 2), (300, 2500, 2179, 3), (300, 4100, 2052, 2)])
 def test_tile_weight_gradients_of_infinite_and_huge_values(hot, rows, k, o, s):
-    """Infinities, NaN and the type's extremes in x and dy, in the tile kernel (both kinds of pieces, an odd last sample): what fp32 products give."""
+    """Infinities, NaN and the type's extremes in x and dy: what fp32 products give."""
     assert hot.hot_linear_kernel_shape(rows, k, o, s, 2) == 0
     g, c = _deep_case(rows + o, o, k)
     x, dy = torch.randn(s, rows, k, device=DEV, generator=g), torch.randn(s, rows, o, device=DEV, generator=g)
@@ -1399,9 +1415,8 @@ def test_tile_weight_gradients_of_infinite_and_huge_values(hot, rows, k, o, s):
 
 
 # Factors of very different size in one sum, the large one beside a small partner or none: in every sixteen terms (at any of their
-# places) or once in a sum, early, in the middle, late.  What the pieces leave out and the accumulations round is relative to the products,
-# 2^-24 (3 + sqrt(six roundings for sixteen terms)) of the magnitude sum (8 for 3: biases, waves and parts add up on top), however
-# large a factor is whose partner is not.
+# places) or once in a sum, early, in the middle, late.  The error stays relative to the products, however large a factor is whose partner
+# is not.
 MIXED = [("each", 1e7), ("each", 1e9), ("first", 1e12), ("first", 1e30), ("middle", 1e22), ("last", 1e30)]
 
 
@@ -1413,10 +1428,6 @@ def _mixed(big, small, dim, where, factor):
     up, down = torch.ones(n, device=DEV), torch.ones(n, device=DEV)
     up[at], down[at] = factor, (1.0 / factor if where == "each" else 0.0)
     return up, down
-
-
-def _mixed_bound(n):
-    return 2.0 ** -24 * (8 + (6 * n / 16) ** 0.5)
 
 
 @pytest.mark.parametrize("rows,k,o,s,own,shape", [(2040, 100, 4092, 2, False, 1621), (2040, 532, 4092, 1, True, 821), (1530, 84, 5400, 2, False, 822),
@@ -1439,8 +1450,8 @@ def test_forward_of_factors_of_very_different_size(hot, rows, k, o, s, own, shap
             xi = (x[i] if own else x).double()
             e = float(((y[i] - (xi @ w[i].t() + b[i])).abs() / (xi.abs() @ w[i].abs().t() + b[i].abs())).max())
             worst[where, factor] = max(worst.get((where, factor), 0.0), e)
-    print("  worst error / magnitude sum:", {m: "%.1e" % e for m, e in worst.items()}, "allowed %.1e" % _mixed_bound(k), flush=True)
-    assert all(e <= _mixed_bound(k) for e in worst.values())
+    print("  worst error / magnitude sum:", {m: "%.1e" % e for m, e in worst.items()}, "allowed %.1e" % _pieces_bound(k), flush=True)
+    assert all(e <= _pieces_bound(k) for e in worst.values())
 
 
 # (launch shape of the input gradients or 0, kernel shape of the weight gradients with a workspace: 0 tiles, else row parts)
@@ -1466,7 +1477,7 @@ def test_backward_of_factors_of_very_different_size(hot, rows, k, o, s, dx_shape
         w, _ = _materialised(hot, c2, s, rng, 0, o * k)
         for i in range(s):
             e = float(((dx[i] - d2[i].double() @ w[i]).abs() / (d2[i].double().abs() @ w[i].abs())).max())
-            worst["dx", where, factor] = max(worst.get(("dx", where, factor), 0.0), e / _mixed_bound(o))
+            worst["dx", where, factor] = max(worst.get(("dx", where, factor), 0.0), e / _pieces_bound(o))
         del d2, dx, w
         up, down = _mixed(x[0], dy[0], 0, where, factor)
         x_by, d_by = (up, down) if large_first else (down, up)
@@ -1474,7 +1485,7 @@ def test_backward_of_factors_of_very_different_size(hot, rows, k, o, s, dx_shape
         gmu, _ = _backward(hot, rng, x2, d2, c, None, _workspace(hot, rows, k, o, s), s)
         P = sum(d2[i].double().t() @ x2[i].double() for i in range(s))
         mag = sum(d2[i].double().abs().t() @ x2[i].double().abs() for i in range(s))
-        worst["dw", where, factor] = float(((gmu - P).abs() / mag).max()) / _mixed_bound(rows)
+        worst["dw", where, factor] = float(((gmu - P).abs() / mag).max()) / _pieces_bound(rows)
         del x2, d2, P, mag
     print("  worst error / allowed:", {m: "%.1e" % e for m, e in worst.items()}, flush=True)
     assert all(e <= 1.0 for e in worst.values())
