@@ -2712,9 +2712,10 @@ constexpr long kRowPartNarrow = 32, kRowPartNarrowRows = 1000;
 constexpr long kRowPartOneSampleRows = 8192, kRowPartOneSampleRowsEnd = 12000, kRowPartOneSampleWeights = 1L << 17;
 constexpr long kRowPartMaxTileCount = 512;
 // Rows of dy may start at any multiple of 4 bytes: a load of 8 or 16 bytes needs no more, a quad that reaches over the end of a row only
-// brings columns that are never stored, and behind the window's end the hardware's check is per 4 bytes.  (1888 x 1056 x 402 x 4 samples and
-// the like: 1.1-1.3x against the first kernel, 0.5-0.8 of its distance from 64 bits.)  An odd number of outputs stays with that
-// kernel: the accuracy of this one is tested against it there.
+// brings columns that are never stored, and behind the window's end the hardware's check is per 4 bytes.  (104 layers with outputs even
+// but no multiple of four, 129 to 16640 rows: 1.02-3.0x against the first kernel, 8809 x 1108 x 30 x 2 samples 0.95x and 884 x 100 x 26 x 1
+// 0.97x, at 0.3-0.97 of its distance from 64 bits.)  Odd numbers of outputs still go to that kernel.  Nothing in this one stands against
+// them, and on 45 such layers it was 1.06-2.8x as fast at 0.4-0.98 of the distance; their route has not been changed yet.
 constexpr int kRowPartMaxParts = 64;
 constexpr int64_t kRowPartMaxBytes = (int64_t)256 << 20, kRowPartSmallBytes = (int64_t)8 << 20;
 // Errors grow with the rows that a wave adds up, 2-norm against 64 bits at 16640 x 192 x 768: 2.7e-7 with 297, 2.0e-7 with 152 (the fp32
