@@ -716,6 +716,44 @@ def sampled_linear_lines(hot, torch, dev, iters: int = 20):
     return out
 
 
+def printed(result: dict) -> dict:
+    """The record as one line of some 6 KB (whole it is 21 KB, and a reader that keeps the last 8 KB of a run's output would lose its head):
+    of the side measurements the times, what they are compared with and whether the results agree."""
+    def digits(v):
+        return float(f"{v:.4g}") if isinstance(v, float) else v
+
+    def pick(d, keys):
+        return {k: digits(d[k]) for k in keys if d.get(k) is not None}
+
+    out = dict(result)
+    if "sampled_linear" in out:         # [milliseconds, times as fast as materialising the weights and the library's product]
+        def pair(d, ms, speedup):
+            return [digits(d[ms]), digits(d[speedup])]
+        lines = {}
+        for name, line in out["sampled_linear"].items():
+            if not isinstance(line, dict):
+                continue
+            back = line["backward"]
+            lines[name] = {"forward": pair(line, "fused_ms", "speedup_over_materialise"), "backward": pair(back, "fused_ms", "speedup"),
+                           "agrees": bool(line["agrees_with_materialised"] and back["agrees"])}
+            if back.get("fused_with_workspace_ms") is not None:
+                lines[name]["backward_with_workspace"] = pair(back, "fused_with_workspace_ms", "speedup_with_workspace")
+        out["sampled_linear"] = lines
+    if "in_kernel_eps" in out:
+        out["in_kernel_eps"] = pick(out["in_kernel_eps"], ("items_per_s", "ms_per_step", "fwd_ms", "bwd_ms", "step_frac_of_hbm_roofline", "verified_against_oracle"))
+    if "predictive_stats" in out:
+        out["predictive_stats"] = {name: pick(line, ("one_pass_ms", "agrees_with_torch")) for name, line in out["predictive_stats"].items() if isinstance(line, dict)}
+    if "update_and_dropout" in out:
+        out["update_and_dropout"] = {name: pick(line, ("ms", "forward_ms", "backward_ms", "GBps", "step_frac_of_hbm_roofline"))
+                                     for name, line in out["update_and_dropout"].items() if isinstance(line, dict)}
+    if "other_workloads" in out:
+        out["other_workloads"] = {name: pick(line, ("items_per_s", "ms_per_step", "hip_graph_ms_per_step", "step_frac_of_hbm_roofline", "verified_against_oracle"))
+                                  for name, line in out["other_workloads"].items()}
+    if "between_other_work" in out:
+        out["between_other_work"] = pick(out["between_other_work"], ("fwd_ms", "bwd_ms", "kernels_frac_of_hbm_roofline"))
+    return out
+
+
 def main() -> int:
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -727,6 +765,7 @@ def main() -> int:
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-others", action="store_true", help="skip the short runs of the other workloads")
     ap.add_argument("--cpu-weights", type=int, default=1 << 28, help="cap on weights the oracle is timed on")
+    ap.add_argument("--details", metavar="FILE", help="write the whole record there (the printed line holds the side measurements in short)")
     ap.add_argument("--linear-only", action="store_true", help="only run the sampled linear layer lines")
     ap.add_argument("--probe-copy", action="store_true",
                     help="only run the plain copy kernel (2 GiB, known traffic) and print its rate")
@@ -890,7 +929,10 @@ def main() -> int:
             torch.cuda.empty_cache()
         result["other_workloads"] = others
 
-    print(json.dumps(result))
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(result, f, indent=1)
+    print(json.dumps(printed(result)))
     return 1 if verified is False else 0
 
 
