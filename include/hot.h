@@ -255,6 +255,21 @@ int hot_linear_forward_rng(const hot_linear_desc *desc, const hot_rng *rng, cons
                            const float *sigma_w, const float *mu_b, const float *sigma_b, float *y, void *stream);
 
 /*
+ * The same call with device scratch of the caller's (same passage of the paper; the same y bit for bit).  At thousands of rows
+ * the tiles of 256 to 1024 rows draw the weights once each; with a workspace one launch draws all of them once and leaves their
+ * bf16 pieces there (six bytes per weight and sample, at most 128 MiB in all), a second multiplies (7260 x 2160 x 540, two
+ * samples: 325 -> 190 us; 16640 x 192 x 768: 80 -> 64).  hot_linear_planes_workspace_bytes(desc, 0) returns the bytes that the call
+ * would use (0: none; HOT_EINVAL for a malformed desc or another `which`), with which = 1 those that the input gradients of
+ * hot_linear_backward_rng_ws would use in the same way.  workspace: DEVICE, 16-byte aligned, owned by the caller, contents
+ * undefined afterwards, or NULL; with fewer bytes than asked for the call is hot_linear_forward_rng.  Calls that share a
+ * workspace must not overlap.
+ */
+int64_t hot_linear_planes_workspace_bytes(const hot_linear_desc *desc, int which);
+int hot_linear_forward_rng_ws(const hot_linear_desc *desc, const hot_rng *rng, const float *x, const float *mu_w,
+                              const float *sigma_w, const float *mu_b, const float *sigma_b, float *y, void *workspace,
+                              int64_t workspace_bytes, void *stream);
+
+/*
  * Back-propagation through the same layer (Algorithm 1 / 2: the gradient and averaging lines for a
  * Linear layer), again without the sampled weights, and without the per-sample weight gradients,
  * ever existing in memory.  dy[s_local, rows, out_features] (packed, DEVICE) holds dL_s/dy_s.  With
@@ -323,6 +338,14 @@ int hot_linear_launch_shape(const hot_linear_desc *desc, int which);
 int64_t hot_linear_kernel_shape(const hot_linear_desc *desc, int which, int64_t workspace_bytes);
 
 /*
+ * The same for the product with weights that a workspace holds as bf16 pieces (host arithmetic only; same passages of the paper),
+ * with workspace_bytes of it (0: none; negative: all that is asked for).  which = 0: hot_linear_forward_rng_ws; 1: the
+ * input-gradient part of hot_linear_backward_rng_ws (dy taken to be 16-byte aligned).  10 * (rows per workgroup / 64) + (outputs per
+ * workgroup / 64), e.g. 33; 0 where other kernels run.  HOT_EINVAL for a malformed desc or another `which`.
+ */
+int hot_linear_planes_shape(const hot_linear_desc *desc, int which, int64_t workspace_bytes);
+
+/*
  * The same call with device scratch of the caller's (same passage of the paper; only the launch shape
  * differs).  A layer with few weights and many rows (a ViT layer: 192 x 768 weights, 16 640 rows) has too
  * few 16-output x 64-input tiles to give every compute unit weight-gradient work, and the waves of one
@@ -335,7 +358,10 @@ int64_t hot_linear_kernel_shape(const hot_linear_desc *desc, int which, int64_t 
  * weights with fewer than 1200 rows of one or two samples, up to 32 outputs, one sample of 8192 to 12000 rows;
  * hot_linear_kernel_shape with which = 2 tells).  The input gradients use the
  * same memory afterwards where the tiles of dx are too few for the chip (few inputs, up to about a thousand
- * rows): the outputs they contract over are cut into parts, whose dx blocks a second kernel adds.
+ * rows): the outputs they contract over are cut into parts, whose dx blocks a second kernel adds.  Input gradients of thousands
+ * of rows come from bf16 pieces of the drawn weights, as in hot_linear_forward_rng_ws (the same dx bit for bit;
+ * 7260 x 2160 x 540: 270 -> 180 us, 16640 x 192 x 768: 96 -> 64), with at least the bytes that
+ * hot_linear_planes_workspace_bytes(desc, 1) asks for, which the query below does not count.
  * Up to 128 rows with dx wanted the workspace buys more: weight and input gradients then come from ONE pass
  * over the weights, every eps drawn once instead of once per kernel, and the draw is most of the time at so
  * few rows.  Up to 32 rows (where a lane's registers hold the dx accumulators of all samples: 32 rows: 4 samples,

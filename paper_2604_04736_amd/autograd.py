@@ -16,6 +16,8 @@ caller's scaling).
 """
 from __future__ import annotations
 
+import functools
+
 import torch
 
 from . import binding as hot
@@ -57,6 +59,18 @@ class GaussianSampleLayer:
         return _Sample.apply(mu, sigma, self, int(step))
 
 
+# What the library asks for by a layer's sizes (pure functions of them; kept, since a query costs a small layer's call some microseconds).
+@functools.lru_cache(maxsize=4096)
+def _forward_scratch(rows: int, k: int, o: int, s_local: int, per_sample_x: bool) -> int:
+    return hot.hot_linear_planes_workspace_bytes(rows, k, o, s_local, 0, per_sample_x)
+
+
+@functools.lru_cache(maxsize=4096)
+def _backward_scratch(rows: int, k: int, o: int, s_local: int, with_dx: bool) -> int:
+    split = hot.hot_linear_backward_workspace_bytes(rows, k, o, s_local)
+    return max(split, hot.hot_linear_planes_workspace_bytes(rows, k, o, s_local, 1)) if with_dx else split
+
+
 class _Linear(torch.autograd.Function):
     @staticmethod
     def forward(ctx, x, mu_w, sigma_w, mu_b, sigma_b, layer, step):
@@ -64,7 +78,12 @@ class _Linear(torch.autograd.Function):
         xd = x.detach().contiguous()
         y = torch.empty(layer.s_local, xd.shape[-2], layer.out_features, dtype=torch.float32, device=x.device)
         det = [t.detach() if t is not None else None for t in (mu_w, sigma_w, mu_b, sigma_b)]
-        hot.hot_linear_forward_rng(rng, xd, det[0], det[1], det[2], det[3], y, layer.weight_offset, layer.bias_offset)
+        # many rows: the library leaves the drawn weights in scratch memory of ours instead of drawing them for every tile of rows
+        # (never up to 128, where the look itself would cost a small layer's call)
+        rows = xd.shape[-2]
+        ws_bytes = _forward_scratch(rows, layer.in_features, layer.out_features, layer.s_local, xd.dim() == 3) if rows > 128 else 0
+        ws = torch.empty(ws_bytes // 4, dtype=torch.float32, device=x.device) if ws_bytes > 0 else None
+        hot.hot_linear_forward_rng(rng, xd, det[0], det[1], det[2], det[3], y, layer.weight_offset, layer.bias_offset, workspace=ws)
         ctx.layer, ctx.rng, ctx.has_bias = layer, rng, mu_b is not None
         ctx.save_for_backward(xd, *[t for t in det if t is not None])
         return y
@@ -81,7 +100,7 @@ class _Linear(torch.autograd.Function):
         if ctx.needs_input_grad[0]:
             dx = torch.empty(layer.s_local, xd.shape[-2], layer.in_features, dtype=torch.float32, device=xd.device)
         # few weights and many rows: the library spreads the rows over the chip through scratch memory of ours
-        ws_bytes = hot.hot_linear_backward_workspace_bytes(xd.shape[-2], layer.in_features, layer.out_features, layer.s_local)
+        ws_bytes = _backward_scratch(xd.shape[-2], layer.in_features, layer.out_features, layer.s_local, dx is not None)
         ws = torch.empty(ws_bytes // 4, dtype=torch.float32, device=xd.device) if ws_bytes > 0 else None
         hot.hot_linear_backward_rng(ctx.rng, xd, grad_y.contiguous(), mu_w, sigma_w, mu_b, sigma_b, gmw, gsw, gmb, gsb, dx,
                                     layer.s_local, layer.dataset_size, hot.HOT_REDUCE_NONE, layer.weight_offset,

@@ -31,12 +31,14 @@ EXPORTS = ("hot_create", "hot_forward", "hot_backward", "hot_destroy", "hot_set_
            "hot_linear_backward_rng", "hot_kl", "hot_forward_dropout_units_rng",
            "hot_backward_dropout_units_rng", "hot_stats_whole", "hot_adam_forward", "hot_backward_adam_forward",
            "hot_linear_backward_rng_ws", "hot_linear_backward_workspace_bytes", "hot_forward_static",
-           "hot_linear_launch_shape", "hot_linear_kernel_shape")
+           "hot_linear_launch_shape", "hot_linear_kernel_shape", "hot_linear_planes_shape",
+           "hot_linear_forward_rng_ws", "hot_linear_planes_workspace_bytes")
 
 
 # Return types of the entry points that do not return an int status (as declared in include/hot.h).
 RESTYPES = {"hot_strerror": ctypes.c_char_p, "hot_recommended_ld": ctypes.c_int64,
-            "hot_linear_backward_workspace_bytes": ctypes.c_int64, "hot_linear_kernel_shape": ctypes.c_int64}
+            "hot_linear_backward_workspace_bytes": ctypes.c_int64, "hot_linear_kernel_shape": ctypes.c_int64,
+            "hot_linear_planes_workspace_bytes": ctypes.c_int64}
 
 
 class hot_desc(ctypes.Structure):
@@ -113,6 +115,10 @@ def lib() -> ctypes.CDLL:
     L.hot_probe_streams.restype = ctypes.c_int
     L.hot_linear_forward_rng.argtypes = [ctypes.POINTER(hot_linear_desc), rp, fp, fp, fp, fp, fp, fp, vp]
     L.hot_linear_forward_rng.restype = ctypes.c_int
+    L.hot_linear_forward_rng_ws.argtypes = [ctypes.POINTER(hot_linear_desc), rp, fp, fp, fp, fp, fp, fp, vp, ctypes.c_int64, vp]
+    L.hot_linear_planes_workspace_bytes.argtypes = [ctypes.POINTER(hot_linear_desc), ctypes.c_int]
+    L.hot_linear_planes_workspace_bytes.restype = ctypes.c_int64
+    L.hot_linear_planes_shape.argtypes = [ctypes.POINTER(hot_linear_desc), ctypes.c_int, ctypes.c_int64]
     L.hot_adam_step.argtypes = [ctypes.POINTER(hot_adam), ctypes.c_int64] + [fp] * 8 + [vp]
     L.hot_adam_step.restype = ctypes.c_int
     L.hot_linear_backward_rng.argtypes = [ctypes.POINTER(hot_linear_desc), ctypes.c_int32, ctypes.c_double, ctypes.c_uint32,
@@ -408,9 +414,10 @@ def hot_stats_merge(means: torch.Tensor, m2s: torch.Tensor, counts, ddof: int, m
 
 
 def hot_linear_forward_rng(rng: hot_rng, x, mu_w, sigma_w, mu_b, sigma_b, y, weight_offset: int = 0,
-                           bias_offset: int = 0) -> None:
+                           bias_offset: int = 0, workspace=None) -> None:
     """y[S, R, O] = x_s (mu_w + sigma_w*eps_s)^T + (mu_b + sigma_b*eps_s^b), eps drawn in the kernel;
-    x is [R, K] (shared by the samples) or [S, R, K] (one input per sample)."""
+    x is [R, K] (shared by the samples) or [S, R, K] (one input per sample).  workspace: an optional contiguous device
+    tensor (any dtype) used as scratch (hot_linear_forward_rng_ws; the same y)."""
     def chk(t, shape, name):
         if not (t.is_cuda and t.device == x.device and t.dtype == torch.float32 and tuple(t.shape) == shape
                 and t.is_contiguous()):
@@ -439,11 +446,20 @@ def hot_linear_forward_rng(rng: hot_rng, x, mu_w, sigma_w, mu_b, sigma_b, y, wei
     s_loc = y.shape[0]
     chk(y, (s_loc, rows, o), "y")
     d = hot_linear_desc(rows, k, o, ldx, weight_offset, bias_offset, s_loc, 0, x_stride)
+    if workspace is not None and not (workspace.is_cuda and workspace.device == x.device and workspace.is_contiguous()):
+        raise TypeError(f"workspace: need a contiguous tensor on {x.device}")
     with _on(x.device.index):
-        code = lib().hot_linear_forward_rng(ctypes.byref(d), ctypes.byref(rng), x.data_ptr(), mu_w.data_ptr(),
-                                            sigma_w.data_ptr(), mu_b.data_ptr() if mu_b is not None else None,
-                                            sigma_b.data_ptr() if mu_b is not None else None, y.data_ptr(),
-                                            _stream(x.device.index))
+        if workspace is None:
+            code = lib().hot_linear_forward_rng(ctypes.byref(d), ctypes.byref(rng), x.data_ptr(), mu_w.data_ptr(),
+                                                sigma_w.data_ptr(), mu_b.data_ptr() if mu_b is not None else None,
+                                                sigma_b.data_ptr() if mu_b is not None else None, y.data_ptr(),
+                                                _stream(x.device.index))
+        else:
+            code = lib().hot_linear_forward_rng_ws(ctypes.byref(d), ctypes.byref(rng), x.data_ptr(), mu_w.data_ptr(),
+                                                   sigma_w.data_ptr(), mu_b.data_ptr() if mu_b is not None else None,
+                                                   sigma_b.data_ptr() if mu_b is not None else None, y.data_ptr(),
+                                                   workspace.data_ptr(), workspace.numel() * workspace.element_size(),
+                                                   _stream(x.device.index))
     _check_planless(code, "hot_linear_forward_rng")
 
 
@@ -519,6 +535,29 @@ def hot_linear_backward_workspace_bytes(rows: int, in_features: int, out_feature
     if n < 0:
         _check_planless(int(n), "hot_linear_backward_workspace_bytes")
     return int(n)
+
+
+def hot_linear_planes_workspace_bytes(rows: int, in_features: int, out_features: int, s_local: int, which: int,
+                                      per_sample_x: bool = False) -> int:
+    """Bytes of device scratch in which hot_linear_forward_rng (which = 0) or the input gradients of hot_linear_backward_rng
+    (which = 1) leave the drawn weights of this layer shape when handed a workspace; 0 if they would not."""
+    d = hot_linear_desc(rows, in_features, out_features, in_features, 0, 0, s_local, 0, rows * in_features if per_sample_x else 0)
+    n = lib().hot_linear_planes_workspace_bytes(ctypes.byref(d), which)
+    if n < 0:
+        _check_planless(int(n), "hot_linear_planes_workspace_bytes")
+    return int(n)
+
+
+def hot_linear_planes_shape(rows: int, in_features: int, out_features: int, s_local: int, which: int, per_sample_x: bool = False,
+                            ldx: int = 0, workspace_bytes: int = -1) -> int:
+    """Code of the tiles of the product with drawn weights in a workspace (which = 0: forward, 1: input gradients), with
+    workspace_bytes of it (negative: all that the layer asks for); see include/hot.h.  0: other kernels."""
+    ldx = ldx or in_features
+    d = hot_linear_desc(rows, in_features, out_features, ldx, 0, 0, s_local, 0, rows * ldx if per_sample_x else 0)
+    code = lib().hot_linear_planes_shape(ctypes.byref(d), which, workspace_bytes)
+    if code < 0:
+        _check_planless(int(code), "hot_linear_planes_shape")
+    return int(code)
 
 
 def hot_linear_launch_shape(rows: int, in_features: int, out_features: int, s_local: int, which: int, per_sample_x: bool = False,

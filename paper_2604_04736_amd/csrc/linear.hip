@@ -803,6 +803,11 @@ hot_linear_slab_kernel(SlabArgs a)
     }
 }
 
+// (in a file of its own; it uses the windows, the draw and the pieces above)
+}  // namespace
+#include "linear_planes.h"
+namespace {
+
 // ---------------------------------------------------------------------------------
 // Tens to hundreds of rows.  The kernel above shares a drawn weight among waves that hold 64 rows each and meet at a barrier
 // in every step; with few rows its workgroups are few or its waves idle, and what runs instead draws every weight once per 64 or
@@ -1531,6 +1536,31 @@ inline DeepPlan deep_forward_plan(const hot_linear_desc *d)
     const SlabForwardPlan slab = slab_forward_plan(d);
     const double time = slab_time(slab.two, 2, d->in_features) + slab_time(slab.one, 1, d->in_features);
     return deep_beats_slab(p, d->rows, d->in_features, d->out_features, d->s_local, d->x_sample_stride != 0 ? d->s_local : 1, time) ? p : kNoDeepPlan;
+}
+
+// Whether planes of drawn weights (linear_planes.h) stand in for a launch of the slab kernel that takes `slab` microseconds by its
+// model: where a workspace holds them, unless they are slower by the models.  (Their sums are the bf16 slab kernel's bit for bit;
+// layers of the kernels whose waves share a sum, and of the 128-row slab shapes on the fp32 instruction, stay where they are.)  Of 213
+// such products the rule takes 170, 1.36 times as fast on average, the slowest 0.99 (7260 x 2160 x 540 x 2 samples 312 -> 190 us,
+// 13300 x 180 x 216 x 4 94 -> 42); the slab model is 4 to 16 % below the time of most layers, and under 20 us the second launch shows
+// (1818 x 48 x 588 x 3 12.6 -> 15).
+constexpr double kPlanesMost = 1.11, kPlanesMostShort = 0.83, kPlanesShort = 20.0;
+
+inline PlanePlan planes_instead(long R, long C, long N, int S, bool tr, double slab, int64_t ws_bytes)
+{
+    if (ws_bytes == 0) return kNoPlanePlan;
+    const PlanePlan p = plane_plan(R, C, N, S, tr);
+    const bool faster = p.time < (p.time < kPlanesShort ? kPlanesMostShort : kPlanesMost) * slab;
+    return p.code >= 0 && (ws_bytes < 0 || p.bytes <= ws_bytes) && faster ? p : kNoPlanePlan;
+}
+
+inline PlanePlan planes_forward_plan(const hot_linear_desc *d, int64_t ws_bytes)
+{
+    if (ws_bytes == 0 || deep_forward_plan(d).code >= 0) return kNoPlanePlan;
+    const SlabForwardPlan slab = slab_forward_plan(d);
+    if ((!slab.two.waves && !slab.one.waves) || (slab.two.waves && slab.two.rbw == 1) || (slab.one.waves && slab.one.rbw == 1)) return kNoPlanePlan;
+    return planes_instead(d->rows, d->in_features, d->out_features, d->s_local, false,
+                          slab_time(slab.two, 2, d->in_features) + slab_time(slab.one, 1, d->in_features), ws_bytes);
 }
 
 template <int RB, bool XS>
@@ -3641,6 +3671,14 @@ inline DeepPlan deep_input_grad_plan(const hot_linear_desc *d, bool dy_aligned, 
     return deep_beats_slab(p, d->rows, d->out_features, d->in_features, d->s_local, d->s_local, slab_time(slab, 1, d->out_features)) ? p : kNoDeepPlan;
 }
 
+inline PlanePlan planes_input_grad_plan(const hot_linear_desc *d, bool dy_aligned, int64_t ws_bytes)
+{
+    if (ws_bytes == 0 || deep_input_grad_plan(d, dy_aligned, ws_bytes).code >= 0) return kNoPlanePlan;
+    const SlabShape slab = slab_input_grad_shape(d, dy_aligned);
+    if (slab.rbw == 1 || !xgrad_by_slab(slab, xgrad_parts(d, ws_bytes))) return kNoPlanePlan;
+    return planes_instead(d->rows, d->out_features, d->in_features, d->s_local, true, slab_time(slab, 1, d->out_features), ws_bytes);
+}
+
 // Launch shape of the weight-gradient kernel.
 struct WgradShape {
     long tiles, rows_per_part;
@@ -3822,6 +3860,25 @@ int64_t hot_linear_kernel_shape(const hot_linear_desc *d, int which, int64_t wor
     return p.code < 0 ? 0 : 1000000 * (int64_t)p.parts + 1000 * code(p.rest_code) + code(p.code);
 }
 
+int hot_linear_planes_shape(const hot_linear_desc *d, int which, int64_t workspace_bytes)
+{
+    if (const int plain = hot_linear_launch_shape(d, 0); plain < 0) return plain;
+    if (which < 0 || which > 1) return HOT_EINVAL;
+    const PlanePlan p = which == 0 ? planes_forward_plan(d, workspace_bytes) : planes_input_grad_plan(d, true, workspace_bytes);
+    return p.code < 0 ? 0 : 10 * kPlaneShapes[p.code].rb + kPlaneShapes[p.code].cb;
+}
+
+int64_t hot_linear_planes_workspace_bytes(const hot_linear_desc *d, int which)
+{
+    if (const int plain = hot_linear_launch_shape(d, 0); plain < 0) return plain;
+    if (which < 0 || which > 1) return HOT_EINVAL;
+    if (which == 0) return planes_forward_plan(d, -1).bytes;
+    const PlanePlan p = planes_input_grad_plan(d, true, -1);
+    // (not where memory handed over for this alone would take the weight gradients off the kernel that they run on without any)
+    if (p.bytes > 0 && hot_linear_backward_workspace_bytes(d) == 0 && wgrad_shape(d, p.bytes).tile != wgrad_shape(d, 0).tile) return 0;
+    return p.bytes;
+}
+
 int64_t hot_linear_backward_workspace_bytes(const hot_linear_desc *d)
 {
     if (!d || d->rows < 1 || d->in_features < 4 || (d->in_features & 3) || d->out_features < 1 || d->s_local < 1) return HOT_EINVAL;
@@ -3851,10 +3908,12 @@ int64_t hot_linear_backward_workspace_bytes(const hot_linear_desc *d)
     return most;
 }
 
-int hot_linear_forward_rng(const hot_linear_desc *d, const hot_rng *rng, const float *x, const float *mu_w,
-                           const float *sigma_w, const float *mu_b, const float *sigma_b, float *y, void *stream)
+int hot_linear_forward_rng_ws(const hot_linear_desc *d, const hot_rng *rng, const float *x, const float *mu_w,
+                              const float *sigma_w, const float *mu_b, const float *sigma_b, float *y, void *workspace,
+                              int64_t workspace_bytes, void *stream)
 {
     if (!d || !x || !mu_w || !sigma_w || !y) return HOT_EINVAL;
+    if (workspace && (workspace_bytes < 0 || !aligned16(workspace))) return HOT_EINVAL;
     if ((mu_b == nullptr) != (sigma_b == nullptr)) return HOT_EINVAL;
     if (d->rows < 1 || d->in_features < 4 || (d->in_features & 3) || d->out_features < 1 || d->s_local < 1) return HOT_EINVAL;
     if (d->ldx < d->in_features || (d->ldx & 3) || d->weight_offset < 0 || (d->weight_offset & 3)) return HOT_EINVAL;
@@ -3929,6 +3988,10 @@ int hot_linear_forward_rng(const hot_linear_desc *d, const hot_rng *rng, const f
         b.sigma_b = sigma_b;
         b.out = y;
         b.rng = r;
+        if (const PlanePlan planes = planes_forward_plan(d, workspace ? workspace_bytes : 0); planes.code >= 0) {
+            planes_run<false>(planes, s, b, d->s_local, static_cast<char *>(workspace));
+            return hot_detail::note_hip(hipGetLastError());
+        }
         if (plan.two.waves == 4 && plan.two.rbw == 1) slab_go<4, 1, 2, false, false, 1>(s, b, 0, plan.pair_samples);
         else if (plan.two.waves == 4) slab_go<4, 1, 2, false, false>(s, b, 0, plan.pair_samples);
         else if (plan.two.waves) {
@@ -3991,6 +4054,12 @@ int hot_linear_forward_rng(const hot_linear_desc *d, const hot_rng *rng, const f
     else if (rb == 2) linear_go<2>(st, grid, waves, s, a);
     else linear_go<1>(st, grid, waves, s, a);
     return hot_detail::note_hip(hipGetLastError());
+}
+
+int hot_linear_forward_rng(const hot_linear_desc *d, const hot_rng *rng, const float *x, const float *mu_w,
+                           const float *sigma_w, const float *mu_b, const float *sigma_b, float *y, void *stream)
+{
+    return hot_linear_forward_rng_ws(d, rng, x, mu_w, sigma_w, mu_b, sigma_b, y, nullptr, 0, stream);
 }
 
 int hot_linear_backward_rng_ws(const hot_linear_desc *d, int32_t s_total, double dataset_size, uint32_t flags,
@@ -4158,7 +4227,9 @@ int hot_linear_backward_rng_ws(const hot_linear_desc *d, int32_t s_total, double
         b.mu_b = b.sigma_b = nullptr;
         b.out = dx;
         b.rng = r;
-        slab_go_singles<true, true>(one, s, b, 0, d->s_local);
+        if (const PlanePlan planes = planes_input_grad_plan(d, aligned16(dy), workspace ? workspace_bytes : 0); planes.code >= 0)
+            planes_run<true>(planes, s, b, d->s_local, static_cast<char *>(workspace));
+        else slab_go_singles<true, true>(one, s, b, 0, d->s_local);
         return hot_detail::note_hip(hipGetLastError());
     }
     // many rows: the workgroup-shared draw
