@@ -28,8 +28,8 @@
 //   backward  hot_linear_wgrad_kernel          weight and bias gradients (per-sample G never stored); variants for
 //                                              few tiles (waves split the rows), many rows (operands prefetched,
 //                                              two output groups per wave), tiles dealt out by XCD
-//             hot_linear_wgrad_tile_kernel     the same for large layers: 128 inputs x 128 outputs per workgroup, rows of
-//                                              x and dy loaded straight into LDS
+//             hot_linear_wgrad_tile_kernel     the same for large layers: 128 inputs x 128 outputs per workgroup, x and dy
+//                                              cut into bf16 pieces once and shared through LDS
 //             hot_linear_wgrad_row_parts_kernel  the same for smaller layers and many rows, with a workspace: the rows cut into
 //                                              parts, bf16 pieces straight from memory, no LDS before the last sum
 //             hot_linear_xgrad_kernel          input gradients where few workgroups are left to it: up to 16 waves split a sum
@@ -2012,31 +2012,24 @@ void wgrad_go(long tiles, int waves, hipStream_t s, const LinearGradArgs &a)
 // ---------------------------------------------------------------------------------
 // Weight gradients of large layers.  The kernel above gives a wave a tile of 16-32 outputs x 64 inputs, about 10
 // flops per byte it loads: at thousands of rows the second-level caches cannot feed that (the matrix pipes were 42 %
-// busy).  Here a workgroup of four waves owns 128 inputs x 128 outputs and takes 16 rows of x and of dy at a time
-// through LDS (32 flops per byte loaded).  The rows go from memory straight into LDS (buffer loads with the LDS
-// bit, 16 bytes per lane, consecutive lanes on consecutive addresses): no registers and no vector-ALU instruction
-// carry them.  A wave multiplies its 64 inputs x 64 outputs as 2 x 2 blocks of v_mfma_f32_32x32x2_f32 with x as
-// the A operand and dy as the B operand, so result registers 4 q .. 4 q + 3 of a lane are the inputs
-// 8 q + 4 (lane / 32) .. + 3 of output lane % 32: one generator quad, as above.  Four pairs of buffers take turns: the
-// rows of a step are sent for three steps ahead, and the one barrier of a step lies in its middle, with the operands
-// of the matrix instructions behind it already in registers (see the row loop); two workgroups share a compute unit,
-// so what one still waits for is covered by the other's matrix instructions.  Rows beyond the last
-// and columns beyond the layer are masked by offsets outside the range-checked windows and arrive as zeros; a wave
-// skips the 32 x 32 blocks that lie outside the layer altogether.  The finished sums leave through LDS so that
-// every store instruction covers 128 contiguous bytes per row of the gradient arrays.
-// Vector-ALU instructions are kept out of the row loop as far as possible, since each takes its cycles from the
-// matrix instructions: the lanes' offsets advance by a uniform step, rows are masked by one comparison per load,
-// and the LDS reads carry their offsets as immediates (volatile: merged into two-address reads they needed a
-// computed base register each).  Measured on the way, at 4096^3 with two samples: 16-row steps staged through
-// registers 123 TFLOP/s; 32-row steps straight into two pairs of LDS buffers, one barrier at the end of a step, one
-// set of accumulators for all samples with the eps-weighted sum built by summation by parts (two draws per sample)
-// 134; this form 136-139 (the kernel above: 114, the library's GEMM alone: 146) and at 1024 x 8192^2, where the
-// draws weigh more, 119 -> 127; tiles of 64 inputs x 256 outputs, 2-8 % slower; row parts through a workspace for
-// layers of fewer tiles, behind the kernel above (7260 x 540 x 2160, five or six parts: 0.46-0.49 against 0.42 ms;
-// 16640 x 192 x 768: 0.21 against 0.17 ms).
+// busy).  Here a workgroup of four waves owns 128 inputs x 128 outputs and takes 16 rows of x and of dy at a time.
+// Every element is loaded and cut into its three bf16 pieces ONCE in the workgroup (by a lane that holds eight rows of two
+// columns, i.e. whole operands of the matrix instruction) and shared through LDS; a wave multiplies 64 inputs x 64 outputs as
+// 2 x 2 blocks with x as the A operand and dy as the B operand, so result registers 4 q .. 4 q + 3 of a lane are the inputs
+// 8 q + 4 (lane / 32) .. + 3 of output lane % 32: one generator quad, as above.  Two samples have accumulators of their own (128
+// registers), and two workgroups share a compute unit and cover each other's draws.
+// What bounds it: matrix and vector instructions, which overlap only in part, at the clock that the card's power leaves (1024 x
+// 8192^2 x 2: matrix pipes 55-60 % busy at 1.7 GHz, 211 TFLOP/s of fp32 work per further row), and at a few hundred rows the draw
+// (43 us of 190 at 300 x 2160 x 8640 x 2) and the 16 bytes per weight of mu, sigma and the gradients.  Measured against its
+// predecessor, which sent fp32 rows straight into LDS, had every wave cut its operands itself (176 instead of 88 vector instructions per
+// 24 matrix instructions), and waited for memory sixteen times per tile on the way out: 1024 x 8192^2 x 2 1654 -> 1502 us, 160 x 8192^2 x 2
+// 505 -> 402, 300 x 2160 x 8640 x 2 221 -> 192, 200 x 4096^2 x 2 153 -> 120.  On the way: the same with the vector instructions where the
+// scheduler put them, in rows, 1680; with fixed places 1650; rows of x and dy sent for two steps ahead 1560; the way out
+// without waits 1502.  Three sets of rows under way instead of two (steps in threes): 1566, with 51 registers spilled.
 // ---------------------------------------------------------------------------------
 constexpr int kTileSide = 128;        // inputs and outputs per workgroup
 constexpr int kTileRows = 16;         // rows per step
+constexpr int kTileBuffer = 2 * kTileSide * kTileRows * 6;      // bytes of the cut columns of a step: four blocks of 32 columns of x, four of dy, three planes each
 constexpr int kTurnPitch = 36;        // floats per row of a wave's 32 x 32 block on its way out (16-byte aligned rows)
 
 
@@ -2109,256 +2102,283 @@ __device__ __forceinline__ void wgrad_tile_again(const LinearGradArgs &a, long o
     }
 }
 
-// WHOLE: every 32 x 32 block of the workgroup's tile reaches into the layer (no block is skipped, no column masked).
-// XB, DB: the four buffers of 16 rows x 128 columns of x and of dy.  Returns whether the wave left a NaN.
-template <bool WHOLE>
-__device__ __forceinline__ bool wgrad_tile_body(const LinearGradArgs &a, lds_float *const (&XB)[4], lds_float *const (&DB)[4], long o0, long k0)
+template <int N>
+struct Number {
+    static constexpr int value = N;
+};
+
+// lds: three buffers of kTileBuffer bytes, the cut columns of x and behind them those of dy.  Returns whether the wave left a NaN.
+__device__ __forceinline__ bool wgrad_tile_body(const LinearGradArgs &a, lds_char *lds, long o0, long k0)
 {
-    constexpr int WK = 2, TK = kTileSide, TO = kTileSide;         // 2 x 2 waves of 64 inputs x 64 outputs
+    constexpr int WK = 2;                                         // 2 x 2 waves of 64 inputs x 64 outputs
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int l32 = lane & 31, half = lane >> 5;
     const int wk = wave % WK, wo = wave / WK;
     const long K = a.in_features, O = a.out_features, R = a.rows;
 
-    // which of this wave's 2 x 2 blocks of 32 x 32 reach into the layer (uniform over the wave): the others are skipped
-    bool ok[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) ok[i][j] = WHOLE || (k0 + 64 * wk + 32 * i < K && o0 + 64 * wo + 32 * j < O);
-    const bool bias_wave = a.mu_b != nullptr && k0 == 0 && wk == 0 && ok[0][0];      // these waves also sum dy over the rows
+    const bool bias_tile = a.mu_b != nullptr && k0 == 0;          // this workgroup also sums dy over the rows
 
-    // As a loading wave: the tiles go from memory straight into LDS (buffer loads with the LDS bit: lane l of
-    // an instruction leaves its 16 bytes at the instruction's LDS address + 16 l, zeros for an offset outside the
-    // window), 64 consecutive quads of a tile per instruction, instruction 4 m + wave of the tile for this wave.
-    // A quad outside the layer's columns gets a row number that is never below the rows left.
-    constexpr int XI = kTileRows * TK / 4 / 256, DI = kTileRows * TO / 4 / 256;       // instructions per wave and tile
-    int x_row[XI], d_row[DI];
-    unsigned x_first[XI], d_first[DI];
-#pragma unroll
-    for (int m = 0; m < XI; ++m) {
-        const int idx = (4 * m + wave) * 64 + lane;
-        const long col = k0 + 4 * (idx % (TK / 4));
-        x_row[m] = (WHOLE || col < K) ? idx / (TK / 4) : 1 << 30;
-        x_first[m] = (unsigned)((idx / (TK / 4) * a.ldx + col) * 4);
-    }
-#pragma unroll
-    for (int m = 0; m < DI; ++m) {
-        const int idx = (4 * m + wave) * 64 + lane;
-        const long col = o0 + 4 * (idx % (TO / 4));
-        d_row[m] = (WHOLE || col < O) ? idx / (TO / 4) : 1 << 30;
-        d_first[m] = (unsigned)((idx / (TO / 4) * O + col) * 4);
-    }
-    const unsigned x_step = (unsigned)(kTileRows * a.ldx * 4), d_step = (unsigned)(kTileRows * O * 4);
-    const int rows = (int)R;
+    // As a loading wave: waves 0 and 1 take the even and the odd rows of x, waves 2 and 3 those of dy; a lane two columns, eight
+    // rows of a step, which make whole operands of the matrix instruction.  Rows behind the last lie outside the window and
+    // arrive as zeros; what columns outside the layer bring is never stored.
+    const bool of_x = wave < 2;
+    const int odd = wave & 1;
+    const unsigned pitch = (unsigned)((of_x ? a.ldx : O) * 4);
+    const unsigned bytes = (unsigned)((of_x ? (R - 1) * a.ldx + K : R * O) * 4);
+    const float *const from = of_x ? a.x : a.dy;
+    const size_t from_stride = of_x ? (size_t)a.x_sample_stride : (size_t)R * (size_t)O;
+    const unsigned lane_off = (unsigned)(((of_x ? k0 : o0) + 2 * lane) * 4);
+    // Column m of a block of 32 lies in slot m / 2 of its plane's half if m is even, 16 + (m / 2 ^ 2) if odd: sixteen lanes then write a
+    // run of 256 bytes, and the lanes that a 16-byte read serves together (0-3, 12-15, 20-27 and the others; found by counting
+    // conflicts, 33 % of the LDS cycles with ^ 12, 1 % with ^ 2) meet all banks.
+    const int put_block = (of_x ? 0 : kTileBuffer / 2) + (lane >> 4) * 3072 + odd * 512;
+    const int put_at = put_block + (lane & 15) * 16, put_at1 = put_block + (16 + ((lane & 15) ^ 2)) * 16;
+    const int slot = (l32 & 1) ? 16 + ((l32 >> 1) ^ 2) : l32 >> 1;
+    const int x_get = wk * 2 * 3072 + half * 512 + slot * 16, d_get = kTileBuffer / 2 + wo * 2 * 3072 + half * 512 + slot * 16;
+    // steps of 16 rows, in pairs (the last one may run on zeros); those of the second sample follow those of the first without a gap
+    const int rows = (int)R, steps = (rows + 2 * kTileRows - 1) / (2 * kTileRows) * 2;
 
-    // The products of one sample over all rows, into the accumulators mm (and the column sums of dy into sb).
-    // A step is 16 rows, the contraction block of the bf16 matrix instruction (see split2_bf16): lanes 0-31 hold the even rows of a
-    // column, lanes 32-63 the odd ones, on both sides alike.  Four buffers, loads three steps ahead.  Step i (buffers i % 4):
-    // read its operands, cut them, multiply; wait for the loads of step i + 1 (sent for two steps ago; those of step i + 2 may
-    // still be on their way), barrier; send for step i + 3 (its buffers held step i - 1, read for the last time before this
-    // barrier).  The steps are taken four at a time so that every access names its buffer; up to three steps behind the last
-    // row run on zeros.
-    auto all_rows = [&](int s, Acc32x32 (&mm)[2][2], float (&sb)[2]) {
-        const window_t x_win = window(a.x + (size_t)s * (size_t)a.x_sample_stride, (unsigned)(((R - 1) * a.ldx + K) * 4));
-        const window_t d_win = window(a.dy + (size_t)s * (size_t)R * (size_t)O, (unsigned)(R * O * 4));
-        unsigned x_off[XI], d_off[DI];
+    f2 raw[2][8];                // the rows of two steps under way
+    auto load = [&](int i, f2 (&raw)[8], int s0, bool two) {
+        const bool second = i >= steps;
+        const int row = second ? (two ? (i - steps) * kTileRows : rows) : i * kTileRows;
+        const window_t win = window(from + (size_t)(two && second ? s0 + 1 : s0) * from_stride, bytes);
+        const unsigned at = (unsigned)((row < rows ? row : rows) + odd) * pitch;
 #pragma unroll
-        for (int m = 0; m < XI; ++m) x_off[m] = x_first[m];
-#pragma unroll
-        for (int m = 0; m < DI; ++m) d_off[m] = d_first[m];
-
-        // requests the next 16 rows of both operands, of which rows_left exist, into one pair of buffers
-        auto request = [&](lds_float *xt, lds_float *dt, int rows_left) {
-#pragma unroll
-            for (int m = 0; m < XI; ++m) {
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(x_win, (lds_void *)(xt + (4 * m + wave) * 256), 16,
-                                                         (int)(x_row[m] < rows_left ? x_off[m] : kOutside), 0, 0, 0);
-                x_off[m] += x_step;
-            }
-#pragma unroll
-            for (int m = 0; m < DI; ++m) {
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(d_win, (lds_void *)(dt + (4 * m + wave) * 256), 16,
-                                                         (int)(d_row[m] < rows_left ? d_off[m] : kOutside), 0, 0, 0);
-                d_off[m] += d_step;
-            }
-        };
-        constexpr int P = kTileRows / 2;                  // pairs of rows per step
-        float av[P][2], bv[P][2];
-        auto read_step = [&](const lds_float *xt, const lds_float *dt) {
-            const volatile lds_float *xb = xt + half * TK + 64 * wk + l32;
-            const volatile lds_float *db = dt + half * TO + 64 * wo + l32;
-#pragma unroll
-            for (int p = 0; p < P; ++p)
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    av[p][i] = xb[2 * p * TK + 32 * i];
-                    bv[p][i] = db[2 * p * TO + 32 * i];
-                }
-        };
-
-        request(XB[0], DB[0], rows);
-        request(XB[1], DB[1], rows - kTileRows);
-        request(XB[2], DB[2], rows - 2 * kTileRows);
-        everything_arrived_then_barrier();
-        for (int left = rows; left > 0;) {
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                read_step(XB[b], DB[b]);
-                if (bias_wave) {
-#pragma unroll
-                    for (int p = 0; p < P; ++p) {
-                        sb[0] += bv[p][0];
-                        sb[1] += bv[p][1];
-                    }
-                }
-                bf8 a1[2], a2[2], a3[2];
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-                    split8_bf16(f4{av[0][i], av[1][i], av[2][i], av[3][i]}, f4{av[4][i], av[5][i], av[6][i], av[7][i]}, a1[i], a2[i], a3[i]);
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    bf8 b1, b2, b3;
-                    split8_bf16(f4{bv[0][j], bv[1][j], bv[2][j], bv[3][j]}, f4{bv[4][j], bv[5][j], bv[6][j], bv[7][j]}, b1, b2, b3);
-#pragma unroll
-                    for (int i = 0; i < 2; ++i)
-                        if (WHOLE || ok[i][j]) {
-                            mm[i][j].mac(a3[i], b1);
-                            mm[i][j].mac(a2[i], b2);
-                            mm[i][j].mac(a1[i], b3);
-                            mm[i][j].mac(a2[i], b1);
-                            mm[i][j].mac(a1[i], b2);
-                            mm[i][j].mac(a1[i], b1);
-                        }
-                }
-                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(XI + DI) : "memory");
-                request(XB[(b + 3) % 4], DB[(b + 3) % 4], left - 3 * kTileRows);
-                left -= kTileRows;
-            }
+        for (int p = 0; p < 8; ++p) raw[p] = __builtin_bit_cast(f2, __builtin_amdgcn_raw_buffer_load_b64(win, (int)(lane_off + (at + 2 * p * pitch)), 0, 0));
+    };
+    // Cutting, in sixteen turns (see split2_bf16): pair n % 4 of rows of column n / 4, first its first piece and remainders, then the rest;
+    // behind a column's last turn its three operands go to LDS.
+    unsigned p1[4], p2[4], p3[4];
+    float r0, r1;
+    auto cut = [&](int turn, const f2 (&raw)[8], lds_char *buffer) {
+        const int n = turn >> 1, e = n >> 2, j = n & 3;
+        if ((turn & 1) == 0) {
+            p1[j] = __builtin_bit_cast(unsigned, __builtin_convertvector(f2{raw[2 * j][e], raw[2 * j + 1][e]}, bf2));
+            r0 = raw[2 * j][e] - __builtin_bit_cast(float, p1[j] << 16);
+            r1 = raw[2 * j + 1][e] - __builtin_bit_cast(float, p1[j] & 0xFFFF0000u);
+            return;
         }
-        everything_arrived_then_barrier();       // every wave is done with the buffers
+        p2[j] = __builtin_bit_cast(unsigned, __builtin_convertvector(f2{r0, r1}, bf2));
+        const float s0 = r0 - __builtin_bit_cast(float, p2[j] << 16), s1 = r1 - __builtin_bit_cast(float, p2[j] & 0xFFFF0000u);
+        p3[j] = __builtin_bit_cast(unsigned, __builtin_convertvector(f2{s0, s1}, bf2));
+        if (j < 3) return;
+        lds_char *const to = buffer + (e ? put_at1 : put_at);
+        *(lds_bf8 *)to = __builtin_bit_cast(bf8, u4{p1[0], p1[1], p1[2], p1[3]});
+        *(lds_bf8 *)(to + 1024) = __builtin_bit_cast(bf8, u4{p2[0], p2[1], p2[2], p2[3]});
+        *(lds_bf8 *)(to + 2048) = __builtin_bit_cast(bf8, u4{p3[0], p3[1], p3[2], p3[3]});
+    };
+    auto add_columns = [&](const f2 (&raw)[8], float (&sb)[2]) {
+#pragma unroll
+        for (int p = 0; p < 8; ++p)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) sb[e] += raw[p][e];
+    };
+    bf8 av[2][3], bv[2][3];
+    auto get_x = [&](int pl, const lds_char *buffer) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) av[i][pl] = *(const volatile lds_bf8 *)(buffer + x_get + i * 3072 + pl * 1024);
+    };
+    auto get_d = [&](int pl, const lds_char *buffer) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) bv[j][pl] = *(const volatile lds_bf8 *)(buffer + d_get + j * 3072 + pl * 1024);
+    };
+    // One step on tile i.  Barrier: every wave has read tile i - 1, and tile i + 1 is in LDS.  Beside the products, tile i + 2 is cut and
+    // put where tile i - 1 was, tile i + 4 is sent for, and every piece of an operand is read as soon as the last product that
+    // needs its predecessor has been issued (the order of the six products makes those spans short), so that one set of registers
+    // suffices.  The order is fixed by hand, a few vector instructions behind every matrix instruction: left to the scheduler they
+    // stand in rows, and the matrix pipes idle behind them.
+    auto step = [&](f2 (&raw)[8], int i, const lds_char *now, const lds_char *next, lds_char *free, int s0, bool two, Acc32x32 (&mm)[2][2], float (&sb)[2][2]) {
+        constexpr int PA[6] = {0, 0, 1, 1, 0, 2}, PB[6] = {2, 1, 1, 0, 0, 0};
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int n = 0; n < 24; ++n) {
+            const int g = n >> 2, bi = n >> 1 & 1, bj = n & 1;
+            mm[bi][bj].mac(av[bi][PA[g]], bv[bj][PB[g]]);
+            if (n < 16) cut(n, raw, free);
+            if (n == 0) get_d(0, now);
+            if (n == 3) get_x(2, now);
+            if (n == 4) get_d(2, next);
+            if (n == 12) get_d(1, next);
+            if (n == 16) {
+                if (bias_tile && !of_x) {
+                    if (i + 2 < steps) add_columns(raw, sb[0]);
+                    else add_columns(raw, sb[1]);
+                }
+                load(i + 4, raw, s0, two);
+                get_x(1, next);
+            }
+            if (n == 20) get_x(0, next);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // the steps i .. i_end - 1 of a sample (an even number), `at` the buffer of step i
+    auto all_steps = [&](int i, int i_end, int &at, int s0, bool two, Acc32x32 (&mm)[2][2], float (&sb)[2][2]) {
+#pragma unroll 1
+        for (; i < i_end; i += 2) {
+            const int b1 = at == 2 * kTileBuffer ? 0 : at + kTileBuffer, b2 = b1 == 2 * kTileBuffer ? 0 : b1 + kTileBuffer;
+            step(raw[0], i, lds + at, lds + b1, lds + b2, s0, two, mm, sb);
+            step(raw[1], i + 1, lds + b1, lds + b2, lds + at, s0, two, mm, sb);
+            at = b2;
+        }
     };
 
     // Two samples at a time, each with accumulators of its own: P_s = sum_r x_s[r] (x) dy_s[r], whose sum and whose sum
     // weighted with eps_s leave together (one draw per sample and weight).  Further pairs of samples add to what the
     // pairs before left in the gradient arrays (the same thread holds the same weights every time); the last pair
     // applies the scale and the KL part.
-    float gb_m[2] = {0.0f, 0.0f}, gb_s[2] = {0.0f, 0.0f};
+    float gb_m = 0.0f, gb_s = 0.0f;
     float special = 0.0f;                    // NaN once this lane has left a NaN (or an infinity, which only costs a look) in the last pass
-    lds_float *const mine = XB[wave];        // a buffer per wave for turning its blocks on their way out
+    lds_float *const mine = (lds_float *)lds + wave * 64 * kTurnPitch;         // for turning a block of either sample on its way out
     for (int s0 = 0; s0 < a.s_loc; s0 += 2) {
         const bool two = s0 + 1 < a.s_loc, first = s0 == 0, last = s0 + 2 >= a.s_loc;
         Acc32x32 m0[2][2], m1[2][2];
-        float sb0[2] = {0.0f, 0.0f}, sb1[2] = {0.0f, 0.0f};
-        all_rows(s0, m0, sb0);
-        if (two) all_rows(s0 + 1, m1, sb1);
+        float sb[2][2] = {{0.0f, 0.0f}, {0.0f, 0.0f}};         // (tile 0 counts for sample s0, whose steps follow)
+        // (the accumulators are not alive yet: four steps' rows are sent for at once)
+        f2 first2[2][8];
+        load(0, first2[0], s0, two);
+        load(1, first2[1], s0, two);
+        load(2, raw[0], s0, two);
+        load(3, raw[1], s0, two);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+#pragma unroll
+            for (int turn = 0; turn < 16; ++turn) cut(turn, first2[i], lds + i * kTileBuffer);
+            if (bias_tile && !of_x) add_columns(first2[i], sb[0]);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        get_d(2, lds);
+        get_d(1, lds);
+        get_x(1, lds);
+        get_x(0, lds);
+        int at = 0;
+        all_steps(0, steps, at, s0, two, m0, sb);
+        if (two) all_steps(steps, 2 * steps, at, s0, two, m1, sb);
+        everything_arrived_then_barrier();       // every wave is done with the buffers
         const MfmaSettled settled;
         special = 0.0f;                      // (not kept through the row loops)
 
-        long o0e = o0 + 64 * wo, k0e = k0 + 64 * wk;
-        asm volatile("" : "+v"(o0e), "+v"(k0e));       // (so that the addresses below are formed here, not ahead of the row loops)
+        // Out: a block of 32 x 32 goes through the wave's own LDS (which executes a wave's instructions in order, so no barrier), after which
+        // a lane holds quads of consecutive inputs, eight lanes 128 contiguous bytes of a row of the gradients.  Two quads at a time: their
+        // eps are drawn, the products of both samples combined, the gradients finished and stored.  mu and sigma of the next two are
+        // sent for ahead of the draw: loads and stores complete in order on this chip, so a load asked for where it is needed waits for
+        // the stores before it (sixteen such waits, one behind the other, were most of the time at a few hundred rows).  All through
+        // range-checked windows, without branches, behind which every outstanding access would have to be waited for.
+        int ov = (int)o0 + 64 * wo, kv = (int)k0 + 64 * wk;
+        asm volatile("" : "+v"(ov), "+v"(kv));         // (so that the addresses below are formed here, not ahead of the row loops)
+        const int oe = __builtin_amdgcn_readfirstlane(ov), ke = __builtin_amdgcn_readfirstlane(kv);
+        const long corner = (long)oe * K + ke;
+        const unsigned win_bytes = (unsigned)(64 * K * 4);
+        const window_t mu_win = window(a.mu_w + corner, win_bytes), sg_win = window(a.sigma_w + corner, win_bytes);
+        const window_t gm_win = window(a.gmu_w + corner, win_bytes), gs_win = window(a.gsig_w + corner, win_bytes);
+        const long quad_corner = a.weight_quad0 + (corner >> 2);
+        // turn n: block n / 4 (inputs 32 (n / 8), outputs 32 (n / 4 % 2)), rows 8 (n % 4) .. + 7 of it
+        auto offset = [&](int n) {
+            const int row = 32 * (n >> 2 & 1) + 8 * (n & 3) + (lane >> 3), col = 32 * (n >> 3) + 4 * (lane & 7);
+            return oe + row < (int)O && ke + col < (int)K ? (unsigned)((row * K + col) * 4) : kOutside;
+        };
+        auto finish = [&](auto plain) {
+            constexpr bool PLAIN = decltype(plain)::value != 0;         // these are the only samples
+            f4 m4[2], sd4[2], next_m4[2], next_sd4[2];
+            auto ask = [&](int n) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+                for (int e = 0; e < 2; ++e) {
+                    next_m4[e] = window_load4<false>(mu_win, offset(n + e));
+                    next_sd4[e] = window_load4<false>(sg_win, offset(n + e));
+                }
+            };
+            if (PLAIN || last) ask(0);
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                if (!ok[i][j]) continue;
-                const f16v p0 = m0[i][j].read(settled), p1 = m1[i][j].read(settled);      // (p1 is zero without a second sample)
-                const long o = o0e + 32 * j + l32;
-                f4 u[4], v[4];
+            for (int b = 0; b < 4; ++b) {
+                const f16v p0 = m0[b >> 1][b & 1].read(settled), p1 = m1[b >> 1][b & 1].read(settled);      // (p1 is zero without a second sample)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const long k = k0e + 32 * i + 8 * q + 4 * half;
-                    f4 sum = {0.0f, 0.0f, 0.0f, 0.0f}, wsum = {0.0f, 0.0f, 0.0f, 0.0f};
-                    if (WHOLE || (o < O && k < K)) {
-                        const long quad = a.weight_quad0 + ((o * K + k) >> 2);
-                        const f4 e0 = eps_quad(quad, s0, a.rng);
+                    *reinterpret_cast<lds_f4 *>(mine + l32 * kTurnPitch + 8 * q + 4 * half) = f4{p0[4 * q], p0[4 * q + 1], p0[4 * q + 2], p0[4 * q + 3]};
+                    *reinterpret_cast<lds_f4 *>(mine + (32 + l32) * kTurnPitch + 8 * q + 4 * half) = f4{p1[4 * q], p1[4 * q + 1], p1[4 * q + 2], p1[4 * q + 3]};
+                }
+#pragma unroll 1
+                for (int n = 4 * b; n < 4 * b + 4; n += 2) {
+                    if (PLAIN || last) {
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) {
-                            sum[c] = p0[4 * q + c];
-                            wsum[c] = p0[4 * q + c] * e0[c];
+                        for (int e = 0; e < 2; ++e) {
+                            m4[e] = next_m4[e];
+                            sd4[e] = next_sd4[e];
                         }
+                        ask(n + 2 < 16 ? n + 2 : n);
+                    }
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const unsigned off = offset(n + e);
+                        const lds_float *const turned = mine + (8 * ((n + e) & 3) + (lane >> 3)) * kTurnPitch + 4 * (lane & 7);
+                        const f4 q0 = *reinterpret_cast<const lds_f4 *>(turned), q1 = *reinterpret_cast<const lds_f4 *>(turned + 32 * kTurnPitch);
+                        const long quad = quad_corner + (off >> 4);
+                        const f4 e0 = eps_quad(quad, s0, a.rng);
+                        f4 om = q0, os;
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) os[c] = q0[c] * e0[c];
                         if (two) {
                             const f4 e1 = eps_quad(quad, s0 + 1, a.rng);
 #pragma unroll
                             for (int c = 0; c < 4; ++c) {
-                                sum[c] += p1[4 * q + c];
-                                wsum[c] = __builtin_fmaf(p1[4 * q + c], e1[c], wsum[c]);
+                                om[c] += q1[c];
+                                os[c] = __builtin_fmaf(q1[c], e1[c], os[c]);
                             }
                         }
-                    }
-                    u[q] = sum;
-                    v[q] = wsum;
-                }
-                // Only this wave touches its buffer and the LDS executes a wave's instructions in order: program order suffices.
-                f4 ut[4], vt[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) *reinterpret_cast<lds_f4 *>(mine + l32 * kTurnPitch + 8 * q + 4 * half) = u[q];
-#pragma unroll
-                for (int it = 0; it < 4; ++it) ut[it] = *reinterpret_cast<const lds_f4 *>(mine + (8 * it + (lane >> 3)) * kTurnPitch + 4 * (lane & 7));
-#pragma unroll
-                for (int q = 0; q < 4; ++q) *reinterpret_cast<lds_f4 *>(mine + l32 * kTurnPitch + 8 * q + 4 * half) = v[q];
-#pragma unroll
-                for (int it = 0; it < 4; ++it) vt[it] = *reinterpret_cast<const lds_f4 *>(mine + (8 * it + (lane >> 3)) * kTurnPitch + 4 * (lane & 7));
-#pragma unroll
-                for (int it = 0; it < 4; ++it) {
-                    const int row = 8 * it + (lane >> 3), quad = lane & 7;
-                    const long oo = o0e + 32 * j + row, k = k0e + 32 * i + 4 * quad;
-                    if (WHOLE || (oo < O && k < K)) {
-                        const long at = oo * K + k;
-                        f4 om = ut[it], os = vt[it];
-                        if (!first) {
-                            om += load4<true, false>(a.gmu_w + at);
-                            os += load4<true, false>(a.gsig_w + at);
+                        if (!PLAIN && !first) {
+                            om += window_load4<false>(gm_win, off);
+                            os += window_load4<false>(gs_win, off);
                         }
-                        if (last) {
-                            const f4 m4 = load4<true, false>(a.mu_w + at), sd4 = load4<true, false>(a.sigma_w + at);
+                        if (PLAIN || last) {
 #pragma unroll
                             for (int c = 0; c < 4; ++c) {
                                 float pm, ps;
-                                finish_pair(om[c], os[c], m4[c], sd4[c], (float)a.g, (float)a.k, pm, ps);
+                                finish_pair(om[c], os[c], m4[e][c], sd4[e][c], (float)a.g, (float)a.k, pm, ps);
                                 om[c] = pm;
                                 os[c] = ps;
                             }
                         }
-                        store4<true, false>(a.gmu_w + at, om);
-                        store4<true, false>(a.gsig_w + at, os);
-                        // (a product that is not finite shows in os; looking at om as well, or in lane masks, costs the row loops
-                        // registers: 300 x 2160 x 8640 x 2 230 us, 235 and 239)
-#pragma unroll
-                        for (int c = 0; c < 4; ++c) special = __builtin_fmaf(os[c], 0.0f, special);
+                        window_store4<false>(gm_win, off, om);
+                        window_store4<false>(gs_win, off, os);
+                        // (a product that is not finite shows in os)
+                        const float look = __builtin_fmaf(os[3], 0.0f, __builtin_fmaf(os[2], 0.0f, __builtin_fmaf(os[1], 0.0f, os[0] * 0.0f)));
+                        special += off != kOutside ? look : 0.0f;
                     }
                 }
             }
-        if (bias_wave) {
+        };
+        if (first && last) finish(Number<1>());
+        else finish(Number<0>());
+        everything_arrived_then_barrier();
+        if (bias_tile) {                         // the column sums of the even and of the odd rows meet in LDS
+            lds_float *const sums = (lds_float *)lds;
+            if (!of_x) {
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const long o = o0 + 64 * wo + 32 * j + l32;
-                if (o < O) {
-                    const float t0 = sb0[j] + __shfl_xor(sb0[j], 32);     // even and odd rows of the steps
-                    gb_m[j] += t0;
-                    gb_s[j] = __builtin_fmaf(t0, pick4(eps_quad(a.bias_quad0 + (o >> 2), s0, a.rng), (int)(o & 3)), gb_s[j]);
-                    if (two) {
-                        const float t1 = sb1[j] + __shfl_xor(sb1[j], 32);
-                        gb_m[j] += t1;
-                        gb_s[j] = __builtin_fmaf(t1, pick4(eps_quad(a.bias_quad0 + (o >> 2), s0 + 1, a.rng), (int)(o & 3)), gb_s[j]);
-                    }
+                for (int n = 0; n < 2; ++n)
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) sums[(n * 2 + odd) * kTileSide + 2 * lane + e] = sb[n][e];
+            }
+            everything_arrived_then_barrier();
+            const long o = o0 + t;
+            if (t < kTileSide && o < O) {
+                const float t0 = sums[t] + sums[kTileSide + t];
+                gb_m += t0;
+                gb_s = __builtin_fmaf(t0, pick4(eps_quad(a.bias_quad0 + (o >> 2), s0, a.rng), (int)(o & 3)), gb_s);
+                if (two) {
+                    const float t1 = sums[2 * kTileSide + t] + sums[3 * kTileSide + t];
+                    gb_m += t1;
+                    gb_s = __builtin_fmaf(t1, pick4(eps_quad(a.bias_quad0 + (o >> 2), s0 + 1, a.rng), (int)(o & 3)), gb_s);
                 }
             }
+            everything_arrived_then_barrier();   // (the buffers go back to the rows of the next pair)
         }
-        everything_arrived_then_barrier();       // (the buffers go back to the rows of the next pair)
     }
-    if (bias_wave && half == 0) {
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const long o = o0 + 64 * wo + 32 * j + l32;
-            if (o < O) {
-                float p, r;
-                finish_pair(gb_m[j], gb_s[j], a.mu_b[o], a.sigma_b[o], (float)a.g, (float)a.k, p, r);
-                a.gmu_b[o] = p;
-                a.gsig_b[o] = r;
-            }
-        }
+    if (bias_tile && t < kTileSide && o0 + t < O) {
+        float p, r;
+        finish_pair(gb_m, gb_s, a.mu_b[o0 + t], a.sigma_b[o0 + t], (float)a.g, (float)a.k, p, r);
+        a.gmu_b[o0 + t] = p;
+        a.gsig_b[o0 + t] = r;
     }
     return __builtin_amdgcn_ballot_w64(special != special) != 0;
 }
@@ -2367,13 +2387,10 @@ __global__ void __launch_bounds__(256, 2)
 hot_linear_wgrad_tile_kernel(LinearGradArgs a)
 {
     constexpr int TK = kTileSide, TO = kTileSide;
-    // four pairs of operand buffers, [16][128] of x and of dy each; at the end every wave turns its blocks in one of them
-    __shared__ __attribute__((aligned(16))) float x0[kTileRows * TK], x1[kTileRows * TK], x2[kTileRows * TK], x3[kTileRows * TK];
-    __shared__ __attribute__((aligned(16))) float d0[kTileRows * TO], d1[kTileRows * TO], d2[kTileRows * TO], d3[kTileRows * TO];
-    static_assert(kTileRows * TK >= 32 * kTurnPitch, "a wave's block fits in any of the buffers");
-    lds_float *XB[4], *DB[4];           // (filled by assignments: as a constant table of LDS addresses it would not link)
-    XB[0] = (lds_float *)x0, XB[1] = (lds_float *)x1, XB[2] = (lds_float *)x2, XB[3] = (lds_float *)x3;
-    DB[0] = (lds_float *)d0, DB[1] = (lds_float *)d1, DB[2] = (lds_float *)d2, DB[3] = (lds_float *)d3;
+    // (at the end every wave turns its blocks on their way out there)
+    __shared__ __attribute__((aligned(16))) char buffers[3 * kTileBuffer];
+    static_assert(3 * kTileBuffer >= 4 * 64 * kTurnPitch * 4, "two blocks of each wave");
+    lds_char *const lds = (lds_char *)buffers;
     const long K = a.in_features, O = a.out_features;
     const long k_tiles = (K + TK - 1) / TK, o_tiles = (O + TO - 1) / TO;
     const long tiles = k_tiles * o_tiles, per_xcd = (tiles + kXcds - 1) / kXcds;
@@ -2387,9 +2404,7 @@ hot_linear_wgrad_tile_kernel(LinearGradArgs a)
     const long height = band < bands ? 8 : o_tiles - 8 * bands, within = tile - (band < bands ? band : bands) * 8 * k_tiles;
     const long o0 = (8 * (band < bands ? band : bands) + within % height) * TO;
     const long k0 = (within / height) * TK;
-    // (uniform over the workgroup, so all its waves meet at the same barriers)
-    const bool special = k0 + TK <= K && o0 + TO <= O ? wgrad_tile_body<true>(a, XB, DB, o0, k0) : wgrad_tile_body<false>(a, XB, DB, o0, k0);
-    if (special) {
+    if (wgrad_tile_body(a, lds, o0, k0)) {
         // (the arguments read once more, so that none is kept for this through the row loops; the last barrier's wait covers the wave's own stores)
         unsigned long long args = (unsigned long long)__builtin_amdgcn_kernarg_segment_ptr();
 #ifdef __OPTIMIZE__       // (without optimisation nothing is kept anyhow, and the address is in no scalar register)
