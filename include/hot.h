@@ -126,6 +126,15 @@ int hot_forward(hot_plan *plan, const float *mu, const float *sigma, const float
 int hot_kl(hot_plan *plan, const float *mu, const float *sigma, double *kl_out, void *stream);
 
 /*
+ * The same term of one small layer (same passage of the paper), weights and biases together, in one launch and without a plan:
+ * kl_out = 1/2 sum over the n_w weights and the n_b biases.  n_w + n_b <= 65536 (else HOT_ERANGE).  n_b = 0 and NULL: no biases.
+ * DEVICE pointers, the arrays 4-byte aligned, kl_out 8-byte aligned.  Runs on the current device.  The sum is that of hot_kl up to the
+ * order in which its fp64 addends are added.
+ */
+int hot_kl_layer(int64_t n_w, const float *mu_w, const float *sigma_w, int64_t n_b, const float *mu_b, const float *sigma_b,
+                 double *kl_out, void *stream);
+
+/*
  * hot_forward for callers that cannot allocate device memory or create a plan: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same kernels, launch geometry and results
  * as hot_forward on a plan made from `desc` (w bit for bit; kl_out is always summed by the one-workgroup finish

@@ -129,9 +129,16 @@ class BayesianLinear:
 
     def kl(self, mu_w, sigma_w, mu_b=None, sigma_b=None) -> torch.Tensor:
         """The layer's KL term (one float64 on the device, detached; its gradient is added by backward)."""
+        parts = (mu_w, sigma_w, mu_b, sigma_b) if self.bias else (mu_w, sigma_w)
+        sizes = [self.in_features * self.out_features] + ([self.out_features] if self.bias else [])
+        if sum(sizes) <= hot.HOT_KL_LAYER_MAX and all(
+                t.is_contiguous() and t.numel() == sizes[i // 2] and (i < 2 or t.dim() == 1) for i, t in enumerate(parts)):
+            det = [t.detach() for t in parts] + [None, None]
+            out = torch.empty((), dtype=torch.float64, device=mu_w.device)
+            hot.hot_kl_layer(det[0], det[1].view_as(det[0]), det[2], det[3], out)         # (small layers: one launch)
+            return out
         if not hasattr(self, "_kl_plans"):
             dev = mu_w.device.index or 0
-            sizes = [self.in_features * self.out_features] + ([self.out_features] if self.bias else [])
             self._kl_plans = [hot.hot_create(n, n, 1, 1, self.dataset_size, dev) for n in sizes]
         out = torch.empty(len(self._kl_plans), dtype=torch.float64, device=mu_w.device)       # (each call below writes its element)
         hot.hot_kl(self._kl_plans[0], mu_w.detach().reshape(-1), sigma_w.detach().reshape(-1), out[0:1])

@@ -19,6 +19,7 @@ LIB_PATH = os.path.join(_HERE, "libhot.so")
 
 HOT_OK, HOT_EINVAL, HOT_ENOMEM, HOT_EHIP, HOT_ERANGE = 0, -1, -2, -3, -4
 HOT_STATIC_MAX_WEIGHTS = 1 << 28
+HOT_KL_LAYER_MAX = 65536
 HOT_REDUCE_SUM, HOT_REDUCE_MEAN, HOT_REDUCE_NONE = 0, 1, 2
 HOT_KERNEL_FORWARD, HOT_KERNEL_BACKWARD, HOT_KERNEL_FORWARD_RNG, HOT_KERNEL_BACKWARD_RNG = 0, 1, 2, 3
 
@@ -32,7 +33,7 @@ EXPORTS = ("hot_create", "hot_forward", "hot_backward", "hot_destroy", "hot_set_
            "hot_backward_dropout_units_rng", "hot_stats_whole", "hot_adam_forward", "hot_backward_adam_forward",
            "hot_linear_backward_rng_ws", "hot_linear_backward_workspace_bytes", "hot_forward_static",
            "hot_linear_launch_shape", "hot_linear_kernel_shape", "hot_linear_planes_shape",
-           "hot_linear_forward_rng_ws", "hot_linear_planes_workspace_bytes")
+           "hot_linear_forward_rng_ws", "hot_linear_planes_workspace_bytes", "hot_kl_layer")
 
 
 # Return types of the entry points that do not return an int status (as declared in include/hot.h).
@@ -92,6 +93,7 @@ def lib() -> ctypes.CDLL:
     L.hot_forward.argtypes = [vp, fp, fp, fp, fp, vp, vp]
     L.hot_backward.argtypes = [vp, fp, fp, fp, fp, fp, fp, vp]
     L.hot_kl.argtypes = [vp, fp, fp, vp, vp]
+    L.hot_kl_layer.argtypes = [ctypes.c_int64, fp, fp, ctypes.c_int64, fp, fp, vp, vp]
     L.hot_forward_static.argtypes = [ctypes.POINTER(hot_desc), fp, fp, fp, fp, vp, vp]
     L.hot_destroy.argtypes = [vp]
     rp = ctypes.POINTER(hot_rng)
@@ -644,6 +646,24 @@ def hot_kl(plan: Plan, mu, sigma, kl_out) -> None:
     code = lib().hot_kl(plan.handle, _vec(mu, d.n_weights, d.device, "mu"), _vec(sigma, d.n_weights, d.device, "sigma"),
                         _kl_ptr(plan, kl_out), _stream(d.device))
     _check(code, "hot_kl", plan)
+
+
+def hot_kl_layer(mu_w, sigma_w, mu_b, sigma_b, kl_out) -> None:
+    """kl_out (one float64 on the device) = the KL term of a layer of up to HOT_KL_LAYER_MAX weights and biases (mu_b, sigma_b may be
+    None), in one launch."""
+    if (mu_b is None) != (sigma_b is None):
+        raise ValueError("give both bias arrays or neither")
+    for t, like, name in ((mu_w, mu_w, "mu_w"), (sigma_w, mu_w, "sigma_w"), (mu_b, mu_b, "mu_b"), (sigma_b, mu_b, "sigma_b")):
+        if t is not None and not (t.is_cuda and t.device == mu_w.device and t.dtype == torch.float32 and t.shape == like.shape and t.is_contiguous()):
+            raise TypeError(f"{name}: need a contiguous float32 tensor of shape {tuple(like.shape)} on {mu_w.device}")
+    if not (kl_out.is_cuda and kl_out.device == mu_w.device and kl_out.dtype == torch.float64 and kl_out.numel() == 1):
+        raise TypeError(f"kl_out: need one float64 on {mu_w.device}")
+    dev = mu_w.device.index
+    with _on(dev):
+        code = lib().hot_kl_layer(mu_w.numel(), mu_w.data_ptr(), sigma_w.data_ptr(), mu_b.numel() if mu_b is not None else 0,
+                                  mu_b.data_ptr() if mu_b is not None else None, sigma_b.data_ptr() if mu_b is not None else None,
+                                  kl_out.data_ptr(), _stream(dev))
+    _check_planless(code, "hot_kl_layer")
 
 
 def hot_forward_dropout_units_rng(plan: Plan, rng: hot_rng, keep: float, in_features: int, unit_offset: int, mu, w) -> None:

@@ -117,3 +117,31 @@ def test_the_layer_hands_over_a_workspace(hot):
     want_dx = torch.empty_like(dx)
     hot.hot_linear_backward_rng(rng, d[0], t["dy"], *d[1:], *[torch.empty_like(v) for v in d[1:]], want_dx, s, 50000.0, hot.HOT_REDUCE_NONE, 0, o * k)
     assert torch.equal(dx, want_dx)
+
+
+@pytest.mark.parametrize("k,o,bias", [(4, 1, True), (4, 1, False), (128, 128, True), (96, 131, True), (1024, 63, True), (16384, 4, False),
+                                      (16384, 4, True), (2048, 33, True)])
+def test_kl_of_a_layer_in_one_launch(hot, k, o, bias):
+    """Up to HOT_KL_LAYER_MAX parameters (the first six; then the two sums of hot_kl): against fp64."""
+    from paper_2604_04736_amd.autograd import BayesianLinear
+    one_launch = k * o + (o if bias else 0) <= hot.HOT_KL_LAYER_MAX
+    g = torch.Generator(device=DEV).manual_seed(k + o)
+    mu_w, sigma_w = torch.randn(o, k, device=DEV, generator=g), torch.rand(o, k, device=DEV, generator=g) + 0.01
+    mu_b, sigma_b = torch.randn(o, device=DEV, generator=g), torch.rand(o, device=DEV, generator=g) + 0.01
+    layer = BayesianLinear(k, o, 1, 100.0, bias=bias)
+    got = layer.kl(mu_w, sigma_w, mu_b if bias else None, sigma_b if bias else None)
+    assert hasattr(layer, "_kl_plans") != one_launch and got.shape == () and got.dtype == torch.float64
+    terms = [(m.double() ** 2, s.double() ** 2) for m, s in [(mu_w, sigma_w)] + ([(mu_b, sigma_b)] if bias else [])]
+    want = sum(0.5 * (s + m - 1.0 - s.log()).sum() for m, s in terms)
+    size = sum(0.5 * (s + m + 1.0 + s.log().abs()).sum() for m, s in terms)
+    # (the hardware's log2 is within 6e-8 of a number in [1/2, 1): 8e-8 of each addend's ln sigma^2)
+    assert abs(got.item() - want.item()) <= 1e-7 * size.item()
+    # a flat view and a strided one: as before
+    assert abs(layer.kl(mu_w.reshape(-1), sigma_w.reshape(-1), mu_b, sigma_b).item() - got.item()) <= 1e-12 * size.item()
+    strided = mu_w.t().contiguous().t()
+    assert abs(layer.kl(strided, sigma_w, mu_b, sigma_b).item() - got.item()) <= 1e-12 * size.item()
+    if one_launch:
+        sigma_w[0, 0] = 0.0
+        assert layer.kl(mu_w, sigma_w, mu_b, sigma_b).item() == float("inf")
+        sigma_w[0, 0] = -1.0
+        assert layer.kl(mu_w, sigma_w, mu_b, sigma_b).isnan()
