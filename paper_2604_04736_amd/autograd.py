@@ -71,43 +71,70 @@ def _backward_scratch(rows: int, k: int, o: int, s_local: int, with_dx: bool) ->
     return max(split, hot.hot_linear_planes_workspace_bytes(rows, k, o, s_local, 1)) if with_dx else split
 
 
+_M32, _M64 = 0xFFFFFFFF, (1 << 64) - 1
+
+
+def _device_and_stream():
+    dev = torch.cuda.current_device()
+    return dev, hot._stream(dev)
+
+
+def _answer(result, where: str):
+    """The answer of a function of hot.host(): a result, None, or an error code, which is raised."""
+    if type(result) is int:
+        hot._check_planless(result, where)
+    return result
+
+
 class _Linear(torch.autograd.Function):
+    """The native functions take what is dense and on the current device (hot.host(); all of a call in one); whatever else the
+    layer is given goes through binding.py."""
+
     @staticmethod
     def forward(ctx, x, mu_w, sigma_w, mu_b, sigma_b, layer, step):
-        rng = hot.hot_rng(seed=layer.seed, step=step, first_sample=layer.first_sample)
-        xd = x.detach().contiguous()
-        y = torch.empty(layer.s_local, xd.shape[-2], layer.out_features, dtype=torch.float32, device=x.device)
-        det = [t.detach() if t is not None else None for t in (mu_w, sigma_w, mu_b, sigma_b)]
+        draw = (layer.seed & _M64, step & _M32, layer.first_sample & _M32)
+        x = x.contiguous()
+        ctx.layer, ctx.draw = layer, draw
+        ctx.save_for_backward(x, mu_w, sigma_w, mu_b, sigma_b)
         # many rows: the library leaves the drawn weights in scratch memory of ours instead of drawing them for every tile of rows
         # (never up to 128, where the look itself would cost a small layer's call)
-        rows = xd.shape[-2]
-        ws_bytes = _forward_scratch(rows, layer.in_features, layer.out_features, layer.s_local, xd.dim() == 3) if rows > 128 else 0
+        rows = x.shape[-2]
+        ws_bytes = _forward_scratch(rows, layer.in_features, layer.out_features, layer.s_local, x.dim() == 3) if rows > 128 else 0
+        if x.is_cuda:
+            y = _answer(hot.host().linear_forward(x, mu_w, sigma_w, mu_b, sigma_b, *draw, layer.s_local, layer.weight_offset, layer.bias_offset,
+                                                 ws_bytes, *_device_and_stream()), "hot_linear_forward_rng")
+            if y is not None:
+                return y
+        y = torch.empty(layer.s_local, rows, layer.out_features, dtype=torch.float32, device=x.device)
+        det = [t.detach() if t is not None else None for t in (mu_w, sigma_w, mu_b, sigma_b)]
         ws = torch.empty(ws_bytes // 4, dtype=torch.float32, device=x.device) if ws_bytes > 0 else None
-        hot.hot_linear_forward_rng(rng, xd, det[0], det[1], det[2], det[3], y, layer.weight_offset, layer.bias_offset, workspace=ws)
-        ctx.layer, ctx.rng, ctx.has_bias = layer, rng, mu_b is not None
-        ctx.save_for_backward(xd, *[t for t in det if t is not None])
+        hot.hot_linear_forward_rng(hot.hot_rng(*draw), x.detach(), det[0], det[1], det[2], det[3], y, layer.weight_offset, layer.bias_offset,
+                                   workspace=ws)
         return y
 
     @staticmethod
     def backward(ctx, grad_y):
-        layer = ctx.layer
-        xd, mu_w, sigma_w = ctx.saved_tensors[:3]
-        mu_b, sigma_b = ctx.saved_tensors[3:] if ctx.has_bias else (None, None)
-        gmw, gsw = torch.empty_like(mu_w), torch.empty_like(sigma_w)
-        gmb = torch.empty_like(mu_b) if ctx.has_bias else None
-        gsb = torch.empty_like(sigma_b) if ctx.has_bias else None
-        dx = None
-        if ctx.needs_input_grad[0]:
-            dx = torch.empty(layer.s_local, xd.shape[-2], layer.in_features, dtype=torch.float32, device=xd.device)
+        layer, draw = ctx.layer, ctx.draw
+        xd, mu_w, sigma_w, mu_b, sigma_b = (t.detach() if t is not None else None for t in ctx.saved_tensors)
+        want_dx, grad_y = ctx.needs_input_grad[0], grad_y.contiguous()
         # few weights and many rows: the library spreads the rows over the chip through scratch memory of ours
-        ws_bytes = _backward_scratch(xd.shape[-2], layer.in_features, layer.out_features, layer.s_local, dx is not None)
-        ws = torch.empty(ws_bytes // 4, dtype=torch.float32, device=xd.device) if ws_bytes > 0 else None
-        hot.hot_linear_backward_rng(ctx.rng, xd, grad_y.contiguous(), mu_w, sigma_w, mu_b, sigma_b, gmw, gsw, gmb, gsb, dx,
-                                    layer.s_local, layer.dataset_size, hot.HOT_REDUCE_NONE, layer.weight_offset,
-                                    layer.bias_offset, workspace=ws)
+        ws_bytes = _backward_scratch(xd.shape[-2], layer.in_features, layer.out_features, layer.s_local, want_dx)
+        grads = None
+        if xd.is_cuda:
+            grads = _answer(hot.host().linear_backward(xd, grad_y, mu_w, sigma_w, mu_b, sigma_b, want_dx, *draw, layer.s_local, layer.dataset_size,
+                                                      layer.weight_offset, layer.bias_offset, ws_bytes, *_device_and_stream()),
+                            "hot_linear_backward_rng_ws" if ws_bytes > 0 else "hot_linear_backward_rng")
+        if grads is None:
+            grads = [torch.empty(layer.s_local, xd.shape[-2], layer.in_features, dtype=torch.float32, device=xd.device) if want_dx else None]
+            grads += [torch.empty_like(t) if t is not None else None for t in (mu_w, sigma_w, mu_b, sigma_b)]
+            ws = torch.empty(ws_bytes // 4, dtype=torch.float32, device=xd.device) if ws_bytes > 0 else None
+            hot.hot_linear_backward_rng(hot.hot_rng(*draw), xd, grad_y, mu_w, sigma_w, mu_b, sigma_b, *grads[1:], grads[0],
+                                        layer.s_local, layer.dataset_size, hot.HOT_REDUCE_NONE, layer.weight_offset,
+                                        layer.bias_offset, workspace=ws)
+        dx = grads[0]
         if dx is not None and xd.dim() == 2:
             dx = dx.sum(0)          # a shared input collects every sample's share
-        return dx, gmw, gsw, gmb, gsb, None, None
+        return (dx, *grads[1:], None, None)
 
 
 class BayesianLinear:
@@ -129,14 +156,12 @@ class BayesianLinear:
 
     def kl(self, mu_w, sigma_w, mu_b=None, sigma_b=None) -> torch.Tensor:
         """The layer's KL term (one float64 on the device, detached; its gradient is added by backward)."""
-        parts = (mu_w, sigma_w, mu_b, sigma_b) if self.bias else (mu_w, sigma_w)
         sizes = [self.in_features * self.out_features] + ([self.out_features] if self.bias else [])
-        if sum(sizes) <= hot.HOT_KL_LAYER_MAX and all(
-                t.is_contiguous() and t.numel() == sizes[i // 2] and (i < 2 or t.dim() == 1) for i, t in enumerate(parts)):
-            det = [t.detach() for t in parts] + [None, None]
-            out = torch.empty((), dtype=torch.float64, device=mu_w.device)
-            hot.hot_kl_layer(det[0], det[1].view_as(det[0]), det[2], det[3], out)         # (small layers: one launch)
-            return out
+        if sum(sizes) <= hot.HOT_KL_LAYER_MAX and mu_w.is_cuda:           # (small layers: one launch)
+            parts = (mu_w, sigma_w, mu_b, sigma_b) if self.bias else (mu_w, sigma_w, None, None)
+            out = _answer(hot.host().kl_layer(*parts, sizes[0], sizes[1] if self.bias else 0, *_device_and_stream()), "hot_kl_layer")
+            if out is not None:
+                return out
         if not hasattr(self, "_kl_plans"):
             dev = mu_w.device.index or 0
             self._kl_plans = [hot.hot_create(n, n, 1, 1, self.dataset_size, dev) for n in sizes]

@@ -254,6 +254,20 @@ def _stream(dev: int) -> int:
 _STAY = contextlib.nullcontext()
 
 
+_host = None
+
+
+def host():
+    """The native functions around the calls that a small layer makes (csrc/host_ops.cpp); imported on first use, since it may still
+    have to be built when this module is."""
+    global _host
+    if _host is None:
+        lib()
+        from . import _hot_host
+        _host = _hot_host
+    return _host
+
+
 def _on(dev: int):
     """The device made current for a call that runs on the current one; nothing to do (1.4 us less) where it is already."""
     return _STAY if torch.cuda.current_device() == dev else torch.cuda.device(dev)
@@ -690,6 +704,11 @@ def hot_backward_dropout_units_rng(plan: Plan, rng: hot_rng, keep: float, in_fea
 
 def hot_stats_whole(yhat: torch.Tensor, ddof: int, mean_out: torch.Tensor, std_out: torch.Tensor) -> None:
     """Mean and standard deviation over the rows of yhat[S, M] in one pass (all samples on this GPU)."""
+    if yhat.is_cuda:
+        dev = torch.cuda.current_device()
+        code = host().stats_whole(yhat, int(ddof), mean_out, std_out, dev, _stream(dev))
+        if code is not None:            # (dense and on the current device, the checks done natively)
+            return _check_planless(code, "hot_stats_whole")
     s, m, ld = _dense2(yhat, torch.float32, "yhat")
     for t, name in ((mean_out, "mean_out"), (std_out, "std_out")):
         if not (t.is_cuda and t.device == yhat.device and t.dtype == torch.float32 and t.dim() == 1

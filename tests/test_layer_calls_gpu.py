@@ -1,0 +1,118 @@
+"""What BayesianLinear takes beside dense arrays on the current device, which the native calls leave to the general path: the same
+results, the same refusals."""
+import threading
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+K, O, S = 96, 130, 3
+
+
+def _layer(rows, own, bias=True, seed=5):
+    from paper_2604_04736_amd.autograd import BayesianLinear
+    g = torch.Generator(device=DEV).manual_seed(rows)
+    x = torch.randn(*((S, rows, K) if own else (rows, K)), device=DEV, generator=g)
+    p = [torch.randn(O, K, device=DEV, generator=g) * 0.1, torch.rand(O, K, device=DEV, generator=g) * 0.1 + 0.01]
+    p += [torch.randn(O, device=DEV, generator=g), torch.rand(O, device=DEV, generator=g) + 0.01] if bias else [None, None]
+    dy = torch.randn(S, rows, O, device=DEV, generator=g)
+    return BayesianLinear(K, O, S, 1000.0, bias=bias, seed=seed, weight_offset=8), x, p, dy
+
+
+def _pass(layer, x, p, dy, step=3):
+    leaves = [t.detach().requires_grad_() for t in [x] + [q for q in p if q is not None]]
+    args = leaves[1:] + [None] * (4 - len(leaves[1:]))
+    y = layer.forward(leaves[0], *args, step=step)
+    return [y.detach()] + list(torch.autograd.grad(y, leaves, dy))
+
+
+def _general(layer, x, p, dy, step=3):
+    """The same pass through binding.py alone."""
+    from paper_2604_04736_amd import binding as hot
+    rows = x.shape[-2]
+    rng = hot.hot_rng(layer.seed, step, layer.first_sample)
+    y = torch.empty(S, rows, O, device=DEV)
+    hot.hot_linear_forward_rng(rng, x, *p, y, layer.weight_offset, layer.bias_offset)
+    grads = [torch.empty_like(q) if q is not None else None for q in p]
+    dx = torch.empty(S, rows, K, device=DEV)
+    n = hot.hot_linear_backward_workspace_bytes(rows, K, O, S)
+    ws = torch.empty(n // 4, device=DEV) if n else None
+    hot.hot_linear_backward_rng(rng, x, dy, *p, *grads, dx, S, 1000.0, hot.HOT_REDUCE_NONE, layer.weight_offset, layer.bias_offset, workspace=ws)
+    return [y, dx if x.dim() == 3 else dx.sum(0)] + [g for g in grads if g is not None]
+
+
+@pytest.mark.parametrize("rows", [1, 64, 200])
+@pytest.mark.parametrize("own", [False, True])
+@pytest.mark.parametrize("bias", [False, True])
+def test_native_calls_are_the_general_path(rows, own, bias):
+    layer, x, p, dy = _layer(rows, own, bias)
+    want = _general(layer, x, p, dy)
+    for got in (_pass(layer, x, p, dy), _pass(layer, x.transpose(-1, -2).contiguous().transpose(-1, -2), p, dy),
+                _pass(layer, x, p, dy.transpose(1, 2).contiguous().transpose(1, 2))):
+        assert len(got) == len(want) and all(torch.equal(a, b) for a, b in zip(got, want))
+    # a strided weight: refused, as in binding.py
+    with pytest.raises(TypeError):
+        layer.forward(x, p[0].t().contiguous().t(), *p[1:], step=3)
+    with pytest.raises(TypeError):
+        layer.forward(x, p[0].double(), *p[1:], step=3)
+    with pytest.raises(TypeError):
+        layer.forward(x.cpu(), *[q.cpu() if q is not None else None for q in p], step=3)
+    with pytest.raises((TypeError, ValueError)):
+        layer.forward(x[..., :K - 4].contiguous(), *p, step=3)
+
+
+def test_hooks_transforms_and_threads():
+    layer, x, p, dy = _layer(64, True)
+    want = _pass(layer, x, p, dy)
+    with torch.autograd.graph.save_on_cpu():
+        assert all(torch.equal(a, b) for a, b in zip(_pass(layer, x, p, dy), want))
+    with pytest.raises(RuntimeError):              # (an autograd function without rules for them)
+        torch.func.grad(lambda m: layer.forward(x, m, *p[1:], step=3).sum())(p[0])
+    with pytest.raises(RuntimeError):
+        torch.func.vmap(lambda v: layer.forward(v, *p, step=3))(torch.stack([x, x]))
+    # a parameter changed between forward and backward is noticed
+    m = p[0].clone().requires_grad_()
+    y = layer.forward(x, m, *p[1:], step=3)
+    with torch.no_grad():
+        m.add_(1.0)
+    with pytest.raises(RuntimeError):
+        torch.autograd.grad(y, m, dy)
+    # several threads, each with a stream of its own
+    results, errors = [None] * 4, []
+
+    def work(i):
+        try:
+            s = torch.cuda.Stream()
+            s.wait_stream(torch.cuda.default_stream())
+            with torch.cuda.stream(s):
+                for _ in range(20):
+                    results[i] = _pass(layer, x, p, dy)
+            s.synchronize()
+        except Exception as e:       # noqa: BLE001 (reported below)
+            errors.append(e)
+    torch.cuda.synchronize()
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors
+    for r in results:
+        assert all(torch.equal(a, b) for a, b in zip(r, want))
+
+
+def test_statistics_of_what_the_native_call_leaves_to_the_general_path():
+    from paper_2604_04736_amd import binding as hot
+    y = torch.randn(5, 40, device=DEV)
+    mean, std = torch.empty(33, device=DEV), torch.empty(33, device=DEV)
+    hot.hot_stats_whole(y[:, :33], 1, mean, std)            # rows with a pitch
+    want, want_std = torch.empty(33, device=DEV), torch.empty(33, device=DEV)
+    hot.hot_stats_whole(y[:, :33].contiguous(), 1, want, want_std)
+    assert torch.equal(mean, want) and torch.equal(std, want_std)
+    assert torch.allclose(mean.double(), y[:, :33].double().mean(0), atol=1e-6)
+    for bad in (mean.double(), mean[:32], mean.cpu()):
+        with pytest.raises(TypeError):
+            hot.hot_stats_whole(y[:, :33], 1, bad, std)
+    with pytest.raises(hot.HotError):
+        hot.hot_stats_whole(y, 5, torch.empty(40, device=DEV), torch.empty(40, device=DEV))      # ddof as large as the samples are many
