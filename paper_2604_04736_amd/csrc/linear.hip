@@ -4054,15 +4054,20 @@ int hot_linear_forward_rng_ws(const hot_linear_desc *d, const hot_rng *rng, cons
     // samples: eight workgroups, 28 us of dependent instructions): the samples then go to workgroups of their own, one each while all
     // waves fit on the chip at two per SIMD, else in as many chunks as do.
     const long waves_all = gx * gy * waves;
-    // (a second wave per SIMD gains the four-tile workgroups nothing: their pairs of samples stay together)
-    const long room = rb == 4 && d->s_local == 2 ? 1024 : 2048;
+    // (a second wave per SIMD gains the four-tile workgroups nothing: their pairs of samples stay together.  Of the workgroups of sixteen
+    // waves one runs on a compute unit at a time, four waves to a SIMD: they may be as many as the compute units.  With 128 before:
+    // 8000 x 2000 x 2 samples x 16 rows 67.7 -> 49.8 us, 5000 x 1100 x 4 77 -> 41, 700 x 540 x 8 16.0 -> 10.4, 2048^2 x 2 20.7 -> 15.5; beyond
+    // 256 a second round begins: 280, 2048 x 2240 x 2, 19.9 -> 24.2.)
+    const bool sixteen = rb == 1 && waves == kMaxWaves;
+    const long room = sixteen ? (long)kMaxWaves * kComputeUnits : rb == 4 && d->s_local == 2 ? 1024 : 2048;
     a.s_chunk = (d->s_local + st - 1) / st * st;
     if (waves_all * d->s_local <= room) {
         st = 1;
         a.s_chunk = 1;
     } else if (2 * waves_all <= room) {
-        const int chunks = (int)(room / waves_all);
-        a.s_chunk = ((d->s_local + chunks - 1) / chunks + st - 1) / st * st;
+        const int chunks = (int)(room / waves_all), per = (d->s_local + chunks - 1) / chunks;
+        if (sixteen && per < st) st = per > 1 ? 2 : 1;
+        a.s_chunk = (per + st - 1) / st * st;
     }
     const dim3 grid((unsigned)gx, (unsigned)gy, (unsigned)((d->s_local + a.s_chunk - 1) / a.s_chunk));
     if (rb == 4) linear_go<4>(st, grid, waves, s, a);

@@ -145,3 +145,21 @@ def test_kl_of_a_layer_in_one_launch(hot, k, o, bias):
         assert layer.kl(mu_w, sigma_w, mu_b, sigma_b).item() == float("inf")
         sigma_w[0, 0] = -1.0
         assert layer.kl(mu_w, sigma_w, mu_b, sigma_b).isnan()
+
+
+@pytest.mark.parametrize("rows,k,o,s,own", [(16, 2048, 2048, 2, True), (3, 2048, 2049, 2, False), (16, 5000, 1100, 4, True), (9, 5000, 1100, 4, False),
+                                            (16, 2048, 1400, 3, True), (16, 1024, 700, 7, False), (1, 700, 1200, 16, True), (16, 2048, 2240, 2, True)])
+def test_samples_in_workgroups_of_their_own(hot, rows, k, o, s, own):
+    """Few rows, sixteen waves to a tile: up to one workgroup per compute unit the samples are dealt out; every sample's y is that of a call
+    with it alone, bit for bit (the last layer is beyond the line)."""
+    print("case dealt samples", rows, k, o, s, own, flush=True)
+    t = _inputs(rows + k + o, rows, k, o, s, own, k)
+
+    def run(x, first, n):
+        y = torch.full((n, rows, o), float("nan"), device=DEV)
+        hot.hot_linear_forward_rng(hot.hot_rng(seed=3, step=1, first_sample=first), x, t["mu_w"], t["sigma_w"], t["mu_b"], t["sigma_b"], y, 0, o * k)
+        return y
+
+    y = run(t["x"], 5, s)
+    for i in range(s):
+        assert torch.equal(y[i], run(t["x"][i].contiguous() if own else t["x"], 5 + i, 1)[0])
