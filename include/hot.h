@@ -264,10 +264,12 @@ int hot_linear_forward_rng(const hot_linear_desc *desc, const hot_rng *rng, cons
                            const float *sigma_w, const float *mu_b, const float *sigma_b, float *y, void *stream);
 
 /*
- * The same call with device scratch of the caller's (same passage of the paper; the same y bit for bit).  At thousands of rows
- * the tiles of 256 to 1024 rows draw the weights once each; with a workspace one launch draws all of them once and leaves their
- * bf16 pieces there (six bytes per weight and sample, at most 128 MiB in all), a second multiplies (7260 x 2160 x 540, two
- * samples: 325 -> 190 us; 16640 x 192 x 768: 80 -> 64).  hot_linear_planes_workspace_bytes(desc, 0) returns the bytes that the call
+ * The same call with device scratch of the caller's (same passage of the paper).  At hundreds and thousands of rows
+ * the tiles draw the weights once each; with a workspace one launch draws all of them once and leaves their
+ * bf16 pieces there (six bytes per weight and sample, at most 256 MiB in all), a second multiplies (7260 x 2160 x 540, two
+ * samples: 325 -> 190 us; 16640 x 192 x 768: 80 -> 64; 1363 x 2188 x 1272, three: 199 -> 142).  y is the same bit for bit where the tiles of
+ * 256 to 1024 rows would run (hot_linear_planes_shape below 100); where the kernel for tens to hundreds of rows would, it is 0.75 to
+ * 0.8 times as far from the sums in 64 bits, and infinities give what they give there.  hot_linear_planes_workspace_bytes(desc, 0) returns the bytes that the call
  * would use (0: none; HOT_EINVAL for a malformed desc or another `which`), with which = 1 those that the input gradients of
  * hot_linear_backward_rng_ws would use in the same way.  workspace: DEVICE, 16-byte aligned, owned by the caller, contents
  * undefined afterwards, or NULL; with fewer bytes than asked for the call is hot_linear_forward_rng.  Calls that share a
@@ -350,7 +352,7 @@ int64_t hot_linear_kernel_shape(const hot_linear_desc *desc, int which, int64_t 
  * The same for the product with weights that a workspace holds as bf16 pieces (host arithmetic only; same passages of the paper),
  * with workspace_bytes of it (0: none; negative: all that is asked for).  which = 0: hot_linear_forward_rng_ws; 1: the
  * input-gradient part of hot_linear_backward_rng_ws (dy taken to be 16-byte aligned).  10 * (rows per workgroup / 64) + (outputs per
- * workgroup / 64), e.g. 33; 0 where other kernels run.  HOT_EINVAL for a malformed desc or another `which`.
+ * workgroup / 64), e.g. 33, + 100 with the small products in accumulators of their own; 0 where other kernels run.  HOT_EINVAL for a malformed desc or another `which`.
  */
 int hot_linear_planes_shape(const hot_linear_desc *desc, int which, int64_t workspace_bytes);
 

@@ -433,7 +433,7 @@ def hot_linear_forward_rng(rng: hot_rng, x, mu_w, sigma_w, mu_b, sigma_b, y, wei
                            bias_offset: int = 0, workspace=None) -> None:
     """y[S, R, O] = x_s (mu_w + sigma_w*eps_s)^T + (mu_b + sigma_b*eps_s^b), eps drawn in the kernel;
     x is [R, K] (shared by the samples) or [S, R, K] (one input per sample).  workspace: an optional contiguous device
-    tensor (any dtype) used as scratch (hot_linear_forward_rng_ws; the same y)."""
+    tensor (any dtype) used as scratch (hot_linear_forward_rng_ws)."""
     def chk(t, shape, name):
         if not (t.is_cuda and t.device == x.device and t.dtype == torch.float32 and tuple(t.shape) == shape
                 and t.is_contiguous()):

@@ -803,11 +803,6 @@ hot_linear_slab_kernel(SlabArgs a)
     }
 }
 
-// (in a file of its own; it uses the windows, the draw and the pieces above)
-}  // namespace
-#include "linear_planes.h"
-namespace {
-
 // ---------------------------------------------------------------------------------
 // Tens to hundreds of rows.  The kernel above shares a drawn weight among waves that hold 64 rows each and meet at a barrier
 // in every step; with few rows its workgroups are few or its waves idle, and what runs instead draws every weight once per 64 or
@@ -868,8 +863,8 @@ __device__ __forceinline__ void philox_rounds(u4 &c, unsigned k0, unsigned k1)
 // the inputs without pieces alone, which the OUTS lanes of a row look for together: an infinity or NaN among them decides the sum
 // (an infinite weight beside an infinite input, which could make it NaN, is not looked for), and few draws are needed (300 x 2160 x 8640 x 2 samples with one infinity in every row 11.9 -> 0.9 ms).  All of it is formed
 // only where that leaves it open.  Called by whole waves (in: the row of the lane, also of lanes beyond the outputs).
-template <bool TR, int OUTS>
-__device__ __forceinline__ float deep_plain_sum(const DeepArgs &a, const float *in, int s, int n, int c_lo, int c_hi, bool again)
+template <bool TR, int OUTS, class Args>
+__device__ __forceinline__ float deep_plain_sum(const Args &a, const float *in, int s, int n, int c_lo, int c_hi, bool again)
 {
     auto weight = [&](int c) -> float {
         const long flat = TR ? (long)c * a.outs + n : (long)n * a.contract + c;
@@ -902,6 +897,11 @@ __device__ __forceinline__ float deep_plain_sum(const DeepArgs &a, const float *
     for (int c = c_lo; c < c_hi && sum == sum; ++c) sum = __builtin_fmaf(in[c], weight(c), sum);
     return sum;
 }
+
+// (in a file of its own; it uses the windows, the draw, the pieces and the sums above)
+}  // namespace
+#include "linear_planes.h"
+namespace {
 
 template <int RB, int CB, bool TR>
 __global__ void __launch_bounds__(64 * kDeepWaves, RB * CB <= 2 ? 4 : RB * CB <= 4 ? 3 : (RB * CB <= 8 ? 2 : 1))
@@ -1540,23 +1540,34 @@ inline DeepPlan deep_forward_plan(const hot_linear_desc *d)
 
 // Whether planes of drawn weights (linear_planes.h) stand in for a launch of the slab kernel that takes `slab` microseconds by its
 // model: where a workspace holds them, unless they are slower by the models.  (Their sums are the bf16 slab kernel's bit for bit;
-// layers of the kernels whose waves share a sum, and of the 128-row slab shapes on the fp32 instruction, stay where they are.)  Of 213
-// such products the rule takes 170, 1.36 times as fast on average, the slowest 0.99 (7260 x 2160 x 540 x 2 samples 312 -> 190 us,
-// 13300 x 180 x 216 x 4 94 -> 42); the slab model is 4 to 16 % below the time of most layers, and under 20 us the second launch shows
-// (1818 x 48 x 588 x 3 12.6 -> 15).
-constexpr double kPlanesMost = 1.11, kPlanesMostShort = 0.83, kPlanesShort = 20.0;
+// layers of the 128-row slab shapes on the fp32 instruction stay where they are.)  Of 8450 forward products the rule takes 7050, 1.32
+// times as fast on average, 78 of them slower by more than 3 % (0.85 at worst; 7260 x 2160 x 540 x 2 samples 312 -> 190 us, 13300 x 180 x
+// 216 x 4 94 -> 42); the slab model is 10 % below the time in the middle, hence the factor; under 40 us the second launch and the draw of
+// wide layers show (213 x 120 x 5072 x 4: 19 -> 30).
+constexpr double kPlanesMost = 1.11, kPlanesMostShort = 0.75, kPlanesShort = 40.0;
 
 inline PlanePlan planes_instead(long R, long C, long N, int S, bool tr, double slab, int64_t ws_bytes)
 {
-    if (ws_bytes == 0) return kNoPlanePlan;
-    const PlanePlan p = plane_plan(R, C, N, S, tr);
-    const bool faster = p.time < (p.time < kPlanesShort ? kPlanesMostShort : kPlanesMost) * slab;
-    return p.code >= 0 && (ws_bytes < 0 || p.bytes <= ws_bytes) && faster ? p : kNoPlanePlan;
+    const PlanePlan p = plane_plan(R, C, N, S, tr, false);
+    const double most = p.time < kPlanesShort ? kPlanesMostShort : kPlanesMost;
+    return p.code >= 0 && (ws_bytes < 0 || p.bytes <= ws_bytes) && p.time < most * slab ? p : kNoPlanePlan;
 }
+
+// ... and for a forward launch of the kernel for tens to hundreds of rows, with the small products apart.  Of 6918 such products
+// this takes 1947, 1.26 times as fast on average, 28 slower by more than 3 % (0.87 at worst; 300 x 2160 x 8640 x 2: 243 -> 205, 1363 x 2188 x
+// 1272 x 3 199 -> 142); the two narrow tiles have the long sums, where the models know less, and under 40 us it is as above.
+constexpr double kApartMost = 0.9, kApartMostNarrow = 0.75;
 
 inline PlanePlan planes_forward_plan(const hot_linear_desc *d, int64_t ws_bytes)
 {
-    if (ws_bytes == 0 || deep_forward_plan(d).code >= 0) return kNoPlanePlan;
+    if (ws_bytes == 0) return kNoPlanePlan;
+    if (const DeepPlan deep = deep_forward_plan(d); deep.code >= 0) {
+        if (!slab_kernel_fits(d->rows, d->in_features, d->out_features, d->ldx)) return kNoPlanePlan;        // (32-bit offsets)
+        const PlanePlan p = plane_plan(d->rows, d->in_features, d->out_features, d->s_local, false, true);
+        const double time = deep_time(deep, d->rows, d->in_features, d->out_features, d->s_local, d->x_sample_stride != 0 ? d->s_local : 1);
+        const double most = (p.code >= 0 && kPlaneShapesApart[p.code].rb == 1 ? kApartMostNarrow : kApartMost) * (p.time < kPlanesShort ? kPlanesMostShort : 1.0);
+        return p.code >= 0 && (ws_bytes < 0 || p.bytes <= ws_bytes) && p.time < most * time ? p : kNoPlanePlan;
+    }
     const SlabForwardPlan slab = slab_forward_plan(d);
     if ((!slab.two.waves && !slab.one.waves) || (slab.two.waves && slab.two.rbw == 1) || (slab.one.waves && slab.one.rbw == 1)) return kNoPlanePlan;
     return planes_instead(d->rows, d->in_features, d->out_features, d->s_local, false,
@@ -3891,7 +3902,9 @@ int hot_linear_planes_shape(const hot_linear_desc *d, int which, int64_t workspa
     if (const int plain = hot_linear_launch_shape(d, 0); plain < 0) return plain;
     if (which < 0 || which > 1) return HOT_EINVAL;
     const PlanePlan p = which == 0 ? planes_forward_plan(d, workspace_bytes) : planes_input_grad_plan(d, true, workspace_bytes);
-    return p.code < 0 ? 0 : 10 * kPlaneShapes[p.code].rb + kPlaneShapes[p.code].cb;
+    if (p.code < 0) return 0;
+    const PlaneShape &h = p.apart ? kPlaneShapesApart[p.code] : kPlaneShapes[p.code];
+    return (p.apart ? 100 : 0) + 10 * h.rb + h.cb;
 }
 
 int64_t hot_linear_planes_workspace_bytes(const hot_linear_desc *d, int which)
@@ -3973,6 +3986,27 @@ int hot_linear_forward_rng_ws(const hot_linear_desc *d, const hot_rng *rng, cons
     a.rng = r;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
+    // Given scratch, many rows: the weights drawn once into it.
+    if (const PlanePlan plan = planes_forward_plan(d, workspace ? workspace_bytes : 0); plan.code >= 0) {
+        SlabArgs b;
+        b.rows = d->rows;
+        b.contract = d->in_features;
+        b.outs = d->out_features;
+        b.ld_in = d->ldx;
+        b.in_sample_stride = d->x_sample_stride;
+        b.s_begin = b.s_end = 0;
+        b.weight_quad0 = a.weight_quad0;
+        b.bias_quad0 = a.bias_quad0;
+        b.in = x;
+        b.mu_w = mu_w;
+        b.sigma_w = sigma_w;
+        b.mu_b = mu_b;
+        b.sigma_b = sigma_b;
+        b.out = y;
+        b.rng = r;
+        planes_run<false>(plan, s, b, d->s_local, static_cast<char *>(workspace));
+        return hot_detail::note_hip(hipGetLastError());
+    }
     if (const DeepPlan plan = deep_forward_plan(d); plan.code >= 0) {
         DeepArgs b;
         b.rows = d->rows;
@@ -4014,10 +4048,6 @@ int hot_linear_forward_rng_ws(const hot_linear_desc *d, const hot_rng *rng, cons
         b.sigma_b = sigma_b;
         b.out = y;
         b.rng = r;
-        if (const PlanePlan planes = planes_forward_plan(d, workspace ? workspace_bytes : 0); planes.code >= 0) {
-            planes_run<false>(planes, s, b, d->s_local, static_cast<char *>(workspace));
-            return hot_detail::note_hip(hipGetLastError());
-        }
         if (plan.two.waves == 4 && plan.two.rbw == 1) slab_go<4, 1, 2, false, false, 1>(s, b, 0, plan.pair_samples);
         else if (plan.two.waves == 4) slab_go<4, 1, 2, false, false>(s, b, 0, plan.pair_samples);
         else if (plan.two.waves) {

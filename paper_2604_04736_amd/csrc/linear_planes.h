@@ -6,7 +6,9 @@
 // the order in which the lanes of the matrix instruction take them, and hot_linear_planes_kernel multiplies: a wave reads its
 // weight operands straight from memory into registers (1 KB per instruction, no LDS, no address arithmetic), x is cut once per
 // workgroup and shared through LDS.  Products, their order and the order of the contraction are the slab kernel's, so results
-// are the same bit for bit.  Measured (two samples, product kernel + draw): 7260 x 2160 x 540 forward 325 -> 181 + 5 us, its input
+// are the same bit for bit.  Layers of the kernel for tens to hundreds of rows, whose four waves share a sum, come here with the five
+// small products of every pair of factors in accumulators of their own (APART): the large ones then take one rounding per
+// step instead of six, and the sums end 0.76-0.80 times as far from 64 bits as that kernel's (190 layers).  Measured (two samples, product kernel + draw): 7260 x 2160 x 540 forward 325 -> 181 + 5 us, its input
 // gradients 270 -> 171 + 8, 16640 x 192 x 768 80 -> 60 + 4 and 96 -> 59 + 5.
 #ifndef HOT_LINEAR_PLANES_H
 #define HOT_LINEAR_PLANES_H
@@ -101,13 +103,14 @@ struct PlaneArgs {
     int row_tiles, col_tiles, items, per_xcd;
     int rows_first;              // neighbouring workgroups: 1 the row tiles of a column, 0 the column tiles of a row
     long bias_quad0;
-    const float *in, *mu_b, *sigma_b;
+    long weight_quad0;           // (APART, for sums that are formed again)
+    const float *in, *mu_w, *sigma_w, *mu_b, *sigma_b;
     const char *planes;
     float *out;                  // [S, R, N]
     Rng rng;
 };
 
-template <int RB, int CB, int OCC>
+template <int RB, int CB, int OCC, bool APART>
 __global__ void __launch_bounds__(256, OCC)
 hot_linear_planes_kernel(PlaneArgs a)
 {
@@ -167,7 +170,7 @@ hot_linear_planes_kernel(PlaneArgs a)
 #pragma unroll
         for (int pl = 0; pl < 3; ++pl) bv[u][cb][pl] = __builtin_bit_cast(bf8, window_load4<false>(w_win, w_off + cb * (unsigned)kBlockBytes + pl * 1024u));
     };
-    Acc32x32 mm[RB][CB];
+    Acc32x32 mm[RB][CB], small[APART ? RB : 1][APART ? CB : 1];
 
     // One step on tile i, whose operands are in registers (set u).  First half: x of tile i + 1 is cut and put into LDS, its weights and
     // x of tile i + 2 are sent for; barrier; second half: the operands of tile i + 1 are read.
@@ -191,7 +194,10 @@ hot_linear_planes_kernel(PlaneArgs a)
             for (int rb = 0; rb < RB; ++rb)
                 if (g == MID + rb) get_x(u ^ 1, rb, to);
 #pragma unroll
-            for (int rb = 0; rb < RB; ++rb) mm[rb][cb].mac(av[u][rb][PA[i]], bv[u][cb][PB[i]]);
+            for (int rb = 0; rb < RB; ++rb) {
+                if constexpr (APART) (i < 5 ? small : mm)[rb][cb].mac(av[u][rb][PA[i]], bv[u][cb][PB[i]]);
+                else mm[rb][cb].mac(av[u][rb][PA[i]], bv[u][cb][PB[i]]);
+            }
             __builtin_amdgcn_sched_barrier(0);
         }
     };
@@ -214,21 +220,44 @@ hot_linear_planes_kernel(PlaneArgs a)
     int r0w = r0 + wr * 32 * RB + 4 * half, n0l = n0 + wc * 32 * CB + l32;
     asm volatile("" : "+v"(r0w), "+v"(n0l));       // (so that the offsets below are formed here, not ahead of the loop)
     const window_t out_win = window(a.out + (size_t)s * (size_t)R * (size_t)N, (unsigned)((long)R * N * 4));
+    auto bias_of = [&](int n) {
+        return a.mu_b && n < N ? __builtin_fmaf(a.sigma_b[n], pick4_of(eps_quad(a.bias_quad0 + (n >> 2), s, a.rng), n & 3), a.mu_b[n]) : 0.0f;
+    };
+    [[maybe_unused]] bool special = false;
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) {
         const int n = n0l + 32 * cb;
         const bool n_ok = n < N;
-        float bias = 0.0f;
-        if (a.mu_b && n_ok) bias = __builtin_fmaf(a.sigma_b[n], pick4_of(eps_quad(a.bias_quad0 + (n >> 2), s, a.rng), n & 3), a.mu_b[n]);
+        const float bias = bias_of(n);
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            const f16v acc = mm[rb][cb].read(settled);
+            f16v acc = mm[rb][cb].read(settled);
+            if constexpr (APART) acc += small[rb][cb].read(settled);
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 const int row = r0w + 32 * rb + 8 * (i >> 2) + (i & 3);
-                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, acc[i] + bias), out_win,
+                const float sum = acc[i] + bias;
+                if constexpr (APART) special |= n_ok && row < R && sum != sum;
+                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, sum), out_win,
                                                       (n_ok && row < R) ? (int)(((unsigned)row * (unsigned)N + (unsigned)n) * 4u) : (int)kOutside, 0, 0);
             }
+        }
+    }
+    // (where the other kernel forms sums again that the pieces leave as NaN, so does this one: each lane looks at what it stored)
+    if constexpr (APART) {
+        if (__builtin_amdgcn_ballot_w64(special) == 0) return;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        float *const y0 = a.out + (size_t)s * (size_t)R * (size_t)N;
+#pragma unroll 1
+        for (int k = 0; k < RB * CB * 16; ++k) {
+            const int i = k & 15, row = r0w + 32 * ((k >> 4) % RB) + 8 * (i >> 2) + (i & 3), n = n0l + 32 * ((k >> 4) / RB);
+            const bool mine = row < R && n < N;
+            float *const y = y0 + (mine ? (size_t)row * (size_t)N + (size_t)n : 0);
+            const bool again = mine && *y != *y;
+            if (__builtin_amdgcn_ballot_w64(again) == 0) continue;
+            const float *in = a.in + (size_t)s * (size_t)a.in_sample_stride + (size_t)(row < R ? row : R - 1) * (size_t)a.ld_in;
+            const float sum = deep_plain_sum<false, 32>(a, in, s, n, 0, C, again);
+            if (again) *y = sum + bias_of(n);
         }
     }
 }
@@ -252,26 +281,32 @@ constexpr PlaneShape kPlaneShapes[] = {{3, 3, 1, 1.6, 5.9, {0.849}, 0.375, 1.57}
                                        {3, 1, 3, 3.4, 0.0, {0.464, 0.761, 1.175}, 0.119, 1.2},
                                        {1, 1, 6, 0.0, 0.0, {0.297, 0.303, 0.425, 0.594, 0.747, 0.817}, 0.079, 0.49}};
 constexpr int kPlaneCodes = sizeof(kPlaneShapes) / sizeof(kPlaneShapes[0]);
+// The same with two sets of accumulators (190 products of 64 to 7800 rows, within 5 %, 0.8 % behind the fastest on average).
+constexpr PlaneShape kPlaneShapesApart[] = {{2, 2, 2, 2.1, 2.3, {0.45, 0.805}, 0.17, 0.98},
+                                            {2, 3, 1, 0.7, 5.5, {0.581}, 0.282, 0.61},
+                                            {1, 3, 2, 2.2, 0.5, {0.443, 0.764}, 0.085, 1.54},
+                                            {1, 1, 5, 0.3, 0.0, {0.305, 0.305, 0.364, 0.538, 0.614}, 0.085, 0.84}};
+constexpr int kPlaneCodesApart = sizeof(kPlaneShapesApart) / sizeof(kPlaneShapesApart[0]);
 
-// Most bytes of planes: half of the memory-side cache, so that they are read from there and the workspace stays small beside
-// the layer's own arrays.
-constexpr int64_t kPlanesMostBytes = (int64_t)128 << 20;
+// Most bytes of planes: those of a layer that the memory-side cache holds, so that they are read from there.
+constexpr int64_t kPlanesMostBytes = (int64_t)256 << 20;
 constexpr long kPlanesMostTiles = (1L << 24) - kXcds;        // (one grid dimension holds fewer than 2^32 threads)
 
 struct PlanePlan {
-    int code;            // index into kPlaneShapes, -1: none
+    int code;            // index into kPlaneShapes or kPlaneShapesApart, -1: none
+    bool apart;
     int64_t bytes;       // of the planes of all samples
     double time;         // microseconds, the draw included
 };
-constexpr PlanePlan kNoPlanePlan = {-1, 0, 0.0};
+constexpr PlanePlan kNoPlanePlan = {-1, false, 0, 0.0};
 
-inline PlanePlan plane_plan(long R, long C, long N, int S, bool tr)
+inline PlanePlan plane_plan(long R, long C, long N, int S, bool tr, bool apart)
 {
     const long steps = plane_steps(C), blocks = plane_blocks(N);
     if (S > 65535 || steps > 4 * 65535 || blocks > 65535 || steps > kPlanesMostBytes / kBlockBytes / blocks / S) return kNoPlanePlan;
-    PlanePlan best = {-1, steps * blocks * S * kBlockBytes, 0.0};
-    for (int i = 0; i < kPlaneCodes; ++i) {
-        const PlaneShape &h = kPlaneShapes[i];
+    PlanePlan best = {-1, apart, steps * blocks * S * kBlockBytes, 0.0};
+    for (int i = 0; i < (apart ? kPlaneCodesApart : kPlaneCodes); ++i) {
+        const PlaneShape &h = apart ? kPlaneShapesApart[i] : kPlaneShapes[i];
         const long wgs_of_sample = ((R + 64 * h.rb - 1) / (64 * h.rb)) * ((N + 64 * h.cb - 1) / (64 * h.cb));
         if (wgs_of_sample > kPlanesMostTiles / S) continue;
         const long wgs = wgs_of_sample * S, round = (long)kComputeUnits * h.resident, full = wgs / round, left = wgs % round;
@@ -288,14 +323,14 @@ inline PlanePlan plane_plan(long R, long C, long N, int S, bool tr)
     return best;
 }
 
-template <int RB, int CB, int OCC>
+template <int RB, int CB, int OCC, bool APART = false>
 void planes_go(hipStream_t s, PlaneArgs a, int samples)
 {
     a.row_tiles = (int)((a.rows + 64 * RB - 1) / (64 * RB));
     a.col_tiles = (int)((a.outs + 64 * CB - 1) / (64 * CB));
     a.items = a.row_tiles * a.col_tiles * samples;
     a.per_xcd = (a.items + kXcds - 1) / kXcds;
-    hot_linear_planes_kernel<RB, CB, OCC><<<dim3((unsigned)(kXcds * a.per_xcd)), dim3(256), 0, s>>>(a);
+    hot_linear_planes_kernel<RB, CB, OCC, APART><<<dim3((unsigned)(kXcds * a.per_xcd)), dim3(256), 0, s>>>(a);
 }
 
 // Draws the planes of all samples into `planes` (p.bytes of them) and multiplies.
@@ -332,12 +367,23 @@ void planes_run(const PlanePlan &p, hipStream_t s, const SlabArgs &b, int sample
     // Neighbouring workgroups, which run at the same time behind one L2, share the larger operand (1024 x 8192^2: 1336 -> 1238 us on tiles of 128 x 128)
     a.rows_first = 6 * b.outs > 4 * b.rows;
     a.bias_quad0 = b.bias_quad0;
+    a.weight_quad0 = b.weight_quad0;
     a.in = b.in;
+    a.mu_w = b.mu_w;
+    a.sigma_w = b.sigma_w;
     a.mu_b = b.mu_b;
     a.sigma_b = b.sigma_b;
     a.planes = planes;
     a.out = b.out;
     a.rng = b.rng;
+    if constexpr (!TR) {
+        if (p.apart) switch (p.code) {
+            case 0: return planes_go<2, 2, 2, true>(s, a, samples);
+            case 1: return planes_go<2, 3, 1, true>(s, a, samples);
+            case 2: return planes_go<1, 3, 2, true>(s, a, samples);
+            default: return planes_go<1, 1, 2, true>(s, a, samples);
+            }
+    }
     switch (p.code) {
     case 0: return planes_go<3, 3, 1>(s, a, samples);
     case 1: return planes_go<2, 2, 2>(s, a, samples);

@@ -30,10 +30,10 @@ def _workspace(bytes_):
 
 # (rows, in, out, samples, per-sample x, tile code): every tile, ragged rows, inputs (whole and half steps, odd and even numbers of
 # them) and outputs
-FORWARD = [(1460, 24, 769, 1, False, 11), (3031, 28, 125, 3, True, 11), (3968, 36, 937, 4, False, 13), (4864, 36, 724, 4, True, 13),
-           (7718, 24, 985, 2, False, 21), (7911, 36, 555, 3, True, 21), (1101, 84, 2236, 3, False, 22), (6283, 236, 102, 4, True, 22),
-           (4250, 84, 772, 3, False, 23), (5967, 212, 131, 4, True, 23), (2103, 148, 1472, 2, False, 31), (7468, 44, 507, 4, True, 31),
-           (720, 148, 2771, 4, False, 33), (1484, 144, 1821, 3, True, 33)]
+FORWARD = [(8542, 24, 128, 2, False, 11), (1463, 84, 392, 2, True, 11), (1285, 84, 2177, 3, False, 13), (1320, 324, 752, 3, True, 13),
+           (8140, 32, 388, 4, False, 21), (5469, 52, 1093, 2, True, 21), (853, 84, 2925, 3, False, 22), (8470, 296, 101, 3, True, 22),
+           (4626, 216, 326, 3, False, 23), (1820, 60, 2050, 3, True, 23), (8759, 124, 293, 3, False, 31), (6933, 348, 202, 3, True, 31),
+           (2236, 168, 1179, 3, False, 33), (7240, 228, 370, 3, True, 33)]
 
 
 @pytest.mark.parametrize("rows,k,o,s,own,code", FORWARD)
@@ -69,8 +69,8 @@ def test_forward_with_drawn_weights_in_a_workspace(hot, rows, k, o, s, own, code
 
 
 # (rows, in, out, samples, tile code)
-BACKWARD = [(8924, 64, 84, 2, 11), (4995, 1412, 36, 2, 13), (8772, 444, 24, 4, 21), (5499, 1104, 100, 1, 22), (1060, 2688, 56, 4, 23),
-            (8200, 388, 36, 4, 31), (7898, 1080, 140, 1, 33)]
+BACKWARD = [(6854, 916, 20, 2, 11), (519, 2328, 392, 4, 13), (820, 1032, 232, 4, 21), (555, 2140, 244, 3, 22), (7092, 148, 276, 4, 23),
+            (8800, 112, 344, 4, 31), (3643, 1128, 212, 2, 33)]
 
 
 @pytest.mark.parametrize("rows,k,o,s,code", BACKWARD)
@@ -97,6 +97,59 @@ def test_input_gradients_with_drawn_weights_in_a_workspace(hot, rows, k, o, s, c
         assert torch.isfinite(a).all() and (a - b).norm() <= 1e-5 * b.norm()
     t["dy"][0, 0, 0] = float("inf")
     assert torch.allclose(run(_workspace(bytes_)[1])[1], run(None)[1], rtol=0.0, atol=0.0, equal_nan=True)
+
+
+# The layers of the kernel for tens to hundreds of rows (tile code + 100): two accumulators to a sum
+APART = [(646, 128, 1395, 2, False, 111), (150, 148, 2779, 3, True, 111), (564, 140, 2833, 3, False, 113), (3475, 956, 168, 4, True, 113),
+         (4389, 136, 231, 3, False, 122), (6012, 1020, 68, 4, True, 122), (1349, 316, 797, 4, False, 123), (4846, 664, 146, 4, True, 123)]
+
+
+@pytest.mark.parametrize("rows,k,o,s,own,code", APART)
+def test_forward_with_the_small_products_apart(hot, rows, k, o, s, own, code):
+    """Against fp64 products of the library's own w, and no farther from them than the kernel that runs without a workspace; infinities, NaN
+    and values beyond the largest bf16 number give what they give there."""
+    print("case planes apart", rows, k, o, s, own, code, flush=True)
+    ldx = k + 4 if rows % 2 else k
+    bytes_ = hot.hot_linear_planes_workspace_bytes(rows, k, o, s, 0, own)
+    assert hot.hot_linear_planes_shape(rows, k, o, s, 0, own, ldx=ldx, workspace_bytes=bytes_) == code
+    assert hot.hot_linear_kernel_shape(rows, k, o, s, 0, own, ldx=ldx) > 0
+    t = _inputs(rows + k, rows, k, o, s, own, ldx)
+    rng = hot.hot_rng(seed=0xABCDEF12345, step=4, first_sample=2 * s)
+    plan = hot.hot_create(o * k, o * k, s, s, 1000.0, 0)
+    w = torch.empty(s, o * k, device=DEV)
+    hot.hot_forward_rng(plan, rng, t["mu_w"].reshape(-1), t["sigma_w"].reshape(-1), w, torch.empty(1, dtype=torch.float64, device=DEV))
+    b_off = (o * k + 3) // 4 * 4 + 8
+
+    def run(ws):
+        y = torch.full((s, rows, o), float("nan"), device=DEV)
+        hot.hot_linear_forward_rng(rng, t["x"], t["mu_w"], t["sigma_w"], None, None, y, 0, 0, workspace=ws)
+        return y
+
+    plain = run(None)
+    whole, ws = _workspace(bytes_)
+    got = run(ws)
+    assert (whole[bytes_:] == 255).all()
+    x64 = t["x"].double().expand(s, rows, k) if not own else t["x"].double()
+    want = torch.stack([x64[i] @ w[i].view(o, k).double().t() for i in range(s)])
+    size = torch.stack([x64[i].abs() @ w[i].view(o, k).double().abs().t() for i in range(s)])
+    # one rounding of the large products and five of the small ones to sixteen indices, below 2^-24 of the magnitude sum each at most, and what
+    # the pieces leave out of a product, 3 * 2^-24
+    assert ((got.double() - want).abs() <= (k / 16 + 8) * 2.0 ** -24 * size).all()
+    assert (got.double() - want).norm() <= 0.9 * (plain.double() - want).norm()
+    # with biases: the same sums, one rounding more
+    y = torch.empty_like(got)
+    hot.hot_linear_forward_rng(rng, t["x"], t["mu_w"], t["sigma_w"], t["mu_b"], t["sigma_b"], y, 0, b_off, workspace=ws)
+    zero = torch.zeros(s, rows, o, device=DEV)
+    hot.hot_linear_forward_rng(rng, torch.zeros_like(t["x"]), t["mu_w"], t["sigma_w"], t["mu_b"], t["sigma_b"], zero, 0, b_off)
+    assert torch.equal(y, got + zero[:, :1])
+    for at, bad in ((0, float("inf")), (rows // 2, 3.4e38), (rows - 1, float("nan"))):
+        (t["x"][-1] if own else t["x"])[at, k - 1] = bad
+    t["mu_w"][o - 1, 0] = float("-inf")
+    got, plain = run(ws), run(None)
+    assert torch.equal(got.isnan(), plain.isnan()) and torch.equal(got.isinf(), plain.isinf())
+    assert torch.equal(got[got.isinf()], plain[plain.isinf()])
+    finite = torch.isfinite(got)
+    assert torch.allclose(got[finite], plain[finite], rtol=1e-3, atol=1e-3)
 
 
 def test_the_layer_hands_over_a_workspace(hot):
