@@ -383,13 +383,12 @@ void bwd_dispatch(int ch, int u, bool al, bool nt, const BwdArgs<EPI> &a)
 // first_row (eps and grad_w point at the first of them); rows = 0 means all of the plan's samples.
 // aligned_out: whether every array the epilogue touches is 16-byte aligned.
 template <class EPI>
-int backward_launch(hot_plan *plan, int kernel, const Rng *rng, const float *mu, const float *sigma,
+int backward_launch(hot_plan *plan, const hot_launch &c, const Rng *rng, const float *mu, const float *sigma,
                     const float *eps, const float *grad_w, const EPI &epi, bool aligned_out, void *stream,
                     int first_row, int rows, bool add_kl)
 {
     const bool gen = rng != nullptr;
     const hot_desc &d = plan->d;
-    const hot_launch &c = plan->cfg[kernel];
     const bool al = aligned16(mu) && aligned16(sigma) && aligned16(grad_w) && aligned_out &&
                     (gen || aligned16(eps)) && (d.ld % 4 == 0);
 
@@ -429,7 +428,7 @@ int backward_impl(hot_plan *plan, int kernel, const Rng *rng, const float *mu, c
         (!gen && !aligned4(eps)))
         return HOT_EINVAL;
     const StoreGrad epi{grad_mu, grad_sigma, accumulate ? 1 : 0};
-    return backward_launch(plan, kernel, rng, mu, sigma, eps, grad_w, epi, aligned16(grad_mu) && aligned16(grad_sigma),
+    return backward_launch(plan, plan->cfg[kernel], rng, mu, sigma, eps, grad_w, epi, aligned16(grad_mu) && aligned16(grad_sigma),
                            stream, first_row, rows, add_kl);
 }
 
@@ -491,7 +490,7 @@ int hot_backward_adam(hot_plan *plan, const hot_rng *rng, const hot_adam *params
     epi.v_sig = v_sigma;
     Rng r;
     if (rng && !make_rng(rng, plan->d.s_local, r)) return HOT_EINVAL;
-    return backward_launch(plan, rng ? HOT_KERNEL_BACKWARD_RNG : HOT_KERNEL_BACKWARD, rng ? &r : nullptr, mu, sigma, eps,
+    return backward_launch(plan, plan->cfg[rng ? HOT_KERNEL_BACKWARD_RNG : HOT_KERNEL_BACKWARD], rng ? &r : nullptr, mu, sigma, eps,
                            grad_w, epi, al, stream, 0, 0, true);
 }
 
@@ -523,11 +522,11 @@ int hot_backward_adam_forward(hot_plan *plan, const hot_rng *rng, const hot_rng 
     epi.s_loc = plan->d.s_local;
     epi.next = rn;
     epi.partials = kl_out ? plan->partials : nullptr;
-    const int rc = backward_launch(plan, HOT_KERNEL_BACKWARD_RNG, &r, mu, sigma, nullptr, grad_w, epi, al, stream, 0, 0, true);
+    const int rc = backward_launch(plan, plan->step, &r, mu, sigma, nullptr, grad_w, epi, al, stream, 0, 0, true);
     if (rc != HOT_OK || !kl_out) return rc;
     DeviceGuard guard(plan->d.device);
     if (guard.err != hipSuccess) return fail_hip(plan, guard.err);
-    const unsigned blocks = tiling_for(plan->d.n_weights, plan->cfg[HOT_KERNEL_BACKWARD_RNG]).grid;
+    const unsigned blocks = tiling_for(plan->d.n_weights, plan->step).grid;
     hot_kl_finish_kernel<<<dim3(1), dim3(kFinishBlock), 0, static_cast<hipStream_t>(stream)>>>(plan->partials, (int)blocks, kl_out);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? HOT_OK : fail_hip(plan, e);

@@ -321,6 +321,7 @@ int hot_set_launch(hot_plan *plan, int kernel, const hot_launch *cfg)
     if (cfg->chunks) c.chunks = cfg->chunks;
     if (cfg->unroll) c.unroll = pick_unroll(cfg->unroll, plan->d.s_local);
     c.nontemporal = cfg->nontemporal;
+    if (kernel == HOT_KERNEL_BACKWARD_RNG) plan->step = c;
     return HOT_OK;
 }
 

@@ -18,6 +18,7 @@ struct hot_plan {
     double g, k;
     double *partials;   // kMaxGrid fp64 KL partial sums, one per forward workgroup, then the arrival counter
     hot_launch cfg[4];  // indexed by HOT_KERNEL_*
+    hot_launch step;    // of the fused backward + Adam + forward pass: its own default until HOT_KERNEL_BACKWARD_RNG is set
     int last_hip;
 };
 
@@ -251,6 +252,13 @@ inline void default_launches(hot_plan &p)
     br.chunks = few_tiles ? (d.s_local >= 4 ? 2 : 1) : 4;
     if (br.chunks > f.chunks) br.chunks = f.chunks;      // (f.chunks: what the number of tiles allows)
     br.unroll = 1;
+    // The fused step (backward, Adam, the next forward) holds nine arrays' quads per chunk: one chunk per thread leaves
+    // it four times the waves to hide its two draws behind, and wins while every tile still has a workgroup of its own
+    // (4 samples: 6.3 M weights 105 -> 97 us, 12 M 187 -> 176, 24 M 377 -> 365, 50 M 724 -> 706).  Past kMaxGrid tiles, 67 M
+    // weights, workgroups would stride over two tiles each, and the backward default is faster (105 M x 4: 1.64 ms with
+    // one chunk, 1.54 with four; x 1: 1.11 and 1.07).
+    p.step = br;
+    if ((d.n_weights + kBlock * 4 - 1) / (kBlock * 4) <= kMaxGrid) p.step.chunks = 1;
 }
 
 // How the N columns are cut into tiles, one workgroup each (capped by the configured bound, beyond which workgroups

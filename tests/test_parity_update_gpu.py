@@ -355,6 +355,35 @@ def test_fused_backward_adam_forward(oracle, hot, n, ld, s, offset, want_kl, lau
     assert np.all(np.abs(w1.cpu().numpy()[:, :n] - w64) <= 1e-5 * np.abs(w64) + 4e-6 * got_sg[None, :].astype(np.float64) * 6.0)
 
 
+@pytest.mark.parametrize("n,s", [(6_300_003, 4), (16_777_221, 2), (65536 * 1024, 1), (65536 * 1024 + 1, 1)])
+def test_fused_step_with_its_own_default_geometry(hot, n, s):
+    """hot_backward_adam_forward with the geometry it takes by itself, where that is not the backward kernel's, at the
+    last size with a workgroup for every tile of one chunk and one past it, against the two calls: parameters,
+    moments and w bit for bit, KL to the rounding of the fp64 sum."""
+    print("case fused step, default geometry", n, s, flush=True)
+    g = torch.Generator(device=DEV).manual_seed(n % 1009)
+    normal = lambda *shape: torch.empty(*shape, device=DEV).normal_(generator=g)
+    names = ("mu", "sigma", "m_mu", "v_mu", "m_sigma", "v_sigma")
+    two = {k: normal(n) for k in names}
+    for k in ("sigma", "v_mu", "v_sigma"):
+        two[k].abs_().add_(0.02)
+    one = {k: t.clone() for k, t in two.items()}
+    grad_w, rng, nxt = normal(s, n), hot.hot_rng(seed=5, step=4, first_sample=0), hot.hot_rng(seed=5, step=5, first_sample=0)
+    params, plan = hot.hot_adam(1e-3, 0.9, 0.999, 1e-8, 1.0, 0.02, 4), hot.hot_create(n, n, s, s, 500.0, 0)
+    w2, w1 = torch.empty(s, n, device=DEV), torch.empty(s, n, device=DEV)
+    kl2, kl1 = (torch.full((1,), -1.0, dtype=torch.float64, device=DEV) for _ in range(2))
+    hot.hot_backward_adam(plan, rng, params, two["mu"], two["sigma"], None, grad_w, *[two[k] for k in names[2:]])
+    hot.hot_forward_rng(plan, nxt, two["mu"], two["sigma"], w2, kl2)
+    hot.hot_backward_adam_forward(plan, rng, nxt, params, one["mu"], one["sigma"], grad_w, *[one[k] for k in names[2:]], w1, kl1)
+    torch.cuda.synchronize()
+    hot.hot_destroy(plan)
+    for k in names:
+        assert torch.equal(one[k], two[k]), k
+    assert torch.equal(w1, w2)
+    scale = 0.5 * float((two["sigma"].square() + two["mu"].square() + 1.0 + 2.0 * two["sigma"].log().abs()).sum(dtype=torch.float64))
+    assert abs(kl1.item() - kl2.item()) <= 1e-13 * scale
+
+
 @pytest.mark.parametrize("n,ld,s,offset", [(700_001, 700_004, 3, 0), (700_001, 700_001, 2, 1)])
 def test_fused_calls_with_non_temporal_accesses(hot, n, ld, s, offset):
     """The three fused calls with the non-temporal variants of their kernels (the default only above
