@@ -239,15 +239,20 @@ inline void default_launches(hot_plan &p)
     // workgroups costs 5-10 %, which one chunk per thread avoids.
     const bool few_tiles = d.n_weights < (16L << 20);
     if (d.s_local < 4 && few_tiles) b.chunks = 1;
-    // The drawing variants have no eps loads to keep in flight.  Forward: as above up to seven samples;
-    // from eight on one chunk per thread (38 registers, eight waves per SIMD) hides the generator's
-    // latencies better than four independent chains in five waves (10-20 % at 8 M to 25 M weights).
+    // The drawing variants have no eps loads to keep in flight.  Forward, with other work between the calls: where the
+    // draws outweigh the reads of mu and sigma (from five samples and 40 M drawn values on, from eight samples on at any
+    // size) one chunk per thread, whose 38 registers leave eight waves per SIMD to hide the generator's latencies behind
+    // (4, 2 and 1 chunks: 12 M weights x 5 samples 68 / 68 / 65 us, x 7 97 / 93 / 82, 25 M x 6 160 / 163 / 147; but
+    // 4 M x 4 26 / 26 / 28, and with the backward call after it 6 M x 5 is level).  Else two where the number of tiles allows (25 M x 1 55 / 54 / 70, 12 M x 2 41 / 40 / 46,
+    // 12 M x 4 59 / 58 / 58); four never were ahead by more than the runs differ there.
+    // hot_adam_forward shares this geometry, and with it the order of the KL sum: 25 M x 1 282 / 277 / 304, x 5 365 / 348 / 358.
     // Backward: single rows in flight at every size (two rows of draws in flight cost registers and with them waves:
     // 209 M weights x 2 samples 1.07 ms against 0.81, 64 M x 3 0.38 against 0.30, 20 M x 8 0.178 against 0.169); four
     // chunks per thread from 16 M weights on, below that two from four samples on (6.3 M x 16, 7.7 M x 13), else one.
     hot_launch &fr = p.cfg[HOT_KERNEL_FORWARD_RNG], &br = p.cfg[HOT_KERNEL_BACKWARD_RNG];
     fr = f;
-    if (d.s_local >= 8) fr.chunks = 1;
+    if (d.s_local >= 8 || (d.s_local >= 5 && d.n_weights > 40000000L / d.s_local)) fr.chunks = 1;
+    else if (fr.chunks > 2) fr.chunks = 2;
     br = b;
     br.chunks = few_tiles ? (d.s_local >= 4 ? 2 : 1) : 4;
     if (br.chunks > f.chunks) br.chunks = f.chunks;      // (f.chunks: what the number of tiles allows)

@@ -184,3 +184,25 @@ def test_full_size_fused_path(oracle, hot, name):
         assert np.all(err <= EPS_RTOL * r64)
         bits_ok = oracle.eps_bits(8, s, rng.seed, rng.step, rng.first_sample, col0=a)
         assert bits_ok.shape == (s, 8)
+
+
+@pytest.mark.parametrize("n,s,chunks", [(8_000_000, 4, 2), (8_000_000, 5, 2), (8_000_001, 5, 1), (2_097_155, 8, 1)])
+def test_default_geometry_of_the_drawing_forward(hot, n, s, chunks):
+    """Both sides of the rule for one and two chunks per thread: the same w and, to the rounding of the fp64 sum, the
+    same KL as with four."""
+    print("case forward_rng default geometry", n, s, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(n % 1009)
+    mu, sigma = torch.empty(n, device="cuda").normal_(generator=g), torch.empty(n, device="cuda").normal_(generator=g).abs_().add_(0.01)
+    plan, rng, out = hot.hot_create(n, n, s, s, 100.0, 0), hot.hot_rng(seed=9, step=3, first_sample=0), []
+    assert hot.hot_get_launch(plan, hot.HOT_KERNEL_FORWARD_RNG)["chunks"] == chunks
+    for launch in (None, dict(chunks=4, unroll=1, nontemporal=1)):
+        if launch:
+            hot.hot_set_launch(plan, hot.HOT_KERNEL_FORWARD_RNG, **launch)
+        w, kl = torch.empty(s, n, device="cuda"), torch.full((1,), -1.0, dtype=torch.float64, device="cuda")
+        hot.hot_forward_rng(plan, rng, mu, sigma, w, kl)
+        torch.cuda.synchronize()
+        out.append((w, kl.item()))
+    hot.hot_destroy(plan)
+    assert torch.equal(out[0][0], out[1][0])
+    scale = 0.5 * float((sigma.square() + mu.square() + 1.0 + 2.0 * sigma.log().abs()).sum(dtype=torch.float64))
+    assert abs(out[0][1] - out[1][1]) <= 1e-13 * scale
