@@ -266,7 +266,7 @@ int hot_linear_forward_rng(const hot_linear_desc *desc, const hot_rng *rng, cons
 /*
  * The same call with device scratch of the caller's (same passage of the paper).  At hundreds and thousands of rows
  * the tiles draw the weights once each; with a workspace one launch draws all of them once and leaves their
- * bf16 pieces there (six bytes per weight and sample, at most 256 MiB in all), a second multiplies (7260 x 2160 x 540, two
+ * bf16 pieces there (six bytes per weight and sample, at most 1 GiB in all), a second multiplies (7260 x 2160 x 540, two
  * samples: 325 -> 190 us; 16640 x 192 x 768: 80 -> 64; 1363 x 2188 x 1272, three: 199 -> 142).  y is the same bit for bit where the tiles of
  * 256 to 1024 rows would run (hot_linear_planes_shape below 100); where the kernel for tens to hundreds of rows would, it is 0.75 to
  * 0.8 times as far from the sums in 64 bits, and infinities give what they give there.  hot_linear_planes_workspace_bytes(desc, 0) returns the bytes that the call

@@ -1554,8 +1554,8 @@ inline PlanePlan planes_instead(long R, long C, long N, int S, bool tr, double s
 }
 
 // ... and for a forward launch of the kernel for tens to hundreds of rows, with the small products apart.  Of 6918 such products
-// this takes 1947, 1.26 times as fast on average, 28 slower by more than 3 % (0.87 at worst; 300 x 2160 x 8640 x 2: 243 -> 205, 1363 x 2188 x
-// 1272 x 3 199 -> 142); the two narrow tiles have the long sums, where the models know less, and under 40 us it is as above.
+// this takes 1947, 1.26 times as fast on average, 28 slower by more than 3 % (0.87 at worst; 826 x 5136 x 1275 x 4: 338 -> 280, 1363 x 2188 x
+// 1272 x 3 199 -> 142; where the models are closer than this the two are level, 300 x 2160 x 8640 x 2 227 and 226, of which 64 are the draw at 5.8 TB/s); the two narrow tiles have the long sums, where the models know less, and under 40 us it is as above.
 constexpr double kApartMost = 0.9, kApartMostNarrow = 0.75;
 
 inline PlanePlan planes_forward_plan(const hot_linear_desc *d, int64_t ws_bytes)

@@ -267,8 +267,11 @@ hot_linear_planes_kernel(PlaneArgs a)
 // workgroups on a compute unit (as many as its registers admit); and per workgroup to a compute unit on average, a step and as a
 // whole (the card's power and memory, which the workgroups share).  Fitted to 300 products of 128 to 16640 rows, 24 to 8192
 // contraction indices and 24 to 8551 outputs (within 6 %); the shape that the model picks is 0.5 % behind the fastest on average, 15 % at
-// worst.  Larger tiles (256 x 192, 256 x 256) are faster per product (1024 x 8192^2: 1093 us), but only where the planes are larger
-// than kPlanesMostBytes.
+// worst.  Tiles of 256 x 256 (302 products of 400 to 12000 rows, within 8 %) hold 256 accumulators, one wave to a SIMD, and are what large
+// products take: 4096^3 x 2 samples 1270 -> 1139 us, 1005 x 7052 x 6900 x 2 1314 -> 1094.  Nothing covers such a workgroup's start and end, so they
+// are taken from kPlaneLongSteps steps on and where the model sees them ahead by kPlaneLargeAhead (by the bare model 1000 products: with under 300
+// indices 0.91 times as fast, 0.96 with 300 to 400, 1.00 with 500 to 600, 1.03 with 700 to 800, 1.08 from 1200 on; whole backward passes 0.97
+// to 1.04).  256 x 192 were hardly ever ahead of both of their neighbours.
 struct PlaneShape {
     int rb, cb, resident;
     double once, round, us[6], share, each;
@@ -279,7 +282,10 @@ constexpr PlaneShape kPlaneShapes[] = {{3, 3, 1, 1.6, 5.9, {0.849}, 0.375, 1.57}
                                        {1, 3, 3, 3.1, 0.0, {0.441, 0.766, 1.185}, 0.082, 1.34},
                                        {2, 1, 4, 2.7, 0.0, {0.357, 0.563, 0.871, 1.159}, 0.065, 0.75},
                                        {3, 1, 3, 3.4, 0.0, {0.464, 0.761, 1.175}, 0.119, 1.2},
-                                       {1, 1, 6, 0.0, 0.0, {0.297, 0.303, 0.425, 0.594, 0.747, 0.817}, 0.079, 0.49}};
+                                       {1, 1, 6, 0.0, 0.0, {0.297, 0.303, 0.425, 0.594, 0.747, 0.817}, 0.079, 0.49},
+                                       {4, 4, 1, 0.0, 5.6, {1.185}, 0.821, 10.1}};
+constexpr long kPlaneLongSteps = 40;
+constexpr double kPlaneLargeAhead = 1.03;
 constexpr int kPlaneCodes = sizeof(kPlaneShapes) / sizeof(kPlaneShapes[0]);
 // The same with two sets of accumulators (190 products of 64 to 7800 rows, within 5 %, 0.8 % behind the fastest on average).
 constexpr PlaneShape kPlaneShapesApart[] = {{2, 2, 2, 2.1, 2.3, {0.45, 0.805}, 0.17, 0.98},
@@ -288,8 +294,11 @@ constexpr PlaneShape kPlaneShapesApart[] = {{2, 2, 2, 2.1, 2.3, {0.45, 0.805}, 0
                                             {1, 1, 5, 0.3, 0.0, {0.305, 0.305, 0.364, 0.538, 0.614}, 0.085, 0.84}};
 constexpr int kPlaneCodesApart = sizeof(kPlaneShapesApart) / sizeof(kPlaneShapesApart[0]);
 
-// Most bytes of planes: those of a layer that the memory-side cache holds, so that they are read from there.
-constexpr int64_t kPlanesMostBytes = (int64_t)256 << 20;
+// Most bytes of planes (below 2 GiB, since offsets into a sample's are 32 bits).  Beyond the 256 MiB of the memory-side cache they are
+// still faster than drawing in every tile: on 42 layers of 256 to 900 MiB 1.14 times forward, 1.12 the whole backward pass, none
+// slower (1337 x 3744 x 6132 x 2 forward 802 -> 625 us, 2048 x 8192^2 x 1 1365 -> 1242, 1024 x 8192^2 x 2 1379 -> 1338).  With the small products
+// apart, for layers of fewer rows, it was not measured and stays at what that cache holds.
+constexpr int64_t kPlanesMostBytes = (int64_t)1024 << 20, kPlanesMostBytesApart = (int64_t)256 << 20;
 constexpr long kPlanesMostTiles = (1L << 24) - kXcds;        // (one grid dimension holds fewer than 2^32 threads)
 
 struct PlanePlan {
@@ -303,7 +312,8 @@ constexpr PlanePlan kNoPlanePlan = {-1, false, 0, 0.0};
 inline PlanePlan plane_plan(long R, long C, long N, int S, bool tr, bool apart)
 {
     const long steps = plane_steps(C), blocks = plane_blocks(N);
-    if (S > 65535 || steps > 4 * 65535 || blocks > 65535 || steps > kPlanesMostBytes / kBlockBytes / blocks / S) return kNoPlanePlan;
+    if (S > 65535 || steps > 4 * 65535 || blocks > 65535 || steps > (apart ? kPlanesMostBytesApart : kPlanesMostBytes) / kBlockBytes / blocks / S)
+        return kNoPlanePlan;
     PlanePlan best = {-1, apart, steps * blocks * S * kBlockBytes, 0.0};
     for (int i = 0; i < (apart ? kPlaneCodesApart : kPlaneCodes); ++i) {
         const PlaneShape &h = apart ? kPlaneShapesApart[i] : kPlaneShapes[i];
@@ -314,7 +324,9 @@ inline PlanePlan plane_plan(long R, long C, long N, int S, bool tr, bool apart)
         double t = h.once + (double)full * (taken * h.us[h.resident - 1] + h.round);
         if (left) t += taken * h.us[(left + kComputeUnits - 1) / kComputeUnits - 1] + h.round;
         t += (double)wgs / kComputeUnits * (taken * h.share + h.each);
-        if (best.code < 0 || t < best.time) {
+        const bool large = h.rb * h.cb == 16;                         // (the last shape)
+        if (large && steps < kPlaneLongSteps) continue;
+        if (best.code < 0 || (large ? kPlaneLargeAhead : 1.0) * t < best.time) {
             best.code = i;
             best.time = t;
         }
@@ -391,7 +403,8 @@ void planes_run(const PlanePlan &p, hipStream_t s, const SlabArgs &b, int sample
     case 3: return planes_go<1, 3, 2>(s, a, samples);
     case 4: return planes_go<2, 1, 2>(s, a, samples);
     case 5: return planes_go<3, 1, 2>(s, a, samples);
-    default: return planes_go<1, 1, 2>(s, a, samples);
+    case 6: return planes_go<1, 1, 2>(s, a, samples);
+    default: return planes_go<4, 4, 1>(s, a, samples);
     }
 }
 

@@ -33,7 +33,9 @@ def _workspace(bytes_):
 FORWARD = [(8542, 24, 128, 2, False, 11), (1463, 84, 392, 2, True, 11), (1285, 84, 2177, 3, False, 13), (1320, 324, 752, 3, True, 13),
            (8140, 32, 388, 4, False, 21), (5469, 52, 1093, 2, True, 21), (853, 84, 2925, 3, False, 22), (8470, 296, 101, 3, True, 22),
            (4626, 216, 326, 3, False, 23), (1820, 60, 2050, 3, True, 23), (8759, 124, 293, 3, False, 31), (6933, 348, 202, 3, True, 31),
-           (2236, 168, 1179, 3, False, 33), (7240, 228, 370, 3, True, 33)]
+           (2236, 168, 1179, 3, False, 33), (7240, 228, 370, 3, True, 33),
+           # tiles of 256 x 256, and planes beyond 256 MiB
+           (8901, 644, 657, 2, True, 44), (1184, 636, 3421, 3, True, 44), (462, 1604, 7070, 4, False, 44), (368, 2828, 7969, 2, False, 23)]
 
 
 @pytest.mark.parametrize("rows,k,o,s,own,code", FORWARD)
@@ -70,7 +72,8 @@ def test_forward_with_drawn_weights_in_a_workspace(hot, rows, k, o, s, own, code
 
 # (rows, in, out, samples, tile code)
 BACKWARD = [(6854, 916, 20, 2, 11), (519, 2328, 392, 4, 13), (820, 1032, 232, 4, 21), (555, 2140, 244, 3, 22), (7092, 148, 276, 4, 23),
-            (8800, 112, 344, 4, 31), (3643, 1128, 212, 2, 33)]
+            (8800, 112, 344, 4, 31), (3643, 1128, 212, 2, 33),
+            (479, 6320, 636, 4, 44), (441, 7672, 1604, 4, 44), (332, 6024, 2048, 4, 33)]
 
 
 @pytest.mark.parametrize("rows,k,o,s,code", BACKWARD)
