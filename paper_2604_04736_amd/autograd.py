@@ -101,8 +101,8 @@ class _Linear(torch.autograd.Function):
         rows = x.shape[-2]
         ws_bytes = _forward_scratch(rows, layer.in_features, layer.out_features, layer.s_local, x.dim() == 3) if rows > 128 else 0
         if x.is_cuda:
-            y = _answer(hot.host().linear_forward(x, mu_w, sigma_w, mu_b, sigma_b, *draw, layer.s_local, layer.weight_offset, layer.bias_offset,
-                                                 ws_bytes, *_device_and_stream()), "hot_linear_forward_rng")
+            y = _answer(hot.host().linear_forward(x, mu_w, sigma_w, mu_b, sigma_b, *draw, layer.in_features, layer.out_features, layer.s_local,
+                                                 layer.weight_offset, layer.bias_offset, ws_bytes, *_device_and_stream()), "hot_linear_forward_rng")
             if y is not None:
                 return y
         y = torch.empty(layer.s_local, rows, layer.out_features, dtype=torch.float32, device=x.device)
@@ -121,8 +121,8 @@ class _Linear(torch.autograd.Function):
         ws_bytes = _backward_scratch(xd.shape[-2], layer.in_features, layer.out_features, layer.s_local, want_dx)
         grads = None
         if xd.is_cuda:
-            grads = _answer(hot.host().linear_backward(xd, grad_y, mu_w, sigma_w, mu_b, sigma_b, want_dx, *draw, layer.s_local, layer.dataset_size,
-                                                      layer.weight_offset, layer.bias_offset, ws_bytes, *_device_and_stream()),
+            grads = _answer(hot.host().linear_backward(xd, grad_y, mu_w, sigma_w, mu_b, sigma_b, want_dx, *draw, layer.in_features, layer.out_features,
+                                                      layer.s_local, layer.dataset_size, layer.weight_offset, layer.bias_offset, ws_bytes, *_device_and_stream()),
                             "hot_linear_backward_rng_ws" if ws_bytes > 0 else "hot_linear_backward_rng")
         if grads is None:
             grads = [torch.empty(layer.s_local, xd.shape[-2], layer.in_features, dtype=torch.float32, device=xd.device) if want_dx else None]

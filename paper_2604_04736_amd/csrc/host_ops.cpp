@@ -31,14 +31,15 @@ struct Draw {
     uint32_t step, first_sample;
 };
 
-// the layer's description, if the arrays are as the C calls want them
-bool describe(const Tensor &x, const Tensor &mu_w, const Tensor &sigma_w, const MaybeTensor &mu_b, const MaybeTensor &sigma_b, int64_t s_local,
-              int64_t weight_offset, int64_t bias_offset, int64_t device, hot_linear_desc &d)
+// the layer's description, if the arrays are as the C calls want them and have the layer's sizes (its draws and offsets are by these:
+// with more outputs than that, the weights' eps would be those of its biases and of the next layer)
+bool describe(const Tensor &x, const Tensor &mu_w, const Tensor &sigma_w, const MaybeTensor &mu_b, const MaybeTensor &sigma_b, int64_t in_features,
+              int64_t out_features, int64_t s_local, int64_t weight_offset, int64_t bias_offset, int64_t device, hot_linear_desc &d)
 {
     if (!plain(x, device) || !plain(mu_w, device) || !plain(sigma_w, device) || s_local < 1 || s_local > INT32_MAX) return false;
     if ((x.dim() != 2 && x.dim() != 3) || mu_w.dim() != 2 || mu_w.sizes() != sigma_w.sizes()) return false;
     const int64_t rows = x.size(-2), k = x.size(-1), o = mu_w.size(0);
-    if (mu_w.size(1) != k || (x.dim() == 3 && x.size(0) != s_local)) return false;
+    if (k != in_features || o != out_features || mu_w.size(1) != k || (x.dim() == 3 && x.size(0) != s_local)) return false;
     if (mu_b.has_value() != sigma_b.has_value() || (mu_b && !(is_vector(mu_b, o, device) && is_vector(sigma_b, o, device)))) return false;
     d.rows = rows;
     d.in_features = k;
@@ -56,11 +57,11 @@ Tensor scratch(int64_t bytes, const Tensor &like) { return bytes > 0 ? at::empty
 
 // y, or the error code, or None
 py::object linear_forward(const Tensor &x, const Tensor &mu_w, const Tensor &sigma_w, const MaybeTensor &mu_b, const MaybeTensor &sigma_b, uint64_t seed,
-                          uint32_t step, uint32_t first_sample, int64_t s_local, int64_t weight_offset, int64_t bias_offset,
-                          int64_t scratch_bytes, int64_t device, uintptr_t stream)
+                          uint32_t step, uint32_t first_sample, int64_t in_features, int64_t out_features, int64_t s_local, int64_t weight_offset,
+                          int64_t bias_offset, int64_t scratch_bytes, int64_t device, uintptr_t stream)
 {
     hot_linear_desc d;
-    if (!describe(x, mu_w, sigma_w, mu_b, sigma_b, s_local, weight_offset, bias_offset, device, d)) return py::none();
+    if (!describe(x, mu_w, sigma_w, mu_b, sigma_b, in_features, out_features, s_local, weight_offset, bias_offset, device, d)) return py::none();
     Tensor y;
     int code;
     {
@@ -77,11 +78,11 @@ py::object linear_forward(const Tensor &x, const Tensor &mu_w, const Tensor &sig
 
 // (dx or None, grad mu_w, grad sigma_w, grad mu_b or None, grad sigma_b or None), or the error code, or None
 py::object linear_backward(const Tensor &x, const Tensor &grad_y, const Tensor &mu_w, const Tensor &sigma_w, const MaybeTensor &mu_b, const MaybeTensor &sigma_b,
-                           bool want_dx, uint64_t seed, uint32_t step, uint32_t first_sample, int64_t s_local, double dataset_size,
-                           int64_t weight_offset, int64_t bias_offset, int64_t scratch_bytes, int64_t device, uintptr_t stream)
+                           bool want_dx, uint64_t seed, uint32_t step, uint32_t first_sample, int64_t in_features, int64_t out_features, int64_t s_local,
+                           double dataset_size, int64_t weight_offset, int64_t bias_offset, int64_t scratch_bytes, int64_t device, uintptr_t stream)
 {
     hot_linear_desc d;
-    if (!describe(x, mu_w, sigma_w, mu_b, sigma_b, s_local, weight_offset, bias_offset, device, d)) return py::none();
+    if (!describe(x, mu_w, sigma_w, mu_b, sigma_b, in_features, out_features, s_local, weight_offset, bias_offset, device, d)) return py::none();
     if (!plain(grad_y, device) || grad_y.dim() != 3 || grad_y.size(0) != s_local || grad_y.size(1) != d.rows || grad_y.size(2) != d.out_features)
         return py::none();
     Tensor dx, gmw, gsw, gmb, gsb;

@@ -116,3 +116,21 @@ def test_statistics_of_what_the_native_call_leaves_to_the_general_path():
             hot.hot_stats_whole(y[:, :33], 1, bad, std)
     with pytest.raises(hot.HotError):
         hot.hot_stats_whole(y, 5, torch.empty(40, device=DEV), torch.empty(40, device=DEV))      # ddof as large as the samples are many
+
+
+@pytest.mark.parametrize("rows", [64, 200])
+def test_parameters_of_another_size_than_the_layer_are_refused(rows):
+    """Dense arrays that fit each other and not the layer: with more outputs than it has, its draws would run into those of its biases
+    and of the next layer."""
+    for height in (O + 30, O - 2):
+        layer, x, p, _ = _layer(rows, True)
+        g = torch.Generator(device=DEV).manual_seed(3)
+        p = [torch.rand(height, K, device=DEV, generator=g), torch.rand(height, K, device=DEV, generator=g),
+             torch.rand(height, device=DEV, generator=g), torch.rand(height, device=DEV, generator=g)]
+        with pytest.raises(TypeError):
+            layer.forward(x, *p, step=3)
+    # another width: input gradients have the layer's
+    layer, x, p, dy = _layer(rows, True)
+    narrow = [t[..., :K - 4].contiguous() for t in (x, p[0], p[1])]
+    with pytest.raises(TypeError):
+        _pass(layer, narrow[0], narrow[1:] + p[2:], dy)
