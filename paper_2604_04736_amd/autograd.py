@@ -17,6 +17,7 @@ caller's scaling).
 from __future__ import annotations
 
 import functools
+import operator
 
 import torch
 
@@ -92,7 +93,8 @@ class _Linear(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, x, mu_w, sigma_w, mu_b, sigma_b, layer, step):
-        draw = (layer.seed & _M64, step & _M32, layer.first_sample & _M32)
+        # (as Python's integers: NumPy's have no room for the mask)
+        draw = (operator.index(layer.seed) & _M64, step & _M32, operator.index(layer.first_sample) & _M32)
         x = x.contiguous()
         ctx.layer, ctx.draw = layer, draw
         ctx.save_for_backward(x, mu_w, sigma_w, mu_b, sigma_b)

@@ -134,3 +134,22 @@ def test_parameters_of_another_size_than_the_layer_are_refused(rows):
     narrow = [t[..., :K - 4].contiguous() for t in (x, p[0], p[1])]
     with pytest.raises(TypeError):
         _pass(layer, narrow[0], narrow[1:] + p[2:], dy)
+
+
+def test_sizes_and_seeds_of_any_integer_type():
+    """NumPy's integers (a seed from a generator, a rank's first sample), as the ctypes calls take them."""
+    import numpy as np
+    from paper_2604_04736_amd.autograd import BayesianLinear
+    layer, x, p, dy = _layer(64, True, seed=5)
+    layer.first_sample = 6
+    want = _pass(layer, x, p, dy)
+    for kind in (np.int32, np.int64, np.uint64):
+        other = BayesianLinear(kind(K), kind(O), kind(S), 1000.0, seed=kind(5), first_sample=kind(6), weight_offset=kind(8))
+        assert all(torch.equal(a, b) for a, b in zip(_pass(other, x, p, dy, step=kind(3)), want))
+    layer.seed = -(1 << 63)                     # (taken modulo 2^64, as ever)
+    want = _pass(layer, x, p, dy)
+    layer.seed = np.int64(-(1 << 63))
+    assert all(torch.equal(a, b) for a, b in zip(_pass(layer, x, p, dy), want))
+    layer.seed = 5.0
+    with pytest.raises(TypeError):
+        _pass(layer, x, p, dy)
