@@ -67,9 +67,20 @@ def _forward_scratch(rows: int, k: int, o: int, s_local: int, per_sample_x: bool
 
 
 @functools.lru_cache(maxsize=4096)
-def _backward_scratch(rows: int, k: int, o: int, s_local: int, with_dx: bool) -> int:
+def _backward_scratch(rows: int, k: int, o: int, s_local: int, with_dx: bool) -> tuple[int, int]:
+    """What is asked for, and what is left of it where there is no room for the planes."""
     split = hot.hot_linear_backward_workspace_bytes(rows, k, o, s_local)
-    return max(split, hot.hot_linear_planes_workspace_bytes(rows, k, o, s_local, 1)) if with_dx else split
+    return max(split, hot.hot_linear_planes_workspace_bytes(rows, k, o, s_local, 1)) if with_dx else split, split
+
+
+def _scratch(wanted: int, least: int, device):
+    """A tensor of `wanted` bytes, or of the `least` where the device has no room for so much, which only buys time."""
+    if wanted > least:
+        try:
+            return torch.empty(wanted // 4, dtype=torch.float32, device=device)
+        except torch.OutOfMemoryError:
+            pass
+    return torch.empty(least // 4, dtype=torch.float32, device=device) if least > 0 else None
 
 
 _M32, _M64 = 0xFFFFFFFF, (1 << 64) - 1
@@ -109,7 +120,7 @@ class _Linear(torch.autograd.Function):
                 return y
         y = torch.empty(layer.s_local, rows, layer.out_features, dtype=torch.float32, device=x.device)
         det = [t.detach() if t is not None else None for t in (mu_w, sigma_w, mu_b, sigma_b)]
-        ws = torch.empty(ws_bytes // 4, dtype=torch.float32, device=x.device) if ws_bytes > 0 else None
+        ws = _scratch(ws_bytes, 0, x.device)
         hot.hot_linear_forward_rng(hot.hot_rng(*draw), x.detach(), det[0], det[1], det[2], det[3], y, layer.weight_offset, layer.bias_offset,
                                    workspace=ws)
         return y
@@ -120,16 +131,16 @@ class _Linear(torch.autograd.Function):
         xd, mu_w, sigma_w, mu_b, sigma_b = (t.detach() if t is not None else None for t in ctx.saved_tensors)
         want_dx, grad_y = ctx.needs_input_grad[0], grad_y.contiguous()
         # few weights and many rows: the library spreads the rows over the chip through scratch memory of ours
-        ws_bytes = _backward_scratch(xd.shape[-2], layer.in_features, layer.out_features, layer.s_local, want_dx)
+        ws_bytes, least = _backward_scratch(xd.shape[-2], layer.in_features, layer.out_features, layer.s_local, want_dx)
         grads = None
         if xd.is_cuda:
             grads = _answer(hot.host().linear_backward(xd, grad_y, mu_w, sigma_w, mu_b, sigma_b, want_dx, *draw, layer.in_features, layer.out_features,
-                                                      layer.s_local, layer.dataset_size, layer.weight_offset, layer.bias_offset, ws_bytes, *_device_and_stream()),
-                            "hot_linear_backward_rng_ws" if ws_bytes > 0 else "hot_linear_backward_rng")
+                                                      layer.s_local, layer.dataset_size, layer.weight_offset, layer.bias_offset, ws_bytes, least,
+                                                      *_device_and_stream()), "hot_linear_backward_rng_ws" if ws_bytes > 0 else "hot_linear_backward_rng")
         if grads is None:
             grads = [torch.empty(layer.s_local, xd.shape[-2], layer.in_features, dtype=torch.float32, device=xd.device) if want_dx else None]
             grads += [torch.empty_like(t) if t is not None else None for t in (mu_w, sigma_w, mu_b, sigma_b)]
-            ws = torch.empty(ws_bytes // 4, dtype=torch.float32, device=xd.device) if ws_bytes > 0 else None
+            ws = _scratch(ws_bytes, least, xd.device)
             hot.hot_linear_backward_rng(hot.hot_rng(*draw), xd, grad_y, mu_w, sigma_w, mu_b, sigma_b, *grads[1:], grads[0],
                                         layer.s_local, layer.dataset_size, hot.HOT_REDUCE_NONE, layer.weight_offset,
                                         layer.bias_offset, workspace=ws)

@@ -53,7 +53,19 @@ bool describe(const Tensor &x, const Tensor &mu_w, const Tensor &sigma_w, const 
     return true;
 }
 
-Tensor scratch(int64_t bytes, const Tensor &like) { return bytes > 0 ? at::empty({bytes}, like.options().dtype(at::kByte)) : Tensor(); }
+// Scratch memory: `bytes`, or the `least` where the device has no room for so much, which only buys time.
+Tensor scratch(int64_t &bytes, int64_t least, const Tensor &like)
+{
+    const auto options = like.options().dtype(at::kByte);
+    if (bytes > least) {
+        try {
+            return at::empty({bytes}, options);
+        } catch (const c10::OutOfMemoryError &) {
+            bytes = least;
+        }
+    }
+    return bytes > 0 ? at::empty({bytes}, options) : Tensor();
+}
 
 // y, or the error code, or None
 py::object linear_forward(const Tensor &x, const Tensor &mu_w, const Tensor &sigma_w, const MaybeTensor &mu_b, const MaybeTensor &sigma_b, uint64_t seed,
@@ -67,7 +79,7 @@ py::object linear_forward(const Tensor &x, const Tensor &mu_w, const Tensor &sig
     {
         py::gil_scoped_release others_run;
         y = at::empty({s_local, d.rows, d.out_features}, x.options());
-        const Tensor ws = scratch(scratch_bytes, x);
+        const Tensor ws = scratch(scratch_bytes, 0, x);
         const hot_rng rng = {seed, step, first_sample};
         code = hot_linear_forward_rng_ws(&d, &rng, data(x), data(mu_w), data(sigma_w), data(mu_b), data(sigma_b), y.mutable_data_ptr<float>(),
                                          scratch_bytes > 0 ? ws.mutable_data_ptr() : nullptr, scratch_bytes, reinterpret_cast<void *>(stream));
@@ -79,7 +91,8 @@ py::object linear_forward(const Tensor &x, const Tensor &mu_w, const Tensor &sig
 // (dx or None, grad mu_w, grad sigma_w, grad mu_b or None, grad sigma_b or None), or the error code, or None
 py::object linear_backward(const Tensor &x, const Tensor &grad_y, const Tensor &mu_w, const Tensor &sigma_w, const MaybeTensor &mu_b, const MaybeTensor &sigma_b,
                            bool want_dx, uint64_t seed, uint32_t step, uint32_t first_sample, int64_t in_features, int64_t out_features, int64_t s_local,
-                           double dataset_size, int64_t weight_offset, int64_t bias_offset, int64_t scratch_bytes, int64_t device, uintptr_t stream)
+                           double dataset_size, int64_t weight_offset, int64_t bias_offset, int64_t scratch_bytes, int64_t least_scratch, int64_t device,
+                           uintptr_t stream)
 {
     hot_linear_desc d;
     if (!describe(x, mu_w, sigma_w, mu_b, sigma_b, in_features, out_features, s_local, weight_offset, bias_offset, device, d)) return py::none();
@@ -96,7 +109,7 @@ py::object linear_backward(const Tensor &x, const Tensor &grad_y, const Tensor &
             gsb = at::empty({d.out_features}, x.options());
         }
         if (want_dx) dx = at::empty({s_local, d.rows, d.in_features}, x.options());
-        const Tensor ws = scratch(scratch_bytes, x);
+        const Tensor ws = scratch(scratch_bytes, least_scratch, x);
         const hot_rng rng = {seed, step, first_sample};
         code = hot_linear_backward_rng_ws(&d, (int32_t)s_local, dataset_size, HOT_REDUCE_NONE, &rng, data(x), data(grad_y), data(mu_w), data(sigma_w),
                                           data(mu_b), data(sigma_b), gmw.mutable_data_ptr<float>(), gsw.mutable_data_ptr<float>(),

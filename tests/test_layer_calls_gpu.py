@@ -153,3 +153,44 @@ def test_sizes_and_seeds_of_any_integer_type():
     layer.seed = 5.0
     with pytest.raises(TypeError):
         _pass(layer, x, p, dy)
+
+
+@pytest.mark.parametrize("native", [True, False])
+def test_without_room_for_the_scratch_a_layer_runs_as_without_it(native, monkeypatch):
+    """Scratch memory for the drawn weights only buys time: where the allocator has none left the call is the one without."""
+    from paper_2604_04736_amd import binding as hot
+    from paper_2604_04736_amd.autograd import BayesianLinear
+    r, k, o, s = 1024, 2048, 2048, 8
+    mib = 1 << 20
+    split = hot.hot_linear_backward_workspace_bytes(r, k, o, s)
+    assert hot.hot_linear_planes_workspace_bytes(r, k, o, s, 0, True) >= 192 * mib and 128 * mib <= split <= 129 * mib
+    assert hot.hot_linear_planes_workspace_bytes(r, k, o, s, 1) >= 192 * mib
+    if not native:
+        for name in ("linear_forward", "linear_backward"):
+            monkeypatch.setattr(hot.host(), name, lambda *a: None)
+    g = torch.Generator(device=DEV).manual_seed(1)
+    x, dy = torch.randn(s, r, k, device=DEV, generator=g), torch.randn(s, r, o, device=DEV, generator=g)
+    p = [torch.randn(o, k, device=DEV, generator=g) * 0.1, torch.rand(o, k, device=DEV, generator=g) * 0.1 + 0.01]
+    layer, rng = BayesianLinear(k, o, s, 1000.0, bias=False, seed=5), hot.hot_rng(5, 3, 0)
+    want = [torch.empty(s, r, o, device=DEV), torch.empty_like(x), torch.empty_like(p[0]), torch.empty_like(p[1])]
+    hot.hot_linear_forward_rng(rng, x, *p, None, None, want[0])
+    ws = torch.empty(split, dtype=torch.uint8, device=DEV)
+    hot.hot_linear_backward_rng(rng, x, dy, *p, None, None, *want[2:], None, None, want[1], s, 1000.0, hot.HOT_REDUCE_NONE, workspace=ws)
+    del ws
+    leaves = [t.requires_grad_() for t in (x, *p)]
+
+    def with_room(bytes_left, call):
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + bytes_left) / torch.cuda.get_device_properties(0).total_memory)
+        try:
+            return call()
+        finally:
+            torch.cuda.set_per_process_memory_fraction(1.0)
+
+    y = with_room((64 + 128) * mib, lambda: layer.forward(*leaves, None, None, step=3))
+    got = [y.detach()] + list(with_room((64 + 32 + 160) * mib, lambda: torch.autograd.grad(y, leaves, dy, retain_graph=True)))
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
+    del got
+    with pytest.raises(torch.OutOfMemoryError):         # (no room for the scratch that the backward pass has always asked for)
+        with_room((64 + 32 + 64) * mib, lambda: torch.autograd.grad(y, leaves, dy))
