@@ -2673,10 +2673,20 @@ __device__ __forceinline__ f4 row_parts_again(const LinearGradArgs &a, int s, lo
 }
 
 // Adds the parts in a fixed order, draws eps and finishes the gradients: thread q owns quad q of the O*K weights, the threads
-// behind them one quad of biases each.
-__global__ void __launch_bounds__(256)
-hot_linear_wgrad_row_parts_finish_kernel(LinearGradArgs a, int parts)
+// behind them one quad of biases each.  A thread sends for eight parts at a time and draws eps behind the first of them.  What bounds it: memory
+// and the draw; with few parts, on large layers, how many waves hide the one behind the other.  So PARTS of them, up to kRowPartUnrolled,
+// are a kernel of their own (0: more): no load is made twice, and mu and sigma, which up to then would be held through the draw, come last
+// (64 registers, seven waves to a SIMD, against 83 and five).  The whole weight gradients, before eight parts were sent for at a
+// time, with eight for all, and now: one part 380 x 416 x 4580 x 2 samples 33.3 / 35.5 / 32.8 us, 157 x 1660 x 876 x 4 31.6 / 35.6 / 30.6;
+// two 850 x 4032 x 372 x 1 31.1 / 34.4 / 31.3; five 1184 x 168 x 4004 x 1 25.2 / 27.0 / 25.3; fourteen 16640 x 192 x 768 x 2 73.8 / 69.2 / 69.5;
+// of 3700 layers with parts the second was more than 3 % behind the first on 530; this is on none of 4900.
+constexpr int kRowPartUnrolled = 8;
+
+template <int PARTS>
+__global__ void __launch_bounds__(64)
+hot_linear_wgrad_row_parts_finish_kernel(LinearGradArgs a, int n_parts)
 {
+    const int parts = PARTS ? PARTS : n_parts;
     const long K = a.in_features, O = a.out_features, quads = O * K / 4, O4 = (O + 3) & ~3L;
     const long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
     const bool weights = q < quads;
@@ -2685,32 +2695,29 @@ hot_linear_wgrad_row_parts_finish_kernel(LinearGradArgs a, int parts)
     const size_t per_part = (size_t)row_part_floats(K, O, a.s_loc), per_sample = (size_t)(weights ? O * K : O4);
     const float *first = a.ws + (weights ? (size_t)q * 4 : (size_t)a.s_loc * (size_t)(O * K) + (size_t)b * 4);
     f4 gm = {0.0f, 0.0f, 0.0f, 0.0f}, gs = gm;
-    // (mu and sigma first, and eight parts under way at a time, eps drawn behind the first of them: with four, each behind a branch, a thread
-    // waited for memory once per four parts and sample: 16640 x 192 x 768 x 2 samples 11.6 -> 6.8 us; 7260 x 2160 x 540 x 2, three parts, moves 47 MB
-    // and stays at 12.8)
     const size_t mine = weights ? (size_t)q * 4 : 0;
-    const f4 m4 = load4<true, false>(a.mu_w + mine), sd4 = load4<true, false>(a.sigma_w + mine);
+    f4 m4, sd4;
+    if constexpr (PARTS == 0) {
+        m4 = load4<true, false>(a.mu_w + mine);
+        sd4 = load4<true, false>(a.sigma_w + mine);
+    }
     for (int s = 0; s < a.s_loc; ++s) {
         const float *theirs = first + (size_t)s * per_sample;
         // (four running sums, so that neither the additions nor their roundings form one long chain)
         f4 of[4], P, e;
 #pragma unroll
         for (int v = 0; v < 4; ++v) of[v] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-        auto add = [&](auto at_a_time) {
-            constexpr int B = decltype(at_a_time)::value;
-            for (int p0 = 0; p0 < parts; p0 += B) {
-                f4 u[B];
+        constexpr int B = PARTS ? PARTS : 8;
+        for (int p0 = 0; p0 < parts; p0 += B) {
+            f4 u[B];
 #pragma unroll
-                for (int v = 0; v < B; ++v) u[v] = load4<true, false>(theirs + (size_t)(p0 + v < parts ? p0 + v : parts - 1) * per_part);
-                if (p0 == 0) e = eps_quad(weights ? a.weight_quad0 + q : a.bias_quad0 + b, s, a.rng);
+            for (int v = 0; v < B; ++v) u[v] = load4<true, false>(theirs + (size_t)(p0 + v < parts ? p0 + v : parts - 1) * per_part);
+            if (p0 == 0) e = eps_quad(weights ? a.weight_quad0 + q : a.bias_quad0 + b, s, a.rng);
 #pragma unroll
-                for (int v = 0; v < B; ++v)
+            for (int v = 0; v < B; ++v)
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) of[v & 3][c] += p0 + v < parts ? u[v][c] : 0.0f;
-            }
-        };
-        if (parts <= 4) add(Number<4>());
-        else add(Number<8>());
+                for (int c = 0; c < 4; ++c) of[v & 3][c] += p0 + v < parts ? u[v][c] : 0.0f;
+        }
 #pragma unroll
         for (int c = 0; c < 4; ++c) P[c] = (of[0][c] + of[1][c]) + (of[2][c] + of[3][c]);
         if (weights && (P[0] != P[0] || P[1] != P[1] || P[2] != P[2] || P[3] != P[3])) P = row_parts_again(a, s, q, parts, theirs, per_part);
@@ -2721,6 +2728,10 @@ hot_linear_wgrad_row_parts_finish_kernel(LinearGradArgs a, int parts)
         }
     }
     if (weights) {
+        if constexpr (PARTS != 0) {
+            m4 = load4<true, false>(a.mu_w + mine);
+            sd4 = load4<true, false>(a.sigma_w + mine);
+        }
         f4 om, os;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
@@ -2815,6 +2826,16 @@ inline int64_t row_parts_budget(const hot_linear_desc *d)
     return most < kRowPartMaxBytes ? most : kRowPartMaxBytes;
 }
 
+// (a wave to a workgroup, so that few reach every compute unit)
+template <int PARTS>
+void row_parts_finish_go(int parts, long threads, hipStream_t s, const LinearGradArgs &a)
+{
+    const dim3 grid((unsigned)((threads + 63) / 64)), block(64);
+    if (parts > kRowPartUnrolled) return hot_linear_wgrad_row_parts_finish_kernel<0><<<grid, block, 0, s>>>(a, parts);
+    if (parts == PARTS) return hot_linear_wgrad_row_parts_finish_kernel<PARTS><<<grid, block, 0, s>>>(a, parts);
+    if constexpr (PARTS > 1) row_parts_finish_go<PARTS - 1>(parts, threads, s, a);
+}
+
 void row_parts_go(const RowPartsPlan &p, hipStream_t s, const LinearGradArgs &a, long tiles)
 {
     const long per_xcd = (tiles * a.s_loc * p.parts + kXcds - 1) / kXcds;
@@ -2823,9 +2844,7 @@ void row_parts_go(const RowPartsPlan &p, hipStream_t s, const LinearGradArgs &a,
     if (p.xbig) hot_linear_wgrad_row_parts_kernel<true><<<grid, block, 0, s>>>(a, p.parts, (int)chunk);
     else hot_linear_wgrad_row_parts_kernel<false><<<grid, block, 0, s>>>(a, p.parts, (int)chunk);
     const long threads = a.out_features * a.in_features / 4 + (a.mu_b ? (a.out_features + 3) / 4 : 0);
-    // (a wave to a workgroup, so that few reach every compute unit, unless there are plenty)
-    const int block_threads = threads >= 1024 * kComputeUnits ? 256 : 64;
-    hot_linear_wgrad_row_parts_finish_kernel<<<dim3((unsigned)((threads + block_threads - 1) / block_threads)), dim3(block_threads), 0, s>>>(a, p.parts);
+    row_parts_finish_go<kRowPartUnrolled>(p.parts, threads, s, a);
 }
 
 // A wave's finished 64-input x 16*RB-row tile of one sample's dx goes to memory.  Register rr of accumulator

@@ -431,6 +431,15 @@ def test_weight_gradients_from_row_parts_in_chunks_match_oracle(oracle, hot, row
     _backward_with_a_workspace(oracle, hot, rows, k, o, s, xs, bias, False, fraction, True)
 
 
+# One to eight parts, added up by a kernel of their own each, and more
+@pytest.mark.parametrize("rows,k,o,s,bias,parts", [(206, 8, 1044, 3, True, 1), (270, 28, 298, 3, False, 2), (558, 44, 4, 1, True, 3), (670, 8, 14, 1, True, 4),
+                                                   (840, 32, 12, 1, False, 5), (1086, 12, 6, 1, True, 6), (1306, 28, 6, 1, True, 7),
+                                                   (1416, 48, 4, 1, True, 8), (1624, 8, 4, 2, True, 9)])
+def test_weight_gradients_from_every_number_of_row_parts_match_oracle(oracle, hot, rows, k, o, s, bias, parts):
+    assert hot.hot_linear_kernel_shape(rows, k, o, s, 2) // 10 % 100 == parts
+    _backward_with_a_workspace(oracle, hot, rows, k, o, s, True, bias, False, 1.0, True)
+
+
 def test_weight_gradients_from_row_parts_with_pitched_x_and_unaligned_dy(hot):
     """Rows of x with padding (holding NaN) behind them and a dy that starts on a 4-byte boundary give the bits of the packed call."""
     rows, k, o, s = 600, 140, 72, 2
