@@ -1544,12 +1544,21 @@ inline DeepPlan deep_forward_plan(const hot_linear_desc *d)
 // times as fast on average, 78 of them slower by more than 3 % (0.85 at worst; 7260 x 2160 x 540 x 2 samples 312 -> 190 us, 13300 x 180 x
 // 216 x 4 94 -> 42); the slab model is 10 % below the time in the middle, hence the factor; under 40 us the second launch and the draw of
 // wide layers show (213 x 120 x 5072 x 4: 19 -> 30).
-constexpr double kPlanesMost = 1.11, kPlanesMostShort = 0.75, kPlanesShort = 40.0;
+// Up to kPlanesFewRows rows that model is right in the middle, and tiles smaller than 256 x 256 are taken only where the models see them ahead:
+// with the factor 46 of 229 forward products were slower by more than 3 % (219 x 304 x 1406 x 16 samples 35 -> 44 us, 444 x 1832 x 4769 x 8 432 ->
+// 493, 153 x 224 x 6932 x 8 54 -> 61), without it 11 are, by 3 to 8 % but for one; of 199 backward passes, their input gradients from planes, 14 (222 x
+// 7776 x 832 x 3 184 -> 203) and none; the products given back were 6 % faster on average.  The tiles of 256 x 256 were behind on none of 16 there.  One
+// sample below 8.3 us by the model: its two launches take longer than that (719 x 96 x 1536 8.9 -> 11.4, 3031 x 96 x 375 9.3 -> 10.9, 1381 x 120 x 862
+// 10.6 -> 11.6; from there on 3596 x 148 x 311 12.7 -> 12.0).
+constexpr double kPlanesMost = 1.11, kPlanesMostFewRows = 1.0, kPlanesMostShort = 0.75, kPlanesShort = 40.0, kPlanesLeastAlone = 8.3;
+constexpr long kPlanesFewRows = 512;
 
 inline PlanePlan planes_instead(long R, long C, long N, int S, bool tr, double slab, int64_t ws_bytes)
 {
     const PlanePlan p = plane_plan(R, C, N, S, tr, false);
-    const double most = p.time < kPlanesShort ? kPlanesMostShort : kPlanesMost;
+    const bool few = R <= kPlanesFewRows && p.code >= 0 && !plane_shape_large(kPlaneShapes[p.code]);
+    const double most = p.time < kPlanesShort ? kPlanesMostShort : few ? kPlanesMostFewRows : kPlanesMost;
+    if (!tr && S == 1 && p.time < kPlanesLeastAlone) return kNoPlanePlan;
     return p.code >= 0 && (ws_bytes < 0 || p.bytes <= ws_bytes) && p.time < most * slab ? p : kNoPlanePlan;
 }
 

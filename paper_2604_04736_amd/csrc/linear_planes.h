@@ -284,6 +284,7 @@ constexpr PlaneShape kPlaneShapes[] = {{3, 3, 1, 1.6, 5.9, {0.849}, 0.375, 1.57}
                                        {3, 1, 3, 3.4, 0.0, {0.464, 0.761, 1.175}, 0.119, 1.2},
                                        {1, 1, 6, 0.0, 0.0, {0.297, 0.303, 0.425, 0.594, 0.747, 0.817}, 0.079, 0.49},
                                        {4, 4, 1, 0.0, 5.6, {1.185}, 0.821, 10.1}};
+constexpr bool plane_shape_large(const PlaneShape &h) { return h.rb * h.cb == 16; }       // (256 x 256, the last shape)
 constexpr long kPlaneLongSteps = 40;
 constexpr double kPlaneLargeAhead = 1.03;
 constexpr int kPlaneCodes = sizeof(kPlaneShapes) / sizeof(kPlaneShapes[0]);
@@ -324,7 +325,7 @@ inline PlanePlan plane_plan(long R, long C, long N, int S, bool tr, bool apart)
         double t = h.once + (double)full * (taken * h.us[h.resident - 1] + h.round);
         if (left) t += taken * h.us[(left + kComputeUnits - 1) / kComputeUnits - 1] + h.round;
         t += (double)wgs / kComputeUnits * (taken * h.share + h.each);
-        const bool large = h.rb * h.cb == 16;                         // (the last shape)
+        const bool large = plane_shape_large(h);
         if (large && steps < kPlaneLongSteps) continue;
         if (best.code < 0 || (large ? kPlaneLargeAhead : 1.0) * t < best.time) {
             best.code = i;

@@ -174,6 +174,15 @@ def test_layers_on_which_the_slab_kernel_is_faster_stay_with_it(hot):
         assert hot.hot_linear_kernel_shape(rows, k, o, s, 0, per_sample_x=True) > 0
 
 
+# (rows, in, out, samples, per-sample x): layers on which the drawn planes were slower, by a tenth and more
+@pytest.mark.parametrize("which,rows,k,o,s,own", [(0, 219, 304, 1406, 16, True), (0, 444, 1832, 4769, 8, True), (0, 153, 224, 6932, 8, True),
+                                                  (0, 389, 392, 4412, 8, True), (0, 719, 96, 1536, 1, True), (0, 3031, 96, 375, 1, True),
+                                                  (0, 1381, 120, 862, 1, False), (1, 222, 7776, 832, 3, True), (1, 246, 4900, 448, 4, True)])
+def test_layers_on_which_drawn_planes_are_slower_stay_without(hot, which, rows, k, o, s, own):
+    assert hot.hot_linear_planes_workspace_bytes(rows, k, o, s, which, own) == 0
+    assert hot.hot_linear_planes_shape(rows, k, o, s, which, own) == 0
+
+
 def test_weight_gradients_of_small_layers_stay_with_one_launch(hot):
     """Row parts take two: few weights with few rows of one or two samples, half-empty tiles, one sample of 8192 to 12000 rows."""
     for rows, k, o, s in [(581, 540, 380, 1), (1199, 92, 112, 1), (317, 124, 1448, 2), (544, 7756, 32, 2), (8300, 192, 128, 1)]:
