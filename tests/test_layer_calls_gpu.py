@@ -1,5 +1,6 @@
 """What BayesianLinear takes beside dense arrays on the current device, which the native calls leave to the general path: the same
 results, the same refusals."""
+import gc
 import threading
 
 import pytest
@@ -168,6 +169,8 @@ def test_without_room_for_the_scratch_a_layer_runs_as_without_it(native, monkeyp
     if not native:
         for name in ("linear_forward", "linear_backward"):
             monkeypatch.setattr(hot.host(), name, lambda *a: None)
+    gc.collect()
+    torch.cuda.empty_cache()                    # (so that what is made now leaves no room inside blocks of other tests)
     g = torch.Generator(device=DEV).manual_seed(1)
     x, dy = torch.randn(s, r, k, device=DEV, generator=g), torch.randn(s, r, o, device=DEV, generator=g)
     p = [torch.randn(o, k, device=DEV, generator=g) * 0.1, torch.rand(o, k, device=DEV, generator=g) * 0.1 + 0.01]
