@@ -37,6 +37,8 @@
 //                                              workspace from 129 rows on in parts (both where the forward kernels above do not run)
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "hot.h"
 #include "vec.h"
 #include "draw.h"
@@ -1565,7 +1567,12 @@ inline PlanePlan planes_instead(long R, long C, long N, int S, bool tr, double s
 // ... and for a forward launch of the kernel for tens to hundreds of rows, with the small products apart.  Of 6918 such products
 // this takes 1947, 1.26 times as fast on average, 28 slower by more than 3 % (0.87 at worst; 826 x 5136 x 1275 x 4: 338 -> 280, 1363 x 2188 x
 // 1272 x 3 199 -> 142; where the models are closer than this the two are level, 300 x 2160 x 8640 x 2 227 and 226, of which 64 are the draw at 5.8 TB/s); the two narrow tiles have the long sums, where the models know less, and under 40 us it is as above.
-constexpr double kApartMost = 0.9, kApartMostNarrow = 0.75;
+// The tall tiles of that kernel (256 rows and more, code 3 on) are further from its model: beside fewer than kApartFewOutputs outputs nearer lines than kApartMostFew lost
+// (of 527 products 8, 2707 x 6776 x 83 x 7 samples 195 -> 236 us, 5288 x 3168 x 97 x 4 122 -> 136; the others there gained 6 %), and with more outputs
+// those of 32 outputs, one workgroup to a compute unit (codes 3 and 4), read rows that are in the L2 already, a third faster than it says: 604 x 7984 x 968 x 4
+// 283 -> 370 and 631 x 1984 x 559 x 7 80 -> 86 where the models see 0.73.  Of the 527, 483 are left, one slower by more than 3 % (was 11).
+constexpr double kApartMost = 0.9, kApartMostNarrow = 0.75, kApartMostFew = 0.84, kApartMostTall = 0.7;
+constexpr long kApartFewOutputs = 450;
 
 inline PlanePlan planes_forward_plan(const hot_linear_desc *d, int64_t ws_bytes)
 {
@@ -1574,7 +1581,10 @@ inline PlanePlan planes_forward_plan(const hot_linear_desc *d, int64_t ws_bytes)
         if (!slab_kernel_fits(d->rows, d->in_features, d->out_features, d->ldx)) return kNoPlanePlan;        // (32-bit offsets)
         const PlanePlan p = plane_plan(d->rows, d->in_features, d->out_features, d->s_local, false, true);
         const double time = deep_time(deep, d->rows, d->in_features, d->out_features, d->s_local, d->x_sample_stride != 0 ? d->s_local : 1);
-        const double most = (p.code >= 0 && kPlaneShapesApart[p.code].rb == 1 ? kApartMostNarrow : kApartMost) * (p.time < kPlanesShort ? kPlanesMostShort : 1.0);
+        double most = p.code >= 0 && kPlaneShapesApart[p.code].rb == 1 ? kApartMostNarrow : kApartMost;
+        if (deep.code >= 3 && d->out_features < kApartFewOutputs) most = std::min(most, kApartMostFew);
+        if (p.time < kPlanesShort) most *= kPlanesMostShort;
+        else if ((deep.code == 3 || deep.code == 4) && d->out_features >= kApartFewOutputs) most = std::min(most, kApartMostTall);
         return p.code >= 0 && (ws_bytes < 0 || p.bytes <= ws_bytes) && p.time < most * time ? p : kNoPlanePlan;
     }
     const SlabForwardPlan slab = slab_forward_plan(d);

@@ -177,7 +177,10 @@ def test_layers_on_which_the_slab_kernel_is_faster_stay_with_it(hot):
 # (rows, in, out, samples, per-sample x): layers on which the drawn planes were slower, by a tenth and more
 @pytest.mark.parametrize("which,rows,k,o,s,own", [(0, 219, 304, 1406, 16, True), (0, 444, 1832, 4769, 8, True), (0, 153, 224, 6932, 8, True),
                                                   (0, 389, 392, 4412, 8, True), (0, 719, 96, 1536, 1, True), (0, 3031, 96, 375, 1, True),
-                                                  (0, 1381, 120, 862, 1, False), (1, 222, 7776, 832, 3, True), (1, 246, 4900, 448, 4, True)])
+                                                  (0, 1381, 120, 862, 1, False), (1, 222, 7776, 832, 3, True), (1, 246, 4900, 448, 4, True),
+                                                  # in the place of the kernel for tens to hundreds of rows
+                                                  (0, 604, 7984, 968, 4, True), (0, 2707, 6776, 83, 7, False), (0, 2518, 2356, 88, 8, False),
+                                                  (0, 5288, 3168, 97, 4, True)])
 def test_layers_on_which_drawn_planes_are_slower_stay_without(hot, which, rows, k, o, s, own):
     assert hot.hot_linear_planes_workspace_bytes(rows, k, o, s, which, own) == 0
     assert hot.hot_linear_planes_shape(rows, k, o, s, which, own) == 0
