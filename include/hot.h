@@ -448,7 +448,7 @@ int hot_backward_adam(hot_plan *plan, const hot_rng *rng, const hot_adam *params
  * next step (normally the same seed with step + 1).  mu, sigma, the four moment arrays [N]: read and
  * overwritten; grad_w [S, ld]: read; w [S, ld]: written, must not be grad_w.  Layout, alignment, stream and
  * error rules as for hot_backward; launch geometry: that of HOT_KERNEL_BACKWARD_RNG once hot_set_launch has set it;
- * until then one chunk per thread where every tile gets a workgroup of its own, else HOT_KERNEL_BACKWARD_RNG's default.
+ * until then one chunk per thread from 2^22 weights on where every tile gets a workgroup of its own, else HOT_KERNEL_BACKWARD_RNG's default.
  */
 int hot_backward_adam_forward(hot_plan *plan, const hot_rng *rng, const hot_rng *rng_next, const hot_adam *params,
                               float *mu, float *sigma, const float *grad_w, float *m_mu, float *v_mu, float *m_sigma,

@@ -261,9 +261,11 @@ inline void default_launches(hot_plan &p)
     // it four times the waves to hide its two draws behind, and wins while every tile still has a workgroup of its own
     // (4 samples: 6.3 M weights 105 -> 97 us, 12 M 187 -> 176, 24 M 377 -> 365, 50 M 724 -> 706).  Past kMaxGrid tiles, 67 M
     // weights, workgroups would stride over two tiles each, and the backward default is faster (105 M x 4: 1.64 ms with
-    // one chunk, 1.54 with four; x 1: 1.11 and 1.07).
+    // one chunk, 1.54 with four; x 1: 1.11 and 1.07).  Below 4 M weights the last round of workgroups decides, either way: of 1000 sizes
+    // 1.45 M x 15 51 us with two chunks and 61 with one, 0.85 M x 11 1.08 times as long with one, 0.7 M x 8 0.88; from there on 0.97, none
+    // above 1.04.  So there the backward default stays.
     p.step = br;
-    if ((d.n_weights + kBlock * 4 - 1) / (kBlock * 4) <= kMaxGrid) p.step.chunks = 1;
+    if (d.n_weights >= (4L << 20) && (d.n_weights + kBlock * 4 - 1) / (kBlock * 4) <= kMaxGrid) p.step.chunks = 1;
 }
 
 // How the N columns are cut into tiles, one workgroup each (capped by the configured bound, beyond which workgroups

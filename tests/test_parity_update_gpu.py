@@ -384,6 +384,31 @@ def test_fused_step_with_its_own_default_geometry(hot, n, s):
     assert abs(kl1.item() - kl2.item()) <= 1e-13 * scale
 
 
+@pytest.mark.parametrize("n,s,chunks", [(1_454_390, 15, 2), (4_194_303, 4, 2), (4_300_001, 4, 1)])
+def test_fused_step_takes_the_backward_geometry_below_four_million_weights(hot, n, s, chunks):
+    """Its KL partials, one per workgroup, are then those of the backward kernel's chunks: the sum is that of a forward pass with
+    them, bit for bit."""
+    print("case fused step, small", n, s, flush=True)
+    g = torch.Generator(device=DEV).manual_seed(n % 1009)
+    normal = lambda *shape: torch.empty(*shape, device=DEV).normal_(generator=g)
+    state = [normal(n) for _ in range(6)]
+    for i in (1, 3, 5):
+        state[i].abs_().add_(0.02)
+    grad_w, rng, nxt = normal(s, n), hot.hot_rng(seed=5, step=4, first_sample=0), hot.hot_rng(seed=5, step=5, first_sample=0)
+    plan, w = hot.hot_create(n, n, s, s, 500.0, 0), torch.empty(s, n, device=DEV)
+    assert hot.hot_get_launch(plan, hot.HOT_KERNEL_BACKWARD_RNG)["chunks"] == 2
+    kl = torch.zeros(2, dtype=torch.float64, device=DEV)
+    hot.hot_backward_adam_forward(plan, rng, nxt, hot.hot_adam(1e-3, 0.9, 0.999, 1e-8, 1.0, 0.02, 4), state[0], state[1], grad_w, *state[2:], w, kl[:1])
+    hot.hot_set_launch(plan, hot.HOT_KERNEL_FORWARD_RNG, chunks=chunks, unroll=1, nontemporal=1)
+    hot.hot_forward_rng(plan, nxt, state[0], state[1], w, kl[1:])
+    other = torch.zeros(1, dtype=torch.float64, device=DEV)
+    hot.hot_set_launch(plan, hot.HOT_KERNEL_FORWARD_RNG, chunks=3 - chunks, unroll=1, nontemporal=1)
+    hot.hot_forward_rng(plan, nxt, state[0], state[1], w, other)
+    torch.cuda.synchronize()
+    hot.hot_destroy(plan)
+    assert kl[0].item() == kl[1].item() and kl[0].item() != other.item()
+
+
 @pytest.mark.parametrize("n,ld,s,offset", [(700_001, 700_004, 3, 0), (700_001, 700_001, 2, 1)])
 def test_fused_calls_with_non_temporal_accesses(hot, n, ld, s, offset):
     """The three fused calls with the non-temporal variants of their kernels (the default only above
