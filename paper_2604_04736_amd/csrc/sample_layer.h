@@ -244,15 +244,19 @@ inline void default_launches(hot_plan &p)
     // size) one chunk per thread, whose 38 registers leave eight waves per SIMD to hide the generator's latencies behind
     // (4, 2 and 1 chunks: 12 M weights x 5 samples 68 / 68 / 65 us, x 7 97 / 93 / 82, 25 M x 6 160 / 163 / 147; but
     // 4 M x 4 26 / 26 / 28, and with the backward call after it 6 M x 5 is level).  Else two where the number of tiles allows (25 M x 1 55 / 54 / 70, 12 M x 2 41 / 40 / 46,
-    // 12 M x 4 59 / 58 / 58); four never were ahead by more than the runs differ there.
-    // hot_adam_forward shares this geometry, and with it the order of the KL sum: 25 M x 1 282 / 277 / 304, x 5 365 / 348 / 358.
+    // 12 M x 4 59 / 58 / 58).
+    // hot_adam_forward shares this geometry, and with it the order of the KL sum: 25 M x 1 282 / 277 / 304.  It sets the ends of both
+    // ranges: from 40 M weights on five to seven samples keep what the number of tiles allows (76 M x 5 1071 us with four chunks and 1147 with one,
+    // 54 M x 6 818 and 862; the forward call alone would be 2 to 8 % faster with one), and from 32 M on fewer samples do (190 M x 1 2009 us with four
+    // and 2115 with two, the forward call 358 and 376; 25 M to 32 M are level).  So do three and more below 4 M, where two leave the last round emptier (2.9 M x 7
+    // 20.7 us with four and 23.1 with two).
     // Backward: single rows in flight at every size (two rows of draws in flight cost registers and with them waves:
     // 209 M weights x 2 samples 1.07 ms against 0.81, 64 M x 3 0.38 against 0.30, 20 M x 8 0.178 against 0.169); four
     // chunks per thread from 16 M weights on, below that two from four samples on (6.3 M x 16, 7.7 M x 13), else one.
     hot_launch &fr = p.cfg[HOT_KERNEL_FORWARD_RNG], &br = p.cfg[HOT_KERNEL_BACKWARD_RNG];
     fr = f;
-    if (d.s_local >= 8 || (d.s_local >= 5 && d.n_weights > 40000000L / d.s_local)) fr.chunks = 1;
-    else if (fr.chunks > 2) fr.chunks = 2;
+    if (d.s_local >= 8 || (d.s_local >= 5 && d.n_weights > 40000000L / d.s_local && d.n_weights < 40000000L)) fr.chunks = 1;
+    else if (fr.chunks > 2 && d.n_weights < (32L << 20) && (d.s_local < 3 || d.n_weights >= (4L << 20))) fr.chunks = 2;
     br = b;
     br.chunks = few_tiles ? (d.s_local >= 4 ? 2 : 1) : 4;
     if (br.chunks > f.chunks) br.chunks = f.chunks;      // (f.chunks: what the number of tiles allows)

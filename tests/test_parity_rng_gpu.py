@@ -186,6 +186,15 @@ def test_full_size_fused_path(oracle, hot, name):
         assert bits_ok.shape == (s, 8)
 
 
+# both sides of each end of the ranges with fewer chunks than the number of tiles allows
+@pytest.mark.parametrize("n,s,chunks", [(3_145_180, 6, 4), (3_145_180, 2, 2), (4_600_000, 6, 2), (33_000_000, 1, 2), (34_000_000, 1, 4), (190_362_083, 1, 4),
+                                        (39_900_000, 5, 1), (40_000_000, 5, 4), (60_000_000, 7, 4), (40_000_000, 8, 1)])
+def test_chunks_of_the_drawing_forward(hot, n, s, chunks):
+    plan = hot.hot_create(n, n, s, s, 100.0, 0)
+    assert hot.hot_get_launch(plan, hot.HOT_KERNEL_FORWARD_RNG)["chunks"] == chunks
+    hot.hot_destroy(plan)
+
+
 @pytest.mark.parametrize("n,s,chunks", [(8_000_000, 4, 2), (8_000_000, 5, 2), (8_000_001, 5, 1), (2_097_155, 8, 1)])
 def test_default_geometry_of_the_drawing_forward(hot, n, s, chunks):
     """Both sides of the rule for one and two chunks per thread: the same w and, to the rounding of the fp64 sum, the
