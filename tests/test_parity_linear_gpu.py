@@ -1406,6 +1406,22 @@ def test_weight_gradients_with_rows_of_dy_off_the_grid(hot, rows, k, o, s, parts
         assert bool(torch.isfinite(gsig[lo:]).all()) and bool(torch.isnan(gmu[:lo]).all()) and bool(torch.isnan(gsig[:lo]).all())
 
 
+@pytest.mark.parametrize("rows,k,o,s", [(300, 2048, 2048, 1), (300, 2052, 2052, 2), (576, 1920, 1284, 3)])
+def test_tile_weight_gradients_of_sixteen_rows_are_as_accurate_as_row_parts(hot, rows, k, o, s):
+    """Only the first sixteen rows are not zero, one step of the matrix instruction in both kernels (a workspace brings the row parts): there a product
+    of small pieces behind the large one shows, as one more rounding.  Both add the same six products of every pair of factors up; what their order
+    among the small ones changes is 2^-8 of a rounding."""
+    g, c = _deep_case(rows + o, o, k)
+    x, dy = torch.randn(s, rows, k, device=DEV, generator=g), torch.randn(s, rows, o, device=DEV, generator=g)
+    x[:, 16:] = 0.0
+    assert hot.hot_linear_kernel_shape(rows, k, o, s, 2) // 1000 == 1
+    rng = hot.hot_rng(seed=83, step=2, first_sample=1)
+    want = sum(dy[i].double().t() @ x[i].double() for i in range(s))
+    tiles, parts = (_distance(_backward(hot, rng, x, dy, c, None, ws, s)[0], want) for ws in (None, _workspace(hot, rows, k, o, s)))
+    print("distance from 64 bits: tiles %.3e, row parts %.3e" % (tiles, parts), flush=True)
+    assert tiles <= 1.01 * parts
+
+
 # the first kernel, and tiles: ragged, with an odd last sample, aligned
 @pytest.mark.parametrize("rows,k,o,s", [(800, 2052, 1537, 2), (300, 2052, 1539, 3), (800, 2948, 1537, 2), (300, 2500, 2179, 3), (300, 4100, 2052, 2)])
 def test_tile_weight_gradients_of_infinite_and_huge_values(hot, rows, k, o, s):
