@@ -203,6 +203,35 @@ def test_kl_of_a_layer_in_one_launch(hot, k, o, bias):
         assert layer.kl(mu_w, sigma_w, mu_b, sigma_b).isnan()
 
 
+@pytest.mark.parametrize("n_w,n_b", [(1, 0), (7, 3), (4096, 1), (65533, 3), (65536, 0)])
+def test_kl_of_arrays_on_any_four_byte_boundary(hot, n_w, n_b):
+    g = torch.Generator(device=DEV).manual_seed(n_w + n_b)
+    flat = torch.rand(2 * (n_w + n_b) + 5, device=DEV, generator=g) + 0.01
+    at, parts = 1, []
+    for n in (n_w, n_w, n_b, n_b):
+        parts.append(flat[at:at + n] if n else None)
+        at += n + 1
+    out = torch.full((3,), -1.0, dtype=torch.float64, device=DEV)
+    hot.hot_kl_layer(*parts, out[1:2])
+    v = torch.cat([q for q in (parts[0], parts[2]) if q is not None]).double(), torch.cat([q for q in (parts[1], parts[3]) if q is not None]).double()
+    want, size = (0.5 * (v[1] ** 2 + v[0] ** 2 + i - 2.0 * f(v[1].log())).sum() for i, f in ((-1.0, lambda t: t), (1.0, lambda t: -t.abs())))
+    assert abs(out[1].item() - want.item()) <= 1e-7 * size.item()          # (as above)
+    assert out[0].item() == -1.0 and out[2].item() == -1.0
+
+
+def test_kl_of_a_layer_refuses_what_it_cannot_take(hot):
+    t, out = torch.ones(65537, device=DEV), torch.zeros(1, dtype=torch.float64, device=DEV)
+    for mu_w, sigma_w, mu_b, sigma_b, code in ((t, t, None, None, hot.HOT_ERANGE), (t[:65536], t[:65536], t[:1], t[:1], hot.HOT_ERANGE),
+                                               (t[:0], t[:0], None, None, hot.HOT_EINVAL)):
+        with pytest.raises(hot.HotError) as e:
+            hot.hot_kl_layer(mu_w, sigma_w, mu_b, sigma_b, out)
+        assert e.value.code == code
+    for args, error in (((t[:4], t[:4], t[:1], None, out), ValueError), ((t[:4], t[:8:2], None, None, out), TypeError),
+                        ((t[:4], t[:4], None, None, out.float()), TypeError), ((t[:4].double(), t[:4], None, None, out), TypeError)):
+        with pytest.raises(error):
+            hot.hot_kl_layer(*args)
+
+
 @pytest.mark.parametrize("rows,k,o,s,own", [(16, 2048, 2048, 2, True), (3, 2048, 2049, 2, False), (16, 5000, 1100, 4, True), (9, 5000, 1100, 4, False),
                                             (16, 2048, 1400, 3, True), (16, 1024, 700, 7, False), (1, 700, 1200, 16, True), (16, 2048, 2240, 2, True)])
 def test_samples_in_workgroups_of_their_own(hot, rows, k, o, s, own):
