@@ -1,7 +1,9 @@
 """torch.autograd plumbing around the C ABI: the Gaussian sample layer as a differentiable
 function of (mu, sigma), so that a PyTorch training loop can use the HIP path unchanged, and the
-sampled linear layer (BayesianLinear, at the end) whose weights and per-sample weight gradients
-never exist in memory.
+sampled linear layer (BayesianLinear, at the end), whose per-sample weight gradients never exist in
+memory, nor its drawn weights up to 128 rows.  With more rows the drawn weights of a call may lie in
+scratch memory, as bf16 pieces (six bytes per weight and sample, at most 1 GiB, from torch's allocator
+and given back when the call returns); where there is no room for them the call runs without.
 
     layer = GaussianSampleLayer(n_weights, s_local, dataset_size)
     w, kl = layer.sample(mu, sigma, step)          # w[s] = mu + sigma * eps_s,  eps drawn in the kernel

@@ -26,11 +26,6 @@ bool is_vector(const MaybeTensor &t, int64_t n, int64_t device) { return t && pl
 const float *data(const Tensor &t) { return t.const_data_ptr<float>(); }
 const float *data(const MaybeTensor &t) { return t ? t->const_data_ptr<float>() : nullptr; }
 
-struct Draw {
-    uint64_t seed;
-    uint32_t step, first_sample;
-};
-
 // the layer's description, if the arrays are as the C calls want them and have the layer's sizes (its draws and offsets are by these:
 // with more outputs than that, the weights' eps would be those of its biases and of the next layer)
 bool describe(const Tensor &x, const Tensor &mu_w, const Tensor &sigma_w, const MaybeTensor &mu_b, const MaybeTensor &sigma_b, int64_t in_features,

@@ -2,7 +2,8 @@
 // (arxiv 2604.04736, Algorithm 1 / 2: reparameterisation line followed by ForwardPass, for the
 // case that the layer is a Linear):
 //     y_s = x (mu_W + sigma_W (.) eps_s)^T + (mu_b + sigma_b (.) eps_s^b)        for every local sample s
-// The sampled weights never exist in memory: a wave draws the eps of a 16-output x 32-input tile
+// The sampled weights do not exist in memory (but for the bf16 pieces that a caller's workspace may hold at many rows,
+// linear_planes.h): a wave draws the eps of a 16-output x 32-input tile
 // in registers (Philox + Box-Muller on the vector ALU), forms w = fma(sigma, eps, mu) and feeds
 // it straight to the matrix cores as the B operand of v_mfma_f32_16x16x4_f32, while the minibatch
 // x is the A operand.  mu_W and sigma_W are read once per block of rows and sample chunk; eps for
@@ -1542,9 +1543,9 @@ inline DeepPlan deep_forward_plan(const hot_linear_desc *d)
 
 // Whether planes of drawn weights (linear_planes.h) stand in for a launch of the slab kernel that takes `slab` microseconds by its
 // model: where a workspace holds them, unless they are slower by the models.  (Their sums are the bf16 slab kernel's bit for bit;
-// layers of the 128-row slab shapes on the fp32 instruction stay where they are.)  Of 8450 forward products the rule takes 7050, 1.32
-// times as fast on average, 78 of them slower by more than 3 % (0.85 at worst; 7260 x 2160 x 540 x 2 samples 312 -> 190 us, 13300 x 180 x
-// 216 x 4 94 -> 42); the slab model is 10 % below the time in the middle, hence the factor; under 40 us the second launch and the draw of
+// layers of the 128-row slab shapes on the fp32 instruction stay where they are.)  Of 9600 forward products that this and the
+// next rule take, drawn over the range, planes are 1.32 times as fast on average, 62 slower by more than 3 % (0.83 at worst, 4317 x 128 x 4302 x 8; 7260 x 2160 x
+// 540 x 2 samples 312 -> 190 us, 13300 x 180 x 216 x 4 94 -> 42); the slab model is 10 % below the time in the middle, hence the factor; under 40 us the second launch and the draw of
 // wide layers show (213 x 120 x 5072 x 4: 19 -> 30).
 // Up to kPlanesFewRows rows that model is right in the middle, and tiles smaller than 256 x 256 are taken only where the models see them ahead:
 // with the factor 46 of 229 forward products were slower by more than 3 % (219 x 304 x 1406 x 16 samples 35 -> 44 us, 444 x 1832 x 4769 x 8 432 ->
@@ -1564,10 +1565,9 @@ inline PlanePlan planes_instead(long R, long C, long N, int S, bool tr, double s
     return p.code >= 0 && (ws_bytes < 0 || p.bytes <= ws_bytes) && p.time < most * slab ? p : kNoPlanePlan;
 }
 
-// ... and for a forward launch of the kernel for tens to hundreds of rows, with the small products apart.  Of 6918 such products
-// this takes 1947, 1.26 times as fast on average, 28 slower by more than 3 % (0.87 at worst; 826 x 5136 x 1275 x 4: 338 -> 280, 1363 x 2188 x
-// 1272 x 3 199 -> 142; where the models are closer than this the two are level, 300 x 2160 x 8640 x 2 227 and 226, of which 64 are the draw at 5.8 TB/s); the two narrow tiles have the long sums, where the models know less, and under 40 us it is as above.
-// The tall tiles of that kernel (256 rows and more, code 3 on) are further from its model: beside fewer than kApartFewOutputs outputs nearer lines than kApartMostFew lost
+// ... and for a forward launch of the kernel for tens to hundreds of rows, with the small products apart.  (826 x 5136 x 1275 x 4: 338 -> 280, 1363 x 2188 x
+// 1272 x 3 199 -> 142; where the models are closer than this the two are level, 300 x 2160 x 8640 x 2 227 and 226, of which 64 are the draw at 5.8 TB/s.)  The two narrow tiles have the long sums, where the models know less, and under 40 us it is as above.
+// The larger tiles of that kernel (eight blocks of 32 x 32 and more, code 3 on) are further from its model: beside fewer than kApartFewOutputs outputs nearer lines than kApartMostFew lost
 // (of 527 products 8, 2707 x 6776 x 83 x 7 samples 195 -> 236 us, 5288 x 3168 x 97 x 4 122 -> 136; the others there gained 6 %), and with more outputs
 // those of 32 outputs, one workgroup to a compute unit (codes 3 and 4), read rows that are in the L2 already, a third faster than it says: 604 x 7984 x 968 x 4
 // 283 -> 370 and 631 x 1984 x 559 x 7 80 -> 86 where the models see 0.73.  Of the 527, 483 are left, one slower by more than 3 % (was 11).
@@ -2050,10 +2050,12 @@ void wgrad_go(long tiles, int waves, hipStream_t s, const LinearGradArgs &a)
 // registers), and two workgroups share a compute unit and cover each other's draws.
 // What bounds it: matrix and vector instructions, which overlap only in part, at the clock that the card's power leaves (1024 x
 // 8192^2 x 2: matrix pipes 55-60 % busy at 1.7 GHz, 211 TFLOP/s of fp32 work per further row), and at a few hundred rows the draw
-// (43 us of 190 at 300 x 2160 x 8640 x 2) and the 16 bytes per weight of mu, sigma and the gradients.  Measured against its
+// (43 us of 196 at 300 x 2160 x 8640 x 2) and the 16 bytes per weight of mu, sigma and the gradients.  Measured against its
 // predecessor, which sent fp32 rows straight into LDS, had every wave cut its operands itself (176 instead of 88 vector instructions per
-// 24 matrix instructions), and waited for memory sixteen times per tile on the way out: 1024 x 8192^2 x 2 1654 -> 1502 us, 160 x 8192^2 x 2
-// 505 -> 402, 300 x 2160 x 8640 x 2 221 -> 192, 200 x 4096^2 x 2 153 -> 120.  On the way: the same with the vector instructions where the
+// 24 matrix instructions), and waited for memory sixteen times per tile on the way out, in turn, nothing else between the calls: 1024 x 8192^2 x 2 1691 -> 1506 us
+// (between the other kernels of a pass, at the clock that those leave, 1790 -> 1660 to 1700), 160 x 8192^2 x 2 522 -> 402, 300 x 2160 x 8640 x 2 222 -> 196,
+// 200 x 4096^2 x 2 157 -> 126; of 1100 layers of 140 to 2000 tiles, edges of every width among them, 0.86 of the time in the middle and none slower, though blocks of 32 x 32
+// outside the layer are multiplied too.  21 registers are spilled (72 bytes of scratch per lane).  On the way (1024 x 8192^2 x 2): the same with the vector instructions where the
 // scheduler put them, in rows, 1680; with fixed places 1650; rows of x and dy sent for two steps ahead 1560; the way out
 // without waits 1502.  Three sets of rows under way instead of two (steps in threes): 1566, with 51 registers spilled.
 // ---------------------------------------------------------------------------------
@@ -2505,6 +2507,7 @@ struct Floats<4> {
 // floats of one part's share of the workspace: per sample the weights, then the biases (a multiple of four, so that quads stay aligned)
 inline __host__ __device__ long row_part_floats(long K, long O, int s_loc) { return (O * K + ((O + 3) & ~3L)) * s_loc; }
 
+// (XBIG spills seven registers, 32 bytes of scratch per lane.)
 template <bool XBIG>
 __global__ void __launch_bounds__(64 * kRowPartWaves, 2)
 hot_linear_wgrad_row_parts_kernel(LinearGradArgs a, int parts, int chunk)
